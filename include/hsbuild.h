@@ -163,8 +163,10 @@ int hsbuild_forward_static(hsbuild_t h, const double k_frac[3], int32_t ng, cons
  *   H = sum_t P_t .* (W0_t^H T_t W0_t),  S = sum_t P_t .* (W0_t^H Lam_t W0_t),
  *   P_t[G'][G] = sum over the atoms a of type t of e^{-i K_G' . tau_a} e^{i K_G . tau_a}
  * (.* entrywise), with contraction width sum_t (N_t + 4 N_L) per entry
- * instead of 4 N_atoms N_L.  Same arguments and results as hsbuild_forward
- * (equal up to FP64 rounding); always FP64, whatever the handle's precision.
+ * instead of 4 N_atoms N_L.  W0_t is real up to a unitary map of m at fixed l
+ * (real harmonics), so the products over L are real times complex (H) and real
+ * times real (S).  Same arguments and results as hsbuild_forward (equal up to
+ * FP64 rounding); always FP64, whatever the handle's precision and options.
  * Workspace: hsbuild_workspace_bytes(h, HSB_MODE_FACTORED, 1, &ng). */
 int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
                              const void* T, void* H, void* S, void* ws, size_t ws_bytes, void* stream);
@@ -177,12 +179,11 @@ int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, co
  * invariant under time reversal, T[(X,l,m),(X',l',m')] = (-1)^(m+m')
  * conj(T[(X,l,-m),(X',l',-m')]), with no entries of odd l + l'.  Then each
  * pair contributes twice the real part of one member's term, so only one atom
- * of each pair is built and the contraction keeps only real parts: about a
- * quarter of the work of hsbuild_forward.  H, S: device double [ng][ng],
+ * of each pair is built and only real parts are kept.  H, S: device double [ng][ng],
  * upper triangle written; equal to the real parts of hsbuild_forward's
  * outputs up to FP64 rounding (undefined if the symmetry does not hold).
  * Other arguments as hsbuild_forward.  A handle created with HSB_FP64 runs
- * the FP64 contraction; one created with HSB_SPLIT_INT8 or a residue form
+ * the type-factored form on real parts; one created with HSB_SPLIT_INT8 or a residue form
  * (HSB_SPLIT_CRT*) runs that split contraction (the real parts of the split
  * products, to the split path's error); HSB_SPLIT_BF16 and HSB_SPLIT_FP16 handles get
  * HSB_ERR_UNSUPPORTED before anything is enqueued.

@@ -62,13 +62,10 @@ struct Layout {
   size_t mx = 0, scale = 0, slL = 0, slS = 0, slY = 0;  // split only (slL, slS, slY: residue planes in the CRT form)
   int K64 = 0, n_res = 0;                              // residue form: rows padded to 64, columns to 256
   size_t crPart = 0, crRes = 0, crResH = 0;            // residue form: partial column norms, residues of S, H
-  // factored only: rows [R_f] of X (E and W0 blocks), XL = lam X, Yx (Y0 on W0 rows, 0 on E rows)
-  int R_f = 0;
-  size_t X = 0, XL = 0, Yx = 0, lamx = 0, kind = 0, tau0 = 0;
   // BLAS baseline only: A and B stacks, X scratch, rocBLAS's device memory
   size_t hA = 0, hB = 0, hX = 0, blas = 0, blas_bytes = 0;
   // real-symmetric only: representative indices and weights, their positions, row weights
-  size_t rep = 0, repw = 0, tau_rep = 0, wrow = 0;
+  size_t rep = 0, tau_rep = 0, wrow = 0;
   // eigensolve only: rocSOLVER's off-diagonal scratch
   size_t eigE = 0;
 };
@@ -93,9 +90,10 @@ hipError_t launch_assemble(const CellArgs& c, int n_pad, const double2* ang, con
 // The same with A and B in separate stacks: A rows atom*N_L + L, B rows N_atoms*N_L + atom*N_L + L.
 hipError_t launch_assemble_split(const CellArgs& c, int n_pad, const double2* ang, const double2* ab, const double* kv,
                                  const double* tau, double2* out, int64_t ld, int n_store, hipStream_t s);
-// Inversion pairs: tau_rep[r] = tau[rep[r]] (r < n_rep); with lam non-null, wrow[k] = w[k / rows]
-// over the stacked rows (0 for k >= n_rep rows) and lam[k] *= wrow[k], k < K_pad.
-hipError_t launch_rep_setup(const double* tau, const int* rep, const double* w, int n_rep, int rows, int K_pad,
+// Inversion pairs: tau_rep[r] = tau[rep[r].atom] (r < n_rep); with lam non-null, wrow[k] = w[k / rows]
+// over the stacked rows (0 for k >= n_rep rows) and lam[k] *= wrow[k], k < K_pad (w: rep's weights).
+struct FactRep;
+hipError_t launch_rep_setup(const double* tau, const FactRep* rep, int n_rep, int rows, int K_pad,
                             double* tau_rep, double* wrow, double* lam, hipStream_t s);
 // X = U B over the stacked B rows (atom, L), U = diag(||udot_l||) of the atom's type.
 hipError_t launch_udot_scale(const CellArgs& c, const TypeConsts* consts, int n_pad, const double2* B, double2* X,
@@ -144,10 +142,6 @@ hipError_t launch_hs_fp64_sk(const double2* W, const double2* WL, const double2*
                              int n_pad, int gr, double2* Hp, double2* Sp, hipStream_t s);
 hipError_t launch_sk_reduce(const double2* Hp, const double2* Sp, int ns, int n, int n_pad, double2* H, double2* S,
                             int64_t ldh, hipStream_t s);
-
-// The same contraction keeping only the real parts, Re(W^H Y) and Re(W^H lam W), as doubles.
-hipError_t launch_hs_fp64_real(const double2* W, const double2* WL, const double2* Y, const double* lam, int K_pad,
-                               int n, int n_pad, int gr, int waves, double* H, double* S, int64_t ldh, hipStream_t s);
 
 // Number of 128 x 64 tiles the contraction covers for a padded basis size.
 int hs_tiles(int n_pad);
@@ -230,20 +224,55 @@ hipError_t launch_crt_combine(const CrtConsts& cc, bool real, const void* res, i
                               const double* scR, int n, void* C, hipStream_t s);
 
 // ---- type-factored form ----
-// Number of 64 x 64 tiles of the factored contraction.
-int fact_tiles(int n_pad);
-// E[a][G] = e^{i K_G . tau_a}, rows a < n_atoms of a [*][n_pad] array.
-hipError_t launch_phases(int n_atoms, int n_pad, const double* kv, const double* tau, double2* E, hipStream_t s);
-// Row blocks of the factored layout: per type with atoms, round16(N_t) E rows then
-// round16(2 N_L) W0 rows.  lamx[r] and the kind of every 16-row chunk.
-hipError_t launch_fact_rows(const CellArgs& c, const TypeConsts* consts, int rows, double* lamx, int* kind,
-                            hipStream_t s);
+// Rows of a type's blocks (R, Y: 2 N_L; phases: its atoms) are padded to a multiple of this.
+constexpr int kFactRows = 16;
+// Radial data of (active type, l) passed by value: u, u', udot, udot', ||udot||^2 (the constants
+// are uploaded instead when the types need more entries).
+constexpr int kRadialArgs = 64;
+struct RadialArgs {
+  double v[kRadialArgs][5];
+};
+// The types with atoms, in order; byte offsets in the workspace of what all k-points share.
+struct FactCell {
+  double bvec[9], pre;
+  int l_max, n_l, n_act;
+  int Mr, Mc;  // 2 N_L rounded up to kFactRows, and to 64 (columns of T')
+  size_t TT, lam;  // T'[r][k] as complex [n_act][k: Mr][r: Mc]; S weights, double [n_act][Mr]
+  int type[HSB_MAX_TYPES], nat[HSB_MAX_TYPES], atom0[HSB_MAX_TYPES];
+  int eoff[HSB_MAX_TYPES];  // first phase row
+  double r_mt[HSB_MAX_TYPES];
+};
+// One k-point: byte offsets in the workspace.  R: double [n_act][Mr][n_pad]; Y: complex (the real
+// form: double), same shape; E: complex [phase rows][n_pad]; kv: double [n_pad][4].
+struct FactK {
+  double kfrac[3];
+  int64_t g_row;    // first row of its G list
+  int64_t kv, R, Y, E;
+  int64_t out_off;  // H, S, in elements (ld = n)
+  int n, n_pad;     // n_pad: a multiple of 64
+  int gblk0, yblk0, tile0;  // first workgroup of each kernel (many k-points)
+};
+// Representative of an inversion pair (real form): atom and multiplicity (2; 1 at the origin).
+struct FactRep {
+  double weight;
+  int atom, pad;
+};
+// Workgroups of the H/S kernel for a basis of n; mi: 16-row blocks per wave side (1 or 2).
+int fact_tiles(int n, int mi);
+// Blocks per wave side for `tiles` workgroups of the larger tile on num_cus compute units.
+int fact_block(int64_t tiles, int num_cus);
+// For one k-point (many == nullptr) or the nk k-points of the device array many; consts: device
+// copy of the type constants, or nullptr to take them from ra.  rep: the real form's
+// representatives (device), else nullptr.
+hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const TypeConsts* consts, const FactK& one,
+                              const FactK* many, int nk, int ngb, const int32_t* g, const double* tau,
+                              const FactRep* rep, const double2* T, char* ws, hipStream_t s);
+hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many, int nk, int nblk, int mi, bool real,
+                         char* ws, hipStream_t s);
+hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int num_wg, int mi, bool real,
+                          int gr, const FactRep* rep, const char* ws, void* H, void* S, hipStream_t s);
 // XL[r][G] = lam[r] X[r][G] for r < rows.
 hipError_t launch_scale_rows(const double2* X, const double* lam, int rows, int n_pad, double2* XL, hipStream_t s);
-// Upper triangles of H = sum_t P_t * (W0_t^H Y0_t), S = sum_t P_t * (W0_t^H Lam_t W0_t), P_t = E_t^H E_t,
-// from the per-type row blocks of X, XL = lam X and Yx (nch chunks of 16 rows, kinds in kind[]).
-hipError_t launch_hs_fact(const double2* X, const double2* XL, const double2* Yx, const int* kind, int nch, int n,
-                          int n_pad, int gr, double2* H, double2* S, int64_t ldh, hipStream_t s);
 
 // ---- the paper's algorithm on rocBLAS (baseline) ----
 int hsdla_blas_create(int device, void** handle, std::string& err);

@@ -49,13 +49,12 @@ struct hsbuild_s {
   hipEvent_t fork = nullptr, join[4] = {};
   hipGraphExec_t graph_exec = nullptr;
   hipEvent_t graph_done = nullptr;
-  BatchMeta* meta_host = nullptr;  // pinned, source of the graph's metadata upload
+  void* meta_host = nullptr;  // pinned, source of the graph's metadata upload (BatchMeta or FactK)
   int meta_cap = 0;
   std::vector<double> key_f;
   std::vector<int64_t> key_i;
   // real-symmetric path: pinned sources of the representative upload and its completion event
-  int32_t* rep_host = nullptr;
-  double* repw_host = nullptr;
+  FactRep* rep_host = nullptr;
   hipEvent_t rep_done = nullptr;
   bool rep_pending = false;
   // BLAS baseline: rocBLAS handle (created on first use) and its device-memory need per basis size
@@ -104,14 +103,81 @@ hipError_t static_scratch(int dev, void** out) {
   return hipSuccess;
 }
 
-// Rows of the factored layout: per type with atoms, round16(N_t) phase rows and round16(2 N_L) W0 rows.
-int fact_rows(const hsbuild_s& h) {
+// ---- type-factored form ----
+
+// The types of `cell` with atoms (the real form's cell holds the representatives).
+FactCell fact_cell(const CellArgs& cell) {
+  FactCell c{};
+  std::memcpy(c.bvec, cell.bvec, sizeof c.bvec);
+  c.pre = cell.pre;
+  c.l_max = cell.l_max;
+  c.n_l = cell.n_l;
+  c.Mr = (int)round_up(2 * cell.n_l, kFactRows);
+  c.Mc = (int)round_up(2 * cell.n_l, 64);
   int rows = 0;
-  for (int t = 0; t < h.n_types; ++t) {
-    const int nt = h.cell.type_start[t + 1] - h.cell.type_start[t];
-    if (nt > 0) rows += (int)round_up(nt, 16) + (int)round_up(2 * h.n_l, 16);
+  for (int t = 0; t < cell.n_types; ++t) {
+    const int nt = cell.type_start[t + 1] - cell.type_start[t];
+    if (nt == 0) continue;
+    const int i = c.n_act++;
+    c.type[i] = t;
+    c.nat[i] = nt;
+    c.atom0[i] = cell.type_start[t];
+    c.eoff[i] = rows;
+    c.r_mt[i] = cell.r_mt[t];
+    rows += (int)round_up(nt, kFactRows);
   }
-  return rows;
+  return c;
+}
+
+int fact_phase_rows(const FactCell& c) {
+  return c.eoff[c.n_act - 1] + (int)round_up(c.nat[c.n_act - 1], kFactRows);
+}
+
+// Workspace of the factored form: what the k-points share, then each one's arrays.  Returns the end.
+// consts: offset of the uploaded type constants; ks[k].n is given.
+size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool real, size_t* consts, size_t* many,
+                   size_t* rep) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off = align256(off + bytes);
+    return o;
+  };
+  *consts = take(sizeof(TypeConsts));
+  c.TT = take((size_t)c.n_act * c.Mr * c.Mc * sizeof(double2));
+  c.lam = take((size_t)c.n_act * c.Mr * sizeof(double));
+  if (many) *many = take((size_t)n_k * sizeof(FactK));
+  if (rep) *rep = take((size_t)h.n_atoms * sizeof(FactRep));
+  for (int k = 0; k < n_k; ++k) {
+    FactK& f = ks[k];
+    f.n_pad = (int)round_up(f.n, 64);
+    const size_t np = (size_t)f.n_pad;
+    f.kv = (int64_t)take(np * 4 * sizeof(double));
+    f.R = (int64_t)take((size_t)c.n_act * c.Mr * np * sizeof(double));
+    f.Y = (int64_t)take((size_t)c.n_act * c.Mr * np * (real ? sizeof(double) : sizeof(double2)));
+    f.E = (int64_t)take((size_t)fact_phase_rows(c) * np * sizeof(double2));
+  }
+  return off;
+}
+
+size_t fact_bytes(const hsbuild_s& h, int ng, bool real) {
+  FactCell c = fact_cell(h.cell);
+  FactK f{};
+  f.n = ng;
+  size_t consts, rep;
+  return fact_layout(h, c, &f, 1, real, &consts, nullptr, real ? &rep : nullptr);
+}
+
+// The radial data by value; false if the types need more entries than RadialArgs holds.
+bool fact_radial(const hsbuild_s& h, const FactCell& c, RadialArgs& ra) {
+  const int nl1 = c.l_max + 1;
+  if (c.n_act * nl1 > kRadialArgs) return false;
+  for (int t = 0; t < c.n_act; ++t)
+    for (int l = 0; l < nl1; ++l) {
+      for (int q = 0; q < 4; ++q) ra.v[t * nl1 + l][q] = h.consts->radial[c.type[t]][l][q];
+      ra.v[t * nl1 + l][4] = h.consts->udot2[c.type[t]][l];
+    }
+  return true;
 }
 
 Layout make_layout(const hsbuild_s& h, int ng, int mode) {
@@ -148,16 +214,8 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.end = off;
     return L;
   }
-  if (mode == HSB_MODE_FACTORED) {
-    L.R_f = fact_rows(h);
-    L.tau0 = take(4 * sizeof(double));
-    L.lamx = take((size_t)L.R_f * sizeof(double));
-    L.kind = take((size_t)(L.R_f / 16) * sizeof(int));
-    L.X = take((size_t)L.R_f * np * sizeof(double2));
-    L.XL = take((size_t)L.R_f * np * sizeof(double2));
-    L.Yx = take((size_t)L.R_f * np * sizeof(double2));
-    L.TT = take((size_t)h.n_types * tprod_kc(2 * h.n_l) * tprod_mp(2 * h.n_l) * sizeof(double2));
-    L.end = off;
+  if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && h.precision == HSB_FP64)) {
+    L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL);
     return L;
   }
   if (mode != HSB_MODE_COEFFICIENTS) {
@@ -166,7 +224,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.W = take((size_t)L.K_pad * np * sizeof(double2));
     L.Y = take((size_t)L.K_pad * np * sizeof(double2));
   }
-  if ((mode == HSB_MODE_FORWARD || mode == HSB_MODE_REAL) && h.precision == HSB_FP64)
+  if (mode == HSB_MODE_FORWARD && h.precision == HSB_FP64)
     L.WL = take((size_t)L.K_pad * np * sizeof(double2));
   if (mode == HSB_MODE_FORWARD && h.precision == HSB_FP64 && h.hs_waves == 8 && h.split_k == 1) {
     L.nsh = hs_stream_shares(L.n_pad, L.K_pad, h.num_cus);
@@ -207,8 +265,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.slY = take(planes);
   }
   if (mode == HSB_MODE_REAL) {
-    L.rep = take((size_t)h.n_atoms * sizeof(int32_t));
-    L.repw = take((size_t)h.n_atoms * sizeof(double));
+    L.rep = take((size_t)h.n_atoms * sizeof(FactRep));
     L.tau_rep = take((size_t)h.n_atoms * 3 * sizeof(double));
     L.wrow = take((size_t)L.K_pad * sizeof(double));
   }
@@ -701,7 +758,6 @@ void hsbuild_destroy(hsbuild_t h) {
     (void)hipEventDestroy(h->rep_done);
   }
   if (h->rep_host) (void)hipHostFree(h->rep_host);
-  if (h->repw_host) (void)hipHostFree(h->repw_host);
   if (h->meta_host) (void)hipHostFree(h->meta_host);
   if (h->consts) (void)hipHostFree(h->consts);
   delete h;
@@ -751,6 +807,67 @@ int hsbuild_coefficients(hsbuild_t h, const double k_frac[3], int32_t ng, const 
 }  // extern "C"
 
 namespace {
+
+// The representatives and their multiplicities into pinned memory (after the previous upload has
+// been consumed).
+int stage_reps(hsbuild_t h, const std::vector<int32_t>& rep, const std::vector<double>& wt) {
+  if (!h->rep_host) {
+    if (hipHostMalloc((void**)&h->rep_host, sizeof(FactRep) * h->n_atoms, hipHostMallocDefault) != hipSuccess ||
+        hipEventCreateWithFlags(&h->rep_done, hipEventDisableTiming) != hipSuccess)
+      return fail(h, HSB_ERR_DEVICE, "pinned buffer or event for the representatives");
+  }
+  if (h->rep_pending && hipEventSynchronize(h->rep_done) != hipSuccess)
+    return fail(h, HSB_ERR_DEVICE, "hipEventSynchronize failed");
+  h->rep_pending = false;
+  for (size_t i = 0; i < rep.size(); ++i) h->rep_host[i] = FactRep{wt[i], rep[i], 0};
+  return HSB_OK;
+}
+
+int upload_reps(hsbuild_t h, void* dst, int n_rep, hipStream_t s) {
+  hipError_t e = hipMemcpyAsync(dst, h->rep_host, sizeof(FactRep) * n_rep, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipEventRecord(h->rep_done, s);
+  if (e != hipSuccess) return launched(h, e, "upload of the representatives");
+  h->rep_pending = true;
+  return HSB_OK;
+}
+
+// The factored form of one k-point in the workspace w; real: on the representatives in `cell`, whose
+// atoms and multiplicities are uploaded from the handle's pinned list.
+int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double k_frac[3], int32_t ng,
+                     const int32_t* g, const double* tau, const void* T, void* H, void* S, char* w, hipStream_t s) {
+  FactCell c = fact_cell(cell);
+  FactK f{};
+  RadialArgs ra;
+  for (int i = 0; i < 3; ++i) f.kfrac[i] = k_frac[i];
+  f.n = ng;
+  size_t consts_off = 0, rep_off = 0;
+  fact_layout(*h, c, &f, 1, real, &consts_off, nullptr, real ? &rep_off : nullptr);
+  const FactRep* rep = nullptr;
+  int rc;
+  mark(h, 0, s);
+  if (real) {
+    if ((rc = upload_reps(h, w + rep_off, cell.n_atoms, s))) return rc;
+    rep = (const FactRep*)(w + rep_off);
+  }
+  const TypeConsts* consts = nullptr;
+  if (!fact_radial(*h, c, ra)) {
+    const hipError_t e = hipMemcpyAsync(w + consts_off, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, s);
+    if ((rc = launched(h, e, "upload of type constants"))) return rc;
+    consts = (const TypeConsts*)(w + consts_off);
+  }
+  const int mi = fact_block(fact_tiles(ng, 2), h->num_cus);
+  rc = launched(h, launch_fact_tables(c, ra, consts, f, nullptr, 1, f.n_pad / 64, g, tau, rep, (const double2*)T, w, s),
+                "k_fact_tables");
+  mark(h, 1, s);
+  if (!rc) rc = launched(h, launch_fact_y(c, f, nullptr, 1, f.n_pad / (32 * mi), mi, real, w, s), "k_fact_y");
+  mark(h, 2, s);
+  if (!rc)
+    rc = launched(h, launch_fact_hs(c, f, nullptr, 1, fact_tiles(ng, mi), mi, real, h->tile_group, rep, w, H, S, s),
+                  "k_fact_hs");
+  mark(h, 3, s);
+  mark(h, 4, s);
+  return rc;
+}
 
 // Body of hsbuild_forward and hsbuild_forward_static once the arguments and the
 // workspace `w` (L.end bytes) have been checked.
@@ -815,76 +932,7 @@ int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, co
   const Layout L = make_layout(*h, ng, HSB_MODE_FACTORED);
   if ((rc = check_ws(h, L, ws, ws_bytes))) return rc;
   if ((rc = check_device(h))) return rc;
-  hipStream_t s = (hipStream_t)stream;
-  char* w = (char*)ws;
-  const int64_t np = L.n_pad;
-  const int M = 2 * h->n_l, Mp = (int)round_up(M, 16);
-  double2* X = (double2*)(w + L.X);
-  double2* XL = (double2*)(w + L.XL);
-  double2* Yx = (double2*)(w + L.Yx);
-  mark(h, 0, s);
-  CellArgs c;
-  if ((rc = enqueue_tables(h, L, k_frac, g, w, s, c))) return rc;
-  const TypeConsts* dconsts = (const TypeConsts*)(w + L.consts);
-  rc = launched(h, launch_fact_rows(c, dconsts, L.R_f, (double*)(w + L.lamx), (int*)(w + L.kind), s), "k_fact_rows");
-  if (rc) return rc;
-  // origin of every type (phase 1): two zero double2 = four zero doubles
-  if ((rc = launched(h, launch_zero_rows((double2*)(w + L.tau0), 2, 0, 1, s), "k_zero_rows"))) return rc;
-  int base = 0;
-  for (int t = 0; t < h->n_types; ++t) {
-    const int a0 = c.type_start[t], nt = c.type_start[t + 1] - a0;
-    if (nt == 0) continue;
-    const int Ep = (int)round_up(nt, 16), rw = base + Ep;
-    // phase rows of the type's atoms, zero pad rows; Yx is zero on the whole phase block
-    rc = launched(h, launch_phases(nt, L.n_pad, (const double*)(w + L.kv), tau + 3 * a0, X + (int64_t)base * np, s),
-                  "k_phases");
-    if (!rc) rc = launched(h, launch_zero_rows(X, np, base + nt, rw, s), "k_zero_rows");
-    if (!rc) rc = launched(h, launch_zero_rows(Yx, np, base, rw, s), "k_zero_rows");
-    // W0_t: the type's coefficients at the origin (one-atom cell of type t), zero pad rows
-    CellArgs c1 = c;
-    c1.n_types = 1;
-    c1.n_atoms = 1;
-    c1.type_start[0] = 0;
-    c1.type_start[1] = 1;
-    c1.r_mt[0] = c.r_mt[t];
-    const double2* ab_t = (const double2*)(w + L.ab) + (int64_t)t * (h->l_max + 1) * np;
-    if (!rc)
-      rc = launched(h, launch_assemble(c1, L.n_pad, (const double2*)(w + L.ang), ab_t, (const double*)(w + L.kv),
-                                       (const double*)(w + L.tau0), X + (int64_t)rw * np, np, L.n_pad, s),
-                    "k_assemble");
-    if (!rc) rc = launched(h, launch_zero_rows(X, np, rw + M, rw + Mp, s), "k_zero_rows");
-    if (!rc) rc = launched(h, launch_zero_rows(Yx, np, rw + M, rw + Mp, s), "k_zero_rows");
-    if (rc) return rc;
-    base = rw + Mp;
-  }
-  mark(h, 1, s);
-  rc = launched(h, launch_tpad((const double2*)T, h->n_types, M, (double2*)(w + L.TT), s), "k_tpad");
-  if (rc) return rc;
-  base = 0;
-  for (int t = 0; t < h->n_types; ++t) {
-    const int nt = c.type_start[t + 1] - c.type_start[t];
-    if (nt == 0) continue;
-    const int rw = base + (int)round_up(nt, 16);
-    CellArgs c1 = c;
-    c1.n_types = 1;
-    c1.n_atoms = 1;
-    c1.type_start[0] = 0;
-    c1.type_start[1] = 1;
-    rc = launched(h, launch_tprod(c1, (const double2*)(w + L.TT) + (int64_t)t * tprod_kc(M) * tprod_mp(M),
-                                  X + (int64_t)rw * np, Yx + (int64_t)rw * np, L.n_pad, s),
-                  "k_tprod3m");
-    if (rc) return rc;
-    base = rw + Mp;
-  }
-  rc = launched(h, launch_scale_rows(X, (const double*)(w + L.lamx), L.R_f, L.n_pad, XL, s), "k_scale_rows");
-  if (rc) return rc;
-  mark(h, 2, s);
-  rc = launched(h, launch_hs_fact(X, XL, Yx, (const int*)(w + L.kind), L.R_f / 16, ng, L.n_pad, h->tile_group,
-                                  (double2*)H, (double2*)S, ng, s),
-                "k_hs_fact");
-  mark(h, 3, s);
-  mark(h, 4, s);
-  return rc;
+  return factored_enqueue(h, h->cell, false, k_frac, ng, g, tau, T, H, S, (char*)ws, (hipStream_t)stream);
 }
 
 int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
@@ -931,30 +979,16 @@ int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const 
   Layout Lr = L;  // the stacked rows of the representatives only
   Lr.K = 2 * n_rep * h->n_l;
   Lr.K_pad = stacked_pad(Lr.K);
-  Lr.WL = 0;  // lam W is formed below, after the pair weights are folded into lam
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
-  // upload the representatives from pinned memory (after the previous upload has been consumed)
-  if (!h->rep_host) {
-    if (hipHostMalloc((void**)&h->rep_host, sizeof(int32_t) * h->n_atoms, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&h->repw_host, sizeof(double) * h->n_atoms, hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&h->rep_done, hipEventDisableTiming) != hipSuccess)
-      return fail(h, HSB_ERR_DEVICE, "pinned buffer or event for the representatives");
-  }
-  if (h->rep_pending && hipEventSynchronize(h->rep_done) != hipSuccess)
-    return fail(h, HSB_ERR_DEVICE, "hipEventSynchronize failed");
-  h->rep_pending = false;
-  std::memcpy(h->rep_host, rep.data(), sizeof(int32_t) * n_rep);
-  std::memcpy(h->repw_host, wt.data(), sizeof(double) * n_rep);
+  if ((rc = stage_reps(h, rep, wt))) return rc;
+  if (h->precision == HSB_FP64) return factored_enqueue(h, crep, true, k_frac, ng, g, tau, T, H, S, w, s);
   mark(h, 0, s);
-  hipError_t e = hipMemcpyAsync(w + L.rep, h->rep_host, sizeof(int32_t) * n_rep, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(w + L.repw, h->repw_host, sizeof(double) * n_rep, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipEventRecord(h->rep_done, s);
-  if (e != hipSuccess) return launched(h, e, "upload of the representatives");
-  h->rep_pending = true;
+  if ((rc = upload_reps(h, w + L.rep, n_rep, s))) return rc;
+  const FactRep* drep = (const FactRep*)(w + L.rep);
   const int rows = 2 * h->n_l;
   double* tau_rep = (double*)(w + L.tau_rep);
-  rc = launched(h, launch_rep_setup(tau, (const int*)(w + L.rep), (const double*)(w + L.repw), n_rep, rows, 0,
+  rc = launched(h, launch_rep_setup(tau, drep, n_rep, rows, 0,
                                     tau_rep, nullptr, nullptr, s),
                 "k_rep_setup");
   if (rc) return rc;
@@ -963,22 +997,11 @@ int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const 
   double* lam = (double*)(w + L.lam);
   double* wrow = (double*)(w + L.wrow);
   double2* Y = (double2*)(w + L.Y);
-  rc = launched(h, launch_rep_setup(tau, (const int*)(w + L.rep), (const double*)(w + L.repw), n_rep, rows, Lr.K_pad,
+  rc = launched(h, launch_rep_setup(tau, drep, n_rep, rows, Lr.K_pad,
                                     tau_rep, wrow, lam, s),
                 "k_rep_setup");
   if (!rc) rc = launched(h, launch_scale_rows(Y, wrow, Lr.K_pad, L.n_pad, Y, s), "k_scale_rows");
-  if (!rc && (h->precision == HSB_SPLIT_INT8 || is_crt(h->precision))) {
-    rc = enqueue_split_real(h, Lr, w, H, S, s);
-  } else if (!rc) {
-    double2* WL = (double2*)(w + L.WL);  // S's right operand, lam W (lam with the pair weights)
-    rc = launched(h, launch_scale_rows((const double2*)(w + L.W), lam, Lr.K_pad, L.n_pad, WL, s), "k_scale_rows");
-    if (!rc)
-      rc = launched(h, launch_hs_fp64_real((const double2*)(w + L.W), WL, Y, lam, Lr.K_pad, ng, L.n_pad,
-                                           h->tile_group, h->hs_waves, H, S, ng, s),
-                    "k_hs_fp64 (real)");
-    mark(h, 3, s);
-    mark(h, 4, s);
-  }
+  if (!rc) rc = enqueue_split_real(h, Lr, w, H, S, s);
   return rc;
 }
 
@@ -1126,6 +1149,90 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
                   "k_gradtau");
 }
 
+}  // extern "C"
+
+namespace {
+
+// Records the batch graph's work on h->cap_stream: the stacked form (an option pins it).
+int record_stacked_batch(hsbuild_t h, const BatchLayout& B, int n_k, const double* k_frac, const int32_t* ng,
+                         const int32_t* g, const int64_t* out_off, const double* tau, const void* T, void* H, void* S,
+                         char* w) {
+  int rc;
+  BatchMeta* meta = (BatchMeta*)h->meta_host;
+  int total = 0;
+  for (int k = 0; k < n_k; ++k) {
+    BatchMeta& m = meta[k];
+    m.w_off = (int64_t)(B.W[k] / sizeof(double2));
+    m.wl_off = (int64_t)(B.WL[k] / sizeof(double2));
+    m.y_off = (int64_t)(B.Y[k] / sizeof(double2));
+    m.out_off = out_off[k];
+    m.n = ng[k];
+    m.n_pad = B.n_pad[k];
+    m.nbr = B.n_pad[k] / kTileN;
+    m.tile_start = total;
+    total += hs_tiles(B.n_pad[k]);
+  }
+  for (int b = 0; b < kBranches; ++b) {
+    if (!h->aux[b] && hipStreamCreateWithFlags(&h->aux[b], hipStreamNonBlocking) != hipSuccess)
+      return fail(h, HSB_ERR_DEVICE, "hipStreamCreateWithFlags failed");
+    if (!h->join[b] && hipEventCreateWithFlags(&h->join[b], hipEventDisableTiming) != hipSuccess)
+      return fail(h, HSB_ERR_DEVICE, "hipEventCreate failed");
+  }
+  if (!h->fork && hipEventCreateWithFlags(&h->fork, hipEventDisableTiming) != hipSuccess)
+    return fail(h, HSB_ERR_DEVICE, "hipEventCreate failed");
+  hipStream_t cs = h->cap_stream;
+  if (hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) != hipSuccess)
+    return fail(h, HSB_ERR_DEVICE, "hipStreamBeginCapture failed");
+  rc = HSB_OK;
+  // shared inputs once: type constants and lam; then the k-points' operands in parallel branches
+  hipError_t ef = hipMemcpyAsync(w + B.consts, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, cs);
+  if (ef == hipSuccess) ef = launch_lambda(h->cell, (const TypeConsts*)(w + B.consts), B.K_pad, (double*)(w + B.lam), cs);
+  if (ef == hipSuccess) ef = launch_tpad((const double2*)T, h->n_types, 2 * h->n_l, (double2*)(w + B.TT), cs);
+  if (ef == hipSuccess) ef = hipEventRecord(h->fork, cs);
+  for (int b = 0; b < kBranches && ef == hipSuccess; ++b) ef = hipStreamWaitEvent(h->aux[b], h->fork, 0);
+  if (ef != hipSuccess) rc = launched(h, ef, "batch graph fork");
+  std::vector<int64_t> g_rows(n_k, 0);
+  for (int k = 1; k < n_k; ++k) g_rows[k] = g_rows[k - 1] + ng[k - 1];
+  for (int k = 0; k < n_k && rc == HSB_OK; ++k) {
+    const int b = k % kBranches;
+    Layout L;
+    L.n = ng[k];
+    L.n_pad = B.n_pad[k];
+    L.K = B.K;
+    L.K_pad = B.K_pad;
+    L.consts = B.consts;
+    L.lam = B.lam;
+    L.TT = B.TT;
+    L.kv = B.kv[b];
+    L.ang = B.ang[b];
+    L.ab = B.ab[b];
+    L.W = B.W[k];
+    L.WL = B.WL[k];
+    L.Y = B.Y[k];
+    rc = enqueue_operands(h, L, k_frac + 3 * k, g + 3 * g_rows[k], tau, T, w, h->aux[b], nullptr, true);
+  }
+  for (int b = 0; b < kBranches; ++b) {  // join every branch back, also after an error
+    hipError_t ej = hipEventRecord(h->join[b], h->aux[b]);
+    if (ej == hipSuccess) ej = hipStreamWaitEvent(cs, h->join[b], 0);
+    if (ej != hipSuccess && rc == HSB_OK) rc = launched(h, ej, "batch graph join");
+  }
+  if (rc == HSB_OK) {
+    hipError_t e = hipMemcpyAsync(w + B.meta, meta, sizeof(BatchMeta) * n_k, hipMemcpyHostToDevice, cs);
+    if (e == hipSuccess) {
+      const int grid = std::max(8, (h->num_cus / 8) * 8);  // one workgroup per CU, a multiple of 8
+      e = launch_hs_fp64_batch((const double2*)w, (const double*)(w + B.lam), B.K_pad,
+                               (const BatchMeta*)(w + B.meta), n_k, total, grid, h->tile_group, h->hs_waves,
+                               (double2*)H, (double2*)S, cs);
+    }
+    if (e != hipSuccess) rc = launched(h, e, "batched contraction");
+  }
+  return rc;
+}
+
+}  // namespace
+
+extern "C" {
+
 int hsbuild_batch(hsbuild_t h, int32_t n_k, const double* k_frac, const int32_t* ng, const int32_t* g,
                   const int64_t* out_off, const double* tau, const void* T, void* H, void* S, void* ws,
                   size_t ws_bytes, void* stream) {
@@ -1177,82 +1284,18 @@ int hsbuild_batch(hsbuild_t h, int32_t n_k, const double* k_frac, const int32_t*
       if (h->meta_host) (void)hipHostFree(h->meta_host);
       h->meta_host = nullptr;
       h->meta_cap = 0;
-      if (hipHostMalloc((void**)&h->meta_host, sizeof(BatchMeta) * n_k, hipHostMallocDefault) != hipSuccess)
+      if (hipHostMalloc(&h->meta_host, std::max(sizeof(BatchMeta), sizeof(FactK)) * n_k, hipHostMallocDefault) != hipSuccess)
         return fail(h, HSB_ERR_DEVICE, "pinned host allocation failed");
       h->meta_cap = n_k;
     }
-    int total = 0;
-    for (int k = 0; k < n_k; ++k) {
-      BatchMeta& m = h->meta_host[k];
-      m.w_off = (int64_t)(B.W[k] / sizeof(double2));
-      m.wl_off = (int64_t)(B.WL[k] / sizeof(double2));
-      m.y_off = (int64_t)(B.Y[k] / sizeof(double2));
-      m.out_off = out_off[k];
-      m.n = ng[k];
-      m.n_pad = B.n_pad[k];
-      m.nbr = B.n_pad[k] / kTileN;
-      m.tile_start = total;
-      total += hs_tiles(B.n_pad[k]);
-    }
-    for (int b = 0; b < kBranches; ++b) {
-      if (!h->aux[b] && hipStreamCreateWithFlags(&h->aux[b], hipStreamNonBlocking) != hipSuccess)
-        return fail(h, HSB_ERR_DEVICE, "hipStreamCreateWithFlags failed");
-      if (!h->join[b] && hipEventCreateWithFlags(&h->join[b], hipEventDisableTiming) != hipSuccess)
-        return fail(h, HSB_ERR_DEVICE, "hipEventCreate failed");
-    }
-    if (!h->fork && hipEventCreateWithFlags(&h->fork, hipEventDisableTiming) != hipSuccess)
-      return fail(h, HSB_ERR_DEVICE, "hipEventCreate failed");
-    hipStream_t cs = h->cap_stream;
-    if (hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) != hipSuccess)
-      return fail(h, HSB_ERR_DEVICE, "hipStreamBeginCapture failed");
-    char* w = (char*)ws;
-    rc = HSB_OK;
     h->capturing = true;
-    // shared inputs once: type constants and lam; then the k-points' operands in parallel branches
-    hipError_t ef = hipMemcpyAsync(w + B.consts, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, cs);
-    if (ef == hipSuccess) ef = launch_lambda(h->cell, (const TypeConsts*)(w + B.consts), B.K_pad, (double*)(w + B.lam), cs);
-    if (ef == hipSuccess) ef = launch_tpad((const double2*)T, h->n_types, 2 * h->n_l, (double2*)(w + B.TT), cs);
-    if (ef == hipSuccess) ef = hipEventRecord(h->fork, cs);
-    for (int b = 0; b < kBranches && ef == hipSuccess; ++b) ef = hipStreamWaitEvent(h->aux[b], h->fork, 0);
-    if (ef != hipSuccess) rc = launched(h, ef, "batch graph fork");
-    std::vector<int64_t> g_rows(n_k, 0);
-    for (int k = 1; k < n_k; ++k) g_rows[k] = g_rows[k - 1] + ng[k - 1];
-    for (int k = 0; k < n_k && rc == HSB_OK; ++k) {
-      const int b = k % kBranches;
-      Layout L;
-      L.n = ng[k];
-      L.n_pad = B.n_pad[k];
-      L.K = B.K;
-      L.K_pad = B.K_pad;
-      L.consts = B.consts;
-      L.lam = B.lam;
-      L.TT = B.TT;
-      L.kv = B.kv[b];
-      L.ang = B.ang[b];
-      L.ab = B.ab[b];
-      L.W = B.W[k];
-      L.WL = B.WL[k];
-      L.Y = B.Y[k];
-      rc = enqueue_operands(h, L, k_frac + 3 * k, g + 3 * g_rows[k], tau, T, w, h->aux[b], nullptr, true);
-    }
-    for (int b = 0; b < kBranches; ++b) {  // join every branch back, also after an error
-      hipError_t ej = hipEventRecord(h->join[b], h->aux[b]);
-      if (ej == hipSuccess) ej = hipStreamWaitEvent(cs, h->join[b], 0);
-      if (ej != hipSuccess && rc == HSB_OK) rc = launched(h, ej, "batch graph join");
-    }
-    if (rc == HSB_OK) {
-      hipError_t e = hipMemcpyAsync(w + B.meta, h->meta_host, sizeof(BatchMeta) * n_k, hipMemcpyHostToDevice, cs);
-      if (e == hipSuccess) {
-        const int grid = std::max(8, (h->num_cus / 8) * 8);  // one workgroup per CU, a multiple of 8
-        e = launch_hs_fp64_batch((const double2*)w, (const double*)(w + B.lam), B.K_pad,
-                                 (const BatchMeta*)(w + B.meta), n_k, total, grid, h->tile_group, h->hs_waves,
-                                 (double2*)H, (double2*)S, cs);
-      }
-      if (e != hipSuccess) rc = launched(h, e, "batched contraction");
-    }
-    hipGraph_t graph = nullptr;
-    const hipError_t ec = hipStreamEndCapture(cs, &graph);
+    rc = record_stacked_batch(h, B, n_k, k_frac, ng, g, out_off, tau, T, H, S, (char*)ws);
     h->capturing = false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    (void)hipStreamIsCapturing(h->cap_stream, &cap);
+    if (cap == hipStreamCaptureStatusNone) return rc;  // the capture was not begun
+    hipGraph_t graph = nullptr;
+    const hipError_t ec = hipStreamEndCapture(h->cap_stream, &graph);
     if (rc != HSB_OK) {
       if (graph) (void)hipGraphDestroy(graph);
       return rc;

@@ -1,28 +1,33 @@
-// Type-factored ("compressed") H and S (the compression of A and B that
-// Sec. 7 names as future work, worked out for the stacked form of Eqs. 6-7).
+// Type-factored H and S (the compression of A and B that Sec. 7 names as future work).
 //
-// Every coefficient of atom a (type t) is its type's coefficient at the origin
-// times the atom's structure phase: W_a[k][G] = E_a(G) W0_t[k][G] with
-// E_a(G) = e^{i K_G . tau_a} and k = (A|B, L).  Because T and the radial data are
-// per type, the atom sum of Eqs. 4-5 factors entry by entry:
+// Every coefficient of atom a (type t) is its type's coefficient at the origin times the atom's
+// structure phase, W_a[k][G] = E_a(G) W0_t[k][G], E_a(G) = e^{i K_G . tau_a}, k = (A|B, l, m).
+// T and the radial data are per type, so the atom sums of Eqs. 4-5 factor entry by entry:
 //
-//   H[G'][G] = sum_t P_t[G'][G] (W0_t^H Y0_t)[G'][G],        Y0_t = T_t W0_t
-//   S[G'][G] = sum_t P_t[G'][G] (W0_t^H Lam_t W0_t)[G'][G]
-//   P_t[G'][G] = sum_{a in t} conj(E_a(G')) E_a(G)
+//   H = sum_t P_t .* (W0_t^H T_t W0_t),  S = sum_t P_t .* (W0_t^H Lam_t W0_t),
+//   P_t[G'][G] = sum_{a in t} conj(E_a(G')) E_a(G).
 //
-// so the contraction width per entry drops from 4 N_atoms N_L (the stacked
-// form) to sum_t (N_t + 4 N_L), plus one complex product per type.
+// W0_t is real up to a unitary map of m at fixed l: with the real harmonics s_{l,mu} of K_hat,
+// i^l conj(Y_lm) = sum_mu c(l,m,mu) s_{l,mu}.  So with R_t[(X,l,mu)][G] = pre x_l(G) s_{l,mu}(G)
+// (real; X = A|B, x_l = a_l|b_l) and T'_t = C^H T_t C,
 //
-// One workgroup per 64 x 64 tile of the upper triangle, 8 waves of 32 x 16
-// (two waves per SIMD).  Per type the tile first contracts the phases (K = N_t
-// rows of E), then W0_t against Y0_t and Lam_t W0_t together (K = 2 N_L, the
-// left operand shared), and folds M_H * P and M_S * P into the running H and S
-// tiles in registers; nothing but the final tile goes back to HBM.  All
-// contractions are complex FP64 on v_mfma_f64_16x16x4f64; rows are copied 16 at
-// a time straight into double-buffered LDS (global_load_lds, no staging
-// registers), the next chunk's copies issued while the current one is
-// contracted; the next chunk may belong to the next phase or type.
+//   W0^H T W0 = R^T (T' R),   W0^H Lam W0 = R^T (Lam R)   (Lam depends on l only),
+//
+// i.e. two real products per H entry and one per S entry and row, where the complex form takes
+// three and three (3M) and stages complex operands.
+//
+//   k_fact_tables  K vectors, phases E, R, and T' per type (one launch, blocks by role)
+//   k_fact_y       Y_t = T'_t R_t
+//   k_fact_hs      the upper triangles of H and S
+//
+// The wave-tile products run on v_mfma_f64_16x16x4f64 with both operands read straight from
+// global memory into registers, one chunk ahead: one MFMA takes 64 cycles of its SIMD, so a wave
+// tile of 2 x 2 blocks needs 72 bytes per lane every 768 cycles, which the vector caches deliver
+// without LDS, and waves need no barrier: they start, run ahead and leave on their own (a wave
+// below the diagonal leaves at once).  A lane holds pairs of neighbouring columns, one for each of
+// its two blocks (16-byte loads, 32-byte stores): block i of a wave covers the columns of parity i.
 #include "hs_internal.h"
+#include "special.h"
 #include "tiles.h"
 
 namespace hsb {
@@ -32,64 +37,457 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-constexpr int FM = 64, FK = 16, FNT = 512;
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
 
-// E[a][G] = e^{i K_G . tau_a} for every atom; one thread per G.
-__global__ void __launch_bounds__(256) k_phases(int n_atoms, int n_pad, const double* __restrict__ kv,
-                                                const double* __restrict__ tau, double2* __restrict__ E) {
-  const int G = blockIdx.x * blockDim.x + threadIdx.x;
-  if (G >= n_pad) return;
-  const double kx = kv[4 * (int64_t)G + 0], ky = kv[4 * (int64_t)G + 1], kz = kv[4 * (int64_t)G + 2];
-  for (int a = blockIdx.y; a < n_atoms; a += gridDim.y) {
-    double s, c;
-    sincos(kx * tau[3 * a + 0] + ky * tau[3 * a + 1] + kz * tau[3 * a + 2], &s, &c);
-    E[(int64_t)a * n_pad + G] = make_double2(c, s);
+// c(l,m,mu): the coefficient of s_{l,mu} in i^l conj(Y_lm); nonzero for |m| = |mu| only.  Without
+// its factor 1/sqrt(2) (m != 0) it is a power of i times a sign: power e of i.
+__device__ inline int harmonic_power(int l, int m, int mu) {
+  // m > 0: c = i^l (s_m - i s_-m);  m < 0: c = (-1)^m i^l (s_|m| + i s_-|m|)
+  int e = l;
+  if (m < 0 && (m & 1)) e += 2;
+  if (mu < 0) e += m > 0 ? 3 : 1;
+  return e & 3;
+}
+
+__device__ inline double2 times_i(double2 v, int e) {
+  switch (e & 3) {
+    case 0: return v;
+    case 1: return make_double2(-v.y, v.x);
+    case 2: return make_double2(-v.x, -v.y);
+    default: return make_double2(v.y, -v.x);
   }
 }
 
-// Row metadata of the factored layout (rows type by type: E block, then W0 block,
-// each padded to 16): lamx[r] (1 on E rows and A rows, ||udot_l||^2 on B rows,
-// 0 on pad rows) and kind[] of each 16-row chunk.
-__global__ void __launch_bounds__(256) k_fact_rows(CellArgs c, const TypeConsts* __restrict__ consts, int rows,
-                                                   double* __restrict__ lamx, int* __restrict__ kind) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  const int K = 2 * c.n_l, Mp = (K + FK - 1) / FK * FK;
-  int base = 0, t = 0, nt = 0, Ep = 0;
-  for (t = 0; t < c.n_types; ++t) {
-    nt = c.type_start[t + 1] - c.type_start[t];
-    if (nt == 0) continue;
-    Ep = (nt + FK - 1) / FK * FK;
-    if (r < base + Ep + Mp) break;
-    base += Ep + Mp;
+__device__ inline void lm_of(int L, int& l, int& m) {
+  l = (int)sqrt((double)L + 0.5);
+  m = L - l * l - l;
+}
+
+__device__ inline int find_block(const FactK* ks, int nk, int b, int FactK::*first) {
+  int lo = 0, hi = nk - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (ks[mid].*first <= b) lo = mid;
+    else hi = mid - 1;
   }
-  const int rr = r - base;  // base is a multiple of 16
-  double lam;
-  int kd;
-  int valid;  // data rows in this row's chunk
-  if (rr < Ep) {
-    lam = rr < nt ? 1.0 : 0.0;
-    kd = rr / FK == Ep / FK - 1 ? 3 : 0;
-    valid = min(FK, nt - rr / FK * FK);
-  } else {
-    const int m = rr - Ep;
-    if (m < c.n_l) {
-      lam = 1.0;
-    } else if (m < K) {
-      const int L = m - c.n_l;
-      int l = 0;
-      while ((l + 1) * (l + 1) <= L) ++l;
-      lam = consts->udot2[t][l];
-    } else {
-      lam = 0.0;
+  return lo;
+}
+
+constexpr int kTabG = 64;  // columns per workgroup of k_fact_tables
+
+// Blocks x < ngb: type blockIdx.y's R rows and phases (and, for the first type, the K vectors) of 64
+// columns; blocks past them: T'.  Latency-bound (a few hundred workgroups of short serial
+// recurrences), so the recurrences are spread over the workgroup: wave 0 runs the backward Bessel
+// recurrence of its 64 columns while waves 1 to 3 run the power series (columns with x < 2; l
+// dealt over the waves) and the Legendre recurrences (m dealt over the waves), whose coefficients
+// are compile-time tables.
+__global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, const TypeConsts* __restrict__ consts,
+                                                     FactK one, const FactK* __restrict__ many, int nk, int ngb,
+                                                     const int32_t* __restrict__ g, const double* __restrict__ tau,
+                                                     const FactRep* __restrict__ rep, const double2* __restrict__ T,
+                                                     char* __restrict__ ws) {
+  extern __shared__ double sh[];
+  const int t = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int lmax = c.l_max, nl1 = lmax + 1;
+  if ((int)blockIdx.x >= ngb) {  // T'[r][k], stored [k][r] zero-padded, and lam
+    const int64_t e = (int64_t)(blockIdx.x - ngb) * 256 + tid;
+    const int k = (int)(e / c.Mc), r = (int)(e % c.Mc);
+    if (k >= c.Mr) return;
+    const int M = 2 * c.n_l;
+    double2 v = make_double2(0.0, 0.0);
+    if (k < M && r < M) {
+      const int xr = r >= c.n_l, xk = k >= c.n_l;
+      int lr, mr, lk, mk;
+      lm_of(r - xr * c.n_l, lr, mr);
+      lm_of(k - xk * c.n_l, lk, mk);
+      const double2* Tt = T + (int64_t)c.type[t] * M * M;
+      const int br = xr * c.n_l + lr * lr + lr, bk = xk * c.n_l + lk * lk + lk;
+      for (int ir = 0; ir < (mr ? 2 : 1); ++ir)
+        for (int ik = 0; ik < (mk ? 2 : 1); ++ik) {
+          const int m1 = ir ? -mr : mr, m2 = ik ? -mk : mk;
+          const double2 x = times_i(Tt[(int64_t)(br + m1) * M + bk + m2],
+                                    harmonic_power(lk, m2, mk) - harmonic_power(lr, m1, mr));
+          v.x += x.x;
+          v.y += x.y;
+        }
+      if (mr && mk) {
+        v.x *= 0.5; v.y *= 0.5;
+      } else if (mr || mk) {
+        v.x *= 0.70710678118654752440; v.y *= 0.70710678118654752440;
+      }
     }
-    kd = m / FK == Mp / FK - 1 ? 2 : 1;
-    valid = min(FK, K - m / FK * FK);
+    ((double2*)(ws + c.TT))[((int64_t)t * c.Mr + k) * c.Mc + r] = v;
+    if (r == 0) {
+      double lam = 0.0;
+      if (k < c.n_l) lam = 1.0;
+      else if (k < M) {
+        int l, m;
+        lm_of(k - c.n_l, l, m);
+        lam = consts ? consts->udot2[c.type[t]][l] : ra.v[t * nl1 + l][4];
+      }
+      ((double*)(ws + c.lam))[t * c.Mr + k] = lam;
+    }
+    return;
   }
-  kd |= ((valid + 3) / 4 - 1) << 2;
-  lamx[r] = lam;
-  if (rr % FK == 0) kind[r / FK] = kd;
+  const FactK& kk = many ? many[find_block(many, nk, blockIdx.x, &FactK::gblk0)] : one;
+  const int64_t n_pad = kk.n_pad;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = (blockIdx.x - kk.gblk0) * kTabG + lane;
+  const bool valid = G < kk.n;
+  double* ang = sh;                            // [n_l][64] real harmonics times pre
+  double* jl = ang + c.n_l * kTabG;            // [l_max + 2][64]
+  double* ab = jl + (lmax + 2) * kTabG;        // [2][l_max + 1][64]
+  double kx = 0.0, ky = 0.0, kz = 0.0;
+  if (valid) {
+    const int32_t* gi = g + 3 * (kk.g_row + G);
+    const double n0 = gi[0] + kk.kfrac[0], n1 = gi[1] + kk.kfrac[1], n2 = gi[2] + kk.kfrac[2];
+    kx = n0 * c.bvec[0] + n1 * c.bvec[3] + n2 * c.bvec[6];
+    ky = n0 * c.bvec[1] + n1 * c.bvec[4] + n2 * c.bvec[7];
+    kz = n0 * c.bvec[2] + n1 * c.bvec[5] + n2 * c.bvec[8];
+  }
+  const double kn = sqrt(kx * kx + ky * ky + kz * kz);
+  const double x = kn * c.r_mt[t];
+  if (wave == 0) {
+    if (t == 0) {
+      double* kv = (double*)(ws + kk.kv);
+      kv[4 * G + 0] = kx; kv[4 * G + 1] = ky; kv[4 * G + 2] = kz; kv[4 * G + 3] = kn;
+    }
+    if (!(x < 2.0)) sph_bessel_back(lmax + 1, x, jl + lane, kTabG);
+  } else {
+    if (x < 2.0) {
+      for (int l = wave - 1; l <= lmax + 1; l += 3) jl[l * kTabG + lane] = sph_bessel_series(l, x);
+    }
+    double ct = 1.0, wr = 0.0, wi = 0.0;
+    if (!(kn < 1e-12)) {
+      const double r = 1.0 / kn;
+      ct = kz * r; wr = kx * r; wi = ky * r;
+    }
+    double pr = c.pre, pi = 0.0;  // pre w^m
+    int mp = 0;
+    for (int m = wave - 1; m <= lmax; m += 3) {
+      for (; mp < m; ++mp) {
+        const double q = pr * wr - pi * wi;
+        pi = pr * wi + pi * wr;
+        pr = q;
+      }
+      const double f = m ? 1.41421356237309504880 : 1.0;
+      const double sr = f * pr, si = f * pi;
+      double p0 = 0.0, p1 = kLegendre.diag[m];
+      for (int l = m; l <= lmax; ++l) {
+        if (l > m) {
+          const double q = kLegendre.a[l][m] * (ct * p1 - kLegendre.b[l][m] * p0);
+          p0 = p1;
+          p1 = q;
+        }
+        ang[(l * l + l + m) * kTabG + lane] = p1 * sr;
+        if (m) ang[(l * l + l - m) * kTabG + lane] = p1 * si;
+      }
+    }
+  }
+  __syncthreads();
+  for (int l = wave; l <= lmax; l += 4) {
+    double u, du, ud, dud;
+    if (consts) {
+      const double* q = consts->radial[c.type[t]][l];
+      u = q[0]; du = q[1]; ud = q[2]; dud = q[3];
+    } else {
+      const double* q = ra.v[t * nl1 + l];
+      u = q[0]; du = q[1]; ud = q[2]; dud = q[3];
+    }
+    const double det = u * dud - ud * du;
+    const double val = jl[l * kTabG + lane];
+    const double up = jl[(l + 1) * kTabG + lane];
+    const double dj = l ? (l * jl[(l - 1) * kTabG + lane] - (l + 1) * up) / (2.0 * l + 1.0) : -up;
+    const double slope = kn * dj;
+    ab[l * kTabG + lane] = (val * dud - ud * slope) / det;
+    ab[(nl1 + l) * kTabG + lane] = (u * slope - du * val) / det;
+  }
+  __syncthreads();
+  double* R = (double*)(ws + kk.R) + (int64_t)t * c.Mr * n_pad + G;
+  for (int L = wave; L < c.n_l; L += 4) {
+    int l, m;
+    lm_of(L, l, m);
+    const double s = ang[L * kTabG + lane];
+    R[(int64_t)L * n_pad] = valid ? s * ab[l * kTabG + lane] : 0.0;
+    R[(int64_t)(c.n_l + L) * n_pad] = valid ? s * ab[(nl1 + l) * kTabG + lane] : 0.0;
+  }
+  for (int r = 2 * c.n_l + wave; r < c.Mr; r += 4) R[(int64_t)r * n_pad] = 0.0;
+  double2* E = (double2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad + G;
+  const int nt = c.nat[t], erows = (nt + kFactRows - 1) / kFactRows * kFactRows;
+  for (int a = wave; a < erows; a += 4) {
+    double2 v = make_double2(0.0, 0.0);
+    if (a < nt && valid) {
+      const int at = rep ? rep[c.atom0[t] + a].atom : c.atom0[t] + a;
+      double s, q;
+      sincos(kx * tau[3 * at + 0] + ky * tau[3 * at + 1] + kz * tau[3 * at + 2], &s, &q);
+      v = make_double2(q, s);
+    }
+    E[(int64_t)a * n_pad] = v;
+  }
+}
+
+// A lane's values of N neighbouring columns, as one load.
+template <int N>
+struct DVec;
+template <>
+struct DVec<1> { typedef double T; static __device__ double get(T v, int) { return v; } };
+template <>
+struct DVec<2> { typedef d2 T; static __device__ double get(T v, int i) { return v[i]; } };
+
+// Y_t = T'_t R_t (real parts only if REAL): workgroup of 2 x 2 waves, each 16 MI rows x 16 NJ columns.
+template <int MI, int NJ, bool REAL>
+__global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
+                                                   char* __restrict__ ws) {
+  constexpr int KC = 2;
+  const FactK& kk = many ? many[find_block(many, nk, blockIdx.x, &FactK::yblk0)] : one;
+  const int t = blockIdx.z;
+  const int64_t n_pad = kk.n_pad;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.y * 32 * MI + (wave >> 1) * 16 * MI;
+  const int col0 = (blockIdx.x - kk.yblk0) * 32 * NJ + (wave & 1) * 16 * NJ;
+  if (row0 >= c.Mr || col0 >= kk.n) return;
+  const d2* tp = (const d2*)(ws + c.TT) + ((int64_t)t * c.Mr + lk) * c.Mc + row0 + MI * lr;
+  const double* rp = (const double*)(ws + kk.R) + ((int64_t)t * c.Mr + lk) * n_pad + col0 + NJ * lr;
+  typedef typename DVec<NJ>::T VB;
+  d4 re[MI][NJ], im[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) re[i][j] = im[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  d2 a[KC][MI], an[KC][MI];
+  VB b[KC], bn[KC];
+  auto load = [&](int ch, d2 (&av)[KC][MI], VB (&bv)[KC]) {
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      const int64_t k = (int64_t)(ch * KC + q) * 4;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) av[q][i] = tp[k * c.Mc + i];
+      bv[q] = *(const VB*)(rp + k * n_pad);
+    }
+  };
+  const int nch = c.Mr / (4 * KC);
+  load(0, a, b);
+  for (int ch = 0; ch < nch; ++ch) {
+    load(ch + 1 < nch ? ch + 1 : ch, an, bn);
+#pragma unroll
+    for (int q = 0; q < KC; ++q)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const double bj = DVec<NJ>::get(b[q], j);
+          re[i][j] = MFMA(a[q][i].x, bj, re[i][j]);
+          if constexpr (!REAL) im[i][j] = MFMA(a[q][i].y, bj, im[i][j]);
+        }
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      b[q] = bn[q];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) a[q][i] = an[q][i];
+    }
+  }
+  // D layout of the 16x16 f64 MFMA: lane l, element q -> row l/16 + 4q, column l%16
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = row0 + MI * (lk + 4 * q) + i;
+      if (row >= c.Mr) continue;
+      const int64_t o = ((int64_t)t * c.Mr + row) * n_pad + col0 + NJ * lr;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if constexpr (REAL) ((double*)(ws + kk.Y))[o + j] = re[i][j][q];
+        else ((d2*)(ws + kk.Y))[o + j] = d2{re[i][j][q], im[i][j][q]};
+      }
+    }
+}
+
+// Upper triangles of H and S: workgroup of 2 x 2 waves, each one wave tile of 16 MI rows (G') x
+// 16 NJ columns (G).  Per type: P_t over the phase rows (complex, three real products:
+// P1 = a_r b_r, P2 = a_i b_i, P3 = (a_r - a_i)(b_r + b_i), Re = P1 + P2, Im = P3 - P1 + P2; the
+// real form two, into one sum, the columns' phases weighted with the atom's multiplicity), then
+// the sums over the R rows (H: R^T Y, S: R^T lam R) in the same registers, then P_t times the sums
+// into the running H and S.
+template <int MI, int NJ, int KC, int WPS, bool REAL>
+__global__ void __launch_bounds__(256, WPS) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
+                                                      int num_wg, int gr, const FactRep* __restrict__ rep,
+                                                      const char* __restrict__ ws, void* __restrict__ H,
+                                                      void* __restrict__ S) {
+  static_assert(kFactRows % (4 * KC) == 0, "rows are padded to whole chunks");
+  int start, len;
+  xcd_range(blockIdx.x % kXcds, num_wg, start, len);
+  const int w = start + blockIdx.x / kXcds;
+  const FactK& kk = many ? many[find_block(many, nk, w, &FactK::tile0)] : one;
+  const int n = kk.n;
+  const int64_t n_pad = kk.n_pad;
+  const int nb = (n + 32 * MI - 1) / (32 * MI);
+  int bi, bj;
+  if (gr > 0) grouped_decode(w - kk.tile0, nb, gr, bi, bj);
+  else tri_decode(w - kk.tile0, nb, bi, bj);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int row0 = bi * 32 * MI + (wave >> 1) * 16 * MI, col0 = bj * 32 * NJ + (wave & 1) * 16 * NJ;
+  if (row0 >= n || col0 >= n || col0 + 16 * NJ <= row0) return;
+
+  typedef typename DVec<MI>::T VA;
+  typedef typename DVec<NJ>::T VB;
+  struct EChunk { d2 a[KC][MI], b[KC][NJ]; double w[KC]; };
+  struct MChunk { VA a[KC]; VB b[KC]; VB yr[KC]; d2 y[KC][NJ]; double lam[KC]; };
+  const int row = row0 + MI * lr, col = col0 + NJ * lr;
+  auto load_e = [&](int t, int ch, EChunk& e) {
+    const d2* base = (const d2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad;
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      const int k = (ch * KC + q) * 4 + lk;
+      const d2* p = base + (int64_t)k * n_pad;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) e.a[q][i] = p[row + i];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) e.b[q][j] = p[col + j];
+      if constexpr (REAL) e.w[q] = k < c.nat[t] ? rep[c.atom0[t] + k].weight : 0.0;
+    }
+  };
+  auto load_m = [&](int t, int ch, MChunk& m) {
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      const int64_t k = (int64_t)t * c.Mr + (ch * KC + q) * 4 + lk;
+      const double* p = (const double*)(ws + kk.R) + k * n_pad;
+      m.a[q] = *(const VA*)(p + row);
+      m.b[q] = *(const VB*)(p + col);
+      m.lam[q] = ((const double*)(ws + c.lam))[k];
+      if constexpr (REAL) {
+        m.yr[q] = *(const VB*)((const double*)(ws + kk.Y) + k * n_pad + col);
+      } else {
+        const d2* yp = (const d2*)(ws + kk.Y) + k * n_pad + col;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) m.y[q][j] = yp[j];
+      }
+    }
+  };
+
+  const d4 z = d4{0.0, 0.0, 0.0, 0.0};
+  d4 pR[MI][NJ], pI[MI][NJ], m1[MI][NJ], m2[MI][NJ], m3[MI][NJ];
+  d4 hR[MI][NJ], hI[MI][NJ], sR[MI][NJ], sI[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) hR[i][j] = hI[i][j] = sR[i][j] = sI[i][j] = z;
+
+  const int ksm = (2 * c.n_l + 3) / 4, ncm = (ksm + KC - 1) / KC;
+  EChunk ec;
+  MChunk mc;
+  load_e(0, 0, ec);
+  for (int t = 0; t < c.n_act; ++t) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) m1[i][j] = m2[i][j] = m3[i][j] = z;
+    load_m(t, 0, mc);  // lands behind the phase sums
+    const int kse = (c.nat[t] + 3) / 4, nce = (kse + KC - 1) / KC;
+    for (int ch = 0; ch < nce; ++ch) {
+      EChunk en;
+      load_e(t, ch + 1 < nce ? ch + 1 : ch, en);
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        if (ch * KC + q < kse) {  // uniform
+          double ad[MI], bs[NJ];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            if constexpr (REAL) ec.b[q][j] *= ec.w[q];
+            bs[j] = ec.b[q][j].x + ec.b[q][j].y;
+          }
+#pragma unroll
+          for (int i = 0; i < MI; ++i) ad[i] = ec.a[q][i].x - ec.a[q][i].y;
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              m1[i][j] = MFMA(ec.a[q][i].x, ec.b[q][j].x, m1[i][j]);
+              if constexpr (REAL) {
+                m1[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m1[i][j]);
+              } else {
+                m2[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m2[i][j]);
+                m3[i][j] = MFMA(ad[i], bs[j], m3[i][j]);
+              }
+            }
+        }
+      }
+      ec = en;
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        pR[i][j] = REAL ? m1[i][j] : m1[i][j] + m2[i][j];
+        pI[i][j] = m3[i][j] - m1[i][j] + m2[i][j];
+        m1[i][j] = m2[i][j] = m3[i][j] = z;
+      }
+    if (t + 1 < c.n_act) load_e(t + 1, 0, ec);  // lands behind the R sums
+    for (int ch = 0; ch < ncm; ++ch) {
+      MChunk mn;
+      load_m(t, ch + 1 < ncm ? ch + 1 : ch, mn);
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        if (ch * KC + q < ksm) {  // uniform
+          double ls[NJ];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) ls[j] = mc.lam[q] * DVec<NJ>::get(mc.b[q], j);
+#pragma unroll
+          for (int i = 0; i < MI; ++i) {
+            const double ai = DVec<MI>::get(mc.a[q], i);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              if constexpr (REAL) {
+                m1[i][j] = MFMA(ai, DVec<NJ>::get(mc.yr[q], j), m1[i][j]);
+              } else {
+                m1[i][j] = MFMA(ai, mc.y[q][j].x, m1[i][j]);
+                m2[i][j] = MFMA(ai, mc.y[q][j].y, m2[i][j]);
+              }
+              m3[i][j] = MFMA(ai, ls[j], m3[i][j]);
+            }
+          }
+        }
+      }
+      mc = mn;
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if constexpr (REAL) {
+          hR[i][j] += pR[i][j] * m1[i][j];
+          sR[i][j] += pR[i][j] * m3[i][j];
+        } else {
+          hR[i][j] += pR[i][j] * m1[i][j] - pI[i][j] * m2[i][j];
+          hI[i][j] += pR[i][j] * m2[i][j] + pI[i][j] * m1[i][j];
+          sR[i][j] += pR[i][j] * m3[i][j];
+          sI[i][j] += pI[i][j] * m3[i][j];
+        }
+      }
+  }
+
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = row0 + MI * (lk + 4 * q) + i;
+      if (r >= n) continue;
+      const int64_t o = kk.out_off + (int64_t)r * n + col;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (col + j < n && col + j >= r) {
+          if constexpr (REAL) {
+            ((double*)H)[o + j] = hR[i][j][q];
+            ((double*)S)[o + j] = sR[i][j][q];
+          } else {
+            ((d2*)H)[o + j] = d2{hR[i][j][q], hI[i][j][q]};
+            ((d2*)S)[o + j] = d2{sR[i][j][q], sI[i][j][q]};
+          }
+        }
+      }
+    }
 }
 
 // XL[r][G] = lam[r] X[r][G]; one thread per G, rows over blockIdx.y.
@@ -103,180 +501,52 @@ __global__ void __launch_bounds__(256) k_scale_rows(const double2* __restrict__ 
   }
 }
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-// Rows of X, XL and Yx come type by type: the type's E rows, then its W0 rows,
-// each block padded with zero rows to a multiple of 16, so every 16-row chunk is
-// one kind: kind[c] & 3 = 0 (phases), 3 (the type's last phase chunk), 1 (W0 rows),
-// 2 (the type's last W0 chunk, after which M * P is folded into H and S); kind[c] >> 2
-// is the number of 4-row steps of the chunk that hold data rows, minus one.
-// XL = lam X (lam = 1 on phase rows, ||udot_l||^2 on B rows) and Yx is zero on
-// phase rows, so a phase chunk adds E^H E to the S slot and nothing to the H slot.
-// The slots sum conj(a) b in the three-product (3M) form, P1 = a_r b_r, P2 = a_i b_i,
-// P3 = (a_r - a_i)(b_r + b_i), and are turned into Re = P1 + P2, Im = P3 - P1 + P2
-// where a slot is captured (P_t) or folded: 3 MFMAs per complex multiply-add.
-__global__ void __launch_bounds__(FNT, 1) k_hs_fact(const d2* __restrict__ X, const d2* __restrict__ XL,
-                                                    const d2* __restrict__ Yx, const int* __restrict__ kind,
-                                                    int nch, int n, int n_pad, int nb, int num_wg, int gr,
-                                                    d2* __restrict__ H, d2* __restrict__ S, int64_t ldh) {
-  // per buffer: L (16 rows x 64 at G'), R (16 x 64 of XL at G), Y (16 x 64 of Yx at G)
-  __shared__ d2 lds[2][3 * FK * FM];
-  const int x = blockIdx.x % kXcds;
-  int start, len;
-  xcd_range(x, num_wg, start, len);
-  const int w = start + blockIdx.x / kXcds;
-  int bi, bj;
-  if (gr > 0) grouped_decode(w, nb, gr, bi, bj);
-  else tri_decode(w, nb, bi, bj);
-  const int row0 = bi * FM, col0 = bj * FM;
-  if (col0 >= n) return;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 2, wc = wave & 3;  // rows wr*32 (two 16-row blocks), columns wc*16
-
-  // staging straight into LDS: 48 row copies of 1 KB per chunk, wave w takes j = w + 8 i;
-  // copy j: array j/16 (X at G', XL at G, Yx at G), row j%16
-  const d2* src0[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int j = wave + 8 * i;
-    const int arr = j >> 4, r = j & 15;
-    const d2* base = arr == 0 ? X + row0 : (arr == 1 ? XL + col0 : Yx + col0);
-    src0[i] = base + (int64_t)r * n_pad;
-  }
-  auto issue = [&](int c, int buf) {
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-      __builtin_amdgcn_global_load_lds((const void*)(src0[i] + (int64_t)c * FK * n_pad + lane),
-                                       (lds_ptr)(&lds[buf][(wave + 8 * i) * FM]), 16, 0, 0);
-  };
-
-  d4 pR[2], pI[2], mh1[2], mh2[2], mh3[2], ms1[2], ms2[2], ms3[2], hR[2], hI[2], sR[2], sI[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    pR[i] = pI[i] = d4{0.0, 0.0, 0.0, 0.0};
-    mh1[i] = mh2[i] = mh3[i] = ms1[i] = ms2[i] = ms3[i] = d4{0.0, 0.0, 0.0, 0.0};
-    hR[i] = hI[i] = sR[i] = sI[i] = d4{0.0, 0.0, 0.0, 0.0};
-  }
-
-  issue(0, 0);
-  for (int c = 0; c < nch; ++c) {
-    const int b = c & 1;
-    const int kc = kind[c];         // uniform
-    const int kd = kc & 3, nks = (kc >> 2) + 1;
-    const bool hslot = kd == 1 || kd == 2;
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of chunk c have landed
-    __syncthreads();                // everyone's have, and buffer b^1 is free
-    // the next chunk's copies go out before step ki, half-way through a full chunk: issued
-    // right after the barrier their LDS writes meet the chunk's first reads (measured:
-    // 3.6 % slower); ki < nks, so the early exit below never skips them
-    const int ki = nks > 2 ? 2 : nks - 1;
-    const d2* L = lds[b];
-    const d2* R = lds[b] + FK * FM;
-    const d2* Yl = lds[b] + 2 * FK * FM;
-    // every chunk adds X^H XL to the S slot (P_t on phase chunks); W0 chunks also add
-    // X^H Yx to the H slot.  Only the 4-row steps that hold data rows are run.
-#pragma unroll
-    for (int ks = 0; ks < FK / 4; ++ks) {
-      if (ks == ki && c + 1 < nch) issue(c + 1, b ^ 1);
-      if (ks >= nks) break;
-      const int kk = ks * 4 + (lane >> 4);
-      double ar[2], ai[2], ad[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const d2 a = L[kk * FM + wr * 32 + i * 16 + (lane & 15)];
-        ar[i] = a.x; ai[i] = a.y; ad[i] = a.x - a.y;
-      }
-      const d2 yv = Yl[kk * FM + wc * 16 + (lane & 15)];
-      const d2 wv = R[kk * FM + wc * 16 + (lane & 15)];
-      const double ws = wv.x + wv.y, ys = yv.x + yv.y;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ms1[i] = MFMA(ar[i], wv.x, ms1[i]);
-        ms2[i] = MFMA(ai[i], wv.y, ms2[i]);
-        ms3[i] = MFMA(ad[i], ws, ms3[i]);
-      }
-      if (hslot) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          mh1[i] = MFMA(ar[i], yv.x, mh1[i]);
-          mh2[i] = MFMA(ai[i], yv.y, mh2[i]);
-          mh3[i] = MFMA(ad[i], ys, mh3[i]);
-        }
-      }
-    }
-    if (kd == 3) {  // the type's last phase chunk: the S slot holds P_t
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        pR[i] = ms1[i] + ms2[i];
-        pI[i] = ms3[i] - ms1[i] + ms2[i];
-        ms1[i] = ms2[i] = ms3[i] = d4{0.0, 0.0, 0.0, 0.0};
-      }
-    } else if (kd == 2) {  // the type's last W0 chunk: fold M * P into H and S
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const d4 mhR = mh1[i] + mh2[i], mhI = mh3[i] - mh1[i] + mh2[i];
-        const d4 msR = ms1[i] + ms2[i], msI = ms3[i] - ms1[i] + ms2[i];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const double p_r = pR[i][q], p_i = pI[i][q];
-          hR[i][q] += mhR[q] * p_r - mhI[q] * p_i;
-          hI[i][q] += mhR[q] * p_i + mhI[q] * p_r;
-          sR[i][q] += msR[q] * p_r - msI[q] * p_i;
-          sI[i][q] += msR[q] * p_i + msI[q] * p_r;
-        }
-        mh1[i] = mh2[i] = mh3[i] = ms1[i] = ms2[i] = ms3[i] = d4{0.0, 0.0, 0.0, 0.0};
-      }
-    }
-  }
-
-  // D layout of the 16x16 f64 MFMA: lane l, element q -> row l/16 + 4q, column l%16
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = row0 + wr * 32 + i * 16 + (lane >> 4) + 4 * q;
-      const int col = col0 + wc * 16 + (lane & 15);
-      if (row < n && col < n && col >= row) {
-        const int64_t o = (int64_t)row * ldh + col;
-        H[o] = d2{hR[i][q], hI[i][q]};
-        S[o] = d2{sR[i][q], sI[i][q]};
-      }
-    }
-}
-
 }  // namespace
 
-int fact_tiles(int n_pad) {
-  const int nb = n_pad / FM;
+int fact_block(int64_t cols, int num_cus) { return 2; }
+
+int fact_tiles(int n, int mi) {
+  const int nb = (n + 32 * mi - 1) / (32 * mi);
   return nb * (nb + 1) / 2;
 }
 
-hipError_t launch_phases(int n_atoms, int n_pad, const double* kv, const double* tau, double2* E, hipStream_t s) {
-  dim3 grid((n_pad + 255) / 256, n_atoms < 64 ? n_atoms : 64);
-  hipLaunchKernelGGL(k_phases, grid, dim3(256), 0, s, n_atoms, n_pad, kv, tau, E);
+hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const TypeConsts* consts, const FactK& one,
+                              const FactK* many, int nk, int ngb, const int32_t* g, const double* tau,
+                              const FactRep* rep, const double2* T, char* ws, hipStream_t s) {
+  const size_t lds = (size_t)(c.n_l + c.l_max + 2 + 2 * (c.l_max + 1)) * kTabG * sizeof(double);
+  const int ntb = (int)(((int64_t)c.Mr * c.Mc + 255) / 256);
+  hipLaunchKernelGGL(k_fact_tables, dim3(ngb + ntb, c.n_act), dim3(256), lds, s, c, ra, consts, one, many, nk, ngb, g,
+                     tau, rep, T, ws);
   return hipGetLastError();
 }
 
-hipError_t launch_fact_rows(const CellArgs& c, const TypeConsts* consts, int rows, double* lamx, int* kind,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_fact_rows, dim3((rows + 255) / 256), dim3(256), 0, s, c, consts, rows, lamx, kind);
+hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many, int nk, int nblk, int mi, bool real,
+                         char* ws, hipStream_t s) {
+  const dim3 grid(nblk, (c.Mr + 32 * mi - 1) / (32 * mi), c.n_act);
+  if (mi == 2 && real) hipLaunchKernelGGL((k_fact_y<2, 2, true>), grid, dim3(256), 0, s, c, one, many, nk, ws);
+  else if (mi == 2) hipLaunchKernelGGL((k_fact_y<2, 2, false>), grid, dim3(256), 0, s, c, one, many, nk, ws);
+  else if (real) hipLaunchKernelGGL((k_fact_y<1, 1, true>), grid, dim3(256), 0, s, c, one, many, nk, ws);
+  else hipLaunchKernelGGL((k_fact_y<1, 1, false>), grid, dim3(256), 0, s, c, one, many, nk, ws);
+  return hipGetLastError();
+}
+
+hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int num_wg, int mi, bool real,
+                          int gr, const FactRep* rep, const char* ws, void* H, void* S, hipStream_t s) {
+  const dim3 grid(num_wg);
+  if (mi == 2 && real)
+    hipLaunchKernelGGL((k_fact_hs<2, 2, 2, 1, true>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
+  else if (mi == 2)
+    hipLaunchKernelGGL((k_fact_hs<2, 2, 2, 1, false>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
+  else if (real)
+    hipLaunchKernelGGL((k_fact_hs<1, 1, 4, 2, true>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
+  else
+    hipLaunchKernelGGL((k_fact_hs<1, 1, 4, 2, false>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
   return hipGetLastError();
 }
 
 hipError_t launch_scale_rows(const double2* X, const double* lam, int rows, int n_pad, double2* XL, hipStream_t s) {
   dim3 grid((n_pad + 255) / 256, rows < 256 ? rows : 256);
   hipLaunchKernelGGL(k_scale_rows, grid, dim3(256), 0, s, X, lam, rows, n_pad, XL);
-  return hipGetLastError();
-}
-
-hipError_t launch_hs_fact(const double2* X, const double2* XL, const double2* Yx, const int* kind, int nch, int n,
-                          int n_pad, int gr, double2* H, double2* S, int64_t ldh, hipStream_t s) {
-  const int nb = n_pad / FM;
-  const int num_wg = fact_tiles(n_pad);
-  hipLaunchKernelGGL(k_hs_fact, dim3(num_wg), dim3(FNT), 0, s, (const d2*)X, (const d2*)XL, (const d2*)Yx, kind, nch,
-                     n, n_pad, nb, num_wg, gr, (d2*)H, (d2*)S, ldh);
   return hipGetLastError();
 }
 

@@ -53,12 +53,10 @@ struct Smem {
 
 // One 128 x 64 tile (rows row0.., columns col0..) of H and S, upper triangle stored.
 // WR x 2 waves; each wave owns (128/WR) x 32 of both outputs: MI x 2 MFMA blocks.
-// REAL: only the real parts, Re(W^H Y) and Re(W^H lam W), into double outputs (the
-// real-symmetric case: half the MFMAs of the complex product).
-template <int WR, bool REAL = false>
+template <int WR>
 __device__ __forceinline__ void hs_tile(Smem& sm, const d2* __restrict__ W, const d2* __restrict__ Y,
                                         const double* __restrict__ lam, int K_pad, int n, int n_pad, int row0,
-                                        int col0, void* __restrict__ Hv, void* __restrict__ Sv, int64_t ldh) {
+                                        int col0, d2* __restrict__ H, d2* __restrict__ S, int64_t ldh) {
   constexpr int NT = 64 * WR * 2;   // threads
   constexpr int MI = BM / WR / 16;  // row blocks per wave
   constexpr int PL = BK * BM / NT, PR = BK * BN / NT;
@@ -135,42 +133,34 @@ __device__ __forceinline__ void hs_tile(Smem& sm, const d2* __restrict__ W, cons
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) hr[i][j] = MFMA(ar[i], yre[j], hr[i][j]);
-      if constexpr (!REAL) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) hi[i][j] = MFMA(ar[i], yim[j], hi[i][j]);
-      }
+        for (int j = 0; j < 2; ++j) hi[i][j] = MFMA(ar[i], yim[j], hi[i][j]);
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) sr[i][j] = MFMA(ar[i], wre[j], sr[i][j]);
-      if constexpr (!REAL) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) si[i][j] = MFMA(ar[i], wim[j], si[i][j]);
-      }
+        for (int j = 0; j < 2; ++j) si[i][j] = MFMA(ar[i], wim[j], si[i][j]);
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) hr[i][j] = MFMA(ai[i], yim[j], hr[i][j]);
-      if constexpr (!REAL) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) hi[i][j] = MFMA(an[i], yre[j], hi[i][j]);
-      }
+        for (int j = 0; j < 2; ++j) hi[i][j] = MFMA(an[i], yre[j], hi[i][j]);
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) sr[i][j] = MFMA(ai[i], wim[j], sr[i][j]);
-      if constexpr (!REAL) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) si[i][j] = MFMA(an[i], wre[j], si[i][j]);
-      }
+        for (int j = 0; j < 2; ++j) si[i][j] = MFMA(an[i], wre[j], si[i][j]);
     }
     __syncthreads();
   }
@@ -188,13 +178,8 @@ __device__ __forceinline__ void hs_tile(Smem& sm, const d2* __restrict__ W, cons
         const int col = col0 + wc * 32 + j * 16 + (lane & 15);
         if (row < n && col < n && col >= row) {
           const int64_t o = (int64_t)row * ldh + col;
-          if constexpr (REAL) {
-            ((double*)Hv)[o] = hr[i][j][q];
-            ((double*)Sv)[o] = sr[i][j][q];
-          } else {
-            ((d2*)Hv)[o] = d2{hr[i][j][q], hi[i][j][q]};
-            ((d2*)Sv)[o] = d2{sr[i][j][q], si[i][j][q]};
-          }
+          H[o] = d2{hr[i][j][q], hi[i][j][q]};
+          S[o] = d2{sr[i][j][q], si[i][j][q]};
         }
       }
 }
@@ -340,11 +325,11 @@ __device__ __forceinline__ void hs_tile3m(Smem& sm, const d2* __restrict__ L, co
       }
 }
 
-template <int WR, bool REAL>
+template <int WR>
 __global__ void __launch_bounds__(128 * WR, 1) k_hs_fp64(const d2* __restrict__ W, const d2* __restrict__ WL,
                                                      const d2* __restrict__ Y, const double* __restrict__ lam,
                                                      int K_pad, int n, int n_pad, int nbr, int num_wg, int gr,
-                                                     void* __restrict__ H, void* __restrict__ S, int64_t ldh) {
+                                                     d2* __restrict__ H, d2* __restrict__ S, int64_t ldh) {
   __shared__ Smem sm;
   // dispatch is round-robin over XCDs: give XCD x the contiguous range of tile numbers
   const int x = blockIdx.x % kXcds;
@@ -354,10 +339,9 @@ __global__ void __launch_bounds__(128 * WR, 1) k_hs_fp64(const d2* __restrict__ 
   int row0, col0;
   tile_origin(w, nbr, gr, row0, col0);
   if (col0 >= n) return;
-  if constexpr (REAL) hs_tile<WR, true>(sm, W, Y, lam, K_pad, n, n_pad, row0, col0, H, S, ldh);
-  else if constexpr (WR == 4)
-    hs_tile3m<WR, true>(sm, W, WL, Y, K_pad, n_pad, n_pad, row0, col0, n, n, true, (d2*)H, (d2*)S, ldh);
-  else hs_tile<WR, false>(sm, W, Y, lam, K_pad, n, n_pad, row0, col0, H, S, ldh);  // 64 x 32 per wave: plain form
+  if constexpr (WR == 4)
+    hs_tile3m<WR, true>(sm, W, WL, Y, K_pad, n_pad, n_pad, row0, col0, n, n, true, H, S, ldh);
+  else hs_tile<WR>(sm, W, Y, lam, K_pad, n, n_pad, row0, col0, H, S, ldh);  // 64 x 32 per wave: plain form
 }
 
 // The 8-wave contraction with the stacked index cut into ns segments of kseg rows: workgroup
@@ -507,7 +491,7 @@ __global__ void __launch_bounds__(128 * WR, 1) k_hs_fp64_batch(const d2* __restr
       hs_tile3m<WR, true>(sm, ws + m.w_off, ws + m.wl_off, ws + m.y_off, K_pad, m.n_pad, m.n_pad, row0, col0, m.n,
                           m.n, true, H + m.out_off, S + m.out_off, m.n);
     else
-      hs_tile<WR, false>(sm, ws + m.w_off, ws + m.y_off, lam, K_pad, m.n, m.n_pad, row0, col0, H + m.out_off,
+      hs_tile<WR>(sm, ws + m.w_off, ws + m.y_off, lam, K_pad, m.n, m.n_pad, row0, col0, H + m.out_off,
                          S + m.out_off, m.n);
   }
 }
@@ -550,131 +534,6 @@ __global__ void __launch_bounds__(512, 1) k_tprod3m(CellArgs c, const d2* __rest
                       Ya, n_pad);
 }
 
-// Real-symmetric contraction on whole 128 x 128 super-tiles: Re(W^H Y) and
-// Re(W^H lam W) keep two of the four real MFMAs per complex multiply-add, so
-// with the 128 x 64 tile above a wave would read twice the LDS per MFMA.
-// Here the tile is 128 x 128 and 8 rows are staged per chunk, copied straight
-// into double-buffered LDS: 8 waves of 32 x 64 (2 x 4 MFMA blocks), the same
-// MFMA work and LDS reads per chunk as the complex kernel.
-constexpr int RN = 128, RK = 8;
-
-struct RSmem {
-  d2 L[2][RK][BM];
-  d2 R[2][RK][RN];
-  d2 Y[2][RK][RN];
-};
-
-__global__ void __launch_bounds__(512, 1) k_hs_real(const d2* __restrict__ W, const d2* __restrict__ WL,
-                                                    const d2* __restrict__ Y, int K_pad, int n, int n_pad, int nbr,
-                                                    int num_wg, int gr, double* __restrict__ H,
-                                                    double* __restrict__ S, int64_t ldh) {
-  __shared__ RSmem sm;
-  const int x = blockIdx.x % kXcds;
-  int start, len;
-  xcd_range(x, num_wg, start, len);
-  const int w = start + blockIdx.x / kXcds;
-  int bi, bj;
-  if (gr > 0) grouped_decode(w, nbr, gr, bi, bj);
-  else tri_decode(w, nbr, bi, bj);
-  const int row0 = bi * BM, col0 = bj * RN;
-  if (col0 >= n) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 1, wc = wave & 1;  // rows wr*32, columns wc*64
-
-  // Staging straight into LDS: 48 copies of 1 KB (64 elements) per 8-row chunk, wave w
-  // takes j = w + 8 i: copies 0..15 are W at the tile rows, 16..31 lam W (prepared in
-  // HBM) and 32..47 Y at the tile columns; copy j covers row (j % 16) / 2, half j % 2.
-  const d2* src0[6];
-  int dst[6];  // d2 offset in buffer 0 of sm (L, R, Y are consecutive members)
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int j = wave + 8 * i, r = (j & 15) >> 1, half = j & 1;
-    if (i < 2) {
-      src0[i] = W + (int64_t)r * n_pad + row0 + half * 64;
-      dst[i] = r * BM + half * 64;
-    } else if (i < 4) {
-      src0[i] = WL + (int64_t)r * n_pad + col0 + half * 64;
-      dst[i] = 2 * RK * BM + r * RN + half * 64;
-    } else {
-      src0[i] = Y + (int64_t)r * n_pad + col0 + half * 64;
-      dst[i] = 2 * RK * BM + 2 * RK * RN + r * RN + half * 64;
-    }
-  }
-  d2* base = &sm.L[0][0][0];
-  auto issue = [&](int c, int buf) {
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      const int off = dst[i] + buf * (i < 2 ? RK * BM : RK * RN);
-      __builtin_amdgcn_global_load_lds((const void*)(src0[i] + (int64_t)c * RK * n_pad + lane),
-                                       (lds_ptr)(base + off), 16, 0, 0);
-    }
-  };
-
-  d4 hr[2][4], sr[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) hr[i][j] = sr[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-
-  const int nchunks = K_pad / RK;
-  issue(0, 0);
-  for (int c = 0; c < nchunks; ++c) {
-    const int b = c & 1;
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of chunk c have landed
-    __syncthreads();                // everyone's have, and buffer b^1 is free
-    if (c + 1 < nchunks) issue(c + 1, b ^ 1);
-#pragma unroll
-    for (int ks = 0; ks < RK / 4; ++ks) {
-      const int kk = ks * 4 + (lane >> 4);
-      double ar[2], ai[2], yre[4], yim[4], wre[4], wim[4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const d2 a = sm.L[b][kk][wr * 32 + i * 16 + (lane & 15)];
-        ar[i] = a.x; ai[i] = a.y;
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const d2 yv = sm.Y[b][kk][wc * 64 + j * 16 + (lane & 15)];
-        const d2 wv = sm.R[b][kk][wc * 64 + j * 16 + (lane & 15)];
-        yre[j] = yv.x; yim[j] = yv.y; wre[j] = wv.x; wim[j] = wv.y;
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) hr[i][j] = MFMA(ar[i], yre[j], hr[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sr[i][j] = MFMA(ar[i], wre[j], sr[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) hr[i][j] = MFMA(ai[i], yim[j], hr[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sr[i][j] = MFMA(ai[i], wim[j], sr[i][j]);
-    }
-  }
-
-  // D layout of the 16x16 f64 MFMA: lane l, element q -> row l/16 + 4q, column l%16
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = row0 + wr * 32 + i * 16 + (lane >> 4) + 4 * q;
-        const int col = col0 + wc * 64 + j * 16 + (lane & 15);
-        if (row < n && col < n && col >= row) {
-          const int64_t o = (int64_t)row * ldh + col;
-          H[o] = hr[i][j][q];
-          S[o] = sr[i][j][q];
-        }
-      }
-}
-
 }  // namespace
 
 int hs_tiles(int n_pad) {
@@ -706,11 +565,11 @@ hipError_t launch_hs_fp64(const double2* W, const double2* WL, const double2* Y,
   const int nbr = n_pad / BM;
   const int num_wg = hs_tiles(n_pad);  // two 128 x 64 tiles per upper-triangle 128 x 128 super-tile
   if (waves == 8)
-    hipLaunchKernelGGL((k_hs_fp64<4, false>), dim3(num_wg), dim3(512), 0, s, (const d2*)W, (const d2*)WL,
-                       (const d2*)Y, lam, K_pad, n, n_pad, nbr, num_wg, gr, (void*)H, (void*)S, ldh);
+    hipLaunchKernelGGL((k_hs_fp64<4>), dim3(num_wg), dim3(512), 0, s, (const d2*)W, (const d2*)WL,
+                       (const d2*)Y, lam, K_pad, n, n_pad, nbr, num_wg, gr, (d2*)H, (d2*)S, ldh);
   else
-    hipLaunchKernelGGL((k_hs_fp64<2, false>), dim3(num_wg), dim3(256), 0, s, (const d2*)W, (const d2*)WL,
-                       (const d2*)Y, lam, K_pad, n, n_pad, nbr, num_wg, gr, (void*)H, (void*)S, ldh);
+    hipLaunchKernelGGL((k_hs_fp64<2>), dim3(num_wg), dim3(256), 0, s, (const d2*)W, (const d2*)WL,
+                       (const d2*)Y, lam, K_pad, n, n_pad, nbr, num_wg, gr, (d2*)H, (d2*)S, ldh);
   return hipGetLastError();
 }
 
@@ -775,20 +634,6 @@ hipError_t launch_sk_reduce(const double2* Hp, const double2* Sp, int ns, int n,
                             int64_t ldh, hipStream_t s) {
   hipLaunchKernelGGL(k_sk_reduce, dim3((n + 255) / 256, n), dim3(256), 0, s, (const d2*)Hp, (const d2*)Sp, ns, n,
                      n_pad, (d2*)H, (d2*)S, ldh);
-  return hipGetLastError();
-}
-
-hipError_t launch_hs_fp64_real(const double2* W, const double2* WL, const double2* Y, const double* lam, int K_pad,
-                               int n, int n_pad, int gr, int waves, double* H, double* S, int64_t ldh, hipStream_t s) {
-  const int nbr = n_pad / BM;
-  const int num_wg = hs_tiles(n_pad);
-  if (K_pad % RK) return hipErrorInvalidValue;
-  if (waves == 8)  // whole 128 x 128 super-tiles
-    hipLaunchKernelGGL(k_hs_real, dim3(num_wg / 2), dim3(512), 0, s, (const d2*)W, (const d2*)WL, (const d2*)Y, K_pad,
-                       n, n_pad, nbr, num_wg / 2, gr, H, S, ldh);
-  else
-    hipLaunchKernelGGL((k_hs_fp64<2, true>), dim3(num_wg), dim3(256), 0, s, (const d2*)W, (const d2*)WL,
-                       (const d2*)Y, lam, K_pad, n, n_pad, nbr, num_wg, gr, (void*)H, (void*)S, ldh);
   return hipGetLastError();
 }
 

@@ -1,0 +1,93 @@
+"""The type-factored kernels at the sizes where their tiles, row padding and radial-data hand-over
+change, against the oracle: bases around multiples of the 16-, 32- and 64-column blocks, atom counts
+around the 4-row steps and 16-row pads of the phase sums, l_max from 0 (where 2 N_L = 2 rows are
+padded to 16) up, and more (type, l) pairs than travel by value.
+
+Bar: the FP64 path's relative Frobenius error <= 1e-12 over the full matrices, the strict lower
+triangle untouched."""
+import numpy as np
+import pytest
+import torch
+
+from flapw_cells.cells import CellConfig, _draw, basis_for_k
+from oracle import hs_oracle as o
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    from paper_1712_07206_amd import _native
+    _native.lib()
+    yield
+
+
+def _case(atoms, l_max, n_g, inversion=False):
+    cfg = CellConfig(20 + l_max, "edge", (15.0, 16.0, 17.0), atoms, (1.2,) * len(atoms), l_max, n_g=n_g,
+                     inversion=inversion)
+    _, case, k_frac, _ = _draw(cfg, None)
+    g, kmax = basis_for_k(case["lattice"], k_frac[0], n_g)
+    case.update(k_frac=k_frac[0].copy(), g=g, n_g=n_g, k_max=kmax)
+    return case
+
+
+def _full(M):
+    return np.triu(M) + np.triu(M, 1).conj().T
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def _check(case, real=False):
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    n = case["n_g"]
+    print("atoms", np.bincount(case["atom_type"]), "l_max", case["l_max"], "N_G", n, flush=True)
+    b = HSBuilder.from_case(case)
+    g, tau, T = case_tensors(case)
+    H = torch.full((n, n), float("nan"), dtype=torch.float64 if real else torch.complex128, device="cuda")
+    S = H.clone()
+    if real:
+        b.forward_real(case["k_frac"], g, tau, case["partner"], T, H, S)
+    else:
+        b.forward_factored(case["k_frac"], g, tau, T, H, S)
+    torch.cuda.synchronize()
+    Hr, Sr = o.hs(case)
+    for M, R in ((H.cpu().numpy(), Hr), (S.cpu().numpy(), Sr)):
+        assert np.all(np.isnan(M[np.tril_indices(n, -1)])), "strict lower triangle was written"
+        e = _rel(_full(M), R.real if real else R)
+        assert e <= TOL, e
+
+
+@pytest.mark.parametrize("n_g", [1, 2, 15, 17, 31, 33, 63, 64, 65, 127, 129])
+def test_basis_around_the_blocks(n_g):
+    _check(_case((3, 1), 2, n_g))
+
+
+@pytest.mark.parametrize("n_g", [2100, 2950])  # on both sides of the rule that picks the tile size
+def test_basis_around_the_tile_choice(n_g):
+    _check(_case((2, 1), 2, n_g))
+
+
+@pytest.mark.parametrize("atoms", [(1,), (4, 5), (16, 17)])
+def test_atom_counts_around_the_steps(atoms):
+    _check(_case(atoms, 3, 90))
+
+
+@pytest.mark.parametrize("l_max", [0, 1, 5, 12])
+def test_row_padding(l_max):
+    _check(_case((2, 2), l_max, 70))
+
+
+@pytest.mark.parametrize("types,l_max", [(5, 12), (8, 7), (9, 7), (16, 4)])  # 65, 64, 72, 80 (type, l) pairs
+def test_radial_data_by_value_and_uploaded(types, l_max):
+    _check(_case((1,) * types, l_max, 100))
+
+
+@pytest.mark.parametrize("atoms,n_g", [((1,), 40), ((2,), 33), ((9, 8), 64), ((34, 2), 129)])
+def test_real_form(atoms, n_g):
+    _check(_case(atoms, 3, n_g, inversion=True), real=True)

@@ -133,8 +133,10 @@ int hsbuild_coefficients(hsbuild_t h, const double k_frac[3], int32_t ng, const 
 /* H and S of one k-point (Eqs. 4-7).  T: device complex128
  * [n_types][2N_L][2N_L], Hermitian, rows/columns ordered (A|B, L).
  * H, S: device complex128 [ng][ng]; upper triangle written.
- * The handle's precision selects the FP64 MFMA contraction or the
- * split-precision (Ozaki slice) contraction. */
+ * The handle's precision selects FP64 or the split-precision contraction.  In
+ * FP64 the call runs the type-factored form (see hsbuild_forward_factored)
+ * unless an option pins the stacked contraction: HSB_OPT_SPLIT_K other than 1,
+ * or HSB_OPT_HS_WAVES = 4. */
 int hsbuild_forward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
                     const void* T, void* H, void* S, void* ws, size_t ws_bytes, void* stream);
 
@@ -247,8 +249,8 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
  * int32[n_k]; g: device int32, the n_k G lists concatenated in k order;
  * out_off: host int64[n_k], element offsets of each k's ng x ng block in H and
  * S (blocks must not overlap: HSB_ERR_SHAPE).  Each block holds exactly what
- * hsbuild_forward writes for that k (bitwise, with the same options and
- * HSB_OPT_SPLIT_K = 0; to FP64 rounding where the forward splits), upper
+ * hsbuild_forward writes for that k (bitwise, with the same options, unless
+ * HSB_OPT_SPLIT_K > 1 has the forward split: to FP64 rounding then), upper
  * triangle only.  FP64 only: a handle with a split precision gets
  * HSB_ERR_UNSUPPORTED.  The calls are recorded once into a hipGraph, replayed
  * while n_k, k_frac, ng, out_off and the device pointers stay the same (the
@@ -280,15 +282,15 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
 /* Tuning options (performance only).
  * HSB_OPT_TILE_GROUP: order in which the upper-triangle tiles of every
  * contraction are dealt to the compute units: 0 = row-major, g > 0 = super-rows
- * (128 rows; 64 for the factored kernel) taken g at a time, column by column
+ * (128 rows; 64 or 32 for the factored kernel) taken g at a time, column by column
  * (0..64; default 8, or 4 on a handle with a split precision).  Results are
  * bitwise independent of it.
- * HSB_OPT_HS_WAVES: waves per workgroup of the FP64 contraction, 4 (64 x 32
+ * HSB_OPT_HS_WAVES: waves per workgroup of the stacked FP64 contraction, 4 (64 x 32
  * outputs per wave, one wave per SIMD; four real products per complex one) or
  * 8 (32 x 32 per wave, two per SIMD; three real products per complex one, the
- * 3M form; 128 x 128 tiles of 32 x 64 for hsbuild_forward_real, which is
- * real); default 8.  The two complex forms agree to FP64 rounding, not
- * bitwise.  On a handle with a residue form (HSB_SPLIT_CRT*) the option
+ * 3M form); default 8.  4 also pins the stacked contraction in hsbuild_forward
+ * and hsbuild_batch (HSB_OPT_SPLIT_K).  The forms agree to FP64 rounding, not
+ * bitwise.  No effect on hsbuild_forward_real in FP64.  On a handle with a residue form (HSB_SPLIT_CRT*) the option
  * picks the layout of the residue contraction instead (256 x 256 blocks): 4
  * (waves of 128 x 128, one per SIMD; the default there) or 8 (64 x 128, two
  * per SIMD); in HSB_SPLIT_CRT the 4-wave layout keeps its int32 sums
@@ -296,7 +298,10 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
  * takes two stages per 64 rows), beyond which the 8-wave layout runs; the
  * 16-bit residue forms run the 8-wave layout only (their default is 8).  All
  * give bitwise the same H and S.
- * HSB_OPT_SPLIT_K: 1 (default) lets the 8-wave FP64 forward run in stream-K
+ * HSB_OPT_SPLIT_K: 1 (default) leaves the form of the FP64 builds to the library:
+ * with HSB_OPT_HS_WAVES = 8 hsbuild_forward and hsbuild_batch run the
+ * type-factored form.  Where the stacked contraction runs
+ * (hsbuild_forward_coefficients), it runs in stream-K
  * form when the upper triangle has fewer than 4 tiles per compute unit and a
  * time model puts it ahead of one pass: the units (128 x 64 tile, 16 stacked
  * rows) are dealt to at most one workgroup per compute unit in equal
@@ -306,10 +311,10 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
  * hsbuild_workspace_bytes includes).
  * The results agree with the one-pass contraction to FP64 rounding, not
  * bitwise, and repeat bitwise on a device with the same compute-unit count.
- * 0 never splits; k = 2..8 cuts the stacked index into k segments (fewer if
+ * 0 runs the stacked contraction in one pass; k = 2..8 cuts the stacked index into k segments (fewer if
  * it is too short), summed in order.
- * Setting HSB_OPT_TILE_GROUP or HSB_OPT_HS_WAVES drops a captured batch graph
- * (the batch contraction never splits). */
+ * Changing HSB_OPT_TILE_GROUP, HSB_OPT_HS_WAVES or the form drops a captured
+ * batch graph (the stacked batch contraction never splits). */
 enum { HSB_OPT_TILE_GROUP = 1, HSB_OPT_HS_WAVES = 2, HSB_OPT_SPLIT_K = 3 };
 int hsbuild_set_option(hsbuild_t h, int32_t option, int32_t value);
 int hsbuild_get_option(hsbuild_t h, int32_t option, int32_t* value);

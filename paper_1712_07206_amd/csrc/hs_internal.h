@@ -50,6 +50,8 @@ struct TypeConsts {
 struct Layout {
   int n = 0, n_pad = 0, K = 0, K_pad = 0;
   size_t W = 0, Y = 0, ang = 0, ab = 0, kv = 0, lam = 0, consts = 0, end = 0;
+  size_t stacked_end = 0;  // forward: the stacked form's part of `end`
+  bool factored = false;   // forward: run the type-factored form
   size_t WL = 0;  // lam W (the FP64 contraction's S operand), forward in FP64 only
   int ns = 1;              // FP64 forward: segments of the stacked index (split contraction when > 1)
   int nsh = 0;             // FP64 forward: workgroups of the stream-K contraction (0: not used)

@@ -105,6 +105,9 @@ hipError_t static_scratch(int dev, void** out) {
 
 // ---- type-factored form ----
 
+// The forward runs the type-factored form unless an option pins the stacked contraction.
+bool use_factored(const hsbuild_s& h) { return h.precision == HSB_FP64 && h.split_k == 1 && h.hs_waves == 8; }
+
 // The types of `cell` with atoms (the real form's cell holds the representatives).
 FactCell fact_cell(const CellArgs& cell) {
   FactCell c{};
@@ -281,6 +284,13 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.partTau = take((size_t)h.n_atoms * gradtau_blocks(ng) * 3 * sizeof(double));
   }
   L.end = off;
+  // the factored form runs in the same memory (the stacked one keeps its place in it: an option or
+  // hsbuild_forward_coefficients may ask for it)
+  L.stacked_end = off;
+  if (mode == HSB_MODE_FORWARD && use_factored(h)) {
+    L.factored = true;
+    L.end = std::max(L.end, fact_bytes(h, ng, false));
+  }
   return L;
 }
 
@@ -554,6 +564,13 @@ BatchLayout make_batch_layout(const hsbuild_s& h, int n_k, const int32_t* ng) {
     B.Y.push_back(take((size_t)B.K_pad * B.n_pad[k] * sizeof(double2)));
   }
   B.end = off;
+  if (use_factored(h)) {
+    FactCell c = fact_cell(h.cell);
+    std::vector<FactK> ks(n_k, FactK{});
+    for (int k = 0; k < n_k; ++k) ks[k].n = ng[k];
+    size_t consts, many;
+    B.end = std::max(B.end, fact_layout(h, c, ks.data(), n_k, false, &consts, &many, nullptr));
+  }
   return B;
 }
 
@@ -874,6 +891,7 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double 
 int forward_enqueue(hsbuild_t h, const Layout& L, const double k_frac[3], int32_t ng, const int32_t* g,
                     const double* tau, const void* T, void* H, void* S, char* w, hipStream_t s) {
   int rc;
+  if (L.factored) return factored_enqueue(h, h->cell, false, k_frac, ng, g, tau, T, H, S, w, s);
   mark(h, 0, s);
   if ((rc = enqueue_operands(h, L, k_frac, g, tau, T, w, s))) return rc;
   if (h->precision == HSB_FP64) {
@@ -910,7 +928,12 @@ int hsbuild_forward_static(hsbuild_t h, const double k_frac[3], int32_t ng, cons
   if (H == S) return fail(h, HSB_ERR_ARG, "H and S must be distinct buffers");
   int rc = check_ng(h, ng);
   if (rc) return rc;
-  const Layout L = make_layout(*h, ng, HSB_MODE_FORWARD);
+  Layout L = make_layout(*h, ng, HSB_MODE_FORWARD);
+  if (L.end > HSB_STATIC_SCRATCH_BYTES && L.stacked_end <= HSB_STATIC_SCRATCH_BYTES) {
+    // many types of very small l_max: the factored form's padded rows are the larger ones
+    L.factored = false;
+    L.end = L.stacked_end;
+  }
   if (L.end > HSB_STATIC_SCRATCH_BYTES)
     return fail(h, HSB_ERR_WORKSPACE,
                 "ng=%d needs %zu bytes of workspace, the static scratch holds %zu; use hsbuild_forward with a "
@@ -1229,6 +1252,54 @@ int record_stacked_batch(hsbuild_t h, const BatchLayout& B, int n_k, const doubl
   return rc;
 }
 
+// Records the batch graph's work on h->cap_stream: the factored form, each of its kernels over all
+// k-points at once.  Nothing here waits on the host or allocates.
+int record_factored_batch(hsbuild_t h, int n_k, const double* k_frac, const int32_t* ng, const int32_t* g,
+                          const int64_t* out_off, const double* tau, const void* T, void* H, void* S, char* w) {
+  FactCell c = fact_cell(h->cell);
+  FactK* ks = (FactK*)h->meta_host;
+  int64_t tiles = 0;
+  for (int k = 0; k < n_k; ++k) {
+    ks[k] = FactK{};
+    ks[k].n = ng[k];
+    tiles += fact_tiles(ng[k], 2);
+  }
+  const int mi = fact_block(tiles, h->num_cus);
+  size_t consts_off = 0, many_off = 0;
+  fact_layout(*h, c, ks, n_k, false, &consts_off, &many_off, nullptr);
+  int64_t g_row = 0, gblk = 0, yblk = 0, tile = 0;
+  for (int k = 0; k < n_k; ++k) {
+    FactK& f = ks[k];
+    for (int i = 0; i < 3; ++i) f.kfrac[i] = k_frac[3 * k + i];
+    f.g_row = g_row;
+    f.out_off = out_off[k];
+    f.gblk0 = (int)gblk;
+    f.yblk0 = (int)yblk;
+    f.tile0 = (int)tile;
+    g_row += f.n;
+    gblk += f.n_pad / 64;
+    yblk += f.n_pad / (32 * mi);
+    tile += fact_tiles(f.n, mi);
+  }
+  if (tile > INT32_MAX) return fail(h, HSB_ERR_SHAPE, "problem too large");
+  RadialArgs ra;
+  const bool by_value = fact_radial(*h, c, ra);
+  hipStream_t cs = h->cap_stream;
+  if (hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed) != hipSuccess)
+    return fail(h, HSB_ERR_DEVICE, "hipStreamBeginCapture failed");
+  hipError_t e = hipMemcpyAsync(w + many_off, ks, sizeof(FactK) * n_k, hipMemcpyHostToDevice, cs);
+  const TypeConsts* consts = by_value ? nullptr : (const TypeConsts*)(w + consts_off);
+  if (e == hipSuccess && consts)
+    e = hipMemcpyAsync(w + consts_off, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, cs);
+  const FactK* many = (const FactK*)(w + many_off);
+  if (e == hipSuccess)
+    e = launch_fact_tables(c, ra, consts, FactK{}, many, n_k, (int)gblk, g, tau, nullptr, (const double2*)T, w, cs);
+  if (e == hipSuccess) e = launch_fact_y(c, FactK{}, many, n_k, (int)yblk, mi, false, w, cs);
+  if (e == hipSuccess)
+    e = launch_fact_hs(c, FactK{}, many, n_k, (int)tile, mi, false, h->tile_group, nullptr, w, H, S, cs);
+  return launched(h, e, "batch graph");
+}
+
 }  // namespace
 
 extern "C" {
@@ -1289,7 +1360,9 @@ int hsbuild_batch(hsbuild_t h, int32_t n_k, const double* k_frac, const int32_t*
       h->meta_cap = n_k;
     }
     h->capturing = true;
-    rc = record_stacked_batch(h, B, n_k, k_frac, ng, g, out_off, tau, T, H, S, (char*)ws);
+    rc = use_factored(*h)
+             ? record_factored_batch(h, n_k, k_frac, ng, g, out_off, tau, T, H, S, (char*)ws)
+             : record_stacked_batch(h, B, n_k, k_frac, ng, g, out_off, tau, T, H, S, (char*)ws);
     h->capturing = false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     (void)hipStreamIsCapturing(h->cap_stream, &cap);
@@ -1365,7 +1438,8 @@ int hsbuild_set_option(hsbuild_t h, int32_t option, int32_t value) {
       return HSB_OK;
     case HSB_OPT_SPLIT_K:
       if (value < 0 || value > 8) return fail(h, HSB_ERR_ARG, "split-K option %d outside [0, 8]", value);
-      h->split_k = value;  // the batch contraction never splits: its graph stays valid
+      if ((value == 1) != (h->split_k == 1)) drop_graph(h);  // between the factored and the stacked form
+      h->split_k = value;
       return HSB_OK;
     default:
       return fail(h, HSB_ERR_ARG, "unknown option %d", option);

@@ -91,3 +91,37 @@ def test_radial_data_by_value_and_uploaded(types, l_max):
 @pytest.mark.parametrize("atoms,n_g", [((1,), 40), ((2,), 33), ((9, 8), 64), ((34, 2), 129)])
 def test_real_form(atoms, n_g):
     _check(_case(atoms, 3, n_g, inversion=True), real=True)
+
+
+def test_default_forward_and_batch_are_the_factored_form():
+    """hsbuild_forward, _static and the blocks of hsbuild_batch (whose tile size follows the whole
+    batch's tiles, not one k-point's) equal hsbuild_forward_factored bitwise."""
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = _case((3, 2), 3, 200)
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    sizes = [200, 1, 65, 130]
+    ks = [np.asarray(case["k_frac"]) * f for f in (1.0, 0.5, -0.25, 0.75)]
+    gl = [g[:n].contiguous() for n in sizes]
+    H, S, off = b.batch(np.stack(ks), gl, tau, T)
+    for k, n in enumerate(sizes):
+        iu = torch.triu_indices(n, n, device="cuda")
+        ref = b.forward_factored(ks[k], gl[k], tau, T)
+        for got in (b.forward(ks[k], gl[k], tau, T), b.forward_static(ks[k], gl[k], tau, T),
+                    [M[int(off[k]):int(off[k]) + n * n].view(n, n) for M in (H, S)]):
+            assert all(torch.equal(x[iu[0], iu[1]], r[iu[0], iu[1]]) for x, r in zip(got, ref)), (k, n)
+
+
+def test_batch_uploads_radial_data_past_the_by_value_limit():
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = _case((1,) * 9, 7, 80)
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    ks = np.stack([case["k_frac"], -np.asarray(case["k_frac"])])
+    ref = [b.forward(k, g, tau, T) for k in ks]
+    iu = torch.triu_indices(80, 80, device="cuda")
+    for _ in range(3):  # recorded, then replayed
+        H, S, off = b.batch(ks, [g, g], tau, T)
+        for k in range(2):
+            for M, r in zip((H, S), ref[k]):
+                assert torch.equal(M[int(off[k]):int(off[k]) + 6400].view(80, 80)[iu[0], iu[1]], r[iu[0], iu[1]])

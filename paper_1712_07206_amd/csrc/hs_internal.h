@@ -56,10 +56,7 @@ struct Layout {
   int ns = 1;              // FP64 forward: segments of the stacked index (split contraction when > 1)
   int nsh = 0;             // FP64 forward: workgroups of the stream-K contraction (0: not used)
   size_t skH = 0, skS = 0;  // partial H and S: per segment (ns > 1), or the stream-K slots (nsh > 0)
-  size_t PH = 0, PS = 0, partT = 0, partTau = 0;  // backward only
-  size_t WT = 0, gHp = 0, gSp = 0;                // backward: operands of the 3M products
   size_t TT = 0;                                  // T^T per type, zero-padded (T products)
-  int Kt = 0;                                     // backward: K_pad rounded up to 128
   int K_pad2 = 0;                                  // split only: stacked rows padded to 32
   size_t mx = 0, scale = 0, slL = 0, slS = 0, slY = 0;  // split only (slL, slS, slY: residue planes in the CRT form)
   int K64 = 0, n_res = 0;                              // residue form: rows padded to 64, columns to 256
@@ -259,6 +256,15 @@ struct FactRep {
   double weight;
   int atom, pad;
 };
+// The adjoint's arrays (byte offsets) and splits; Mt = 0: none of it.  RT: R transposed, double
+// [n_act][n_pad][Mt]; ET: the phases transposed, complex [n_pad][et_ld]; UT: complex [types of one
+// pass][n_pad][Mt]; partT: complex [n_act][ngt][Mt][Mt]; partTau: double [nseg][ngb][et_ld][3].
+struct FactAdj {
+  int Mt = 0, et_ld = 0;      // 2 N_L rounded up to 32; phase rows
+  int ngt = 0;                // segments of G in R Z R^T
+  int nseg = 0, ngb = 0;      // segments of G' and blocks of columns in the phase sums
+  size_t RT = 0, ET = 0, UT = 0, partT = 0, partTau = 0;
+};
 // Workgroups of the H/S kernel for a basis of n; mi: 16-row blocks per wave side (1 or 2).
 int fact_tiles(int n, int mi);
 // Blocks per wave side for `tiles` workgroups of the larger tile on num_cus compute units.
@@ -268,7 +274,7 @@ int fact_block(int64_t tiles, int num_cus);
 // representatives (device), else nullptr.
 hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const TypeConsts* consts, const FactK& one,
                               const FactK* many, int nk, int ngb, const int32_t* g, const double* tau,
-                              const FactRep* rep, const double2* T, char* ws, hipStream_t s);
+                              const FactRep* rep, const FactAdj& ad, const double2* T, char* ws, hipStream_t s);
 hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many, int nk, int nblk, int mi, bool real,
                          char* ws, hipStream_t s);
 hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int num_wg, int mi, bool real,
@@ -292,22 +298,15 @@ int eig_workspace(void* handle, int n, bool vectors, size_t* bytes, std::string&
 // a[i] = conj(a[i]) for i < count.
 hipError_t launch_conj(double2* a, int64_t count, hipStream_t s);
 
-// ---- adjoint ----
-int gradtau_blocks(int n);
-// P_H = W gH and P_S = W gS ([K_pad][n_pad]) in the 3M form from W^T ([n_pad][Kt], Kt a multiple
-// of 128, zeros past K_pad) and gS, gH zero-padded to [n_pad][n_pad].
-hipError_t launch_pgemm3m(const double2* WT, const double2* gSp, const double2* gHp, int Kt, int K_pad, int n_pad,
-                          double2* PH, double2* PS, hipStream_t s);
-// WT[G][k] = W[k][G] (k < K_pad), 0 for K_pad <= k < Kt.
-hipError_t launch_transpose(const double2* W, int K_pad, int n_pad, int Kt, double2* WT, hipStream_t s);
-// gp = g ([n][n]) zero-padded to [n_pad][n_pad].
-hipError_t launch_pad_square(const double2* g, int n, int n_pad, double2* gp, hipStream_t s);
-// gT[t] = sum over atoms of type t of P_H,a W_a^H (part: [n_atoms][2N_L][2N_L] scratch).
-hipError_t launch_gradT(const CellArgs& c, const double2* PH, const double2* W, int n_pad, double2* part,
-                        double2* gT, hipStream_t s);
-// gtau[a] = -2 sum_G K_G Im c_a(G) (part: [n_atoms][gradtau_blocks(n)][3] scratch).
-hipError_t launch_gradtau(const CellArgs& c, const double2* PH, const double2* PS, const double2* Y,
-                          const double2* W, const double* lam, const double* kv, int n, int n_pad, double* part,
-                          double* gtau, hipStream_t s);
+// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1, mi as for the H/S kernel) ----
+// Z, Q: complex [nt][n_pad][n_pad].
+hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int mi, const double2* gH,
+                         const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s);
+hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, int mi, char* ws,
+                         const double2* Z, const double2* Q, hipStream_t s);
+hipError_t launch_adj_gt(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
+                         hipStream_t s);
+hipError_t launch_adj_reduce(const FactCell& c, const FactAdj& ad, int n_types, int n_atoms, const char* ws,
+                             double2* gT, double* gtau, hipStream_t s);
 
 }  // namespace hsb

@@ -171,6 +171,56 @@ size_t fact_bytes(const hsbuild_s& h, int ng, bool real) {
   return fact_layout(h, c, &f, 1, real, &consts, nullptr, real ? &rep : nullptr);
 }
 
+// The adjoint's workspace: the factored arrays, their transposes, and Z and Q of `pass` types at a
+// time: all of them, unless that takes more than the stacked operands of the same problem
+// (5 stacked arrays and two N_G x N_G ones) would.
+struct AdjointPlan {
+  FactCell c;
+  FactK f{};
+  FactAdj ad;
+  size_t consts = 0, Z = 0, Q = 0, end = 0;
+  int mi = 2, pass = 1;
+};
+
+AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
+  AdjointPlan p;
+  FactCell& c = p.c;
+  c = fact_cell(h.cell);
+  p.f.n = ng;
+  size_t off = fact_layout(h, c, &p.f, 1, false, &p.consts, nullptr, nullptr);
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off = align256(off + bytes);
+    return o;
+  };
+  const int64_t np = p.f.n_pad, nb = np / 64;
+  FactAdj& ad = p.ad;
+  ad.Mt = (int)round_up(2 * h.n_l, 32);
+  ad.et_ld = fact_phase_rows(c);
+  p.mi = fact_block(nb * nb * c.n_act, h.num_cus);
+  // waves for twice the SIMDs, where the sizes give them
+  const int64_t waves = 8 * (int64_t)std::max(1, h.num_cus);
+  const int64_t gt_tiles = (int64_t)(ad.Mt / 32) * (ad.Mt / 32) * c.n_act;
+  ad.ngt = (int)std::min<int64_t>(np / 64, std::max<int64_t>(1, waves / gt_tiles));
+  int64_t c_tiles = 0;
+  for (int t = 0; t < c.n_act; ++t) c_tiles += (c.nat[t] + 15) / 16;
+  ad.ngb = (int)(np / (16 * p.mi));
+  ad.nseg = (int)std::min<int64_t>(np / 64, std::max<int64_t>(1, waves / (c_tiles * ad.ngb)));
+  ad.RT = take((size_t)c.n_act * np * ad.Mt * sizeof(double));
+  ad.ET = take((size_t)np * ad.et_ld * sizeof(double2));
+  ad.partT = take((size_t)c.n_act * ad.ngt * ad.Mt * ad.Mt * sizeof(double2));
+  ad.partTau = take((size_t)ad.nseg * ad.ngb * ad.et_ld * 3 * sizeof(double));
+  const size_t per_type = (2 * (size_t)np * np + (size_t)np * ad.Mt) * sizeof(double2);
+  const size_t stacked = (5 * (size_t)stacked_pad(2 * h.n_atoms * h.n_l) * np + 2 * (size_t)np * np) * sizeof(double2);
+  p.pass = c.n_act;
+  while (p.pass > 1 && off + p.pass * per_type > stacked) --p.pass;
+  ad.UT = take((size_t)p.pass * np * ad.Mt * sizeof(double2));
+  p.Z = take((size_t)p.pass * np * np * sizeof(double2));
+  p.Q = take((size_t)p.pass * np * np * sizeof(double2));
+  p.end = off;
+  return p;
+}
+
 // The radial data by value; false if the types need more entries than RadialArgs holds.
 bool fact_radial(const hsbuild_s& h, const FactCell& c, RadialArgs& ra) {
   const int nl1 = c.l_max + 1;
@@ -215,6 +265,10 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.blas_bytes = h.blas_ng == ng ? h.blas_need : 0;
     L.blas = take(L.blas_bytes);
     L.end = off;
+    return L;
+  }
+  if (mode == HSB_MODE_BACKWARD) {
+    L.end = adjoint_plan(h, ng).end;
     return L;
   }
   if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && h.precision == HSB_FP64)) {
@@ -271,17 +325,6 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.rep = take((size_t)h.n_atoms * sizeof(FactRep));
     L.tau_rep = take((size_t)h.n_atoms * 3 * sizeof(double));
     L.wrow = take((size_t)L.K_pad * sizeof(double));
-  }
-  if (mode == HSB_MODE_BACKWARD) {
-    const size_t M = 2 * (size_t)h.n_l;
-    L.PH = take((size_t)L.K_pad * np * sizeof(double2));
-    L.PS = take((size_t)L.K_pad * np * sizeof(double2));
-    L.Kt = (int)round_up(L.K_pad, 128);
-    L.WT = take((size_t)np * L.Kt * sizeof(double2));
-    L.gHp = take((size_t)np * np * sizeof(double2));
-    L.gSp = take((size_t)np * np * sizeof(double2));
-    L.partT = take((size_t)h.n_atoms * M * M * sizeof(double2));
-    L.partTau = take((size_t)h.n_atoms * gradtau_blocks(ng) * 3 * sizeof(double));
   }
   L.end = off;
   // the factored form runs in the same memory (the stacked one keeps its place in it: an option or
@@ -873,7 +916,8 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double 
     consts = (const TypeConsts*)(w + consts_off);
   }
   const int mi = fact_block(fact_tiles(ng, 2), h->num_cus);
-  rc = launched(h, launch_fact_tables(c, ra, consts, f, nullptr, 1, f.n_pad / 64, g, tau, rep, (const double2*)T, w, s),
+  rc = launched(h, launch_fact_tables(c, ra, consts, f, nullptr, 1, f.n_pad / 64, g, tau, rep, FactAdj{},
+                                      (const double2*)T, w, s),
                 "k_fact_tables");
   mark(h, 1, s);
   if (!rc) rc = launched(h, launch_fact_y(c, f, nullptr, 1, f.n_pad / (32 * mi), mi, real, w, s), "k_fact_y");
@@ -1151,25 +1195,29 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
   if ((rc = check_device(h))) return rc;
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
-  if ((rc = enqueue_operands(h, L, k_frac, g, tau, T, w, s))) return rc;
-  CellArgs c = h->cell;
-  const double2* W = (const double2*)(w + L.W);
-  double2* PH = (double2*)(w + L.PH);
-  double2* PS = (double2*)(w + L.PS);
-  // P_H = W gH, P_S = W gS in the 3M form, from W^T and zero-padded gH, gS
-  double2* WT = (double2*)(w + L.WT);
-  double2* gHp = (double2*)(w + L.gHp);
-  double2* gSp = (double2*)(w + L.gSp);
-  rc = launched(h, launch_transpose(W, L.K_pad, L.n_pad, L.Kt, WT, s), "k_transpose");
-  if (!rc) rc = launched(h, launch_pad_square((const double2*)gH, ng, L.n_pad, gHp, s), "k_pad_square");
-  if (!rc) rc = launched(h, launch_pad_square((const double2*)gS, ng, L.n_pad, gSp, s), "k_pad_square");
-  if (!rc) rc = launched(h, launch_pgemm3m(WT, gSp, gHp, L.Kt, L.K_pad, L.n_pad, PH, PS, s), "k_pgemm3m");
+  AdjointPlan p = adjoint_plan(*h, ng);
+  const FactCell& c = p.c;
+  for (int i = 0; i < 3; ++i) p.f.kfrac[i] = k_frac[i];
+  RadialArgs ra;
+  const TypeConsts* consts = nullptr;
+  if (!fact_radial(*h, c, ra)) {
+    const hipError_t e = hipMemcpyAsync(w + p.consts, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, s);
+    if ((rc = launched(h, e, "upload of type constants"))) return rc;
+    consts = (const TypeConsts*)(w + p.consts);
+  }
+  rc = launched(h, launch_fact_tables(c, ra, consts, p.f, nullptr, 1, p.f.n_pad / 64, g, tau, nullptr, p.ad,
+                                      (const double2*)T, w, s),
+                "k_fact_tables");
+  if (!rc) rc = launched(h, launch_fact_y(c, p.f, nullptr, 1, p.f.n_pad / (32 * p.mi), p.mi, false, w, s), "k_fact_y");
+  double2 *Z = (double2*)(w + p.Z), *Q = (double2*)(w + p.Q);
+  for (int t0 = 0; t0 < c.n_act && !rc; t0 += p.pass) {
+    const int nt = std::min(p.pass, c.n_act - t0);
+    rc = launched(h, launch_adj_zq(c, p.f, t0, nt, p.mi, (const double2*)gH, (const double2*)gS, w, Z, Q, s), "k_adj_zq");
+    if (!rc) rc = launched(h, launch_adj_uc(c, p.f, p.ad, t0, nt, p.mi, w, Z, Q, s), "k_adj_uc");
+    if (!rc) rc = launched(h, launch_adj_gt(c, p.f, p.ad, t0, nt, w, s), "k_adj_gt");
+  }
   if (rc) return rc;
-  rc = launched(h, launch_gradT(c, PH, W, L.n_pad, (double2*)(w + L.partT), (double2*)gT, s), "k_gradT");
-  if (rc) return rc;
-  return launched(h, launch_gradtau(c, PH, PS, (const double2*)(w + L.Y), W, (const double*)(w + L.lam),
-                                    (const double*)(w + L.kv), ng, L.n_pad, (double*)(w + L.partTau), gtau, s),
-                  "k_gradtau");
+  return launched(h, launch_adj_reduce(c, p.ad, h->n_types, h->n_atoms, w, (double2*)gT, gtau, s), "k_adj_reduce");
 }
 
 }  // extern "C"
@@ -1293,7 +1341,8 @@ int record_factored_batch(hsbuild_t h, int n_k, const double* k_frac, const int3
     e = hipMemcpyAsync(w + consts_off, h->consts, sizeof(TypeConsts), hipMemcpyHostToDevice, cs);
   const FactK* many = (const FactK*)(w + many_off);
   if (e == hipSuccess)
-    e = launch_fact_tables(c, ra, consts, FactK{}, many, n_k, (int)gblk, g, tau, nullptr, (const double2*)T, w, cs);
+    e = launch_fact_tables(c, ra, consts, FactK{}, many, n_k, (int)gblk, g, tau, nullptr, FactAdj{}, (const double2*)T, w,
+                           cs);
   if (e == hipSuccess) e = launch_fact_y(c, FactK{}, many, n_k, (int)yblk, mi, false, w, cs);
   if (e == hipSuccess)
     e = launch_fact_hs(c, FactK{}, many, n_k, (int)tile, mi, false, h->tile_group, nullptr, w, H, S, cs);

@@ -1,246 +1,341 @@
-// Adjoint of the H/S build for a real loss L(H, S) with Hermitian incoming
-// gradients gH = dL/dRe H + i dL/dIm H and gS (likewise).
+// Adjoint of the H/S build for a real loss L(H, S) with incoming gradients gH = dL/dRe H + i dL/dIm H
+// and gS (likewise), in the type-factored form (k_fact.hip: R_t real, Y_t = T'_t R_t, phases E):
 //
-// With W the stacked coefficients (rows k = (atom, A|B, L)), Y_a = T_t W_a and
-// P_H = W gH, P_S = W gS (both [K][N_G]):
-//   grad T_t   = sum_{a in t} P_H,a W_a^H                          (2N_L x 2N_L per type)
-//   grad tau_a = -2 sum_G K_G Im c_a(G),
-//   c_a(G)     = sum_{k in a} conj(P_H[k][G]) Y[k][G] + conj(P_S[k][G]) lam_k W[k][G]
-// since every coefficient of atom a carries the phase e^{iK_G.tau_a}
-// (A and B of Eq. 2) and H, S are the sums of Eqs. 4-5.  Nothing is kept
-// from the forward: W and Y are rebuilt by the same kernels.
+//   P_t   = E_t^H E_t,   M_t = R_t^T Y_t,   N_t = R_t^T Lam R_t                       (N_G x N_G)
+//   Z_t   = gH .* conj(P_t),   Q_t = conj(gH) .* M_t + conj(gS) .* N_t
+//   grad T'_t   = R_t Z_t R_t^T,  grad T_t = C grad T'_t C^H  (C: real to complex harmonics)
+//   grad tau_a  = -2 sum_G K_G Im( E_a(G) sum_G' conj(E_a(G')) Q_t[G'][G] ),   a in t
 //
-//   k_transpose,   W^T and zero-padded gH, gS for the products P_H and P_S, which
-//   k_pad_square   run in the 3M form in k_pgemm3m (with the forward's tile routine)
-//   k_gradT        per-atom partials P_H,a W_a^H (FP64 MFMA), one workgroup per
-//                  (64 x 64 tile, atom); k_gradT_reduce sums the atoms of a type
-//                  in a fixed order (deterministic)
-//   k_gradtau      per (atom, 256-column block) partial sums; k_gradtau_reduce
-//                  adds the blocks in a fixed order
+// since T enters through M_t only and tau through the phases only (Eqs. 4-5).  Neither T nor gH, gS
+// is taken to be Hermitian.  Per type and pair of columns: 6 N_L real products for M_t, N_t, as many
+// for R Z, 6 N_t for the phases, where the atom by atom form takes 24 N_t N_L; nothing is kept
+// from the forward.
+//
+//   k_adj_zq      P_t, M_t, N_t per wave tile (as k_fact_hs), Z_t and Q_t to memory
+//   k_adj_uc      (R Z)^T = Z^T R^T, rows G; and the phase sums of grad tau, reduced over the rows
+//                 of a tile to one partial per atom and segment of G'
+//   k_adj_gt      R Z R^T in segments of G
+//   k_adj_reduce  the segments' sums in order, turned back to complex harmonics; grad tau likewise
+//
+// All on v_mfma_f64_16x16x4f64 with operands read straight into registers, one chunk ahead; the
+// transposed copies of R and E (k_fact_tables) keep every operand contiguous along the MFMA's
+// row or column index.  Deterministic: fixed orders, no atomics.
+#include "harmonics.h"
 #include "hs_internal.h"
+#include "wave_tile.h"
 
 namespace hsb {
 
 namespace {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef double d2 __attribute__((ext_vector_type(2)));
-
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
-
-// ---- grad T partials: part[atom][r][c] = sum_G P_H[a*M + r][G] conj(W[a*M + c][G]) ---------
-constexpr int TT = 64, TKG = 16;
-
-__global__ void __launch_bounds__(256) k_gradT(const d2* __restrict__ P, const d2* __restrict__ W, int M, int n_pad,
-                                               d2* __restrict__ part) {
-  __shared__ d2 sP[TKG][TT + 1];
-  __shared__ d2 sW[TKG][TT + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int ntile = (M + TT - 1) / TT;
-  const int r0 = (blockIdx.x / ntile) * TT, c0 = (blockIdx.x % ntile) * TT;
-  const int atom = blockIdx.y;
-  const d2* Pa = P + (int64_t)atom * M * n_pad;
-  const d2* Wa = W + (int64_t)atom * M * n_pad;
-  d4 gr[2][2], gi[2][2];
+// Wave tile of Z_t, Q_t (zeros outside n x n, up to n_pad): all tiles of the square, types over y.
+template <int MI, int NJ, int KC, int WPS>
+__global__ void __launch_bounds__(256, WPS) k_adj_zq(FactCell c, FactK kk, int t0, const d2* __restrict__ gH,
+                                                     const d2* __restrict__ gS, const char* __restrict__ ws,
+                                                     d2* __restrict__ Z, d2* __restrict__ Q) {
+  const int n = kk.n;
+  const int64_t n_pad = kk.n_pad;
+  const int t = t0 + blockIdx.y;
+  const int nb = kk.n_pad / (32 * NJ);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.x / nb * 32 * MI + (wave >> 1) * 16 * MI;
+  const int col0 = blockIdx.x % nb * 32 * NJ + (wave & 1) * 16 * NJ;
+  const int col = col0 + NJ * lr;
+  d4 m1[MI][NJ], m2[MI][NJ], m3[MI][NJ], pR[MI][NJ], pI[MI][NJ];
+  if (row0 < n && col0 < n) {
+    TypedTile<MI, NJ, KC, false> tile(c, kk, row0, col0, nullptr, ws);
+    tile.load_e(t, 0, tile.ec);
+    tile.sums(t, false, m1, m2, m3, pR, pI);
+  } else {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      gr[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-      gi[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    }
-  for (int kc = 0; kc < n_pad; kc += TKG) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
-      const int g = e & 15, r = e >> 4;
-      d2 vp = d2{0.0, 0.0}, vw = d2{0.0, 0.0};
-      if (r0 + r < M) vp = Pa[(int64_t)(r0 + r) * n_pad + kc + g];
-      if (c0 + r < M) vw = Wa[(int64_t)(c0 + r) * n_pad + kc + g];
-      sP[g][r] = vp;
-      sW[g][r] = vw;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < TKG / 4; ++ks) {
-      const int kk = ks * 4 + (lane >> 4);
-      double pr[2], pi[2], wre[2], wim[2], wneg[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const d2 a = sP[kk][wr * 32 + i * 16 + (lane & 15)];
-        pr[i] = a.x; pi[i] = a.y;
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const d2 b = sW[kk][wc * 32 + j * 16 + (lane & 15)];
-        wre[j] = b.x; wim[j] = b.y; wneg[j] = -b.y;
-      }
-      // P conj(W): re = pr wr + pi wi, im = pi wr - pr wi
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gr[i][j] = MFMA(pr[i], wre[j], gr[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gi[i][j] = MFMA(pi[i], wre[j], gi[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gr[i][j] = MFMA(pi[i], wim[j], gr[i][j]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gi[i][j] = MFMA(pr[i], wneg[j], gi[i][j]);
-    }
-    __syncthreads();
+      for (int j = 0; j < NJ; ++j) m1[i][j] = m2[i][j] = m3[i][j] = pR[i][j] = pI[i][j] = d4{0.0, 0.0, 0.0, 0.0};
   }
-  d2* out = part + (int64_t)atom * M * M;
+  d2* z = Z + (int64_t)blockIdx.y * n_pad * n_pad;
+  d2* qq = Q + (int64_t)blockIdx.y * n_pad * n_pad;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int q = 0; q < 4; ++q) {
+      const int r = row0 + MI * (lk + 4 * q) + i;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = r0 + wr * 32 + i * 16 + (lane >> 4) + 4 * q;
-        const int c = c0 + wc * 32 + j * 16 + (lane & 15);
-        if (r < M && c < M) out[(int64_t)r * M + c] = d2{gr[i][j][q], gi[i][j][q]};
+      for (int j = 0; j < NJ; ++j) {
+        d2 h = d2{0.0, 0.0}, s = d2{0.0, 0.0};
+        if (r < n && col + j < n) {
+          h = gH[(int64_t)r * n + col + j];
+          s = gS[(int64_t)r * n + col + j];
+        }
+        const double a = m1[i][j][q], b = m2[i][j][q], d = m3[i][j][q], pr = pR[i][j][q], pi = pI[i][j][q];
+        d2 vz = d2{h.x * pr + h.y * pi, h.y * pr - h.x * pi};
+        d2 vq = d2{h.x * a + h.y * b + s.x * d, h.x * b - h.y * a - s.y * d};
+        if (r >= n || col + j >= n) vz = vq = d2{0.0, 0.0};  // (the sums of pad columns may hold anything)
+        z[(int64_t)r * n_pad + col + j] = vz;
+        qq[(int64_t)r * n_pad + col + j] = vq;
       }
+    }
 }
 
-__global__ void __launch_bounds__(256) k_gradT_reduce(CellArgs c, const d2* __restrict__ part, int M,
-                                                      d2* __restrict__ gT) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int t = blockIdx.y;
-  if (idx >= (int64_t)M * M) return;
-  d2 acc = d2{0.0, 0.0};
-  for (int a = c.type_start[t]; a < c.type_start[t + 1]; ++a) acc += part[(int64_t)a * M * M + idx];
-  gT[(int64_t)t * M * M + idx] = acc;
+// Complex A [k][row], real B [k][col]: re, im += sum over k in [4 k0, 4 k1) (4-row steps), both
+// operands with their leading dimensions, in chunks of KC steps (k1 - k0 a multiple of KC).
+template <int MI, int NJ, int KC>
+__device__ __forceinline__ void product_cr(const d2* __restrict__ A, int64_t ldA, const double* __restrict__ B,
+                                           int64_t ldB, int k0, int k1, d4 (&re)[MI][NJ], d4 (&im)[MI][NJ]) {
+  typedef typename DVec<NJ>::T VB;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  const d2* ap = A + (int64_t)lk * ldA + MI * lr;
+  const double* bp = B + (int64_t)lk * ldB + NJ * lr;
+  struct Chunk { d2 a[KC][MI]; VB b[KC]; };
+  auto load = [&](int s, Chunk& x) {
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      const int64_t k = (int64_t)(s + q) * 4;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) x.a[q][i] = ap[k * ldA + i];
+      x.b[q] = *(const VB*)(bp + k * ldB);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) re[i][j] = im[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  if (k0 >= k1) return;
+  Chunk x;
+  load(k0, x);
+  for (int s = k0; s < k1; s += KC) {
+    Chunk y;
+    load(s + KC < k1 ? s + KC : s, y);
+#pragma unroll
+    for (int q = 0; q < KC; ++q)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const double b = DVec<NJ>::get(x.b[q], j);
+          re[i][j] = MFMA(x.a[q][i].x, b, re[i][j]);
+          im[i][j] = MFMA(x.a[q][i].y, b, im[i][j]);
+        }
+    x = y;
+  }
 }
 
-// ---- grad tau --------------------------------------------------------------------------
-constexpr int TB = 256;
-
-__global__ void __launch_bounds__(TB) k_gradtau(const d2* __restrict__ PH, const d2* __restrict__ PS,
-                                                const d2* __restrict__ Y, const d2* __restrict__ W,
-                                                const double* __restrict__ lam, const double* __restrict__ kv,
-                                                int M, int n, int n_pad, double* __restrict__ part) {
-  __shared__ double red[3][TB / 64];
-  const int G = blockIdx.x * TB + threadIdx.x;
-  const int atom = blockIdx.y;
-  double s = 0.0;
-  if (G < n) {
-    const int64_t base = (int64_t)atom * M * n_pad + G;
-    for (int r = 0; r < M; ++r) {
-      const int64_t o = base + (int64_t)r * n_pad;
-      const d2 ph = PH[o], y = Y[o], ps = PS[o], w = W[o];
-      const double l = lam[atom * M + r];
-      // Im(conj(ph) y) + l Im(conj(ps) w)
-      s += ph.x * y.y - ph.y * y.x + l * (ps.x * w.y - ps.y * w.x);
+// Workgroups blockIdx.x < nu: tiles of UT[G][k] = sum_G' Z[G'][G] RT[G'][k] (2 x 2 waves, rows G).
+// Past them: the phase sums.  One wave per (16 MI columns G, 16 atoms, segment of G'):
+// D[G][a] = sum_G' Q[G'][G] conj(ET[G'][a]) (three real products: P1 = q_r e_r, P2 = q_i e_i,
+// P3 = (q_r + q_i)(e_r - e_i), Re = P1 + P2, Im = P3 - P1 + P2), then sum_G K_G Im(E_a(G) D[G][a])
+// over the tile's columns into part[seg][column block][phase row][3].
+template <int MI, int KC>
+__global__ void __launch_bounds__(256, 2) k_adj_uc(FactCell c, FactK kk, FactAdj ad, int t0, int nu, int nab,
+                                                   const char* __restrict__ ws, const d2* __restrict__ Z,
+                                                   const d2* __restrict__ Q) {
+  const int64_t n_pad = kk.n_pad;
+  const int t = t0 + blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int steps = kk.n_pad / 4;
+  if ((int)blockIdx.x < nu) {
+    const int nkb = (ad.Mt + 32 * MI - 1) / (32 * MI);
+    const int row0 = blockIdx.x / nkb * 32 * MI + (wave >> 1) * 16 * MI;
+    const int col0 = blockIdx.x % nkb * 32 * MI + (wave & 1) * 16 * MI;
+    if (row0 >= kk.n_pad || col0 >= ad.Mt) return;
+    d4 re[MI][MI], im[MI][MI];
+    product_cr<MI, MI, KC>(Z + (int64_t)blockIdx.y * n_pad * n_pad + row0, n_pad,
+                           (const double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + col0, ad.Mt, 0, steps, re, im);
+    d2* U = (d2*)(ws + ad.UT) + (int64_t)blockIdx.y * n_pad * ad.Mt;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+          U[(int64_t)(row0 + MI * (lk + 4 * q) + i) * ad.Mt + col0 + MI * lr + j] = d2{re[i][j][q], im[i][j][q]};
+    return;
+  }
+  const int w = ((int)blockIdx.x - nu) * 4 + wave;  // (column block, atom block, segment), segment fastest
+  const int seg = w % ad.nseg, ab = w / ad.nseg % nab, gb = w / ad.nseg / nab;
+  const int row0 = gb * 16 * MI, a0 = ab * 16;
+  if (row0 >= kk.n_pad || a0 >= c.nat[t]) return;
+  const int nch = steps / KC;
+  const int k0 = (int)((int64_t)nch * seg / ad.nseg) * KC, k1 = (int)((int64_t)nch * (seg + 1) / ad.nseg) * KC;
+  const d2* ET = (const d2*)(ws + ad.ET) + c.eoff[t] + a0;
+  const d2* qp = Q + (int64_t)blockIdx.y * n_pad * n_pad + (int64_t)lk * n_pad + row0 + MI * lr;
+  const d2* ep = ET + (int64_t)lk * ad.et_ld + lr;
+  struct Chunk { d2 a[KC][MI], b[KC]; };
+  auto load = [&](int s, Chunk& x) {
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      const int64_t k = (int64_t)(s + q) * 4;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) x.a[q][i] = qp[k * n_pad + i];
+      x.b[q] = ep[k * ad.et_ld];
+    }
+  };
+  d4 p1[MI], p2[MI], p3[MI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) p1[i] = p2[i] = p3[i] = d4{0.0, 0.0, 0.0, 0.0};
+  if (k0 < k1) {
+    Chunk x;
+    load(k0, x);
+    for (int s = k0; s < k1; s += KC) {
+      Chunk y;
+      load(s + KC < k1 ? s + KC : s, y);
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        const double es = x.b[q].x - x.b[q].y;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          p1[i] = MFMA(x.a[q][i].x, x.b[q].x, p1[i]);
+          p2[i] = MFMA(x.a[q][i].y, x.b[q].y, p2[i]);
+          p3[i] = MFMA(x.a[q][i].x + x.a[q][i].y, es, p3[i]);
+        }
+      }
+      x = y;
     }
   }
+  // lane: atom a0 + lr, columns G = row0 + MI (lk + 4 q) + i; pads of E are zero
+  const double* kv = (const double*)(ws + kk.kv);
   double v[3] = {0.0, 0.0, 0.0};
-  if (G < n) {
-    v[0] = s * kv[4 * (int64_t)G + 0];
-    v[1] = s * kv[4 * (int64_t)G + 1];
-    v[2] = s * kv[4 * (int64_t)G + 2];
-  }
-  // wave reduction (fixed butterfly order), then across the block's waves
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[d] += __shfl_xor(v[d], off, 64);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane == 0) {
-    red[0][wave] = v[0];
-    red[1][wave] = v[1];
-    red[2][wave] = v[2];
+    for (int q = 0; q < 4; ++q) {
+      const int G = row0 + MI * (lk + 4 * q) + i;
+      const d2 e = ET[(int64_t)G * ad.et_ld + lr];
+      const double re = p1[i][q] + p2[i][q], im = p3[i][q] - p1[i][q] + p2[i][q];
+      const double s = e.x * im + e.y * re;
+      v[0] += s * kv[4 * G + 0];
+      v[1] += s * kv[4 * G + 1];
+      v[2] += s * kv[4 * G + 2];
+    }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    v[d] += __shfl_xor(v[d], 16, 64);
+    v[d] += __shfl_xor(v[d], 32, 64);
   }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    double acc = 0.0;
-    for (int w = 0; w < TB / 64; ++w) acc += red[threadIdx.x][w];
-    part[((int64_t)atom * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = acc;
+  if (lk == 0 && a0 + lr < c.nat[t]) {
+    double* part = (double*)(ws + ad.partTau) + (((int64_t)seg * ad.ngb + gb) * ad.et_ld + c.eoff[t] + a0 + lr) * 3;
+    part[0] = v[0];
+    part[1] = v[1];
+    part[2] = v[2];
   }
 }
 
-__global__ void __launch_bounds__(64) k_gradtau_reduce(const double* __restrict__ part, int nblocks, int n_atoms,
-                                                       double* __restrict__ gtau) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 3 * n_atoms) return;
-  const int atom = i / 3, d = i % 3;
-  double acc = 0.0;
-  for (int b = 0; b < nblocks; ++b) acc += part[((int64_t)atom * nblocks + b) * 3 + d];
-  gtau[i] = -2.0 * acc;
+// part[t][seg][k][k'] = sum over the segment's G of UT[G][k] RT[G][k'].
+template <int MI, int KC>
+__global__ void __launch_bounds__(256, 2) k_adj_gt(FactCell c, FactK kk, FactAdj ad, int t0,
+                                                   const char* __restrict__ ws) {
+  const int64_t n_pad = kk.n_pad;
+  const int t = t0 + blockIdx.y, seg = blockIdx.z;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int nkb = (ad.Mt + 32 * MI - 1) / (32 * MI);
+  const int row0 = blockIdx.x / nkb * 32 * MI + (wave >> 1) * 16 * MI;
+  const int col0 = blockIdx.x % nkb * 32 * MI + (wave & 1) * 16 * MI;
+  if (row0 >= ad.Mt || col0 >= ad.Mt) return;
+  const int nch = kk.n_pad / 4 / KC;
+  const int k0 = (int)((int64_t)nch * seg / ad.ngt) * KC, k1 = (int)((int64_t)nch * (seg + 1) / ad.ngt) * KC;
+  d4 re[MI][MI], im[MI][MI];
+  product_cr<MI, MI, KC>((const d2*)(ws + ad.UT) + (int64_t)blockIdx.y * n_pad * ad.Mt + row0, ad.Mt,
+                         (const double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + col0, ad.Mt, k0, k1, re, im);
+  d2* out = (d2*)(ws + ad.partT) + ((int64_t)t * ad.ngt + seg) * ad.Mt * ad.Mt;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < MI; ++j)
+        out[(int64_t)(row0 + MI * (lk + 4 * q) + i) * ad.Mt + col0 + MI * lr + j] = d2{re[i][j][q], im[i][j][q]};
 }
 
-// ---- operand preparation for the 3M products --------------------------------------
-// WT[G][k] = W[k][G] for k < K_pad, 0 for K_pad <= k < Kt; 32 x 32 tiles through LDS.
-__global__ void __launch_bounds__(256) k_transpose(const d2* __restrict__ W, int K_pad, int n_pad, int Kt,
-                                                   d2* __restrict__ WT) {
-  __shared__ d2 t[32][33];
-  const int k0 = blockIdx.x * 32, g0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+// grad T[(X,l,m)][(X',l',m')] = sum c(l,m,mu) (sum over segments of part)[mu][mu'] conj(c(l',m',mu')),
+// zero for a type without atoms; and grad tau[a] = -2 sum of its partials (blocks past the T ones).
+__global__ void __launch_bounds__(256) k_adj_reduce(FactCell c, FactAdj ad, int n_types, int ntb,
+                                                    const char* __restrict__ ws, d2* __restrict__ gT,
+                                                    double* __restrict__ gtau) {
+  if ((int)blockIdx.x >= ntb) {
+    const int i = ((int)blockIdx.x - ntb) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;  // wave: (atom, axis)
+    int t = 0, a = i / 3;
+    while (t < c.n_act && a >= c.nat[t]) a -= c.nat[t++];
+    if (t >= c.n_act || blockIdx.y > 0) return;
+    const double* part = (const double*)(ws + ad.partTau) + (int64_t)(c.eoff[t] + a) * 3 + i % 3;
+    double s = 0.0;
+    for (int b = lane; b < ad.nseg * ad.ngb; b += 64) s += part[(int64_t)b * ad.et_ld * 3];
 #pragma unroll
-  for (int r = ty; r < 32; r += 8) {
-    const int k = k0 + r;
-    t[r][tx] = k < K_pad ? W[(int64_t)k * n_pad + g0 + tx] : d2{0.0, 0.0};
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) gtau[(c.atom0[t] + a) * 3 + i % 3] = -2.0 * s;
+    return;
   }
-  __syncthreads();
-#pragma unroll
-  for (int r = ty; r < 32; r += 8) WT[(int64_t)(g0 + r) * Kt + k0 + tx] = t[tx][r];
-}
-
-// gp[r][c] = g[r][c] for r, c < n, 0 elsewhere (r, c < n_pad).
-__global__ void __launch_bounds__(256) k_pad_square(const d2* __restrict__ g, int n, int n_pad, d2* __restrict__ gp) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= n_pad) return;
-  for (int r = blockIdx.y; r < n_pad; r += gridDim.y)
-    gp[(int64_t)r * n_pad + c] = (r < n && c < n) ? g[(int64_t)r * n + c] : d2{0.0, 0.0};
+  const int M = 2 * c.n_l;
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (int64_t)M * M) return;
+  const int t = blockIdx.y, r = (int)(idx / M), k = (int)(idx % M);
+  int at = 0;
+  while (at < c.n_act && c.type[at] != t) ++at;
+  d2 v = d2{0.0, 0.0};
+  if (at < c.n_act) {
+    const int xr = r >= c.n_l, xk = k >= c.n_l;
+    int lr, mr, lk, mk;
+    lm_of(r - xr * c.n_l, lr, mr);
+    lm_of(k - xk * c.n_l, lk, mk);
+    const int br = xr * c.n_l + lr * lr + lr, bk = xk * c.n_l + lk * lk + lk;
+    const d2* part = (const d2*)(ws + ad.partT) + (int64_t)at * ad.ngt * ad.Mt * ad.Mt;
+    for (int ir = 0; ir < (mr ? 2 : 1); ++ir)
+      for (int ik = 0; ik < (mk ? 2 : 1); ++ik) {
+        const int u1 = ir ? -mr : mr, u2 = ik ? -mk : mk;
+        d2 s = d2{0.0, 0.0};
+        for (int g = 0; g < ad.ngt; ++g) s += part[((int64_t)g * ad.Mt + br + u1) * ad.Mt + bk + u2];
+        const double2 x = times_i(make_double2(s.x, s.y), harmonic_power(lr, mr, u1) - harmonic_power(lk, mk, u2));
+        v += d2{x.x, x.y};
+      }
+    if (mr && mk) v *= 0.5;
+    else if (mr || mk) v *= 0.70710678118654752440;
+  }
+  gT[(int64_t)t * M * M + idx] = v;
 }
 
 }  // namespace
 
-int gradtau_blocks(int n) { return (n + TB - 1) / TB; }
-
-hipError_t launch_transpose(const double2* W, int K_pad, int n_pad, int Kt, double2* WT, hipStream_t s) {
-  if (Kt % 32 || n_pad % 32 || Kt < K_pad) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_transpose, dim3(Kt / 32, n_pad / 32), dim3(256), 0, s, (const d2*)W, K_pad, n_pad, Kt,
-                     (d2*)WT);
+hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int mi, const double2* gH,
+                         const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s) {
+  const int nb = kk.n_pad / (32 * mi);
+  const dim3 grid(nb * nb, nt);
+  if (mi == 2)
+    hipLaunchKernelGGL((k_adj_zq<2, 2, 2, 1>), grid, dim3(256), 0, s, c, kk, t0, (const d2*)gH, (const d2*)gS, ws,
+                       (d2*)Z, (d2*)Q);
+  else
+    hipLaunchKernelGGL((k_adj_zq<1, 1, 4, 2>), grid, dim3(256), 0, s, c, kk, t0, (const d2*)gH, (const d2*)gS, ws,
+                       (d2*)Z, (d2*)Q);
   return hipGetLastError();
 }
 
-hipError_t launch_pad_square(const double2* g, int n, int n_pad, double2* gp, hipStream_t s) {
-  hipLaunchKernelGGL(k_pad_square, dim3((n_pad + 255) / 256, n_pad < 4096 ? n_pad : 4096), dim3(256), 0, s,
-                     (const d2*)g, n, n_pad, (d2*)gp);
+hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, int mi, char* ws,
+                         const double2* Z, const double2* Q, hipStream_t s) {
+  const int nkb = (ad.Mt + 32 * mi - 1) / (32 * mi);
+  const int nu = kk.n_pad / (32 * mi) * nkb;
+  int nab = 0;
+  for (int t = t0; t < t0 + nt; ++t) nab = nab > (c.nat[t] + 15) / 16 ? nab : (c.nat[t] + 15) / 16;
+  const int nc = (kk.n_pad / (16 * mi) * nab * ad.nseg + 3) / 4;
+  const dim3 grid(nu + nc, nt);
+  if (mi == 2)
+    hipLaunchKernelGGL((k_adj_uc<2, 4>), grid, dim3(256), 0, s, c, kk, ad, t0, nu, nab, ws, (const d2*)Z, (const d2*)Q);
+  else
+    hipLaunchKernelGGL((k_adj_uc<1, 4>), grid, dim3(256), 0, s, c, kk, ad, t0, nu, nab, ws, (const d2*)Z, (const d2*)Q);
   return hipGetLastError();
 }
 
-hipError_t launch_gradT(const CellArgs& c, const double2* PH, const double2* W, int n_pad, double2* part,
-                        double2* gT, hipStream_t s) {
-  const int M = 2 * c.n_l;
-  const int ntile = (M + TT - 1) / TT;
-  hipLaunchKernelGGL(k_gradT, dim3(ntile * ntile, c.n_atoms), dim3(256), 0, s, (const d2*)PH, (const d2*)W, M,
-                     n_pad, (d2*)part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gradT_reduce, dim3((M * M + 255) / 256, c.n_types), dim3(256), 0, s, c, (const d2*)part, M,
-                     (d2*)gT);
+hipError_t launch_adj_gt(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
+                         hipStream_t s) {
+  const int nkb = (ad.Mt + 63) / 64;
+  hipLaunchKernelGGL((k_adj_gt<2, 4>), dim3(nkb * nkb, nt, ad.ngt), dim3(256), 0, s, c, kk, ad, t0, ws);
   return hipGetLastError();
 }
 
-hipError_t launch_gradtau(const CellArgs& c, const double2* PH, const double2* PS, const double2* Y,
-                          const double2* W, const double* lam, const double* kv, int n, int n_pad, double* part,
-                          double* gtau, hipStream_t s) {
-  const int M = 2 * c.n_l;
-  const int nb = gradtau_blocks(n);
-  hipLaunchKernelGGL(k_gradtau, dim3(nb, c.n_atoms), dim3(TB), 0, s, (const d2*)PH, (const d2*)PS, (const d2*)Y,
-                     (const d2*)W, lam, kv, M, n, n_pad, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gradtau_reduce, dim3((3 * c.n_atoms + 63) / 64), dim3(64), 0, s, (const double*)part, nb,
-                     c.n_atoms, gtau);
+hipError_t launch_adj_reduce(const FactCell& c, const FactAdj& ad, int n_types, int n_atoms, const char* ws,
+                             double2* gT, double* gtau, hipStream_t s) {
+  const int M = 2 * c.n_l, ntb = (M * M + 255) / 256;
+  hipLaunchKernelGGL(k_adj_reduce, dim3(ntb + (3 * n_atoms + 3) / 4, n_types), dim3(256), 0, s, c, ad, n_types, ntb, ws,
+                     (d2*)gT, gtau);
   return hipGetLastError();
 }
 

@@ -26,42 +26,15 @@
 // without LDS, and waves need no barrier: they start, run ahead and leave on their own (a wave
 // below the diagonal leaves at once).  A lane holds pairs of neighbouring columns, one for each of
 // its two blocks (16-byte loads, 32-byte stores): block i of a wave covers the columns of parity i.
+#include "harmonics.h"
 #include "hs_internal.h"
 #include "special.h"
 #include "tiles.h"
+#include "wave_tile.h"
 
 namespace hsb {
 
 namespace {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef double d2 __attribute__((ext_vector_type(2)));
-
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
-
-// c(l,m,mu): the coefficient of s_{l,mu} in i^l conj(Y_lm); nonzero for |m| = |mu| only.  Without
-// its factor 1/sqrt(2) (m != 0) it is a power of i times a sign: power e of i.
-__device__ inline int harmonic_power(int l, int m, int mu) {
-  // m > 0: c = i^l (s_m - i s_-m);  m < 0: c = (-1)^m i^l (s_|m| + i s_-|m|)
-  int e = l;
-  if (m < 0 && (m & 1)) e += 2;
-  if (mu < 0) e += m > 0 ? 3 : 1;
-  return e & 3;
-}
-
-__device__ inline double2 times_i(double2 v, int e) {
-  switch (e & 3) {
-    case 0: return v;
-    case 1: return make_double2(-v.y, v.x);
-    case 2: return make_double2(-v.x, -v.y);
-    default: return make_double2(v.y, -v.x);
-  }
-}
-
-__device__ inline void lm_of(int L, int& l, int& m) {
-  l = (int)sqrt((double)L + 0.5);
-  m = L - l * l - l;
-}
 
 __device__ inline int find_block(const FactK* ks, int nk, int b, int FactK::*first) {
   int lo = 0, hi = nk - 1;
@@ -73,7 +46,8 @@ __device__ inline int find_block(const FactK* ks, int nk, int b, int FactK::*fir
   return lo;
 }
 
-constexpr int kTabG = 64;  // columns per workgroup of k_fact_tables
+constexpr int kTabG = 64;          // columns per workgroup of k_fact_tables
+constexpr int kTabS = kTabG + 1;  // their stride in LDS: the transposed copies read along the rows
 
 // Blocks x < ngb: type blockIdx.y's R rows and phases (and, for the first type, the K vectors) of 64
 // columns; blocks past them: T'.  Latency-bound (a few hundred workgroups of short serial
@@ -84,8 +58,8 @@ constexpr int kTabG = 64;  // columns per workgroup of k_fact_tables
 __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, const TypeConsts* __restrict__ consts,
                                                      FactK one, const FactK* __restrict__ many, int nk, int ngb,
                                                      const int32_t* __restrict__ g, const double* __restrict__ tau,
-                                                     const FactRep* __restrict__ rep, const double2* __restrict__ T,
-                                                     char* __restrict__ ws) {
+                                                     const FactRep* __restrict__ rep, FactAdj ad,
+                                                     const double2* __restrict__ T, char* __restrict__ ws) {
   extern __shared__ double sh[];
   const int t = blockIdx.y;
   const int tid = threadIdx.x;
@@ -136,8 +110,8 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
   const int G = (blockIdx.x - kk.gblk0) * kTabG + lane;
   const bool valid = G < kk.n;
   double* ang = sh;                            // [n_l][64] real harmonics times pre
-  double* jl = ang + c.n_l * kTabG;            // [l_max + 2][64]
-  double* ab = jl + (lmax + 2) * kTabG;        // [2][l_max + 1][64]
+  double* jl = ang + c.n_l * kTabS;            // [l_max + 2][64]
+  double* ab = jl + (lmax + 2) * kTabS;        // [2][l_max + 1][64]
   double kx = 0.0, ky = 0.0, kz = 0.0;
   if (valid) {
     const int32_t* gi = g + 3 * (kk.g_row + G);
@@ -153,10 +127,10 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
       double* kv = (double*)(ws + kk.kv);
       kv[4 * G + 0] = kx; kv[4 * G + 1] = ky; kv[4 * G + 2] = kz; kv[4 * G + 3] = kn;
     }
-    if (!(x < 2.0)) sph_bessel_back(lmax + 1, x, jl + lane, kTabG);
+    if (!(x < 2.0)) sph_bessel_back(lmax + 1, x, jl + lane, kTabS);
   } else {
     if (x < 2.0) {
-      for (int l = wave - 1; l <= lmax + 1; l += 3) jl[l * kTabG + lane] = sph_bessel_series(l, x);
+      for (int l = wave - 1; l <= lmax + 1; l += 3) jl[l * kTabS + lane] = sph_bessel_series(l, x);
     }
     double ct = 1.0, wr = 0.0, wi = 0.0;
     if (!(kn < 1e-12)) {
@@ -180,8 +154,8 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
           p0 = p1;
           p1 = q;
         }
-        ang[(l * l + l + m) * kTabG + lane] = p1 * sr;
-        if (m) ang[(l * l + l - m) * kTabG + lane] = p1 * si;
+        ang[(l * l + l + m) * kTabS + lane] = p1 * sr;
+        if (m) ang[(l * l + l - m) * kTabS + lane] = p1 * si;
       }
     }
   }
@@ -196,21 +170,21 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
       u = q[0]; du = q[1]; ud = q[2]; dud = q[3];
     }
     const double det = u * dud - ud * du;
-    const double val = jl[l * kTabG + lane];
-    const double up = jl[(l + 1) * kTabG + lane];
-    const double dj = l ? (l * jl[(l - 1) * kTabG + lane] - (l + 1) * up) / (2.0 * l + 1.0) : -up;
+    const double val = jl[l * kTabS + lane];
+    const double up = jl[(l + 1) * kTabS + lane];
+    const double dj = l ? (l * jl[(l - 1) * kTabS + lane] - (l + 1) * up) / (2.0 * l + 1.0) : -up;
     const double slope = kn * dj;
-    ab[l * kTabG + lane] = (val * dud - ud * slope) / det;
-    ab[(nl1 + l) * kTabG + lane] = (u * slope - du * val) / det;
+    ab[l * kTabS + lane] = (val * dud - ud * slope) / det;
+    ab[(nl1 + l) * kTabS + lane] = (u * slope - du * val) / det;
   }
   __syncthreads();
   double* R = (double*)(ws + kk.R) + (int64_t)t * c.Mr * n_pad + G;
   for (int L = wave; L < c.n_l; L += 4) {
     int l, m;
     lm_of(L, l, m);
-    const double s = ang[L * kTabG + lane];
-    R[(int64_t)L * n_pad] = valid ? s * ab[l * kTabG + lane] : 0.0;
-    R[(int64_t)(c.n_l + L) * n_pad] = valid ? s * ab[(nl1 + l) * kTabG + lane] : 0.0;
+    const double s = ang[L * kTabS + lane];
+    R[(int64_t)L * n_pad] = valid ? s * ab[l * kTabS + lane] : 0.0;
+    R[(int64_t)(c.n_l + L) * n_pad] = valid ? s * ab[(nl1 + l) * kTabS + lane] : 0.0;
   }
   for (int r = 2 * c.n_l + wave; r < c.Mr; r += 4) R[(int64_t)r * n_pad] = 0.0;
   double2* E = (double2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad + G;
@@ -224,16 +198,25 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
       v = make_double2(q, s);
     }
     E[(int64_t)a * n_pad] = v;
+    if (ad.Mt) ((double2*)(ws + ad.ET))[(int64_t)G * ad.et_ld + c.eoff[t] + a] = v;
+  }
+  if (!ad.Mt) return;
+  // transposed copy of R: lanes along the rows
+  const int G0 = (blockIdx.x - kk.gblk0) * kTabG;
+  double* RT = (double*)(ws + ad.RT) + ((int64_t)t * n_pad + G0) * ad.Mt;
+  for (int e = tid; e < kTabG * ad.Mt; e += 256) {
+    const int q = e / ad.Mt, r = e - q * ad.Mt;
+    double v = 0.0;
+    if (r < 2 * c.n_l && G0 + q < kk.n) {
+      const int x2 = r >= c.n_l, L = r - x2 * c.n_l;
+      int l, m;
+      lm_of(L, l, m);
+      v = ang[L * kTabS + q] * ab[(x2 * nl1 + l) * kTabS + q];
+    }
+    RT[(int64_t)q * ad.Mt + r] = v;
   }
 }
 
-// A lane's values of N neighbouring columns, as one load.
-template <int N>
-struct DVec;
-template <>
-struct DVec<1> { typedef double T; static __device__ double get(T v, int) { return v; } };
-template <>
-struct DVec<2> { typedef d2 T; static __device__ double get(T v, int i) { return v[i]; } };
 
 // Y_t = T'_t R_t (real parts only if REAL): workgroup of 2 x 2 waves, each 16 MI rows x 16 NJ columns.
 template <int MI, int NJ, bool REAL>
@@ -305,17 +288,13 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
 }
 
 // Upper triangles of H and S: workgroup of 2 x 2 waves, each one wave tile of 16 MI rows (G') x
-// 16 NJ columns (G).  Per type: P_t over the phase rows (complex, three real products:
-// P1 = a_r b_r, P2 = a_i b_i, P3 = (a_r - a_i)(b_r + b_i), Re = P1 + P2, Im = P3 - P1 + P2; the
-// real form two, into one sum, the columns' phases weighted with the atom's multiplicity), then
-// the sums over the R rows (H: R^T Y, S: R^T lam R) in the same registers, then P_t times the sums
-// into the running H and S.
+// 16 NJ columns (G): per type P_t times the sums over its R rows (TypedTile), into the running H
+// and S.
 template <int MI, int NJ, int KC, int WPS, bool REAL>
 __global__ void __launch_bounds__(256, WPS) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
                                                       int num_wg, int gr, const FactRep* __restrict__ rep,
                                                       const char* __restrict__ ws, void* __restrict__ H,
                                                       void* __restrict__ S) {
-  static_assert(kFactRows % (4 * KC) == 0, "rows are padded to whole chunks");
   int start, len;
   xcd_range(blockIdx.x % kXcds, num_wg, start, len);
   const int w = start + blockIdx.x / kXcds;
@@ -331,127 +310,17 @@ __global__ void __launch_bounds__(256, WPS) k_fact_hs(FactCell c, FactK one, con
   const int row0 = bi * 32 * MI + (wave >> 1) * 16 * MI, col0 = bj * 32 * NJ + (wave & 1) * 16 * NJ;
   if (row0 >= n || col0 >= n || col0 + 16 * NJ <= row0) return;
 
-  typedef typename DVec<MI>::T VA;
-  typedef typename DVec<NJ>::T VB;
-  struct EChunk { d2 a[KC][MI], b[KC][NJ]; double w[KC]; };
-  struct MChunk { VA a[KC]; VB b[KC]; VB yr[KC]; d2 y[KC][NJ]; double lam[KC]; };
-  const int row = row0 + MI * lr, col = col0 + NJ * lr;
-  auto load_e = [&](int t, int ch, EChunk& e) {
-    const d2* base = (const d2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad;
-#pragma unroll
-    for (int q = 0; q < KC; ++q) {
-      const int k = (ch * KC + q) * 4 + lk;
-      const d2* p = base + (int64_t)k * n_pad;
-#pragma unroll
-      for (int i = 0; i < MI; ++i) e.a[q][i] = p[row + i];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) e.b[q][j] = p[col + j];
-      if constexpr (REAL) e.w[q] = k < c.nat[t] ? rep[c.atom0[t] + k].weight : 0.0;
-    }
-  };
-  auto load_m = [&](int t, int ch, MChunk& m) {
-#pragma unroll
-    for (int q = 0; q < KC; ++q) {
-      const int64_t k = (int64_t)t * c.Mr + (ch * KC + q) * 4 + lk;
-      const double* p = (const double*)(ws + kk.R) + k * n_pad;
-      m.a[q] = *(const VA*)(p + row);
-      m.b[q] = *(const VB*)(p + col);
-      m.lam[q] = ((const double*)(ws + c.lam))[k];
-      if constexpr (REAL) {
-        m.yr[q] = *(const VB*)((const double*)(ws + kk.Y) + k * n_pad + col);
-      } else {
-        const d2* yp = (const d2*)(ws + kk.Y) + k * n_pad + col;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) m.y[q][j] = yp[j];
-      }
-    }
-  };
-
-  const d4 z = d4{0.0, 0.0, 0.0, 0.0};
-  d4 pR[MI][NJ], pI[MI][NJ], m1[MI][NJ], m2[MI][NJ], m3[MI][NJ];
+  const int col = col0 + NJ * lr;
   d4 hR[MI][NJ], hI[MI][NJ], sR[MI][NJ], sI[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) hR[i][j] = hI[i][j] = sR[i][j] = sI[i][j] = z;
-
-  const int ksm = (2 * c.n_l + 3) / 4, ncm = (ksm + KC - 1) / KC;
-  EChunk ec;
-  MChunk mc;
-  load_e(0, 0, ec);
+    for (int j = 0; j < NJ; ++j) hR[i][j] = hI[i][j] = sR[i][j] = sI[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  TypedTile<MI, NJ, KC, REAL> tile(c, kk, row0, col0, rep, ws);
+  tile.load_e(0, 0, tile.ec);
   for (int t = 0; t < c.n_act; ++t) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) m1[i][j] = m2[i][j] = m3[i][j] = z;
-    load_m(t, 0, mc);  // lands behind the phase sums
-    const int kse = (c.nat[t] + 3) / 4, nce = (kse + KC - 1) / KC;
-    for (int ch = 0; ch < nce; ++ch) {
-      EChunk en;
-      load_e(t, ch + 1 < nce ? ch + 1 : ch, en);
-#pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        if (ch * KC + q < kse) {  // uniform
-          double ad[MI], bs[NJ];
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            if constexpr (REAL) ec.b[q][j] *= ec.w[q];
-            bs[j] = ec.b[q][j].x + ec.b[q][j].y;
-          }
-#pragma unroll
-          for (int i = 0; i < MI; ++i) ad[i] = ec.a[q][i].x - ec.a[q][i].y;
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-              m1[i][j] = MFMA(ec.a[q][i].x, ec.b[q][j].x, m1[i][j]);
-              if constexpr (REAL) {
-                m1[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m1[i][j]);
-              } else {
-                m2[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m2[i][j]);
-                m3[i][j] = MFMA(ad[i], bs[j], m3[i][j]);
-              }
-            }
-        }
-      }
-      ec = en;
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        pR[i][j] = REAL ? m1[i][j] : m1[i][j] + m2[i][j];
-        pI[i][j] = m3[i][j] - m1[i][j] + m2[i][j];
-        m1[i][j] = m2[i][j] = m3[i][j] = z;
-      }
-    if (t + 1 < c.n_act) load_e(t + 1, 0, ec);  // lands behind the R sums
-    for (int ch = 0; ch < ncm; ++ch) {
-      MChunk mn;
-      load_m(t, ch + 1 < ncm ? ch + 1 : ch, mn);
-#pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        if (ch * KC + q < ksm) {  // uniform
-          double ls[NJ];
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) ls[j] = mc.lam[q] * DVec<NJ>::get(mc.b[q], j);
-#pragma unroll
-          for (int i = 0; i < MI; ++i) {
-            const double ai = DVec<MI>::get(mc.a[q], i);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-              if constexpr (REAL) {
-                m1[i][j] = MFMA(ai, DVec<NJ>::get(mc.yr[q], j), m1[i][j]);
-              } else {
-                m1[i][j] = MFMA(ai, mc.y[q][j].x, m1[i][j]);
-                m2[i][j] = MFMA(ai, mc.y[q][j].y, m2[i][j]);
-              }
-              m3[i][j] = MFMA(ai, ls[j], m3[i][j]);
-            }
-          }
-        }
-      }
-      mc = mn;
-    }
+    d4 pR[MI][NJ], pI[MI][NJ], m1[MI][NJ], m2[MI][NJ], m3[MI][NJ];
+    tile.sums(t, t + 1 < c.n_act, m1, m2, m3, pR, pI);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -512,11 +381,11 @@ int fact_tiles(int n, int mi) {
 
 hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const TypeConsts* consts, const FactK& one,
                               const FactK* many, int nk, int ngb, const int32_t* g, const double* tau,
-                              const FactRep* rep, const double2* T, char* ws, hipStream_t s) {
-  const size_t lds = (size_t)(c.n_l + c.l_max + 2 + 2 * (c.l_max + 1)) * kTabG * sizeof(double);
+                              const FactRep* rep, const FactAdj& ad, const double2* T, char* ws, hipStream_t s) {
+  const size_t lds = (size_t)(c.n_l + c.l_max + 2 + 2 * (c.l_max + 1)) * kTabS * sizeof(double);
   const int ntb = (int)(((int64_t)c.Mr * c.Mc + 255) / 256);
   hipLaunchKernelGGL(k_fact_tables, dim3(ngb + ntb, c.n_act), dim3(256), lds, s, c, ra, consts, one, many, nk, ngb, g,
-                     tau, rep, T, ws);
+                     tau, rep, ad, T, ws);
   return hipGetLastError();
 }
 

@@ -125,3 +125,58 @@ def test_batch_uploads_radial_data_past_the_by_value_limit():
         for k in range(2):
             for M, r in zip((H, S), ref[k]):
                 assert torch.equal(M[int(off[k]):int(off[k]) + 6400].view(80, 80)[iu[0], iu[1]], r[iu[0], iu[1]])
+
+
+@pytest.mark.parametrize("atoms,l_max,n_g", [((1,), 0, 1), ((2,), 4, 33), ((3, 1, 2), 3, 64), ((17, 16), 2, 65),
+                                             ((1, 1, 1), 1, 300),  # one type per pass: its Z and Q fill the workspace
+                                             ((2, 0, 1), 5, 129), ((1,) * 9, 7, 80)])
+def test_adjoint_of_general_matrices(atoms, l_max, n_g):
+    """hsbuild_backward against the stacked formulas grad T_t = sum_a W_a gH W_a^H and
+    c_a = conj(W_a gH) . (T W_a) + conj(W_a gS) . (lam W_a), with T, gH and gS none of them
+    Hermitian: neither path may assume it.  Bar: FP64 rounding through two products of at most
+    300 x 300 terms, 1e-12 relative for T; 1e-11 for tau, whose sums cancel."""
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = _case(atoms, l_max, n_g)
+    print("atoms", atoms, "l_max", l_max, "N_G", n_g, flush=True)
+    rng = np.random.default_rng(5)
+    z = lambda *s: rng.normal(size=s) + 1j * rng.normal(size=s)  # noqa: E731
+    m = 2 * case["n_l"]
+    case["T"] = z(case["n_types"], m, m)
+    gH, gS = z(n_g, n_g), z(n_g, n_g)
+    b = HSBuilder.from_case(case)
+    g, tau, T = case_tensors(case)
+    gT, gtau = b.backward(case["k_frac"], g, tau, T, torch.as_tensor(gH, device="cuda"),
+                          torch.as_tensor(gS, device="cuda"))
+    W = o.coefficients(case).reshape(case["n_atoms"], m, n_g)
+    lv = np.concatenate([[l] * (2 * l + 1) for l in range(l_max + 1)])
+    K = (case["g"] + case["k_frac"]) @ (2.0 * np.pi * np.linalg.inv(case["lattice"]).T)
+    rT, rtau = np.zeros_like(case["T"]), np.zeros((case["n_atoms"], 3))
+    for a, t in enumerate(case["atom_type"]):
+        lam = np.concatenate([np.ones(len(lv)), case["udot_norm2"][t][lv]])[:, None]
+        PH, PS = W[a] @ gH, W[a] @ gS
+        rT[t] += PH @ W[a].conj().T
+        c = (PH.conj() * (case["T"][t] @ W[a]) + PS.conj() * (lam * W[a])).sum(axis=0)
+        rtau[a] = -2.0 * (K * c.imag[:, None]).sum(axis=0)
+    eT, etau = _rel(gT.cpu().numpy(), rT), _rel(gtau.cpu().numpy(), rtau)
+    print("grad T %.2e grad tau %.2e" % (eT, etau), flush=True)
+    assert eT <= 1e-12 and etau <= 1e-11
+
+
+def test_forward_of_a_general_T():
+    """The upper triangle of W^H T W for a T that is not Hermitian (the library does not use that
+    it is), in every FP64 form."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = _case((3, 2), 4, 100)
+    rng = np.random.default_rng(6)
+    m = 2 * case["n_l"]
+    case["T"] = rng.normal(size=(2, m, m)) + 1j * rng.normal(size=(2, m, m))
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    W = o.coefficients(case).reshape(case["n_atoms"], m, 100)
+    ref = sum(W[a].conj().T @ case["T"][t] @ W[a] for a, t in enumerate(case["atom_type"]))
+    iu = np.triu_indices(100)
+    for mode in (1, 0):
+        b.set_option(N.HSB_OPT_SPLIT_K, mode)
+        H, _ = b.forward(case["k_frac"], g, tau, T)
+        assert _rel(H.cpu().numpy()[iu], ref[iu]) <= TOL

@@ -72,10 +72,14 @@ enum {
  * Gaussian integers, multiplies their residues modulo n_slices coprime moduli
  * below 256 on the int8 matrix cores (exact int32 sums, two products per
  * modulus for a complex product) and recovers the integer products by the
- * Chinese remainder theorem in FP64.  HSB_SPLIT_CRT_BF16 and
+ * Chinese remainder theorem in FP64.  hsbuild_forward and hsbuild_forward_real
+ * take the columns per atom type (see hsbuild_forward_factored), with the phase
+ * sums and S in FP64; hsbuild_forward_coefficients takes the stacked ones, for
+ * H and for S.  HSB_SPLIT_CRT_BF16 and
  * HSB_SPLIT_CRT_FP16 are the same residue form with the residues as bfloat16
  * or half integers on the 16-bit matrix cores (FP32 sums, exact for integers
- * below 2^24: reduced modulo each modulus every 1024 stacked rows); the three
+ * below 2^24: the stacked form reduces them modulo each modulus every 1024
+ * rows); the three
  * give bitwise the same H and S. */
 enum { HSB_FP64 = 0, HSB_SPLIT_FP16 = 1, HSB_SPLIT_BF16 = 2, HSB_SPLIT_INT8 = 3, HSB_SPLIT_CRT = 4,
        HSB_SPLIT_CRT_BF16 = 5, HSB_SPLIT_CRT_FP16 = 6 };
@@ -185,9 +189,9 @@ int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, co
  * upper triangle written; equal to the real parts of hsbuild_forward's
  * outputs up to FP64 rounding (undefined if the symmetry does not hold).
  * Other arguments as hsbuild_forward.  A handle created with HSB_FP64 runs
- * the type-factored form on real parts; one created with HSB_SPLIT_INT8 or a residue form
- * (HSB_SPLIT_CRT*) runs that split contraction (the real parts of the split
- * products, to the split path's error); HSB_SPLIT_BF16 and HSB_SPLIT_FP16 handles get
+ * the type-factored form on real parts, as does one with a residue form
+ * (HSB_SPLIT_CRT*), with H by residues; HSB_SPLIT_INT8 runs its split contraction (the real
+ * parts of the split products); both to the split path's error; HSB_SPLIT_BF16 and HSB_SPLIT_FP16 handles get
  * HSB_ERR_UNSUPPORTED before anything is enqueued.
  * Workspace: hsbuild_workspace_bytes(h, HSB_MODE_REAL, 1, &ng). */
 int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
@@ -291,11 +295,12 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
  * 3M form); default 8.  4 also pins the stacked contraction in hsbuild_forward
  * and hsbuild_batch (HSB_OPT_SPLIT_K).  The forms agree to FP64 rounding, not
  * bitwise.  No effect on hsbuild_forward_real in FP64.  On a handle with a residue form (HSB_SPLIT_CRT*) the option
- * picks the layout of the residue contraction instead (256 x 256 blocks): 4
+ * picks the layout of the stacked residue contraction instead
+ * (hsbuild_forward_coefficients; 256 x 256 blocks): 4
  * (waves of 128 x 128, one per SIMD; the default there) or 8 (64 x 128, two
  * per SIMD); in HSB_SPLIT_CRT the 4-wave layout keeps its int32 sums
- * unreduced and so runs up to 2048 stages of 64 stacked rows (the real form
- * takes two stages per 64 rows), beyond which the 8-wave layout runs; the
+ * unreduced and so runs up to 2048 stages of 64 stacked rows, beyond which
+ * the 8-wave layout runs; the
  * 16-bit residue forms run the 8-wave layout only (their default is 8).  All
  * give bitwise the same H and S.
  * HSB_OPT_SPLIT_K: 1 (default) leaves the form of the FP64 builds to the library:

@@ -177,12 +177,9 @@ struct CrtConsts {
   int n_mod;
   int m[kCrtMaxModuli];      // coprime moduli, each a power of a prime p = 1 (mod 4), below 256
   int j[kCrtMaxModuli];      // j^2 = -1 (mod m)
-  int inv2[kCrtMaxModuli];   // 2^{-1} (mod m)
-  int inv2j[kCrtMaxModuli];  // (2 j)^{-1} (mod m)
-  double h[kCrtMaxModuli];   // y_i / m_i = h_i + l_i, y_i = (M / m_i)^{-1} (mod m_i), h_i on a 2^-42 grid
-  double l[kCrtMaxModuli];
-  // the same split of (2^{-1} y_i mod m_i) / m_i and ((2 j)^{-1} y_i mod m_i) / m_i on a 2^-41 grid:
-  // the weights of P + Q and P - Q, whose residues need no reduction
+  int y[kCrtMaxModuli];      // y_i = (M / m_i)^{-1} (mod m_i)
+  // (2^{-1} y_i mod m_i) / m_i and ((2 j)^{-1} y_i mod m_i) / m_i as h + l, h on a 2^-41 grid: the
+  // weights of P + Q and P - Q, whose residues need no reduction
   double h_re[kCrtMaxModuli], l_re[kCrtMaxModuli];
   double h_im[kCrtMaxModuli], l_im[kCrtMaxModuli];
   double M;                  // product of the moduli (rounded)
@@ -212,15 +209,14 @@ inline int crt_unit_rows(int ek) { return ek == 0 ? 16 : 8; }
 hipError_t launch_crt_residues(const CrtConsts& cc, int ek, const double2* X, const double* lam, int use_lam, int K,
                                int n_pad, int n_res, int QK, const double* scale, void* out, hipStream_t s);
 // Residues of the upper triangle of conj(L)^T R per modulus: res [n_mod][2][n_res][n_res] signed
-// bytes, P then Q (the images of the product under the two factors of Z[i]/m); the real form
-// [n_mod][n_res][n_res], its one product.  256 x 256 blocks; waves: 8 (waves of 64 x 128) or
-// 4 (128 x 128).
-hipError_t launch_hs_crt(const CrtConsts& cc, int ek, bool real, const void* L, const void* R, int QK, int n,
-                         int n_res, int gr, int waves, void* res, hipStream_t s);
+// bytes, P then Q (the images of the product under the two factors of Z[i]/m).  256 x 256 blocks;
+// waves: 8 (waves of 64 x 128) or 4 (128 x 128).
+hipError_t launch_hs_crt(const CrtConsts& cc, int ek, const void* L, const void* R, int QK, int n, int n_res, int gr,
+                         int waves, void* res, hipStream_t s);
 // C[row][col] (row <= col < n, ld n) from the residues (Re, Im from P, Q per modulus), scaled by
-// 1 / (scL[row] scR[col]); complex or real.
-hipError_t launch_crt_combine(const CrtConsts& cc, bool real, const void* res, int n_res, const double* scL,
-                              const double* scR, int n, void* C, hipStream_t s);
+// 1 / (scL[row] scR[col]).
+hipError_t launch_crt_combine(const CrtConsts& cc, const void* res, int n_res, const double* scL, const double* scR,
+                              int n, double2* C, hipStream_t s);
 
 // ---- type-factored form ----
 // Rows of a type's blocks (R, Y: 2 N_L; phases: its atoms) are padded to a multiple of this.
@@ -265,6 +261,24 @@ struct FactAdj {
   int nseg = 0, ngb = 0;      // segments of G' and blocks of columns in the phase sums
   size_t RT = 0, ET = 0, UT = 0, partT = 0, partTau = 0;
 };
+// Residue form of the factored build.  A, B: operand streams of every 64 columns (a_len, b_len bytes each; a type's
+// part from aoff, boff); inv: reciprocal column scales, double [2][n_act][n_pad] (R, Y).
+struct FactCrt {
+  int n_mod, ks;  // moduli; MFMA steps of a type's 2 N_L rows
+  int n_f, n_r;   // chunks of a type's R rows and of its residues
+  int64_t A, B, inv, a_len, b_len, aoff[HSB_MAX_TYPES], boff[HSB_MAX_TYPES];
+  double M, bound;  // product of the moduli; bound of a scaled column's 2-norm
+  // y_i / m_i = h_i + l_i (mod 1), y_i = (M / m_i)^{-1} (mod m_i), |h_i| <= 1/2 on a 2^-27 grid
+  double m[kCrtMaxModuli], inv_m[kCrtMaxModuli], h[kCrtMaxModuli], l[kCrtMaxModuli];
+};
+// Host: sizes (all but A, B, inv), moduli and weights for element kind ek (crt_kind).
+FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real);
+// After launch_fact_y: the streams (rep: the real form), then H from the residues and S in FP64 (upper
+// triangles).
+hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, const FactRep* rep, char* ws,
+                            hipStream_t s);
+hipError_t launch_fact_crt(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, int gr,
+                           const char* ws, void* H, void* S, hipStream_t s);
 // Workgroups of the H/S kernel for a basis of n; mi: 16-row blocks per wave side (1 or 2).
 int fact_tiles(int n, int mi);
 // Blocks per wave side for `tiles` workgroups of the larger tile on num_cus compute units.

@@ -105,8 +105,11 @@ hipError_t static_scratch(int dev, void** out) {
 
 // ---- type-factored form ----
 
-// The forward runs the type-factored form unless an option pins the stacked contraction.
-bool use_factored(const hsbuild_s& h) { return h.precision == HSB_FP64 && h.split_k == 1 && h.hs_waves == 8; }
+// The forward runs the type-factored form in FP64, unless an option pins the stacked contraction, and in
+// the residue forms.
+bool use_factored(const hsbuild_s& h) {
+  return is_crt(h.precision) || (h.precision == HSB_FP64 && h.split_k == 1 && h.hs_waves == 8);
+}
 
 // The types of `cell` with atoms (the real form's cell holds the representatives).
 FactCell fact_cell(const CellArgs& cell) {
@@ -137,9 +140,9 @@ int fact_phase_rows(const FactCell& c) {
 }
 
 // Workspace of the factored form: what the k-points share, then each one's arrays.  Returns the end.
-// consts: offset of the uploaded type constants; ks[k].n is given.
+// consts: offset of the uploaded type constants; ks[k].n is given.  cr: the residue form (one k-point).
 size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool real, size_t* consts, size_t* many,
-                   size_t* rep) {
+                   size_t* rep, FactCrt* cr = nullptr) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -160,15 +163,23 @@ size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool rea
     f.Y = (int64_t)take((size_t)c.n_act * c.Mr * np * (real ? sizeof(double) : sizeof(double2)));
     f.E = (int64_t)take((size_t)fact_phase_rows(c) * np * sizeof(double2));
   }
+  if (cr) {
+    *cr = fact_crt(h.crt, c, crt_kind(h.precision), real);
+    const size_t blocks = (size_t)ks->n_pad / 64;
+    cr->A = (int64_t)take(blocks * cr->a_len);
+    cr->B = (int64_t)take(blocks * cr->b_len);
+    cr->inv = (int64_t)take((size_t)2 * c.n_act * ks->n_pad * sizeof(double));
+  }
   return off;
 }
 
-size_t fact_bytes(const hsbuild_s& h, int ng, bool real) {
+size_t fact_bytes(const hsbuild_s& h, int ng, bool real, bool crt) {
   FactCell c = fact_cell(h.cell);
   FactK f{};
+  FactCrt cr;
   f.n = ng;
   size_t consts, rep;
-  return fact_layout(h, c, &f, 1, real, &consts, nullptr, real ? &rep : nullptr);
+  return fact_layout(h, c, &f, 1, real, &consts, nullptr, real ? &rep : nullptr, crt ? &cr : nullptr);
 }
 
 // The adjoint's workspace: the factored arrays, their transposes, and Z and Q of `pass` types at a
@@ -271,8 +282,8 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.end = adjoint_plan(h, ng).end;
     return L;
   }
-  if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && h.precision == HSB_FP64)) {
-    L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL);
+  if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && (h.precision == HSB_FP64 || is_crt(h.precision)))) {
+    L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL, mode == HSB_MODE_REAL && is_crt(h.precision));
     return L;
   }
   if (mode != HSB_MODE_COEFFICIENTS) {
@@ -297,7 +308,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
       L.skS = take((size_t)L.ns * np * np * sizeof(double2));
     }
   }
-  if ((mode == HSB_MODE_FORWARD || mode == HSB_MODE_REAL) && is_crt(h.precision)) {
+  if (mode == HSB_MODE_FORWARD && is_crt(h.precision)) {
     L.K64 = (int)round_up(L.K, kCrtRows);
     L.n_res = crt_cols(ng);
     const size_t nr = (size_t)L.n_res;
@@ -308,8 +319,8 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.slL = take(planes);
     L.slS = take(planes);
     L.slY = take(planes);
-    L.crRes = take((size_t)h.crt.n_mod * nr * nr * (mode == HSB_MODE_REAL ? 1 : 2));
-    L.crResH = take((size_t)h.crt.n_mod * nr * nr * (mode == HSB_MODE_REAL ? 1 : 2));
+    L.crRes = take((size_t)h.crt.n_mod * nr * nr * 2);
+    L.crResH = take((size_t)h.crt.n_mod * nr * nr * 2);
   } else if ((mode == HSB_MODE_FORWARD && h.precision != HSB_FP64) ||
              (mode == HSB_MODE_REAL && h.precision == HSB_SPLIT_INT8)) {
     L.K_pad2 = (int)round_up(L.K, 32);
@@ -332,7 +343,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
   L.stacked_end = off;
   if (mode == HSB_MODE_FORWARD && use_factored(h)) {
     L.factored = true;
-    L.end = std::max(L.end, fact_bytes(h, ng, false));
+    L.end = std::max(L.end, fact_bytes(h, ng, false, is_crt(h.precision)));
   }
   return L;
 }
@@ -459,10 +470,10 @@ int enqueue_fp64_hs(hsbuild_t h, const Layout& L, char* w, int ng, void* H, void
   return rc;
 }
 
-// Residue form of the split contraction (complex, or real parts only): column scales, the
+// Residue form of the stacked split contraction (hsbuild_forward_coefficients): column scales, the
 // residue planes of W, lam W and Y, then per matrix the residue contraction and the FP64
-// recombination.  L.K is the number of stacked rows used (the representatives' in the real case).
-int enqueue_crt(hsbuild_t h, const Layout& L, char* w, void* H, void* S, bool real, hipStream_t s) {
+// recombination.
+int enqueue_crt(hsbuild_t h, const Layout& L, char* w, double2* H, double2* S, hipStream_t s) {
   const double2* W = (const double2*)(w + L.W);
   const double2* Y = (const double2*)(w + L.Y);
   const double* lam = (const double*)(w + L.lam);
@@ -480,24 +491,24 @@ int enqueue_crt(hsbuild_t h, const Layout& L, char* w, void* H, void* S, bool re
     rc = launched(h, launch_crt_residues(cc, ek, Y, lam, 0, L.K, L.n_pad, nr, QK, sc + 2 * nr, w + L.slY, s), "residues");
   mark(h, 2, s);  // (again) the operand preparation ends here: the contraction stage starts
   if (!rc)
-    rc = launched(h, launch_hs_crt(cc, ek, real, w + L.slL, w + L.slS, QK, L.n, nr, h->tile_group, h->hs_waves,
+    rc = launched(h, launch_hs_crt(cc, ek, w + L.slL, w + L.slS, QK, L.n, nr, h->tile_group, h->hs_waves,
                                    w + L.crRes, s),
                   "residue contraction (S)");
   if (!rc)
-    rc = launched(h, launch_hs_crt(cc, ek, real, w + L.slL, w + L.slY, QK, L.n, nr, h->tile_group, h->hs_waves,
+    rc = launched(h, launch_hs_crt(cc, ek, w + L.slL, w + L.slY, QK, L.n, nr, h->tile_group, h->hs_waves,
                                    w + L.crResH, s),
                   "residue contraction (H)");
   mark(h, 3, s);
-  if (!rc) rc = launched(h, launch_crt_combine(cc, real, w + L.crRes, nr, sc, sc + nr, L.n, S, s), "recombination (S)");
+  if (!rc) rc = launched(h, launch_crt_combine(cc, w + L.crRes, nr, sc, sc + nr, L.n, S, s), "recombination (S)");
   if (!rc)
-    rc = launched(h, launch_crt_combine(cc, real, w + L.crResH, nr, sc, sc + 2 * nr, L.n, H, s), "recombination (H)");
+    rc = launched(h, launch_crt_combine(cc, w + L.crResH, nr, sc, sc + 2 * nr, L.n, H, s), "recombination (H)");
   mark(h, 4, s);
   return rc;
 }
 
 // Split-precision contraction: column scales, slices of W, lam W and Y, then S and H.
 int enqueue_split(hsbuild_t h, const Layout& L, char* w, double2* H, double2* S, hipStream_t s) {
-  if (is_crt(h->precision)) return enqueue_crt(h, L, w, H, S, false, s);
+  if (is_crt(h->precision)) return enqueue_crt(h, L, w, H, S, s);
   const double2* W = (const double2*)(w + L.W);
   const double2* Y = (const double2*)(w + L.Y);
   const double* lam = (const double*)(w + L.lam);
@@ -533,7 +544,6 @@ int enqueue_split(hsbuild_t h, const Layout& L, char* w, double2* H, double2* S,
 // Real-symmetric int8 split contraction on the representatives' rows (L.K): column scales and
 // slices as in the complex form, then S = Re(W^H lam W) and H = Re(W^H Y) into real arrays.
 int enqueue_split_real(hsbuild_t h, const Layout& L, char* w, double* H, double* S, hipStream_t s) {
-  if (is_crt(h->precision)) return enqueue_crt(h, L, w, H, S, true, s);
   const double2* W = (const double2*)(w + L.W);
   const double2* Y = (const double2*)(w + L.Y);
   const double* lam = (const double*)(w + L.lam);
@@ -893,7 +903,7 @@ int upload_reps(hsbuild_t h, void* dst, int n_rep, hipStream_t s) {
 
 // The factored form of one k-point in the workspace w; real: on the representatives in `cell`, whose
 // atoms and multiplicities are uploaded from the handle's pinned list.
-int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double k_frac[3], int32_t ng,
+int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, bool crt, const double k_frac[3], int32_t ng,
                      const int32_t* g, const double* tau, const void* T, void* H, void* S, char* w, hipStream_t s) {
   FactCell c = fact_cell(cell);
   FactK f{};
@@ -901,7 +911,8 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double 
   for (int i = 0; i < 3; ++i) f.kfrac[i] = k_frac[i];
   f.n = ng;
   size_t consts_off = 0, rep_off = 0;
-  fact_layout(*h, c, &f, 1, real, &consts_off, nullptr, real ? &rep_off : nullptr);
+  FactCrt cr;
+  fact_layout(*h, c, &f, 1, real, &consts_off, nullptr, real ? &rep_off : nullptr, crt ? &cr : nullptr);
   const FactRep* rep = nullptr;
   int rc;
   mark(h, 0, s);
@@ -919,10 +930,14 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double 
   rc = launched(h, launch_fact_tables(c, ra, consts, f, nullptr, 1, f.n_pad / 64, g, tau, rep, FactAdj{},
                                       (const double2*)T, w, s),
                 "k_fact_tables");
+  const int ek = crt_kind(h->precision);
   mark(h, 1, s);
   if (!rc) rc = launched(h, launch_fact_y(c, f, nullptr, 1, f.n_pad / (32 * mi), mi, real, w, s), "k_fact_y");
+  if (!rc && crt) rc = launched(h, launch_fact_pack(c, f, cr, ek, rep, w, s), "k_fact_pack");
   mark(h, 2, s);
-  if (!rc)
+  if (!rc && crt)
+    rc = launched(h, launch_fact_crt(c, f, cr, ek, real, h->tile_group, w, H, S, s), "k_fact_crt");
+  else if (!rc)
     rc = launched(h, launch_fact_hs(c, f, nullptr, 1, fact_tiles(ng, mi), mi, real, h->tile_group, rep, w, H, S, s),
                   "k_fact_hs");
   mark(h, 3, s);
@@ -935,7 +950,8 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, const double 
 int forward_enqueue(hsbuild_t h, const Layout& L, const double k_frac[3], int32_t ng, const int32_t* g,
                     const double* tau, const void* T, void* H, void* S, char* w, hipStream_t s) {
   int rc;
-  if (L.factored) return factored_enqueue(h, h->cell, false, k_frac, ng, g, tau, T, H, S, w, s);
+  if (L.factored)
+    return factored_enqueue(h, h->cell, false, is_crt(h->precision), k_frac, ng, g, tau, T, H, S, w, s);
   mark(h, 0, s);
   if ((rc = enqueue_operands(h, L, k_frac, g, tau, T, w, s))) return rc;
   if (h->precision == HSB_FP64) {
@@ -999,7 +1015,7 @@ int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, co
   const Layout L = make_layout(*h, ng, HSB_MODE_FACTORED);
   if ((rc = check_ws(h, L, ws, ws_bytes))) return rc;
   if ((rc = check_device(h))) return rc;
-  return factored_enqueue(h, h->cell, false, k_frac, ng, g, tau, T, H, S, (char*)ws, (hipStream_t)stream);
+  return factored_enqueue(h, h->cell, false, false, k_frac, ng, g, tau, T, H, S, (char*)ws, (hipStream_t)stream);
 }
 
 int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
@@ -1049,7 +1065,8 @@ int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const 
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
   if ((rc = stage_reps(h, rep, wt))) return rc;
-  if (h->precision == HSB_FP64) return factored_enqueue(h, crep, true, k_frac, ng, g, tau, T, H, S, w, s);
+  if (h->precision == HSB_FP64 || is_crt(h->precision))
+    return factored_enqueue(h, crep, true, is_crt(h->precision), k_frac, ng, g, tau, T, H, S, w, s);
   mark(h, 0, s);
   if ((rc = upload_reps(h, w + L.rep, n_rep, s))) return rc;
   const FactRep* drep = (const FactRep*)(w + L.rep);

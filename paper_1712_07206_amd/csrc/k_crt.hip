@@ -1,6 +1,7 @@
 // Split-precision contraction by residues (Chinese remainder theorem) on the int8 matrix
-// cores, or on the BF16/FP16 matrix cores with the residues as 16-bit integers: the residue
-// forms of the split path.
+// cores, or on the BF16/FP16 matrix cores with the residues as 16-bit integers: the stacked residue
+// form, which hsbuild_forward_coefficients runs (any coefficients; the builds themselves take the
+// residues per atom type, k_fact_crt.hip).
 //
 // Every operand column (one G: the vector over the stacked index k) is scaled by a
 // power of two 2^f_G and rounded to Gaussian integers x' = rint(2^f x) (exact in
@@ -34,6 +35,7 @@
 #include <cmath>
 
 #include "hs_internal.h"
+#include "residues.h"
 #include "tiles.h"
 
 namespace hsb {
@@ -95,24 +97,6 @@ __global__ void __launch_bounds__(256) k_crt_scale(const double* __restrict__ pa
     sc = ldexp(1.0, e - 1);
   }
   scale[i] = sc;
-}
-
-// v - m * round(v / m), in [-(m-1)/2, (m-1)/2], for an integer-valued double |v| < 2^48 and an
-// odd modulus 113 <= m < 256.  The computed v * fl(1/m) is within |v/m| 2^-52 < 2^-10 of v/m,
-// while v/m, with m odd, is never closer than 1/(2m) > 2^-9 to a half-integer: the rounded
-// quotient is exact, and so are q m and the difference (fma).
-__device__ __forceinline__ double smod_d(double v, double m, double inv_m) {
-  return fma(-rint(v * inv_m), m, v);
-}
-
-// Residue r (an integer in [-(m-1)/2, (m-1)/2], as a double) as the element of kind EK: a signed
-// byte (0), or the bits of a bfloat16 (1) or an IEEE half (2), both exact for |r| <= 256.
-template <int EK>
-__device__ __forceinline__ unsigned residue_bits(double r) {
-  if constexpr (EK == 0) return (unsigned)(int)r & 0xffu;
-  else if constexpr (EK == 1) return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)(float)r);
-  // through int and float (both exact here): a direct double -> half cast is rounded in software
-  else return (unsigned)__builtin_bit_cast(unsigned short, (_Float16)(float)(int)r);
 }
 
 // One thread per (column G, unit q of RU = 16 (bytes) or 8 (16-bit elements) rows): the 2 n_mod
@@ -213,7 +197,7 @@ __device__ __forceinline__ int smod_i(int v, int m, double inv_m, int h) {
   return r;
 }
 
-// Contraction tile: one product (P, Q, or the real product) over a 256 x 256 block of
+// Contraction tile: one product (P or Q) over a 256 x 256 block of
 // (G', G) per workgroup, so each side needs one residue plane: a chunk of the stacked index
 // is 16 KB of left and 16 KB of right residues, copied straight into LDS
 // (global_load_lds_dwordx4) through a ring of four 32 KB stages, three chunks ahead of its use.
@@ -238,22 +222,19 @@ constexpr int kCrtNoReduce = 2048;
 // s_waitcnt immediates (gfx9 encoding): vector-memory count N, the other counters not waited on.
 constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// Workgroup w: (modulus, product) = w / num_tiles, product fastest (P then Q; the real form has
-// one), 256 x 256 block w % num_tiles of the upper triangle (XCD-contiguous numbering, so the
+// Workgroup w: (modulus, product) = w / num_tiles, product fastest (P then Q),
+// 256 x 256 block w % num_tiles of the upper triangle (XCD-contiguous numbering, so the
 // blocks an XCD runs together belong to one modulus and product and to a compact patch of the
 // triangle).  P multiplies the left plane 1 (x_r - j x_i) by the right plane 0 (y_r + j y_i), Q
-// the left plane 0 by the right plane 1.  The real form wants Re = (P + Q) / 2 only: it adds both
-// products into one sum, running through 2 x (chunks) stages, each chunk once with the planes
-// of P and once with those of Q.
-// res: residues in [-(m-1)/2, (m-1)/2] as signed bytes, [n_mod][nprod][n_res][n_res] (the real
-// form: of Re), written for row <= col < n (the 4-wave layout writes the whole of each 256 x 256
-// block it computes, inside the plane).
-template <int EK, int WAVES, bool REAL>
+// the left plane 0 by the right plane 1.
+// res: residues in [-(m-1)/2, (m-1)/2] as signed bytes, [n_mod][2][n_res][n_res], written for
+// row <= col < n (the 4-wave layout writes the whole of each 256 x 256 block it computes, inside the
+// plane).
+template <int EK, int WAVES>
 __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__ L, const u4* __restrict__ R,
                                                           CrtConsts cc, int QK, int n, int NB, int nbs,
                                                           int num_tiles, int num_wg, int gr, int8_t* __restrict__ res,
                                                           int64_t ld) {
-  constexpr int NPROD = REAL ? 1 : 2;
   constexpr int WRN = WAVES / 2;           // wave rows
   constexpr int RB = 8 / WRN;              // 32-row blocks per wave (2 or 4); 4 column blocks
   constexpr int NPW = kCrtCopies / WAVES;  // copies per wave and chunk (4 or 8)
@@ -268,19 +249,19 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
   xcd_range(x, num_wg, start, len);
   const int w = start + blockIdx.x / kXcds;
   const int mp = w / num_tiles;
-  const int mod = mp / NPROD, prod = mp - mod * NPROD;
+  const int mod = mp / 2, prod = mp - mod * 2;
   int bi, bj;
   if (gr > 0) grouped_decode(w - mp * num_tiles, nbs, gr, bi, bj);
   else tri_decode(w - mp * num_tiles, nbs, bi, bj);
   const int row0 = bi * 256, col0 = bj * 256;
   if (col0 >= n) return;
-  const int planeL = 1 - prod, planeR = prod;  // the real form starts with P's planes
+  const int planeL = 1 - prod, planeR = prod;
   const int64_t modstride = (int64_t)2 * NB * QK * 64, cstride = (int64_t)NB * 512;  // units
   const u4* Lm = L + mod * modstride;
   const u4* Rm = R + mod * modstride;
 
   const u4* src[NPW];
-  int dst[NPW], dlt[NPW];
+  int dst[NPW];
 #pragma unroll
   for (int i = 0; i < NPW; ++i) {
     const int j = wave + WAVES * i;  // copy j: side j / 16, block (j / 4) % 4, row group j % 4
@@ -289,13 +270,8 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
     const int b0 = side ? (col0 >> 6) : (row0 >> 6);
     src[i] = base + (((b0 + b) * 2 + (side ? planeR : planeL)) * 4 + qq) * 64;
     dst[i] = side * kCrtSideUnits + (b * 4 + qq) * 64;
-    dlt[i] = side ? 256 : -256;  // real form, Q's stage: the other plane of each side
   }
-  // stage v: chunk v (complex), or chunk v / 2 with P's (v even) or Q's (v odd) planes (real)
-  auto at = [&](int i, int v) -> const u4* {
-    if constexpr (REAL) return src[i] + (v >> 1) * cstride + (v & 1) * dlt[i];
-    else return src[i] + v * cstride;
-  };
+  auto at = [&](int i, int v) -> const u4* { return src[i] + v * cstride; };
   auto issue = [&](int v, int buf) {
 #pragma unroll
     for (int i = 0; i < NPW; ++i)
@@ -333,7 +309,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
   // kCrtSideUnits + ((4 wc + cb) / 2 * 4 + 2 s + qh) * 64 + (cb & 1) * 32 + g32.
   const int la = qh * 64 + g32;
   const int ra = kCrtSideUnits + (2 * wc * 4 + qh) * 64 + g32;
-  const int nchunks = (QK >> 2) * (REAL ? 2 : 1);  // stages
+  const int nchunks = QK >> 2;
 #pragma unroll
   for (int i = 0; i < kCrtStages - 1; ++i)
     if (i < nchunks) issue(i, i);
@@ -410,7 +386,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
     }
   }
 
-  // Residues of the product (the real form: of (P + Q) / 2).  Output element r of a 32 x 32 block:
+  // Residues of the product.  Output element r of a 32 x 32 block:
   // row 8 (r / 4) + 4 qh + r % 4, column g32.
   if constexpr (WAVES == 4) {
     // Each sum is an exact integer below 2^31 in magnitude, reduced in FP64 as the residues of
@@ -419,13 +395,8 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
     // recombination reads row <= col < n only.  The wave's base is made visibly uniform, so the
     // per-element offsets are scalar arithmetic.
     const double md = (double)m;
-    const double inv2 = REAL ? (double)cc.inv2[mod] : 0.0;
-    auto residue = [&](double v) -> int8_t {
-      double r = smod_d(v, md, inv_m);
-      if constexpr (REAL) r = smod_d(r * inv2, md, inv_m);  // (P + Q) / 2
-      return (int8_t)(int)r;
-    };
-    const uint64_t wb = (uint64_t)(res + (int64_t)(mod * NPROD + prod) * ld * ld +
+    auto residue = [&](double v) -> int8_t { return (int8_t)(int)smod_d(v, md, inv_m); };
+    const uint64_t wb = (uint64_t)(res + (int64_t)(mod * 2 + prod) * ld * ld +
                                    (int64_t)(row0 + wr * 32 * RB) * ld + col0 + wc * 128);
     // (readfirstlane returns a signed int: each half goes through unsigned, or the low one would
     // sign-extend into the high word)
@@ -444,10 +415,9 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
   } else {
     // (the 8-wave layout keeps per-element bounds: written this way, the 16-bit forms measured
     // 5 % faster than with the 4-wave epilogue)
-    const int inv2 = REAL ? cc.inv2[mod] : 0;
     int rbase = row0 + wr * 32 * RB + 4 * qh, cbase = col0 + wc * 128 + g32;
     asm volatile("" : "+v"(rbase), "+v"(cbase));
-    int8_t* out = res + (int64_t)(mod * NPROD + prod) * ld * ld;
+    int8_t* out = res + (int64_t)(mod * 2 + prod) * ld * ld;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -457,27 +427,24 @@ __global__ void __launch_bounds__(WAVES * 64, 1) k_hs_crt(const u4* __restrict__
           const int row = rbase + rb * 32 + 8 * (r >> 2) + (r & 3);
           const int col = cbase + cb * 32;
           if (row < n && col < n && col >= row) {
-            int v = smod_i((int)acc[rb][cb][r], m, inv_m, hm);  // 16-bit forms: an exact integer < 2^24
-            if constexpr (REAL) v = smod_i(v * inv2, m, inv_m, hm);  // (P + Q) / 2
-            out[(int64_t)row * ld + col] = (int8_t)v;
+            // 16-bit forms: an exact integer < 2^24
+            out[(int64_t)row * ld + col] = (int8_t)smod_i((int)acc[rb][cb][r], m, inv_m, hm);
           }
         }
   }
 }
 
 // Recovery of each upper-triangle entry from its residues: value = M * frac(sum_i r_i y_i / m_i),
-// times 2^-(f_row + f_col), with r_i the residue of the real form's one product, or of
-// Re = (P + Q) / 2 and Im = (P - Q) / (2 j) (mod m).  The fraction depends on r_i only modulo m_i,
-// so the complex form takes r_i = P + Q and P - Q as they are (|r_i| <= 240) against the weights
-// 2^{-1} y_i and (2 j)^{-1} y_i (mod m_i), with no reduction.  sum r_i h_i is exact (h_i on a
-// 2^-42 grid with |r_i| < 2^7, or on a 2^-41 grid with |r_i| < 2^8; n <= 13 terms, so the sums
+// times 2^-(f_row + f_col), with r_i the residue of Re = (P + Q) / 2 and of Im = (P - Q) / (2 j)
+// (mod m).  The fraction depends on r_i only modulo m_i, so r_i = P + Q and P - Q are taken as they are
+// (|r_i| <= 240) against the weights 2^{-1} y_i and (2 j)^{-1} y_i (mod m_i), with no reduction.
+// sum r_i h_i is exact (h_i on a 2^-41 grid with |r_i| < 2^8; n <= 13 terms, so the sums
 // stay below 2^12), the rounding to the nearest integer is exact and the fraction keeps FP64
 // precision.  One thread per four consecutive columns of a row (4-byte
 // loads of the residues; the rows are n_res bytes long, so the four are always in the row).
-template <bool REAL>
 __global__ void __launch_bounds__(256) k_crt_combine(CrtConsts cc, const int8_t* __restrict__ res, int64_t ld,
                                                      const double* __restrict__ scL, const double* __restrict__ scR,
-                                                     int n, void* __restrict__ Cv) {
+                                                     int n, d2* __restrict__ C) {
   const int row = blockIdx.y;
   const int col0 = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (col0 >= n || col0 + 3 < row) return;
@@ -485,28 +452,17 @@ __global__ void __launch_bounds__(256) k_crt_combine(CrtConsts cc, const int8_t*
   double hr[4] = {0.0, 0.0, 0.0, 0.0}, lr[4] = {0.0, 0.0, 0.0, 0.0};
   double hi[4] = {0.0, 0.0, 0.0, 0.0}, li[4] = {0.0, 0.0, 0.0, 0.0};
   for (int i = 0; i < cc.n_mod; ++i) {
-    if constexpr (REAL) {
-      const double h = cc.h[i], l = cc.l[i];
-      const unsigned v = *(const unsigned*)(res + i * mstride + e);
+    const unsigned vp = *(const unsigned*)(res + (2 * i) * mstride + e);
+    const unsigned vq = *(const unsigned*)(res + (2 * i + 1) * mstride + e);
+    const double h_re = cc.h_re[i], l_re = cc.l_re[i], h_im = cc.h_im[i], l_im = cc.l_im[i];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double r = (double)(int8_t)(v >> (8 * u));
-        hr[u] += r * h;
-        lr[u] += r * l;
-      }
-    } else {
-      const unsigned vp = *(const unsigned*)(res + (2 * i) * mstride + e);
-      const unsigned vq = *(const unsigned*)(res + (2 * i + 1) * mstride + e);
-      const double h_re = cc.h_re[i], l_re = cc.l_re[i], h_im = cc.h_im[i], l_im = cc.l_im[i];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int p = (int8_t)(vp >> (8 * u)), q = (int8_t)(vq >> (8 * u));
-        const double r = (double)(p + q), t = (double)(p - q);
-        hr[u] += r * h_re;
-        lr[u] += r * l_re;
-        hi[u] += t * h_im;
-        li[u] += t * l_im;
-      }
+    for (int u = 0; u < 4; ++u) {
+      const int p = (int8_t)(vp >> (8 * u)), q = (int8_t)(vq >> (8 * u));
+      const double r = (double)(p + q), t = (double)(p - q);
+      hr[u] += r * h_re;
+      lr[u] += r * l_re;
+      hi[u] += t * h_im;
+      li[u] += t * l_im;
     }
   }
   const double sl = cc.M / scL[row];
@@ -516,12 +472,8 @@ __global__ void __launch_bounds__(256) k_crt_combine(CrtConsts cc, const int8_t*
     if (col < n && col >= row) {
       const double sc = sl / scR[col];
       const double fr = (hr[u] - rint(hr[u])) + lr[u];
-      if constexpr (REAL) {
-        ((double*)Cv)[(int64_t)row * n + col] = fr * sc;
-      } else {
-        const double fi = (hi[u] - rint(hi[u])) + li[u];
-        ((d2*)Cv)[(int64_t)row * n + col] = d2{fr * sc, fi * sc};
-      }
+      const double fi = (hi[u] - rint(hi[u])) + li[u];
+      C[(int64_t)row * n + col] = d2{fr * sc, fi * sc};
     }
   }
 }
@@ -559,8 +511,6 @@ bool crt_make_consts(int n_mod, CrtConsts* cc) {
     while ((j * j + 1) % m) ++j;
     cc->m[k] = m;
     cc->j[k] = j;
-    cc->inv2[k] = inverse_mod(2, m);
-    cc->inv2j[k] = inverse_mod(2 * j, m);
     ++k;
   }
   if (k < n_mod) return false;
@@ -572,15 +522,15 @@ bool crt_make_consts(int n_mod, CrtConsts* cc) {
     for (int t = 0; t < n_mod; ++t)
       if (t != i) c = c * (cc->m[t] % mi) % mi;
     const int y = inverse_mod(c, mi);
-    // w / m_i = h + l with h on a 2^-bits grid; w - h m_i is exact (h has at most 42 fractional
+    // w / m_i = h + l with h on a 2^-bits grid; w - h m_i is exact (h has at most 41 fractional
     // bits, m_i 8 bits)
+    cc->y[i] = y;
     auto split = [mi](int w, int bits, double& h, double& l) {
       h = std::ldexp(std::rint(std::ldexp((double)w / mi, bits)), -bits);
       l = ((double)w - h * mi) / mi;
     };
-    split(y, 42, cc->h[i], cc->l[i]);
-    split(cc->inv2[i] * y % mi, 41, cc->h_re[i], cc->l_re[i]);
-    split(cc->inv2j[i] * y % mi, 41, cc->h_im[i], cc->l_im[i]);
+    split(inverse_mod(2, mi) * y % mi, 41, cc->h_re[i], cc->l_re[i]);
+    split(inverse_mod(2 * cc->j[i], mi) * y % mi, 41, cc->h_im[i], cc->l_im[i]);
   }
   cc->M = M;
   cc->bound = std::sqrt(0.5 * M * (1.0 - 0x1p-10));
@@ -622,36 +572,19 @@ hipError_t launch_crt_residues(const CrtConsts& cc, int ek, const double2* X, co
 }
 
 namespace {
-template <int EK>
-void launch_hs_crt_k(bool real, bool four, dim3 grid, const u4* l, const u4* r, const CrtConsts& cc, int QK, int n,
-                     int NB, int nbs, int num_tiles, int num_wg, int gr, int8_t* o, int64_t ld, hipStream_t s) {
-  if constexpr (EK == 0) {
-    if (four) {
-      if (real)
-        hipLaunchKernelGGL((k_hs_crt<EK, 4, true>), grid, dim3(256), 0, s, l, r, cc, QK, n, NB, nbs, num_tiles,
-                           num_wg, gr, o, ld);
-      else
-        hipLaunchKernelGGL((k_hs_crt<EK, 4, false>), grid, dim3(256), 0, s, l, r, cc, QK, n, NB, nbs, num_tiles,
-                           num_wg, gr, o, ld);
-      return;
-    }
-  }
-  {
-    if (real)
-      hipLaunchKernelGGL((k_hs_crt<EK, 8, true>), grid, dim3(512), 0, s, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg,
-                         gr, o, ld);
-    else
-      hipLaunchKernelGGL((k_hs_crt<EK, 8, false>), grid, dim3(512), 0, s, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg,
-                         gr, o, ld);
-  }
+template <int EK, int WAVES>
+void launch_hs_crt_k(dim3 grid, const u4* l, const u4* r, const CrtConsts& cc, int QK, int n, int NB, int nbs,
+                     int num_tiles, int num_wg, int gr, int8_t* o, int64_t ld, hipStream_t s) {
+  hipLaunchKernelGGL((k_hs_crt<EK, WAVES>), grid, dim3(WAVES * 64), 0, s, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg,
+                     gr, o, ld);
 }
 }  // namespace
 
-hipError_t launch_hs_crt(const CrtConsts& cc, int ek, bool real, const void* L, const void* R, int QK, int n,
-                         int n_res, int gr, int waves, void* res, hipStream_t s) {
+hipError_t launch_hs_crt(const CrtConsts& cc, int ek, const void* L, const void* R, int QK, int n, int n_res, int gr,
+                         int waves, void* res, hipStream_t s) {
   const int nbs = n_res / 256;
   const int num_tiles = crt_tiles(n_res);
-  const int num_wg = num_tiles * cc.n_mod * (real ? 1 : 2);
+  const int num_wg = num_tiles * cc.n_mod * 2;
   const int NB = n_res / 64;
   const dim3 grid(num_wg);
   const u4 *l = (const u4*)L, *r = (const u4*)R;
@@ -660,21 +593,18 @@ hipError_t launch_hs_crt(const CrtConsts& cc, int ek, bool real, const void* L, 
   // The byte form's 4-wave layout has no reduction of its sums: it runs up to kCrtNoReduce stages.
   // The 16-bit forms reduce their FP32 sums every 32 chunks, which the 4-wave layout, its 256
   // sums in AGPRs, could only do by spilling inside the loop: they run the 8-wave layout.
-  const bool four = waves == 4 && ek == 0 && QK / 4 * (real ? 2 : 1) <= kCrtNoReduce;
-  if (ek == 0) launch_hs_crt_k<0>(real, four, grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
-  else if (ek == 1) launch_hs_crt_k<1>(real, four, grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
-  else launch_hs_crt_k<2>(real, four, grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
+  if (ek == 1) launch_hs_crt_k<1, 8>(grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
+  else if (ek == 2) launch_hs_crt_k<2, 8>(grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
+  else if (waves == 4 && QK / 4 <= kCrtNoReduce)
+    launch_hs_crt_k<0, 4>(grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
+  else launch_hs_crt_k<0, 8>(grid, l, r, cc, QK, n, NB, nbs, num_tiles, num_wg, gr, o, ld, s);
   return hipGetLastError();
 }
 
-hipError_t launch_crt_combine(const CrtConsts& cc, bool real, const void* res, int n_res, const double* scL,
-                              const double* scR, int n, void* C, hipStream_t s) {
-  dim3 grid((n + 1023) / 1024, n);
-  const int8_t* r = (const int8_t*)res;
-  if (real)
-    hipLaunchKernelGGL((k_crt_combine<true>), grid, dim3(256), 0, s, cc, r, (int64_t)n_res, scL, scR, n, C);
-  else
-    hipLaunchKernelGGL((k_crt_combine<false>), grid, dim3(256), 0, s, cc, r, (int64_t)n_res, scL, scR, n, C);
+hipError_t launch_crt_combine(const CrtConsts& cc, const void* res, int n_res, const double* scL, const double* scR,
+                              int n, double2* C, hipStream_t s) {
+  hipLaunchKernelGGL(k_crt_combine, dim3((n + 1023) / 1024, n), dim3(256), 0, s, cc, (const int8_t*)res, (int64_t)n_res,
+                     scL, scR, n, (d2*)C);
   return hipGetLastError();
 }
 

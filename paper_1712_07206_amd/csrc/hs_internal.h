@@ -221,6 +221,7 @@ hipError_t launch_crt_combine(const CrtConsts& cc, const void* res, int n_res, c
 // ---- type-factored form ----
 // Rows of a type's blocks (R, Y: 2 N_L; phases: its atoms) are padded to a multiple of this.
 constexpr int kFactRows = 16;
+constexpr size_t kFactSlack = 32 * 1024;
 // Radial data of (active type, l) passed by value: u, u', udot, udot', ||udot||^2 (the constants
 // are uploaded instead when the types need more entries).
 constexpr int kRadialArgs = 64;
@@ -232,17 +233,21 @@ struct FactCell {
   double bvec[9], pre;
   int l_max, n_l, n_act;
   int Mr, Mc;  // 2 N_L rounded up to kFactRows, and to 64 (columns of T')
-  size_t TT, lam;  // T'[r][k] as complex [n_act][k: Mr][r: Mc]; S weights, double [n_act][Mr]
+  size_t TT;  // T'[r][k] as complex [n_act][k: Mr][r: Mc]
   int type[HSB_MAX_TYPES], nat[HSB_MAX_TYPES], atom0[HSB_MAX_TYPES];
   int eoff[HSB_MAX_TYPES];  // first phase row
+  int e_rows;               // phase rows
   double r_mt[HSB_MAX_TYPES];
 };
-// One k-point: byte offsets in the workspace.  R: double [n_act][Mr][n_pad]; Y: complex (the real
-// form: double), same shape; E: complex [phase rows][n_pad]; kv: double [n_pad][4].
+// One k-point: byte offsets in the workspace.  Arrays are block-major, a block being 64 columns: R, and
+// LR = lam R, double [blocks][n_act][Mr][64]; Y: complex (the real form: double), same shape; E: complex
+// [blocks][e_rows][64]; EW: E times the atoms' multiplicities (E itself but for the real form); kv: double
+// [n_pad][4].  What a tile reads of one array, block and type is one run.  kFactSlack bytes may be read past
+// the last of them.
 struct FactK {
   double kfrac[3];
   int64_t g_row;    // first row of its G list
-  int64_t kv, R, Y, E;
+  int64_t kv, R, LR, Y, E, EW;
   int64_t out_off;  // H, S, in elements (ld = n)
   int n, n_pad;     // n_pad: a multiple of 64
   int gblk0, yblk0, tile0;  // first workgroup of each kernel (many k-points)
@@ -273,16 +278,14 @@ struct FactCrt {
 };
 // Host: sizes (all but A, B, inv), moduli and weights for element kind ek (crt_kind).
 FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real);
-// After launch_fact_y: the streams (rep: the real form), then H from the residues and S in FP64 (upper
+// After launch_fact_y: the streams, then H from the residues and S in FP64 (upper
 // triangles).
-hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, const FactRep* rep, char* ws,
+hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
                             hipStream_t s);
 hipError_t launch_fact_crt(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, int gr,
                            const char* ws, void* H, void* S, hipStream_t s);
-// Workgroups of the H/S kernel for a basis of n; mi: 16-row blocks per wave side (1 or 2).
-int fact_tiles(int n, int mi);
-// Blocks per wave side for `tiles` workgroups of the larger tile on num_cus compute units.
-int fact_block(int64_t tiles, int num_cus);
+// 64 x 64 tiles of the upper triangle of a basis of n.
+int fact_tiles(int n);
 // For one k-point (many == nullptr) or the nk k-points of the device array many; consts: device
 // copy of the type constants, or nullptr to take them from ra.  rep: the real form's
 // representatives (device), else nullptr.
@@ -291,8 +294,8 @@ hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const Typ
                               const FactRep* rep, const FactAdj& ad, const double2* T, char* ws, hipStream_t s);
 hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many, int nk, int nblk, int mi, bool real,
                          char* ws, hipStream_t s);
-hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int num_wg, int mi, bool real,
-                          int gr, const FactRep* rep, const char* ws, void* H, void* S, hipStream_t s);
+hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int tiles, bool real, int gr,
+                          int num_cus, const char* ws, void* H, void* S, hipStream_t s);
 // XL[r][G] = lam[r] X[r][G] for r < rows.
 hipError_t launch_scale_rows(const double2* X, const double* lam, int rows, int n_pad, double2* XL, hipStream_t s);
 
@@ -312,9 +315,9 @@ int eig_workspace(void* handle, int n, bool vectors, size_t* bytes, std::string&
 // a[i] = conj(a[i]) for i < count.
 hipError_t launch_conj(double2* a, int64_t count, hipStream_t s);
 
-// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1, mi as for the H/S kernel) ----
+// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1; mi: 16-row blocks per wave side) ----
 // Z, Q: complex [nt][n_pad][n_pad].
-hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int mi, const double2* gH,
+hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s);
 hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, int mi, char* ws,
                          const double2* Z, const double2* Q, hipStream_t s);

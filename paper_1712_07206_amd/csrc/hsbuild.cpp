@@ -132,11 +132,8 @@ FactCell fact_cell(const CellArgs& cell) {
     c.r_mt[i] = cell.r_mt[t];
     rows += (int)round_up(nt, kFactRows);
   }
+  c.e_rows = rows;
   return c;
-}
-
-int fact_phase_rows(const FactCell& c) {
-  return c.eoff[c.n_act - 1] + (int)round_up(c.nat[c.n_act - 1], kFactRows);
 }
 
 // Workspace of the factored form: what the k-points share, then each one's arrays.  Returns the end.
@@ -151,7 +148,6 @@ size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool rea
   };
   *consts = take(sizeof(TypeConsts));
   c.TT = take((size_t)c.n_act * c.Mr * c.Mc * sizeof(double2));
-  c.lam = take((size_t)c.n_act * c.Mr * sizeof(double));
   if (many) *many = take((size_t)n_k * sizeof(FactK));
   if (rep) *rep = take((size_t)h.n_atoms * sizeof(FactRep));
   for (int k = 0; k < n_k; ++k) {
@@ -160,9 +156,12 @@ size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool rea
     const size_t np = (size_t)f.n_pad;
     f.kv = (int64_t)take(np * 4 * sizeof(double));
     f.R = (int64_t)take((size_t)c.n_act * c.Mr * np * sizeof(double));
+    f.LR = (int64_t)take((size_t)c.n_act * c.Mr * np * sizeof(double));
     f.Y = (int64_t)take((size_t)c.n_act * c.Mr * np * (real ? sizeof(double) : sizeof(double2)));
-    f.E = (int64_t)take((size_t)fact_phase_rows(c) * np * sizeof(double2));
+    f.E = (int64_t)take((size_t)c.e_rows * np * sizeof(double2));
+    f.EW = real ? (int64_t)take((size_t)c.e_rows * np * sizeof(double2)) : f.E;
   }
+  take(kFactSlack);
   if (cr) {
     *cr = fact_crt(h.crt, c, crt_kind(h.precision), real);
     const size_t blocks = (size_t)ks->n_pad / 64;
@@ -204,11 +203,10 @@ AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
     off = align256(off + bytes);
     return o;
   };
-  const int64_t np = p.f.n_pad, nb = np / 64;
+  const int64_t np = p.f.n_pad;
   FactAdj& ad = p.ad;
   ad.Mt = (int)round_up(2 * h.n_l, 32);
-  ad.et_ld = fact_phase_rows(c);
-  p.mi = fact_block(nb * nb * c.n_act, h.num_cus);
+  ad.et_ld = c.e_rows;
   // waves for twice the SIMDs, where the sizes give them
   const int64_t waves = 8 * (int64_t)std::max(1, h.num_cus);
   const int64_t gt_tiles = (int64_t)(ad.Mt / 32) * (ad.Mt / 32) * c.n_act;
@@ -230,6 +228,12 @@ AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
   p.Q = take((size_t)p.pass * np * np * sizeof(double2));
   p.end = off;
   return p;
+}
+
+// Blocks per wave side of Y = T' R over `cols` columns: 64 x 64 workgroups where they are enough for
+// every compute unit, else 32 x 32.
+int y_block(const FactCell& c, int64_t cols, int num_cus) {
+  return cols / 64 * ((c.Mr + 63) / 64) * c.n_act < num_cus ? 1 : 2;
 }
 
 // The radial data by value; false if the types need more entries than RadialArgs holds.
@@ -926,19 +930,19 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, bool crt, con
     if ((rc = launched(h, e, "upload of type constants"))) return rc;
     consts = (const TypeConsts*)(w + consts_off);
   }
-  const int mi = fact_block(fact_tiles(ng, 2), h->num_cus);
+  const int mi = y_block(c, f.n_pad, h->num_cus);
   rc = launched(h, launch_fact_tables(c, ra, consts, f, nullptr, 1, f.n_pad / 64, g, tau, rep, FactAdj{},
                                       (const double2*)T, w, s),
                 "k_fact_tables");
   const int ek = crt_kind(h->precision);
   mark(h, 1, s);
   if (!rc) rc = launched(h, launch_fact_y(c, f, nullptr, 1, f.n_pad / (32 * mi), mi, real, w, s), "k_fact_y");
-  if (!rc && crt) rc = launched(h, launch_fact_pack(c, f, cr, ek, rep, w, s), "k_fact_pack");
+  if (!rc && crt) rc = launched(h, launch_fact_pack(c, f, cr, ek, real, w, s), "k_fact_pack");
   mark(h, 2, s);
   if (!rc && crt)
     rc = launched(h, launch_fact_crt(c, f, cr, ek, real, h->tile_group, w, H, S, s), "k_fact_crt");
   else if (!rc)
-    rc = launched(h, launch_fact_hs(c, f, nullptr, 1, fact_tiles(ng, mi), mi, real, h->tile_group, rep, w, H, S, s),
+    rc = launched(h, launch_fact_hs(c, f, nullptr, 1, fact_tiles(ng), real, h->tile_group, h->num_cus, w, H, S, s),
                   "k_fact_hs");
   mark(h, 3, s);
   mark(h, 4, s);
@@ -1225,11 +1229,13 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
   rc = launched(h, launch_fact_tables(c, ra, consts, p.f, nullptr, 1, p.f.n_pad / 64, g, tau, nullptr, p.ad,
                                       (const double2*)T, w, s),
                 "k_fact_tables");
-  if (!rc) rc = launched(h, launch_fact_y(c, p.f, nullptr, 1, p.f.n_pad / (32 * p.mi), p.mi, false, w, s), "k_fact_y");
+  const int y_mi = y_block(c, p.f.n_pad, h->num_cus);
+  if (!rc) rc = launched(h, launch_fact_y(c, p.f, nullptr, 1, p.f.n_pad / (32 * y_mi), y_mi, false, w, s), "k_fact_y");
   double2 *Z = (double2*)(w + p.Z), *Q = (double2*)(w + p.Q);
   for (int t0 = 0; t0 < c.n_act && !rc; t0 += p.pass) {
     const int nt = std::min(p.pass, c.n_act - t0);
-    rc = launched(h, launch_adj_zq(c, p.f, t0, nt, p.mi, (const double2*)gH, (const double2*)gS, w, Z, Q, s), "k_adj_zq");
+    rc = launched(h, launch_adj_zq(c, p.f, t0, nt, h->num_cus, (const double2*)gH, (const double2*)gS, w, Z, Q, s),
+                  "k_adj_zq");
     if (!rc) rc = launched(h, launch_adj_uc(c, p.f, p.ad, t0, nt, p.mi, w, Z, Q, s), "k_adj_uc");
     if (!rc) rc = launched(h, launch_adj_gt(c, p.f, p.ad, t0, nt, w, s), "k_adj_gt");
   }
@@ -1323,13 +1329,13 @@ int record_factored_batch(hsbuild_t h, int n_k, const double* k_frac, const int3
                           const int64_t* out_off, const double* tau, const void* T, void* H, void* S, char* w) {
   FactCell c = fact_cell(h->cell);
   FactK* ks = (FactK*)h->meta_host;
-  int64_t tiles = 0;
+  int64_t cols = 0;
   for (int k = 0; k < n_k; ++k) {
     ks[k] = FactK{};
     ks[k].n = ng[k];
-    tiles += fact_tiles(ng[k], 2);
+    cols += (int64_t)round_up(ng[k], 64);
   }
-  const int mi = fact_block(tiles, h->num_cus);
+  const int mi = y_block(c, cols, h->num_cus);
   size_t consts_off = 0, many_off = 0;
   fact_layout(*h, c, ks, n_k, false, &consts_off, &many_off, nullptr);
   int64_t g_row = 0, gblk = 0, yblk = 0, tile = 0;
@@ -1344,9 +1350,9 @@ int record_factored_batch(hsbuild_t h, int n_k, const double* k_frac, const int3
     g_row += f.n;
     gblk += f.n_pad / 64;
     yblk += f.n_pad / (32 * mi);
-    tile += fact_tiles(f.n, mi);
+    tile += fact_tiles(f.n);
   }
-  if (tile > INT32_MAX) return fail(h, HSB_ERR_SHAPE, "problem too large");
+  if (2 * tile > INT32_MAX) return fail(h, HSB_ERR_SHAPE, "problem too large");
   RadialArgs ra;
   const bool by_value = fact_radial(*h, c, ra);
   hipStream_t cs = h->cap_stream;
@@ -1362,7 +1368,7 @@ int record_factored_batch(hsbuild_t h, int n_k, const double* k_frac, const int3
                            cs);
   if (e == hipSuccess) e = launch_fact_y(c, FactK{}, many, n_k, (int)yblk, mi, false, w, cs);
   if (e == hipSuccess)
-    e = launch_fact_hs(c, FactK{}, many, n_k, (int)tile, mi, false, h->tile_group, nullptr, w, H, S, cs);
+    e = launch_fact_hs(c, FactK{}, many, n_k, (int)tile, false, h->tile_group, h->num_cus, w, H, S, cs);
   return launched(h, e, "batch graph");
 }
 

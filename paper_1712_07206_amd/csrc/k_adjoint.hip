@@ -11,15 +11,15 @@
 // for R Z, 6 N_t for the phases, where the atom by atom form takes 24 N_t N_L; nothing is kept
 // from the forward.
 //
-//   k_adj_zq      P_t, M_t, N_t per wave tile (as k_fact_hs), Z_t and Q_t to memory
+//   k_adj_zq      P_t, M_t, N_t per tile (as k_fact_hs), Z_t and Q_t to memory
 //   k_adj_uc      (R Z)^T = Z^T R^T, rows G; and the phase sums of grad tau, reduced over the rows
 //                 of a tile to one partial per atom and segment of G'
 //   k_adj_gt      R Z R^T in segments of G
 //   k_adj_reduce  the segments' sums in order, turned back to complex harmonics; grad tau likewise
 //
-// All on v_mfma_f64_16x16x4f64 with operands read straight into registers, one chunk ahead; the
-// transposed copies of R and E (k_fact_tables) keep every operand contiguous along the MFMA's
-// row or column index.  Deterministic: fixed orders, no atomics.
+// All on v_mfma_f64_16x16x4f64; k_adj_uc and k_adj_gt read their operands straight into registers, one
+// chunk ahead, and the transposed copies of R and E (k_fact_tables) keep every operand contiguous along
+// the MFMA's row or column index.  Deterministic: fixed orders, no atomics.
 #include "harmonics.h"
 #include "hs_internal.h"
 #include "wave_tile.h"
@@ -28,52 +28,39 @@ namespace hsb {
 
 namespace {
 
-// Wave tile of Z_t, Q_t (zeros outside n x n, up to n_pad): all tiles of the square, types over y.
-template <int MI, int NJ, int KC, int WPS>
-__global__ void __launch_bounds__(256, WPS) k_adj_zq(FactCell c, FactK kk, int t0, const d2* __restrict__ gH,
-                                                     const d2* __restrict__ gS, const char* __restrict__ ws,
-                                                     d2* __restrict__ Z, d2* __restrict__ Q) {
+// Z_t and Q_t (zeros outside n x n, up to n_pad): 64 x 64 tiles of the square (MI = 2) or their halves (MI = 1,
+// interleaved in blockIdx.y), types over z.
+template <int MI>
+__global__ void __launch_bounds__(512, 2) k_adj_zq(FactCell c, FactK kk, int t0, const d2* __restrict__ gH,
+                                                   const d2* __restrict__ gS, const char* __restrict__ ws,
+                                                   d2* __restrict__ Z, d2* __restrict__ Q) {
+  constexpr int PARTS = 2 / MI;
+  __shared__ __align__(16) char lds[TypedTile<MI, false>::lds_bytes];
   const int n = kk.n;
   const int64_t n_pad = kk.n_pad;
-  const int t = t0 + blockIdx.y;
-  const int nb = kk.n_pad / (32 * NJ);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 15, lk = lane >> 4;
-  const int row0 = blockIdx.x / nb * 32 * MI + (wave >> 1) * 16 * MI;
-  const int col0 = blockIdx.x % nb * 32 * NJ + (wave & 1) * 16 * NJ;
-  const int col = col0 + NJ * lr;
-  d4 m1[MI][NJ], m2[MI][NJ], m3[MI][NJ], pR[MI][NJ], pI[MI][NJ];
-  if (row0 < n && col0 < n) {
-    TypedTile<MI, NJ, KC, false> tile(c, kk, row0, col0, nullptr, ws);
-    tile.load_e(t, 0, tile.ec);
-    tile.sums(t, false, m1, m2, m3, pR, pI);
-  } else {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) m1[i][j] = m2[i][j] = m3[i][j] = pR[i][j] = pI[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  }
-  d2* z = Z + (int64_t)blockIdx.y * n_pad * n_pad;
-  d2* qq = Q + (int64_t)blockIdx.y * n_pad * n_pad;
+  const int t = t0 + blockIdx.z;
+  TypedTile<MI, false> tile(c, kk, ws, lds, blockIdx.y / PARTS, blockIdx.y % PARTS, blockIdx.x, t, t + 1);
+  const bool active = tile.row0() < n && tile.col0() < n;
+  const int col = tile.col();
+  d2* z = Z + (int64_t)blockIdx.z * n_pad * n_pad + col;
+  d2* qq = Q + (int64_t)blockIdx.z * n_pad * n_pad + col;
+  d4 pR[MI], pI[MI], m1[MI], m2[MI], F[MI];
+  tile.phase_sums(t, active, pR, pI);
+  tile.row_sums(active, m1, m2, F);
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r = row0 + MI * (lk + 4 * q) + i;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        d2 h = d2{0.0, 0.0}, s = d2{0.0, 0.0};
-        if (r < n && col + j < n) {
-          h = gH[(int64_t)r * n + col + j];
-          s = gS[(int64_t)r * n + col + j];
-        }
-        const double a = m1[i][j][q], b = m2[i][j][q], d = m3[i][j][q], pr = pR[i][j][q], pi = pI[i][j][q];
-        d2 vz = d2{h.x * pr + h.y * pi, h.y * pr - h.x * pi};
-        d2 vq = d2{h.x * a + h.y * b + s.x * d, h.x * b - h.y * a - s.y * d};
-        if (r >= n || col + j >= n) vz = vq = d2{0.0, 0.0};  // (the sums of pad columns may hold anything)
-        z[(int64_t)r * n_pad + col + j] = vz;
-        qq[(int64_t)r * n_pad + col + j] = vq;
+      const int r = tile.row(i, q);
+      d2 vz = d2{0.0, 0.0}, vq = d2{0.0, 0.0};  // (the sums of pad columns may hold anything)
+      if (r < n && col < n) {
+        const d2 h = gH[(int64_t)r * n + col], s = gS[(int64_t)r * n + col];
+        const double a = m1[i][q], b = m2[i][q], d = F[i][q], pr = pR[i][q], pi = pI[i][q];
+        vz = d2{h.x * pr + h.y * pi, h.y * pr - h.x * pi};
+        vq = d2{h.x * a + h.y * b + s.x * d, h.x * b - h.y * a - s.y * d};
       }
+      z[(int64_t)r * n_pad] = vz;
+      qq[(int64_t)r * n_pad] = vq;
     }
 }
 
@@ -296,16 +283,15 @@ __global__ void __launch_bounds__(256) k_adj_reduce(FactCell c, FactAdj ad, int 
 
 }  // namespace
 
-hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int mi, const double2* gH,
+hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s) {
-  const int nb = kk.n_pad / (32 * mi);
-  const dim3 grid(nb * nb, nt);
-  if (mi == 2)
-    hipLaunchKernelGGL((k_adj_zq<2, 2, 2, 1>), grid, dim3(256), 0, s, c, kk, t0, (const d2*)gH, (const d2*)gS, ws,
-                       (d2*)Z, (d2*)Q);
-  else
-    hipLaunchKernelGGL((k_adj_zq<1, 1, 4, 2>), grid, dim3(256), 0, s, c, kk, t0, (const d2*)gH, (const d2*)gS, ws,
-                       (d2*)Z, (d2*)Q);
+  const int nb = kk.n_pad / 64;
+  const bool halves = 2 * nb * nb * nt <= num_cus;  // as in launch_fact_hs
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nb, halves ? 2 * nb : nb, nt), dim3(512), 0, s, c, kk, t0, (const d2*)gH,
+                       (const d2*)gS, ws, (d2*)Z, (d2*)Q);
+  };
+  halves ? go(k_adj_zq<1>) : go(k_adj_zq<2>);
   return hipGetLastError();
 }
 

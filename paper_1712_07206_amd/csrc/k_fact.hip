@@ -20,12 +20,15 @@
 //   k_fact_y       Y_t = T'_t R_t
 //   k_fact_hs      the upper triangles of H and S
 //
-// The wave-tile products run on v_mfma_f64_16x16x4f64 with both operands read straight from
-// global memory into registers, one chunk ahead: one MFMA takes 64 cycles of its SIMD, so a wave
-// tile of 2 x 2 blocks needs 72 bytes per lane every 768 cycles, which the vector caches deliver
-// without LDS, and waves need no barrier: they start, run ahead and leave on their own (a wave
-// below the diagonal leaves at once).  A lane holds pairs of neighbouring columns, one for each of
-// its two blocks (16-byte loads, 32-byte stores): block i of a wave covers the columns of parity i.
+// k_fact_hs runs on v_mfma_f64_16x16x4f64 with its operands fed through LDS (TypedTile in wave_tile.h), one 64 x 64
+// tile per workgroup of 8 waves; R, lam R, Y and E are block-major so that a tile reads contiguous runs.
+// Bound by the FP64 matrix cores: at N_G = 12000, 128 atoms, l_max = 10 they are busy for 76 % of its 8.3 ms (at
+// 2.3 GHz); the rest is waits at the ring's barriers and the copies.  The same tile on 2 x 2 waves with operands read
+// straight from global memory into registers, no barriers, took 9.2 ms; with the copies and their address
+// arithmetic right behind the barrier 8.9; with a wave's row and column not known to be uniform, so that the ring
+// ran on vector registers, 9.9.  The FP64 vector units share the matrix cores' pipe: the addition theorem's sum over l in
+// place of the S product has fewer operations and was slower in every form tried (8.3 with the tile of 64 x 32 its
+// registers allow and S apart).
 #include "harmonics.h"
 #include "hs_internal.h"
 #include "special.h"
@@ -64,7 +67,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
   const int t = blockIdx.y;
   const int tid = threadIdx.x;
   const int lmax = c.l_max, nl1 = lmax + 1;
-  if ((int)blockIdx.x >= ngb) {  // T'[r][k], stored [k][r] zero-padded, and lam
+  if ((int)blockIdx.x >= ngb) {  // T'[r][k], stored [k][r] zero-padded
     const int64_t e = (int64_t)(blockIdx.x - ngb) * 256 + tid;
     const int k = (int)(e / c.Mc), r = (int)(e % c.Mc);
     if (k >= c.Mr) return;
@@ -92,16 +95,6 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
       }
     }
     ((double2*)(ws + c.TT))[((int64_t)t * c.Mr + k) * c.Mc + r] = v;
-    if (r == 0) {
-      double lam = 0.0;
-      if (k < c.n_l) lam = 1.0;
-      else if (k < M) {
-        int l, m;
-        lm_of(k - c.n_l, l, m);
-        lam = consts ? consts->udot2[c.type[t]][l] : ra.v[t * nl1 + l][4];
-      }
-      ((double*)(ws + c.lam))[t * c.Mr + k] = lam;
-    }
     return;
   }
   const FactK& kk = many ? many[find_block(many, nk, blockIdx.x, &FactK::gblk0)] : one;
@@ -178,26 +171,35 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     ab[(nl1 + l) * kTabS + lane] = (u * slope - du * val) / det;
   }
   __syncthreads();
-  double* R = (double*)(ws + kk.R) + (int64_t)t * c.Mr * n_pad + G;
+  const int blk = blockIdx.x - kk.gblk0;
+  double* R = (double*)(ws + kk.R) + ((int64_t)blk * c.n_act + t) * c.Mr * 64 + lane;
+  double* LR = (double*)(ws + kk.LR) + ((int64_t)blk * c.n_act + t) * c.Mr * 64 + lane;
   for (int L = wave; L < c.n_l; L += 4) {
     int l, m;
     lm_of(L, l, m);
     const double s = ang[L * kTabS + lane];
-    R[(int64_t)L * n_pad] = valid ? s * ab[l * kTabS + lane] : 0.0;
-    R[(int64_t)(c.n_l + L) * n_pad] = valid ? s * ab[(nl1 + l) * kTabS + lane] : 0.0;
+    const double xa = valid ? s * ab[l * kTabS + lane] : 0.0, xb = valid ? s * ab[(nl1 + l) * kTabS + lane] : 0.0;
+    R[L * 64] = xa;
+    LR[L * 64] = xa;
+    R[(c.n_l + L) * 64] = xb;
+    LR[(c.n_l + L) * 64] = (consts ? consts->udot2[c.type[t]][l] : ra.v[t * nl1 + l][4]) * xb;
   }
-  for (int r = 2 * c.n_l + wave; r < c.Mr; r += 4) R[(int64_t)r * n_pad] = 0.0;
-  double2* E = (double2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad + G;
+  for (int r = 2 * c.n_l + wave; r < c.Mr; r += 4) R[r * 64] = LR[r * 64] = 0.0;
+  double2* E = (double2*)(ws + kk.E) + ((int64_t)blk * c.e_rows + c.eoff[t]) * 64 + lane;
+  double2* EW = (double2*)(ws + kk.EW) + ((int64_t)blk * c.e_rows + c.eoff[t]) * 64 + lane;
   const int nt = c.nat[t], erows = (nt + kFactRows - 1) / kFactRows * kFactRows;
   for (int a = wave; a < erows; a += 4) {
     double2 v = make_double2(0.0, 0.0);
+    double wt = 1.0;
     if (a < nt && valid) {
       const int at = rep ? rep[c.atom0[t] + a].atom : c.atom0[t] + a;
+      if (rep) wt = rep[c.atom0[t] + a].weight;
       double s, q;
       sincos(kx * tau[3 * at + 0] + ky * tau[3 * at + 1] + kz * tau[3 * at + 2], &s, &q);
       v = make_double2(q, s);
     }
-    E[(int64_t)a * n_pad] = v;
+    E[a * 64] = v;
+    if (rep) EW[a * 64] = make_double2(wt * v.x, wt * v.y);
     if (ad.Mt) ((double2*)(ws + ad.ET))[(int64_t)G * ad.et_ld + c.eoff[t] + a] = v;
   }
   if (!ad.Mt) return;
@@ -225,14 +227,14 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
   constexpr int KC = 2;
   const FactK& kk = many ? many[find_block(many, nk, blockIdx.x, &FactK::yblk0)] : one;
   const int t = blockIdx.z;
-  const int64_t n_pad = kk.n_pad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const int row0 = blockIdx.y * 32 * MI + (wave >> 1) * 16 * MI;
   const int col0 = (blockIdx.x - kk.yblk0) * 32 * NJ + (wave & 1) * 16 * NJ;
   if (row0 >= c.Mr || col0 >= kk.n) return;
   const d2* tp = (const d2*)(ws + c.TT) + ((int64_t)t * c.Mr + lk) * c.Mc + row0 + MI * lr;
-  const double* rp = (const double*)(ws + kk.R) + ((int64_t)t * c.Mr + lk) * n_pad + col0 + NJ * lr;
+  const int64_t blk = col0 / 64;  // a workgroup's columns lie in one block
+  const double* rp = (const double*)(ws + kk.R) + ((blk * c.n_act + t) * c.Mr + lk) * 64 + col0 % 64 + NJ * lr;
   typedef typename DVec<NJ>::T VB;
   d4 re[MI][NJ], im[MI][NJ];
 #pragma unroll
@@ -247,7 +249,7 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
       const int64_t k = (int64_t)(ch * KC + q) * 4;
 #pragma unroll
       for (int i = 0; i < MI; ++i) av[q][i] = tp[k * c.Mc + i];
-      bv[q] = *(const VB*)(rp + k * n_pad);
+      bv[q] = *(const VB*)(rp + k * 64);
     }
   };
   const int nch = c.Mr / (4 * KC);
@@ -278,7 +280,7 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
     for (int q = 0; q < 4; ++q) {
       const int row = row0 + MI * (lk + 4 * q) + i;
       if (row >= c.Mr) continue;
-      const int64_t o = ((int64_t)t * c.Mr + row) * n_pad + col0 + NJ * lr;
+      const int64_t o = ((blk * c.n_act + t) * c.Mr + row) * 64 + col0 % 64 + NJ * lr;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         if constexpr (REAL) ((double*)(ws + kk.Y))[o + j] = re[i][j][q];
@@ -287,73 +289,61 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
     }
 }
 
-// Upper triangles of H and S: workgroup of 2 x 2 waves, each one wave tile of 16 MI rows (G') x
-// 16 NJ columns (G): per type P_t times the sums over its R rows (TypedTile), into the running H
-// and S.
-template <int MI, int NJ, int KC, int WPS, bool REAL>
-__global__ void __launch_bounds__(256, WPS) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
-                                                      int num_wg, int gr, const FactRep* __restrict__ rep,
-                                                      const char* __restrict__ ws, void* __restrict__ H,
-                                                      void* __restrict__ S) {
+// Upper triangles of H and S: per type P_t times the sums over its R rows (TypedTile), into the running H and S.
+// 64 x 64 tiles (MI = 2), or two halves of each (MI = 1).
+template <int MI, bool REAL>
+__global__ void __launch_bounds__(512, 2) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
+                                                    int num_wg, int gr, const char* __restrict__ ws,
+                                                    void* __restrict__ H, void* __restrict__ S) {
+  constexpr int PARTS = 2 / MI;
+  __shared__ __align__(16) char lds[TypedTile<MI, REAL>::lds_bytes];
   int start, len;
   xcd_range(blockIdx.x % kXcds, num_wg, start, len);
   const int w = start + blockIdx.x / kXcds;
-  const FactK& kk = many ? many[find_block(many, nk, w, &FactK::tile0)] : one;
-  const int n = kk.n;
-  const int64_t n_pad = kk.n_pad;
-  const int nb = (n + 32 * MI - 1) / (32 * MI);
+  FactK kk = one;
+  if (many) kk = many[find_block(many, nk, w / PARTS, &FactK::tile0)];
+  const int n = kk.n, nb = (n + 63) / 64;
   int bi, bj;
-  if (gr > 0) grouped_decode(w - kk.tile0, nb, gr, bi, bj);
-  else tri_decode(w - kk.tile0, nb, bi, bj);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 15, lk = lane >> 4;
-  const int row0 = bi * 32 * MI + (wave >> 1) * 16 * MI, col0 = bj * 32 * NJ + (wave & 1) * 16 * NJ;
-  if (row0 >= n || col0 >= n || col0 + 16 * NJ <= row0) return;
-
-  const int col = col0 + NJ * lr;
-  d4 hR[MI][NJ], hI[MI][NJ], sR[MI][NJ], sI[MI][NJ];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) hR[i][j] = hI[i][j] = sR[i][j] = sI[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  TypedTile<MI, NJ, KC, REAL> tile(c, kk, row0, col0, rep, ws);
-  tile.load_e(0, 0, tile.ec);
+  if (gr > 0) grouped_decode(w / PARTS - kk.tile0, nb, gr, bi, bj);
+  else tri_decode(w / PARTS - kk.tile0, nb, bi, bj);
+  if (bi * 64 + w % PARTS * 32 >= n) return;
+  TypedTile<MI, REAL> tile(c, kk, ws, lds, bi, w % PARTS, bj, 0, c.n_act);
+  const int r0 = tile.row0(), c0 = tile.col0();
+  const bool active = r0 < n && c0 < n && c0 + 16 > r0;
+  d4 hR[MI], hI[MI], sR[MI], sI[MI];
+  clear(hR);
+  clear(hI);
+  clear(sR);
+  clear(sI);
   for (int t = 0; t < c.n_act; ++t) {
-    d4 pR[MI][NJ], pI[MI][NJ], m1[MI][NJ], m2[MI][NJ], m3[MI][NJ];
-    tile.sums(t, t + 1 < c.n_act, m1, m2, m3, pR, pI);
+    d4 pR[MI], pI[MI], m1[MI], m2[MI], F[MI];
+    tile.phase_sums(t, active, pR, pI);
+    tile.row_sums(active, m1, m2, F);
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if constexpr (REAL) {
-          hR[i][j] += pR[i][j] * m1[i][j];
-          sR[i][j] += pR[i][j] * m3[i][j];
-        } else {
-          hR[i][j] += pR[i][j] * m1[i][j] - pI[i][j] * m2[i][j];
-          hI[i][j] += pR[i][j] * m2[i][j] + pI[i][j] * m1[i][j];
-          sR[i][j] += pR[i][j] * m3[i][j];
-          sI[i][j] += pI[i][j] * m3[i][j];
-        }
+    for (int i = 0; i < MI; ++i) {
+      sR[i] += pR[i] * F[i];
+      if constexpr (REAL) {
+        hR[i] += pR[i] * m1[i];
+      } else {
+        sI[i] += pI[i] * F[i];
+        hR[i] += pR[i] * m1[i] - pI[i] * m2[i];
+        hI[i] += pR[i] * m2[i] + pI[i] * m1[i];
       }
+    }
   }
-
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r = row0 + MI * (lk + 4 * q) + i;
-      if (r >= n) continue;
-      const int64_t o = kk.out_off + (int64_t)r * n + col;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (col + j < n && col + j >= r) {
-          if constexpr (REAL) {
-            ((double*)H)[o + j] = hR[i][j][q];
-            ((double*)S)[o + j] = sR[i][j][q];
-          } else {
-            ((d2*)H)[o + j] = d2{hR[i][j][q], hI[i][j][q]};
-            ((d2*)S)[o + j] = d2{sR[i][j][q], sI[i][j][q]};
-          }
+      const int r = tile.row(i, q), col = tile.col();
+      if (r < n && col < n && col >= r) {
+        const int64_t o = kk.out_off + (int64_t)r * n + col;
+        if constexpr (REAL) {
+          ((double*)H)[o] = hR[i][q];
+          ((double*)S)[o] = sR[i][q];
+        } else {
+          ((d2*)H)[o] = d2{hR[i][q], hI[i][q]};
+          ((d2*)S)[o] = d2{sR[i][q], sI[i][q]};
         }
       }
     }
@@ -372,10 +362,8 @@ __global__ void __launch_bounds__(256) k_scale_rows(const double2* __restrict__ 
 
 }  // namespace
 
-int fact_block(int64_t cols, int num_cus) { return 2; }
-
-int fact_tiles(int n, int mi) {
-  const int nb = (n + 32 * mi - 1) / (32 * mi);
+int fact_tiles(int n) {
+  const int nb = (n + 63) / 64;
   return nb * (nb + 1) / 2;
 }
 
@@ -399,17 +387,18 @@ hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many,
   return hipGetLastError();
 }
 
-hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int num_wg, int mi, bool real,
-                          int gr, const FactRep* rep, const char* ws, void* H, void* S, hipStream_t s) {
-  const dim3 grid(num_wg);
-  if (mi == 2 && real)
-    hipLaunchKernelGGL((k_fact_hs<2, 2, 2, 1, true>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
-  else if (mi == 2)
-    hipLaunchKernelGGL((k_fact_hs<2, 2, 2, 1, false>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
-  else if (real)
-    hipLaunchKernelGGL((k_fact_hs<1, 1, 4, 2, true>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
-  else
-    hipLaunchKernelGGL((k_fact_hs<1, 1, 4, 2, false>), grid, dim3(256), 0, s, c, one, many, nk, num_wg, gr, rep, ws, H, S);
+hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int tiles, bool real, int gr,
+                          int num_cus, const char* ws, void* H, void* S, hipStream_t s) {
+  // Halves of tiles while all of them run at once: half the products per workgroup, but each operand read for
+  // half as many, so a half takes 0.73 of a tile's time (5-type cell of l_max 8: 120 tiles 67 us as halves, 81 whole;
+  // 136 tiles, 272 halves on 256 compute units, 96 and 84; 1128 tiles of another 289 and 253).
+  const bool halves = 2 * tiles <= num_cus;
+  const int num_wg = halves ? 2 * tiles : tiles;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(num_wg), dim3(512), 0, s, c, one, many, nk, num_wg, gr, ws, H, S);
+  };
+  if (halves) real ? go(k_fact_hs<1, true>) : go(k_fact_hs<1, false>);
+  else real ? go(k_fact_hs<2, true>) : go(k_fact_hs<2, false>);
   return hipGetLastError();
 }
 

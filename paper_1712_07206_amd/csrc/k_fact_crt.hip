@@ -73,6 +73,7 @@ struct ResMma<2> {
 // Rows and steps past the ends are zero.  A's residues hold the columns of each 32 even ones first (k_fact_crt).
 // (The same pieces from arrays of whole rows, 1 KB out of every 192 at N_G = 12000: 15.2 ms against 12.4.)
 constexpr int kRowsE = 12, kRowsF = 24, kChunk = 24 * 1024;
+typedef Ring<6, kChunk> CrtRing;
 template <bool REAL>
 struct Stream {
   static constexpr int NC = REAL ? 1 : 2;        // products per modulus
@@ -87,7 +88,6 @@ struct Stream {
 constexpr int kPackWaves = 16;
 template <int EK, bool REAL>
 __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK kk, FactCrt cr,
-                                                               const FactRep* __restrict__ rep,
                                                                char* __restrict__ ws) {
   constexpr int RU = EK == 0 ? 16 : 8, EB = 16 / RU, PER = 4 / EB;
   typedef Stream<REAL> St;
@@ -101,27 +101,21 @@ __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK
   const int n_e = (nat + kRowsE - 1) / kRowsE;
   char* out = ws + (is_b ? cr.B + blockIdx.x * cr.b_len + cr.boff[t] : cr.A + blockIdx.x * cr.a_len + cr.aoff[t]);
   {
-    const d2* e = (const d2*)(ws + kk.E) + (int64_t)c.eoff[t] * np + G;
+    const d2* e = (const d2*)(ws + (is_b ? kk.EW : kk.E)) + ((int64_t)blockIdx.x * c.e_rows + c.eoff[t]) * 64 + lane;
     d2* o = (d2*)out + lane;
-    for (int k = wave; k < n_e * kRowsE; k += kPackWaves) {
-      d2 v = d2{0.0, 0.0};
-      if (k < nat) {
-        v = e[k * np];
-        if (REAL && is_b) v *= rep[c.atom0[t] + k].weight;
-      }
-      o[k * 64] = v;
-    }
+    for (int k = wave; k < n_e * kRowsE; k += kPackWaves) o[k * 64] = k < nat ? e[k * 64] : d2{0.0, 0.0};
     out += n_e * (kChunk / 2);
   }
-  const double* R = (const double*)(ws + kk.R) + (int64_t)t * c.Mr * np + G;
+  const int64_t r0 = ((int64_t)blockIdx.x * c.n_act + t) * c.Mr;
+  const double* R = (const double*)(ws + kk.R) + r0 * 64 + lane;
   {
-    const double* lam = (const double*)(ws + c.lam) + t * c.Mr;
+    const double* r = is_b ? (const double*)(ws + kk.LR) + r0 * 64 + lane : R;
     double* o = (double*)out + lane;
-    for (int k = wave; k < cr.n_f * kRowsF; k += kPackWaves) o[k * 64] = k < M ? (is_b ? lam[k] : 1.0) * R[k * np] : 0.0;
+    for (int k = wave; k < cr.n_f * kRowsF; k += kPackWaves) o[k * 64] = k < M ? r[k * 64] : 0.0;
     out += cr.n_f * (kChunk / 2);
   }
-  const double* x = is_b ? (const double*)(ws + kk.Y) + ((int64_t)t * c.Mr * np + G) * parts : R;
-  const int64_t ld = np * parts;
+  const double* x = is_b ? (const double*)(ws + kk.Y) + (r0 * 64 + lane) * parts : R;
+  const int ld = 64 * parts;
   double sq = 0.0;
   for (int k = wave; k < M; k += kPackWaves)
     for (int p = 0; p < parts; ++p) {
@@ -166,16 +160,9 @@ __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK
 
 // Upper triangles of H and S, 64 x 64 tiles on 2 x 4 waves of 32 x 16.
 //
-// Chunks are copied straight into LDS (global_load_lds_dwordx4: 24 copies of 1 KB, three per wave), six stages,
-// five chunks ahead, one barrier per chunk.  A residue step is 64 cycles of a wave's matrix core and as many of
-// its FP64 vector unit, and what misses L2 takes thousands: operands read straight into registers two steps
-// ahead took 14.0 ms.  P, H, S and the residue sums of 64 x 64 outputs fill the register file.
-typedef __attribute__((address_space(3))) void* lds_ptr;
-constexpr int kStages = 6, kWaveCopies = 3;
-
-// s_waitcnt immediate (gfx9 encoding): at most n vector-memory operations pending, LDS operations done.
-constexpr int vm_pending(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
-
+// A residue step is 64 cycles of a wave's matrix core and as many of its FP64 vector unit, and what misses L2
+// takes thousands: operands read straight into registers two steps ahead took 14.0 ms.  P, H, S and the residue sums
+// of 64 x 64 outputs fill the register file.
 template <int EK, bool REAL>
 __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactCrt cr, int num_wg, int gr,
                                                      const char* __restrict__ ws, void* __restrict__ H,
@@ -183,9 +170,8 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
   typedef ResMma<EK> Mma;
   typedef Stream<REAL> St;
   constexpr int NC = St::NC, SPC = St::SPC;
-  // One array: with several the compiler waits for every pending copy before each read.
-  __shared__ __align__(16) char lds[kStages * kChunk + 2 * HSB_MAX_TYPES * 64 * 8];
-  double* const inv_row = (double*)(lds + kStages * kChunk);  // [type][64]
+  __shared__ __align__(16) char lds[CrtRing::bytes + 2 * HSB_MAX_TYPES * 64 * 8];
+  double* const inv_row = (double*)(lds + CrtRing::bytes);  // [type][64]
   double* const inv_col = inv_row + HSB_MAX_TYPES * 64;
   int start, len;
   xcd_range(blockIdx.x % kXcds, num_wg, start, len);
@@ -211,19 +197,18 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
   }
 
   const int M = 2 * c.n_l, steps = cr.n_mod * cr.ks;
-  int left = 0;  // chunks not yet waited for
-  for (int t = 0; t < c.n_act; ++t) left += (c.nat[t] + kRowsE - 1) / kRowsE + cr.n_f + cr.n_r;
-  // next chunk to issue: its parts of the streams, chunks until the type's residues and the next type; stages
+  CrtRing ring{lds, 0};
+  for (int t = 0; t < c.n_act; ++t) ring.left += (c.nat[t] + kRowsE - 1) / kRowsE + cr.n_f + cr.n_r;
+  // next chunk to issue: its parts of the streams, chunks until the type's residues and the next type
   const char* pa = ws + cr.A + bi * cr.a_len;
   const char* pb = ws + cr.B + bj * cr.b_len;
-  int it = 0, to_res = (c.nat[0] + kRowsE - 1) / kRowsE + cr.n_f, to_type = cr.n_r, istage = 0, cstage = 0;
+  int it = 0, to_res = (c.nat[0] + kRowsE - 1) / kRowsE + cr.n_f, to_type = cr.n_r;
   auto issue = [&]() {
     if (it >= c.n_act) return;
-    char* st = lds + istage * kChunk + wave * 1024;
-    istage = istage == kStages - 1 ? 0 : istage + 1;
+    char* st = ring.stage(wave);
     const int na = to_res > 0 ? kChunk / 2 : St::a_res;
 #pragma unroll
-    for (int i = 0; i < kWaveCopies; ++i) {
+    for (int i = 0; i < CrtRing::copies; ++i) {
       const int o = (wave + 8 * i) * 1024;
       __builtin_amdgcn_global_load_lds((const void*)((o < na ? pa : pb - na) + o + lane * 16), (lds_ptr)(st + i * 8192), 16, 0, 0);
     }
@@ -236,24 +221,12 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
       if (++it < c.n_act) to_res = (c.nat[it] + kRowsE - 1) / kRowsE + cr.n_f;
     }
   };
-  // Waits for the next chunk, everyone's copies of it; the stage of the one before is free after it, and
-  // another chunk goes there.
   auto arrive = [&]() -> const char* {
-    --left;
-    if (left >= 4) __builtin_amdgcn_s_waitcnt(vm_pending(4 * kWaveCopies));
-    else if (left == 3) __builtin_amdgcn_s_waitcnt(vm_pending(3 * kWaveCopies));
-    else if (left == 2) __builtin_amdgcn_s_waitcnt(vm_pending(2 * kWaveCopies));
-    else if (left == 1) __builtin_amdgcn_s_waitcnt(vm_pending(kWaveCopies));
-    else __builtin_amdgcn_s_waitcnt(vm_pending(0));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const char* st = lds + cstage * kChunk;
-    cstage = cstage == kStages - 1 ? 0 : cstage + 1;
+    const char* st = ring.arrive();
     issue();
     return st;
   };
-  for (int i = 0; i < kStages - 1; ++i) issue();
+  for (int i = 0; i < CrtRing::stages - 1; ++i) issue();
 
   const d4 z = d4{0.0, 0.0, 0.0, 0.0};
   d4 hR[2], hI[2], sR[2], sI[2];
@@ -445,19 +418,19 @@ FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real) {
   return r;
 }
 
-hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, const FactRep* rep, char* ws,
+hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
                             hipStream_t s) {
   const dim3 grid(kk.n_pad / 64, c.n_act, 2), block(64 * kPackWaves);
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, c, kk, cr, rep, ws); };
-  if (ek == 0) rep ? go(k_fact_pack<0, true>) : go(k_fact_pack<0, false>);
-  else if (ek == 1) rep ? go(k_fact_pack<1, true>) : go(k_fact_pack<1, false>);
-  else rep ? go(k_fact_pack<2, true>) : go(k_fact_pack<2, false>);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, c, kk, cr, ws); };
+  if (ek == 0) real ? go(k_fact_pack<0, true>) : go(k_fact_pack<0, false>);
+  else if (ek == 1) real ? go(k_fact_pack<1, true>) : go(k_fact_pack<1, false>);
+  else real ? go(k_fact_pack<2, true>) : go(k_fact_pack<2, false>);
   return hipGetLastError();
 }
 
 hipError_t launch_fact_crt(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, int gr,
                            const char* ws, void* H, void* S, hipStream_t s) {
-  const int num_wg = fact_tiles(kk.n, 2);
+  const int num_wg = fact_tiles(kk.n);
   const dim3 grid(num_wg), block(512);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, c, kk, cr, num_wg, gr, ws, H, S); };
   if (ek == 0) real ? go(k_fact_crt<0, true>) : go(k_fact_crt<0, false>);

@@ -1,8 +1,5 @@
-// Wave tiles of the type-factored kernels: 16 MI rows x 16 NJ columns per wave on
-// v_mfma_f64_16x16x4f64, operands read straight from global memory into registers one chunk (KC
-// steps of 4 rows) ahead.  A lane holds MI (NJ) neighbouring rows (columns), one for each block:
-// block i covers the rows of index i modulo MI, so one load serves all blocks.
-// Output of the 16x16 f64 MFMA: lane l, element q -> row l/16 + 4q, column l%16 of the block.
+// Tiles of the type-factored kernels on v_mfma_f64_16x16x4f64 (A: lane l holds row l % 16 of step row l / 16; B
+// likewise its column; output: lane l, element q -> row l / 16 + 4 q, column l % 16).
 #pragma once
 
 #include "hs_internal.h"
@@ -11,6 +8,7 @@ namespace hsb {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void* lds_ptr;
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
 
@@ -22,144 +20,292 @@ struct DVec<1> { typedef double T; static __device__ double get(T v, int) { retu
 template <>
 struct DVec<2> { typedef d2 T; static __device__ double get(T v, int i) { return v[i]; } };
 
-// The sums of one (G', G) wave tile for a type t with phases E, rows R and Y:
-//   P = E^H E:  three real products per complex one (P1 = a_r b_r, P2 = a_i b_i,
-//     P3 = (a_r - a_i)(b_r + b_i), Re = P1 + P2, Im = P3 - P1 + P2); the real form takes two, into
-//     one sum, the columns' phases weighted with the atom's multiplicity;
-//   m1 + i m2 = R^T Y (the real form: m1 only),  m3 = R^T lam R.
-// P is summed in the registers of the m's, which come after it.
-template <int MI, int NJ, int KC, bool REAL>
-struct TypedTile {
-  static_assert(kFactRows % (4 * KC) == 0, "rows are padded to whole chunks");
-  typedef typename DVec<MI>::T VA;
-  typedef typename DVec<NJ>::T VB;
-  struct EChunk { d2 a[KC][MI], b[KC][NJ]; double w[KC]; };
-  struct MChunk { VA a[KC]; VB b[KC]; VB yr[KC]; d2 y[KC][NJ]; double lam[KC]; };
+template <int MI, int NJ>
+__device__ __forceinline__ void clear(d4 (&x)[MI][NJ]) {
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) x[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+}
+template <int MI>
+__device__ __forceinline__ void clear(d4 (&x)[MI]) {
+#pragma unroll
+  for (int i = 0; i < MI; ++i) x[i] = d4{0.0, 0.0, 0.0, 0.0};
+}
 
+// s_waitcnt immediate (gfx9 encoding): at most n vector-memory operations pending, LDS operations done.
+constexpr int vm_pending(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
+
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)p >> 32));
+  return (const char*)(((uintptr_t)hi << 32) | lo);
+}
+
+// LDS ring of a workgroup of eight waves: chunks of BYTES, copied straight there (global_load_lds_dwordx4) as
+// copies of 1 KB, copy 8 i + w of a chunk by wave w; STAGES - 1 chunks ahead, one barrier per chunk.
+// The ring has to be the kernel's only __shared__ array: with several the compiler waits for every pending
+// copy before each read of one.
+template <int STAGES, int BYTES>
+struct Ring {
+  static constexpr int stages = STAGES, chunk = BYTES, copies = BYTES / 8192, bytes = STAGES * BYTES;
+  char* lds;
+  int left;  // chunks not yet waited for
+  int istage = 0, cstage = 0;
+  // This wave's part of the next stage.
+  __device__ __forceinline__ char* stage(int wave) {
+    char* st = lds + istage * BYTES + wave * 1024;
+    istage = istage == STAGES - 1 ? 0 : istage + 1;
+    return st;
+  }
+  // Waits for the next chunk, everyone's copies of it; the stage of the chunk before is free after it.
+  __device__ __forceinline__ const char* arrive() {
+    --left;
+    if (left >= STAGES - 2) __builtin_amdgcn_s_waitcnt(vm_pending((STAGES - 2) * copies));
+    else if (STAGES > 4 && left == 3) __builtin_amdgcn_s_waitcnt(vm_pending(3 * copies));
+    else if (STAGES > 3 && left == 2) __builtin_amdgcn_s_waitcnt(vm_pending(2 * copies));
+    else if (left == 1) __builtin_amdgcn_s_waitcnt(vm_pending(copies));
+    else __builtin_amdgcn_s_waitcnt(vm_pending(0));
+    // a plain s_barrier: __syncthreads would wait for the copies in flight as well
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const char* st = lds + cstage * BYTES;
+    cstage = cstage == STAGES - 1 ? 0 : cstage + 1;
+    return st;
+  }
+};
+
+// One tile of 32 MI (G') x 64 (G) of the type-factored products on 2 x 4 waves of 16 MI x 16: MI = 2 the 64 x 64
+// blocks of the arrays, MI = 1 the upper or lower half of one.  A lane holds MI neighbouring rows, one for each of
+// its blocks: block i covers the rows of index i modulo MI.  Two waves per SIMD: at MI = 2 nine sums and operands
+// take 206 registers.
+//
+// Chunks of 48 KB are 24 phase rows (E at G', EW at G), then 24 of the type's R rows (R at G'; lam R and Y at G; the
+// real form 32), contiguous runs of the block-major arrays; rows past a type's are copied but not used.
+// (Chunks of half that in twice the stages: the same at N_G = 12000, 3 to 15 % more where a type has fewer chunks.)
+template <int MI, bool REAL>
+struct TypedTile {
+  static constexpr int RE = 24, RM = REAL ? 32 : 24;
+  typedef Ring<3, 48 * 1024> R;
+  static constexpr int lds_bytes = R::bytes;
+  typedef typename DVec<MI>::T VA;
   const FactCell& c;
   const FactK& kk;
-  const FactRep* rep;
   const char* ws;
-  int64_t n_pad;
-  int lk, row, col;
-  EChunk ec;
-  MChunk mc;
+  R ring;
+  int bi, half, bj, t_end;
+  int wave, lr, lk, arow, bcol;
+  // The next chunk to issue: its type, chunks left of the type's phases or rows; this wave's three copies of it: the
+  // phases' and rows' next sources, the rows' step per chunk and what it takes from the last to the next type's first.
+  int it, n_left;
+  bool irows = false;
+  const char *pa, *pb;               // E, EW
+  const char *p0, *p1, *p2, *p3;
+  int adj, adj3;
 
-  __device__ __forceinline__ TypedTile(const FactCell& cell, const FactK& k, int row0, int col0, const FactRep* reps,
-                                       const char* base)
-      : c(cell), kk(k), rep(reps), ws(base), n_pad(k.n_pad) {
+  __device__ __forceinline__ TypedTile(const FactCell& cell, const FactK& k, const char* base, char* lds, int block_i,
+                                       int which_half, int block_j, int t0, int t1)
+      : c(cell), kk(k), ws(base), bi(block_i), half(which_half), bj(block_j), t_end(t1), it(t0) {
     const int lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lr = lane & 15;
     lk = lane >> 4;
-    row = row0 + MI * (lane & 15);
-    col = col0 + NJ * (lane & 15);
+    arow = half * 32 + (wave >> 2) * 16 * MI + MI * lr;
+    bcol = (wave & 3) * 16 + lr;
+    ring.lds = lds;
+    ring.left = 0;
+    for (int t = t0; t < t1; ++t) ring.left += (c.nat[t] + RE - 1) / RE + (2 * c.n_l + RM - 1) / RM;
+    n_left = (c.nat[it] + RE - 1) / RE;
+    const int n_f = (2 * c.n_l + RM - 1) / RM;
+    const int64_t ra = ((int64_t)bi * c.n_act + it) * c.Mr, rb = ((int64_t)bj * c.n_act + it) * c.Mr;
+    const char* r = ws + kk.R + ra * 512;
+    const char* l = ws + kk.LR + rb * 512;
+    const char* y = ws + kk.Y + rb * (REAL ? 512 : 1024);
+    p0 = uniform(r + wave * 1024);
+    p1 = REAL ? p0 : uniform(wave < 4 ? r + (wave + 8) * 1024 : l + (wave - 4) * 1024);
+    p2 = uniform(l + (REAL ? wave : wave + 4) * 1024);
+    p3 = uniform(y + wave * 1024);
+    adj = (c.Mr - n_f * RM) * 512;
+    adj3 = adj * (REAL ? 1 : 2);
+    phase_source();
+    for (int i = 0; i < R::stages - 1; ++i) issue();
   }
-  __device__ __forceinline__ void load_e(int t, int ch, EChunk& e) const {
-    const d2* base = (const d2*)(ws + kk.E) + (int64_t)c.eoff[t] * n_pad;
-#pragma unroll
-    for (int q = 0; q < KC; ++q) {
-      const int k = (ch * KC + q) * 4 + lk;
-      const d2* p = base + (int64_t)k * n_pad;
-#pragma unroll
-      for (int i = 0; i < MI; ++i) e.a[q][i] = p[row + i];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) e.b[q][j] = p[col + j];
-      if constexpr (REAL) e.w[q] = k < c.nat[t] ? rep[c.atom0[t] + k].weight : 0.0;
-    }
+  // First row and column of this wave's part (uniform).
+  __device__ __forceinline__ int row0() const { return bi * 64 + half * 32 + (wave >> 2) * 16 * MI; }
+  __device__ __forceinline__ int col0() const { return bj * 64 + (wave & 3) * 16; }
+  // Row of element q of block i, and the column, of this lane's sums.
+  __device__ __forceinline__ int row(int i, int q) const { return row0() + MI * (lk + 4 * q) + i; }
+  __device__ __forceinline__ int col() const { return bj * 64 + bcol; }
+
+  __device__ __forceinline__ void phase_source() {
+    pa = uniform(ws + kk.E + ((int64_t)bi * c.e_rows + c.eoff[it]) * 1024 + wave * 1024);
+    pb = uniform(ws + kk.EW + ((int64_t)bj * c.e_rows + c.eoff[it]) * 1024 + wave * 1024);
   }
-  __device__ __forceinline__ void load_m(int t, int ch, MChunk& m) const {
+  __device__ __forceinline__ void issue() {
+    if (it >= t_end) return;
+    char* st = ring.stage(wave);
+    const unsigned off = (threadIdx.x & 63) * 16;
+    auto copy = [&](const char* p, int i) {
+      __builtin_amdgcn_global_load_lds((const void*)(p + off), (lds_ptr)(st + i * 8192), 16, 0, 0);
+    };
+    if (!irows) {
 #pragma unroll
-    for (int q = 0; q < KC; ++q) {
-      const int64_t k = (int64_t)t * c.Mr + (ch * KC + q) * 4 + lk;
-      const double* p = (const double*)(ws + kk.R) + k * n_pad;
-      m.a[q] = *(const VA*)(p + row);
-      m.b[q] = *(const VB*)(p + col);
-      m.lam[q] = ((const double*)(ws + c.lam))[k];
+      for (int i = 0; i < 3; ++i) {
+        copy(pa + i * 8192, i);
+        copy(pb + i * 8192, i + 3);
+      }
+      pa += RE * 1024;
+      pb += RE * 1024;
+      if (--n_left == 0) {
+        irows = true;
+        n_left = (2 * c.n_l + RM - 1) / RM;
+      }
+    } else {
       if constexpr (REAL) {
-        m.yr[q] = *(const VB*)((const double*)(ws + kk.Y) + k * n_pad + col);
+        copy(p0, 0);
+        copy(p0 + 8192, 1);
+        copy(p2, 2);
+        copy(p2 + 8192, 3);
+        copy(p3, 4);
+        copy(p3 + 8192, 5);
+        p0 += RM * 512;
+        p2 += RM * 512;
+        p3 += RM * 512;
       } else {
-        const d2* yp = (const d2*)(ws + kk.Y) + k * n_pad + col;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) m.y[q][j] = yp[j];
+        copy(p0, 0);
+        copy(p1, 1);
+        copy(p2, 2);
+        copy(p3, 3);
+        copy(p3 + 8192, 4);
+        copy(p3 + 16384, 5);
+        p0 += RM * 512;
+        p1 += RM * 512;
+        p2 += RM * 512;
+        p3 += RM * 1024;
+      }
+      if (--n_left == 0) {
+        irows = false;
+        if (++it < t_end) {
+          p0 += adj;
+          p1 += adj;
+          p2 += adj;
+          p3 += adj3;
+          n_left = (c.nat[it] + RE - 1) / RE;
+          phase_source();
+        }
       }
     }
   }
-  // ec holds type t's first phase chunk; with more, type t + 1's is loaded on the way.
-  __device__ __forceinline__ void sums(int t, bool more, d4 (&m1)[MI][NJ], d4 (&m2)[MI][NJ], d4 (&m3)[MI][NJ],
-                                       d4 (&pR)[MI][NJ], d4 (&pI)[MI][NJ]) {
-    const d4 z = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) m1[i][j] = m2[i][j] = m3[i][j] = z;
-    load_m(t, 0, mc);  // lands behind the phase sums
-    const int kse = (c.nat[t] + 3) / 4, nce = (kse + KC - 1) / KC;
-    for (int ch = 0; ch < nce; ++ch) {
-      EChunk en;
-      load_e(t, ch + 1 < nce ? ch + 1 : ch, en);
-#pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        if (ch * KC + q < kse) {  // uniform
-          double ad[MI], bs[NJ];
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            if constexpr (REAL) ec.b[q][j] *= ec.w[q];
-            bs[j] = ec.b[q][j].x + ec.b[q][j].y;
-          }
-#pragma unroll
-          for (int i = 0; i < MI; ++i) ad[i] = ec.a[q][i].x - ec.a[q][i].y;
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-              m1[i][j] = MFMA(ec.a[q][i].x, ec.b[q][j].x, m1[i][j]);
-              if constexpr (REAL) {
-                m1[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m1[i][j]);
-              } else {
-                m2[i][j] = MFMA(ec.a[q][i].y, ec.b[q][j].y, m2[i][j]);
-                m3[i][j] = MFMA(ad[i], bs[j], m3[i][j]);
-              }
-            }
-        }
+  // A section (a type's phases, or its rows) of `steps` 4-row steps, PER of them a chunk: read(stage, s) gives a
+  // step's operands, mac(x) takes the products.  The next step's operands are read ahead of a step's
+  // products, over the barrier too, and the copies of another chunk go out behind the first
+  // step's: right behind the barrier, where all waves are, they and their addresses leave the matrix cores
+  // idle.
+  template <int PER, class Read, class Mac>
+  __device__ __forceinline__ void section(int steps, bool active, Read read, Mac mac) {
+    const int chunks = (steps + PER - 1) / PER;
+    if (!active) {  // uniform
+      for (int i = 0; i < chunks; ++i) {
+        ring.arrive();
+        issue();
       }
-      ec = en;
+      return;
     }
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        pR[i][j] = REAL ? m1[i][j] : m1[i][j] + m2[i][j];
-        pI[i][j] = m3[i][j] - m1[i][j] + m2[i][j];
-        m1[i][j] = m2[i][j] = m3[i][j] = z;
+    // a step's products with the next one's reads behind the first block's (the wait for a step's own
+    // operands is then not one for theirs too)
+    auto step = [&](const auto& x, const char* st, int next) {
+      if constexpr (MI == 2) {
+        mac(x, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    if (more) load_e(t + 1, 0, ec);  // lands behind the R sums
-    const int ksm = (2 * c.n_l + 3) / 4, ncm = (ksm + KC - 1) / KC;
-    for (int ch = 0; ch < ncm; ++ch) {
-      MChunk mn;
-      load_m(t, ch + 1 < ncm ? ch + 1 : ch, mn);
+      auto y = read(st, next);
+      __builtin_amdgcn_sched_barrier(0);
+      mac(x, MI - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      return y;
+    };
+    const char* st = ring.arrive();
+    auto x = read(st, 0);
+    for (int i = 1; i < chunks; ++i) {
 #pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        if (ch * KC + q < ksm) {  // uniform
-          double ls[NJ];
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) ls[j] = mc.lam[q] * DVec<NJ>::get(mc.b[q], j);
-#pragma unroll
-          for (int i = 0; i < MI; ++i) {
-            const double ai = DVec<MI>::get(mc.a[q], i);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-              if constexpr (REAL) {
-                m1[i][j] = MFMA(ai, DVec<NJ>::get(mc.yr[q], j), m1[i][j]);
-              } else {
-                m1[i][j] = MFMA(ai, mc.y[q][j].x, m1[i][j]);
-                m2[i][j] = MFMA(ai, mc.y[q][j].y, m2[i][j]);
-              }
-              m3[i][j] = MFMA(ai, ls[j], m3[i][j]);
-            }
-          }
-        }
+      for (int s = 0; s < PER; ++s) {
+        if (s == PER - 1) st = ring.arrive();
+        x = step(x, st, s == PER - 1 ? 0 : s + 1);
+        if (s == 0) issue();
       }
-      mc = mn;
     }
+    const int rest = steps - (chunks - 1) * PER;
+    mac(x, 0);
+    if constexpr (MI == 2) mac(x, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    issue();
+#pragma unroll
+    for (int s = 1; s < PER; ++s)
+      if (s < rest) {
+        x = read(st, s);
+        mac(x, 0);
+        if constexpr (MI == 2) mac(x, 1);
+      }
+  }
+  struct Phases { d2 a[MI], b; };
+  __device__ __forceinline__ Phases read_phases(const char* st, int s) const {
+    Phases x;
+    const d2* A = (const d2*)(st + (4 * s + lk) * 1024) + arow;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) x.a[i] = A[i];
+    x.b = ((const d2*)(st + (RE + 4 * s + lk) * 1024))[bcol];
+    return x;
+  }
+  // P_t = E_t^H E_t: three real products per complex one (P1 = a_r b_r, P2 = a_i b_i,
+  // P3 = (a_r - a_i)(b_r + b_i), Re = P1 + P2, Im = P3 - P1 + P2); the real form, its columns' phases weighted with the
+  // atoms' multiplicities, takes two, into one sum (pI is not set).
+  __device__ __forceinline__ void phase_sums(int t, bool active, d4 (&pR)[MI], d4 (&pI)[MI]) {
+    d4 p1[MI], p2[MI], p3[MI];
+    clear(p1);
+    clear(p2);
+    clear(p3);
+    section<RE / 4>((c.nat[t] + 3) / 4, active, [&](const char* st, int s) { return read_phases(st, s); },
+                    [&](const Phases& x, int i) {
+                      p1[i] = MFMA(x.a[i].x, x.b.x, p1[i]);
+                      if constexpr (REAL) {
+                        p1[i] = MFMA(x.a[i].y, x.b.y, p1[i]);
+                      } else {
+                        p2[i] = MFMA(x.a[i].y, x.b.y, p2[i]);
+                        p3[i] = MFMA(x.a[i].x - x.a[i].y, x.b.x + x.b.y, p3[i]);
+                      }
+                    });
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      pR[i] = REAL ? p1[i] : p1[i] + p2[i];
+      if constexpr (!REAL) pI[i] = p3[i] - p1[i] + p2[i];
+    }
+  }
+  struct Rows { VA a; d2 y; double yr, l; };
+  __device__ __forceinline__ Rows read_rows(const char* st, int s) const {
+    Rows x;
+    x.a = *(const VA*)((const double*)(st + (4 * s + lk) * 512) + arow);
+    x.l = ((const double*)(st + RM * 512 + (4 * s + lk) * 512))[bcol];
+    if constexpr (REAL) x.yr = ((const double*)(st + 2 * RM * 512 + (4 * s + lk) * 512))[bcol];
+    else x.y = ((const d2*)(st + 2 * RM * 512 + (4 * s + lk) * 1024))[bcol];
+    return x;
+  }
+  // m1 + i m2 = R_t^T Y_t (the real form: m1 only), F = R_t^T Lam_t R_t.
+  __device__ __forceinline__ void row_sums(bool active, d4 (&m1)[MI], d4 (&m2)[MI], d4 (&F)[MI]) {
+    clear(m1);
+    if constexpr (!REAL) clear(m2);
+    clear(F);
+    section<RM / 4>((2 * c.n_l + 3) / 4, active, [&](const char* st, int s) { return read_rows(st, s); },
+                    [&](const Rows& x, int i) {
+                      const double a = DVec<MI>::get(x.a, i);
+                      if constexpr (REAL) {
+                        m1[i] = MFMA(a, x.yr, m1[i]);
+                      } else {
+                        m1[i] = MFMA(a, x.y.x, m1[i]);
+                        m2[i] = MFMA(a, x.y.y, m2[i]);
+                      }
+                      F[i] = MFMA(a, x.l, F[i]);
+                    });
   }
 };
 

@@ -1,6 +1,6 @@
 """The type-factored kernels at the sizes where their tiles, row padding and radial-data hand-over
 change, against the oracle: bases around multiples of the 16-, 32- and 64-column blocks, atom counts
-around the 4-row steps and 16-row pads of the phase sums, l_max from 0 (where 2 N_L = 2 rows are
+around the 4-row steps, 16-row pads and 24-row chunks of the phase sums, l_max from 0 (where 2 N_L = 2 rows are
 padded to 16) up, and more (type, l) pairs than travel by value.
 
 Bar: the FP64 path's relative Frobenius error <= 1e-12 over the full matrices, the strict lower
@@ -68,12 +68,12 @@ def test_basis_around_the_blocks(n_g):
     _check(_case((3, 1), 2, n_g))
 
 
-@pytest.mark.parametrize("n_g", [2100, 2950])  # on both sides of the rule that picks the tile size
+@pytest.mark.parametrize("n_g", [960, 961])  # 120 and 136 tiles: on both sides of the rule that halves them
 def test_basis_around_the_tile_choice(n_g):
     _check(_case((2, 1), 2, n_g))
 
 
-@pytest.mark.parametrize("atoms", [(1,), (4, 5), (16, 17)])
+@pytest.mark.parametrize("atoms", [(1,), (4, 5), (16, 17), (24, 25)])
 def test_atom_counts_around_the_steps(atoms):
     _check(_case(atoms, 3, 90))
 
@@ -91,6 +91,11 @@ def test_radial_data_by_value_and_uploaded(types, l_max):
 @pytest.mark.parametrize("atoms,n_g", [((1,), 40), ((2,), 33), ((9, 8), 64), ((34, 2), 129)])
 def test_real_form(atoms, n_g):
     _check(_case(atoms, 3, n_g, inversion=True), real=True)
+
+
+@pytest.mark.parametrize("l_max", [0, 2, 4, 7])
+def test_real_form_row_padding(l_max):
+    _check(_case((3, 2), l_max, 70, inversion=True), real=True)
 
 
 def test_default_forward_and_batch_are_the_factored_form():

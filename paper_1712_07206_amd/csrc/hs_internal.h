@@ -266,21 +266,21 @@ struct FactAdj {
   int nseg = 0, ngb = 0;      // segments of G' and blocks of columns in the phase sums
   size_t RT = 0, ET = 0, UT = 0, partT = 0, partTau = 0;
 };
-// Residue form of the factored build.  A, B: operand streams of every 64 columns (a_len, b_len bytes each; a type's
-// part from aoff, boff); inv: reciprocal column scales, double [2][n_act][n_pad] (R, Y).
+// Residue form of the factored build.  A, B: residues of R and of Y, a_bytes and b_bytes for every 64 columns; inv:
+// reciprocal column scales, double [2][n_act][n_pad] (R, Y).
 struct FactCrt {
   int n_mod, ks;  // moduli; MFMA steps of a type's 2 N_L rows
   int n_f, n_r;   // chunks of a type's R rows and of its residues
-  int64_t A, B, inv, a_len, b_len, aoff[HSB_MAX_TYPES], boff[HSB_MAX_TYPES];
+  int64_t A, B, inv, a_bytes, b_bytes;
   double M, bound;  // product of the moduli; bound of a scaled column's 2-norm
   // y_i / m_i = h_i + l_i (mod 1), y_i = (M / m_i)^{-1} (mod m_i), |h_i| <= 1/2 on a 2^-27 grid
   double m[kCrtMaxModuli], inv_m[kCrtMaxModuli], h[kCrtMaxModuli], l[kCrtMaxModuli];
 };
 // Host: sizes (all but A, B, inv), moduli and weights for element kind ek (crt_kind).
 FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real);
-// After launch_fact_y: the streams, then H from the residues and S in FP64 (upper
+// After launch_fact_y: the residues, then H from them and S in FP64 (upper
 // triangles).
-hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
+hipError_t launch_fact_residues(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
                             hipStream_t s);
 hipError_t launch_fact_crt(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, int gr,
                            const char* ws, void* H, void* S, hipStream_t s);

@@ -165,8 +165,8 @@ size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool rea
   if (cr) {
     *cr = fact_crt(h.crt, c, crt_kind(h.precision), real);
     const size_t blocks = (size_t)ks->n_pad / 64;
-    cr->A = (int64_t)take(blocks * cr->a_len);
-    cr->B = (int64_t)take(blocks * cr->b_len);
+    cr->A = (int64_t)take(blocks * cr->a_bytes);
+    cr->B = (int64_t)take(blocks * cr->b_bytes);
     cr->inv = (int64_t)take((size_t)2 * c.n_act * ks->n_pad * sizeof(double));
   }
   return off;
@@ -937,7 +937,7 @@ int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, bool crt, con
   const int ek = crt_kind(h->precision);
   mark(h, 1, s);
   if (!rc) rc = launched(h, launch_fact_y(c, f, nullptr, 1, f.n_pad / (32 * mi), mi, real, w, s), "k_fact_y");
-  if (!rc && crt) rc = launched(h, launch_fact_pack(c, f, cr, ek, real, w, s), "k_fact_pack");
+  if (!rc && crt) rc = launched(h, launch_fact_residues(c, f, cr, ek, real, w, s), "k_fact_residues");
   mark(h, 2, s);
   if (!rc && crt)
     rc = launched(h, launch_fact_crt(c, f, cr, ek, real, h->tile_group, w, H, S, s), "k_fact_crt");

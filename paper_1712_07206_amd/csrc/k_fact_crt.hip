@@ -15,10 +15,11 @@
 // part to FP64 precision.  The v_i need no reduction modulo m_i for that.  The only approximation is
 // the rounding of the scaled columns.  R is real, so a complex product takes two products per modulus.
 //
-// Measured at N_G = 12000, 128 atoms, l_max = 10, 11 moduli: k_fact_crt 7.95 ms, of which the FP64
-// and integer matrix cores are busy 3.2 and the FP64 vector units 0.7 (they share the FP64 ones' pipe);
-// without its copies 5.9, its copies alone 4.9 (66 GB from L2).  k_fact_pack 0.26 ms.  The stacked residue
-// contraction over the 30976 rows of all atoms took 110 ms, with H off by 2e-11 of its norm against 2e-12 here.
+// Measured at N_G = 12000, 128 atoms, l_max = 10, 11 moduli: k_fact_crt 7.15 ms (7.95 with chunks of half the
+// size and the copies right behind the barrier), of which the FP64 and integer matrix cores take 3.2 and the FP64
+// vector units, which share the FP64 ones' pipe, 0.7; its copies alone 4.9 (66 GB from L2).  k_fact_residues
+// 0.18 ms.  The stacked residue contraction over the 30976 rows of all atoms took 110 ms, with H off by 2e-11 of its
+// norm against 2e-12 here.
 #include <cmath>
 
 #include "hs_internal.h"
@@ -64,60 +65,47 @@ struct ResMma<2> {
   }
 };
 
-// Operand streams.  A tile reads the stream A of its 64 rows and the stream B of its 64 columns, one after the other
-// in chunks of 24 KB (both streams' parts), per type:
-//   phases   chunks of 12 rows (1 KB a row and stream): E; B's weighted with the atoms' multiplicities (real form)
-//   R rows   chunks of 24 rows (512 bytes each): A R, B lam R
-//   residues chunks of SPC steps, [modulus][step]: A R's 4 units of 64 columns, B Y's [4][NC][64 columns] (NC: real
-//            and imaginary part)
-// Rows and steps past the ends are zero.  A's residues hold the columns of each 32 even ones first (k_fact_crt).
-// (The same pieces from arrays of whole rows, 1 KB out of every 192 at N_G = 12000: 15.2 ms against 12.4.)
-constexpr int kRowsE = 12, kRowsF = 24, kChunk = 24 * 1024;
-typedef Ring<6, kChunk> CrtRing;
+// A tile reads chunks of 48 KB, per type
+//   phases   24 rows (1 KB each): E of its 64 rows, EW of its 64 columns
+//   R rows   48 rows (512 bytes each): R of its rows, lam R of its columns
+//   residues SPC steps, [modulus][step]: of its rows R's 4 units of 64 columns, of its columns Y's
+//            [4][NC][64 columns] (NC: real and imaginary part)
+// The residues lie block-major, a stream of each 64 columns for R (A) and for Y (B), steps past the last
+// modulus zero; A holds the columns of each 32 even ones first (k_fact_crt).  (The same pieces from arrays of whole
+// rows, 1 KB out of every 192 at N_G = 12000, took 15.2 ms against 12.4.)
+constexpr int kChunk = 48 * 1024, kRowsE = kChunk / 2048, kRowsF = kChunk / 1024;
+typedef Ring<3, kChunk> CrtRing;
 template <bool REAL>
 struct Stream {
   static constexpr int NC = REAL ? 1 : 2;        // products per modulus
-  static constexpr int SPC = 24 / (4 + 4 * NC);  // steps per chunk
+  static constexpr int SPC = kChunk / 1024 / (4 + 4 * NC);  // steps per chunk
   static constexpr int a_res = SPC * 4 * 1024;   // A's bytes of a residue chunk (of the others: half)
 };
 
-// Stream A (blockIdx.z = 0) or B (1) of type blockIdx.y and the 64 columns blockIdx.x, and the reciprocal scales.
-// The scale is the largest power of two 2^f with 2^f ||x|| + sqrt(2 M) / 2 <= bound (the second term bounds the
-// norm of the rounding errors), 1 for a zero column.  Bandwidth-bound on what it writes (n_mod bytes or
-// 16-bit values per value of 8 bytes read, twice, the second time from cache).
-constexpr int kPackWaves = 16;
+// Residues of R (blockIdx.z = 0, stream A) or Y (1, B) of type blockIdx.y and the 64 columns blockIdx.x, and the
+// reciprocal scales.  The scale is the largest power of two 2^f with 2^f ||x|| + sqrt(2 M) / 2 <= bound (the second
+// term bounds the norm of the rounding errors), 1 for a zero column.  Bandwidth-bound on what it writes (n_mod
+// bytes or 16-bit values per value of 8 bytes read, twice, the second time from cache).
+constexpr int kResWaves = 16;
 template <int EK, bool REAL>
-__global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK kk, FactCrt cr,
+__global__ void __launch_bounds__(64 * kResWaves) k_fact_residues(FactCell c, FactK kk, FactCrt cr,
                                                                char* __restrict__ ws) {
   constexpr int RU = EK == 0 ? 16 : 8, EB = 16 / RU, PER = 4 / EB;
   typedef Stream<REAL> St;
-  __shared__ double part[kPackWaves][64];
+  __shared__ double part[kResWaves][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int t = blockIdx.y, G = blockIdx.x * 64 + lane;
   const bool is_b = blockIdx.z;
   const int parts = is_b ? St::NC : 1;  // values per row
   const int64_t np = kk.n_pad;
-  const int M = 2 * c.n_l, nat = c.nat[t];
-  const int n_e = (nat + kRowsE - 1) / kRowsE;
-  char* out = ws + (is_b ? cr.B + blockIdx.x * cr.b_len + cr.boff[t] : cr.A + blockIdx.x * cr.a_len + cr.aoff[t]);
-  {
-    const d2* e = (const d2*)(ws + (is_b ? kk.EW : kk.E)) + ((int64_t)blockIdx.x * c.e_rows + c.eoff[t]) * 64 + lane;
-    d2* o = (d2*)out + lane;
-    for (int k = wave; k < n_e * kRowsE; k += kPackWaves) o[k * 64] = k < nat ? e[k * 64] : d2{0.0, 0.0};
-    out += n_e * (kChunk / 2);
-  }
-  const int64_t r0 = ((int64_t)blockIdx.x * c.n_act + t) * c.Mr;
-  const double* R = (const double*)(ws + kk.R) + r0 * 64 + lane;
-  {
-    const double* r = is_b ? (const double*)(ws + kk.LR) + r0 * 64 + lane : R;
-    double* o = (double*)out + lane;
-    for (int k = wave; k < cr.n_f * kRowsF; k += kPackWaves) o[k * 64] = k < M ? r[k * 64] : 0.0;
-    out += cr.n_f * (kChunk / 2);
-  }
-  const double* x = is_b ? (const double*)(ws + kk.Y) + (r0 * 64 + lane) * parts : R;
+  const int M = 2 * c.n_l;
+  const int64_t len = (int64_t)cr.n_r * (is_b ? kChunk - St::a_res : St::a_res);  // a type's part
+  char* out = ws + (is_b ? cr.B : cr.A) + ((int64_t)blockIdx.x * c.n_act + t) * len;
+  const double* x = (const double*)(ws + (is_b ? kk.Y : kk.R)) +
+                    (((int64_t)blockIdx.x * c.n_act + t) * c.Mr * 64 + lane) * parts;
   const int ld = 64 * parts;
   double sq = 0.0;
-  for (int k = wave; k < M; k += kPackWaves)
+  for (int k = wave; k < M; k += kResWaves)
     for (int p = 0; p < parts; ++p) {
       const double v = x[k * ld + p];
       sq += v * v;
@@ -125,7 +113,7 @@ __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK
   part[wave][lane] = sq;
   __syncthreads();
   sq = 0.0;
-  for (int i = 0; i < kPackWaves; ++i) sq += part[i][lane];
+  for (int i = 0; i < kResWaves; ++i) sq += part[i][lane];
   double sc = 1.0, inv = 1.0;
   if (sq > 0.0) {
     const double q = (cr.bound - 0.5 * sqrt(2.0 * (double)M)) / sqrt(sq) * (1.0 - 0x1p-30);
@@ -137,7 +125,7 @@ __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK
   if (wave == 0) ((double*)(ws + cr.inv))[((int64_t)blockIdx.z * c.n_act + t) * np + G] = inv;
   u4* o = (u4*)out + (is_b ? lane : (lane & 32) | ((lane & 1) << 4) | ((lane & 31) >> 1));
   const int units = 4 * cr.ks;
-  for (int u = wave; u < units * parts; u += kPackWaves) {
+  for (int u = wave; u < units * parts; u += kResWaves) {
     const int unit = u / parts, p = u - unit * parts;
     double v[RU];
 #pragma unroll
@@ -155,7 +143,7 @@ __global__ void __launch_bounds__(64 * kPackWaves) k_fact_pack(FactCell c, FactK
   }
   // steps past the last modulus
   for (int u = cr.n_mod * units * parts + wave; u < cr.n_r * St::SPC * 4 * parts;
-       u += kPackWaves) o[u * 64] = u4{0u, 0u, 0u, 0u};
+       u += kResWaves) o[u * 64] = u4{0u, 0u, 0u, 0u};
 }
 
 // Upper triangles of H and S, 64 x 64 tiles on 2 x 4 waves of 32 x 16.
@@ -199,33 +187,46 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
   const int M = 2 * c.n_l, steps = cr.n_mod * cr.ks;
   CrtRing ring{lds, 0};
   for (int t = 0; t < c.n_act; ++t) ring.left += (c.nat[t] + kRowsE - 1) / kRowsE + cr.n_f + cr.n_r;
-  // next chunk to issue: its parts of the streams, chunks until the type's residues and the next type
-  const char* pa = ws + cr.A + bi * cr.a_len;
-  const char* pb = ws + cr.B + bj * cr.b_len;
-  int it = 0, to_res = (c.nat[0] + kRowsE - 1) / kRowsE + cr.n_f, to_type = cr.n_r;
+  // The next chunk to issue: type, part (0 phases, 1 R rows, 2 residues), chunks left of the part, sources.
+  int it = 0, part = 0, n_left = 0;
+  const char *pa = nullptr, *pb = nullptr;
+  auto enter = [&]() {
+    const int64_t ta = (int64_t)bi * c.n_act + it, tb = (int64_t)bj * c.n_act + it;
+    if (part == 0) {
+      n_left = (c.nat[it] + kRowsE - 1) / kRowsE;
+      pa = ws + kk.E + ((int64_t)bi * c.e_rows + c.eoff[it]) * 1024;
+      pb = ws + kk.EW + ((int64_t)bj * c.e_rows + c.eoff[it]) * 1024;
+    } else if (part == 1) {
+      n_left = cr.n_f;
+      pa = ws + kk.R + ta * c.Mr * 512;
+      pb = ws + kk.LR + tb * c.Mr * 512;
+    } else {
+      n_left = cr.n_r;
+      pa = ws + cr.A + ta * cr.n_r * St::a_res;
+      pb = ws + cr.B + tb * cr.n_r * (kChunk - St::a_res);
+    }
+  };
   auto issue = [&]() {
     if (it >= c.n_act) return;
     char* st = ring.stage(wave);
-    const int na = to_res > 0 ? kChunk / 2 : St::a_res;
+    const int na = part == 2 ? St::a_res : kChunk / 2;
 #pragma unroll
     for (int i = 0; i < CrtRing::copies; ++i) {
       const int o = (wave + 8 * i) * 1024;
-      __builtin_amdgcn_global_load_lds((const void*)((o < na ? pa : pb - na) + o + lane * 16), (lds_ptr)(st + i * 8192), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)((o < na ? pa : pb - na) + o + lane * 16), (lds_ptr)(st + i * 8192),
+                                       16, 0, 0);
     }
     pa += na;
     pb += kChunk - na;
-    if (to_res > 0) {
-      --to_res;
-    } else if (--to_type == 0) {
-      to_type = cr.n_r;
-      if (++it < c.n_act) to_res = (c.nat[it] + kRowsE - 1) / kRowsE + cr.n_f;
+    if (--n_left == 0) {
+      if (++part == 3) {
+        part = 0;
+        ++it;
+      }
+      if (it < c.n_act) enter();
     }
   };
-  auto arrive = [&]() -> const char* {
-    const char* st = ring.arrive();
-    issue();
-    return st;
-  };
+  enter();
   for (int i = 0; i < CrtRing::stages - 1; ++i) issue();
 
   const d4 z = d4{0.0, 0.0, 0.0, 0.0};
@@ -236,34 +237,28 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
   // this order, even ones first) and, rows dealt to the lanes in this order, for the FP64 ones.
   const int arow = wr * 32 + 2 * ((lr >> 2) + 4 * (lr & 3)), bcol = wc * 16 + lr;
   for (int t = 0; t < c.n_act; ++t) {
-    const int nt = c.nat[t];
     d4 pR[2], pI[2];
     {
       d4 p1[2], p2[2], p3[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) p1[i] = p2[i] = p3[i] = z;
-      for (int k0 = 0; k0 < nt; k0 += kRowsE) {
-        const char* st = arrive();
-#pragma unroll
-        for (int s = 0; s < kRowsE / 4; ++s) {
-          if (active && k0 + 4 * s < nt) {  // uniform
+      clear(p1);
+      clear(p2);
+      clear(p3);
+      struct Phases { d2 a[2], b; };
+      section<kRowsE / 4, 2>(
+          ring, (c.nat[t] + 3) / 4, active, issue,
+          [&](const char* st, int s) {
             const d2* A = (const d2*)(st + (4 * s + lk) * 1024) + arow;
-            const d2 b = ((const d2*)(st + (kRowsE + 4 * s + lk) * 1024))[bcol];
-            const double bs = b.x + b.y;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-              const d2 a = A[i];
-              p1[i] = MFMA(a.x, b.x, p1[i]);
-              if constexpr (REAL) {
-                p1[i] = MFMA(a.y, b.y, p1[i]);
-              } else {
-                p2[i] = MFMA(a.y, b.y, p2[i]);
-                p3[i] = MFMA(a.x - a.y, bs, p3[i]);
-              }
+            return Phases{{A[0], A[1]}, ((const d2*)(st + (kRowsE + 4 * s + lk) * 1024))[bcol]};
+          },
+          [&](const Phases& x, int i) {
+            p1[i] = MFMA(x.a[i].x, x.b.x, p1[i]);
+            if constexpr (REAL) {
+              p1[i] = MFMA(x.a[i].y, x.b.y, p1[i]);
+            } else {
+              p2[i] = MFMA(x.a[i].y, x.b.y, p2[i]);
+              p3[i] = MFMA(x.a[i].x - x.a[i].y, x.b.x + x.b.y, p3[i]);
             }
-          }
-        }
-      }
+          });
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         pR[i] = REAL ? p1[i] : p1[i] + p2[i];
@@ -272,26 +267,15 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
     }
     {
       d4 F[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) F[i] = z;
-      for (int k0 = 0; k0 < M; k0 += kRowsF) {
-        const char* st = arrive();
-        if (!active) continue;
-        d2 a[kRowsF / 4];
-        double b[kRowsF / 4];
-#pragma unroll
-        for (int s = 0; s < kRowsF / 4; ++s) {
-          a[s] = *(const d2*)((const double*)(st + (4 * s + lk) * 512) + arow);
-          b[s] = ((const double*)(st + 12 * 1024 + (4 * s + lk) * 512))[bcol];
-        }
-#pragma unroll
-        for (int s = 0; s < kRowsF / 4; ++s) {
-          if (k0 + 4 * s < M) {  // uniform
-#pragma unroll
-            for (int i = 0; i < 2; ++i) F[i] = MFMA(a[s][i], b[s], F[i]);
-          }
-        }
-      }
+      clear(F);
+      struct Rows { d2 a; double b; };
+      section<kRowsF / 4, 2>(
+          ring, (M + 3) / 4, active, issue,
+          [&](const char* st, int s) {
+            return Rows{*(const d2*)((const double*)(st + (4 * s + lk) * 512) + arow),
+                        ((const double*)(st + kChunk / 2 + (4 * s + lk) * 512))[bcol]};
+          },
+          [&](const Rows& x, int i) { F[i] = MFMA(x.a[i], x.b, F[i]); });
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         sR[i] += pR[i] * F[i];
@@ -308,46 +292,43 @@ __global__ void __launch_bounds__(512, 2) k_fact_crt(FactCell c, FactK kk, FactC
         acc[p][i] = typename Mma::T{0, 0, 0, 0};
       }
     int mod = 0, k = 0;
-    for (int s0 = 0; s0 < steps; s0 += SPC) {
-      const char* st = arrive();
-      if (!active) continue;
-      u4 a[SPC][2], b[SPC][NC];
+    double h = cr.h[0], l = cr.l[0];  // of the modulus being summed
+    struct Residues { u4 a[2], b[NC]; };
+    section<SPC, 2>(
+        ring, steps, active, issue,
+        [&](const char* st, int s) {
+          const u4* A = (const u4*)(st + (s * 4 + lk) * 1024) + wr * 32 + lr;
+          const u4* B = (const u4*)(st + St::a_res + (s * 4 + lk) * NC * 1024) + bcol;
+          Residues x;
 #pragma unroll
-      for (int s = 0; s < SPC; ++s) {
-        const u4* A = (const u4*)(st + (s * 4 + lk) * 1024) + wr * 32 + lr;
-        const u4* B = (const u4*)(st + St::a_res + (s * 4 + lk) * NC * 1024) + bcol;
+          for (int i = 0; i < 2; ++i) x.a[i] = A[16 * i];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) a[s][i] = A[16 * i];
+          for (int p = 0; p < NC; ++p) x.b[p] = B[64 * p];
+          return x;
+        },
+        [&](const Residues& x, int i) {
 #pragma unroll
-        for (int p = 0; p < NC; ++p) b[s][p] = B[64 * p];
-      }
-#pragma unroll
-      for (int s = 0; s < SPC; ++s) {
-        if (s0 + s < steps) {  // uniform
-#pragma unroll
-          for (int p = 0; p < NC; ++p)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) acc[p][i] = Mma::mma(a[s][i], b[s][p], acc[p][i]);
-          if (++k == cr.ks) {
+          for (int p = 0; p < NC; ++p) acc[p][i] = Mma::mma(x.a[i], x.b[p], acc[p][i]);
+          if (i == 1 && ++k == cr.ks) {  // uniform
             k = 0;
-            const double h = cr.h[mod], l = cr.l[mod];
-            ++mod;
 #pragma unroll
             for (int p = 0; p < NC; ++p)
 #pragma unroll
-              for (int i = 0; i < 2; ++i) {
+              for (int e = 0; e < 2; ++e) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                  const double v = (double)acc[p][i][q];
-                  hs[p][i][q] = fma(v, h, hs[p][i][q]);
-                  ls[p][i][q] = fma(v, l, ls[p][i][q]);
+                  const double v = (double)acc[p][e][q];
+                  hs[p][e][q] = fma(v, h, hs[p][e][q]);
+                  ls[p][e][q] = fma(v, l, ls[p][e][q]);
                 }
-                acc[p][i] = typename Mma::T{0, 0, 0, 0};
+                acc[p][e] = typename Mma::T{0, 0, 0, 0};
               }
+            if (++mod < cr.n_mod) {
+              h = cr.h[mod];
+              l = cr.l[mod];
+            }
           }
-        }
-      }
-    }
+        });
     const double ic = inv_col[t * 64 + bcol];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -397,14 +378,8 @@ FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real) {
   r.ks = (M + rows - 1) / rows;
   r.n_f = (M + kRowsF - 1) / kRowsF;
   r.n_r = (r.n_mod * r.ks + spc - 1) / spc;
-  for (int t = 0; t < c.n_act; ++t) {
-    r.aoff[t] = r.a_len;
-    r.boff[t] = r.b_len;
-    const int64_t half = (int64_t)((c.nat[t] + kRowsE - 1) / kRowsE + r.n_f) * (kChunk / 2);
-    const int64_t a = real ? Stream<true>::a_res : Stream<false>::a_res;
-    r.a_len += half + r.n_r * a;
-    r.b_len += half + r.n_r * (kChunk - a);
-  }
+  r.a_bytes = (int64_t)c.n_act * r.n_r * (real ? Stream<true>::a_res : Stream<false>::a_res);
+  r.b_bytes = (int64_t)c.n_act * r.n_r * kChunk - r.a_bytes;
   r.M = cc.M;
   r.bound = cc.bound;
   for (int i = 0; i < cc.n_mod; ++i) {
@@ -418,13 +393,13 @@ FactCrt fact_crt(const CrtConsts& cc, const FactCell& c, int ek, bool real) {
   return r;
 }
 
-hipError_t launch_fact_pack(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
+hipError_t launch_fact_residues(const FactCell& c, const FactK& kk, const FactCrt& cr, int ek, bool real, char* ws,
                             hipStream_t s) {
-  const dim3 grid(kk.n_pad / 64, c.n_act, 2), block(64 * kPackWaves);
+  const dim3 grid(kk.n_pad / 64, c.n_act, 2), block(64 * kResWaves);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, c, kk, cr, ws); };
-  if (ek == 0) real ? go(k_fact_pack<0, true>) : go(k_fact_pack<0, false>);
-  else if (ek == 1) real ? go(k_fact_pack<1, true>) : go(k_fact_pack<1, false>);
-  else real ? go(k_fact_pack<2, true>) : go(k_fact_pack<2, false>);
+  if (ek == 0) real ? go(k_fact_residues<0, true>) : go(k_fact_residues<0, false>);
+  else if (ek == 1) real ? go(k_fact_residues<1, true>) : go(k_fact_residues<1, false>);
+  else real ? go(k_fact_residues<2, true>) : go(k_fact_residues<2, false>);
   return hipGetLastError();
 }
 

@@ -76,6 +76,56 @@ struct Ring {
   }
 };
 
+// A section (say, a type's rows) of `steps` steps of the matrix cores, PER of them a chunk: read(stage, s) gives a step's
+// operands, mac(x, i) takes the products of block i of MI.  The next step's operands are read ahead, over
+// the barrier too, behind the first block's products (the wait for a step's own operands is then not one for
+// theirs too), and the copies of another chunk (issue) go out behind the first step's: right behind the
+// barrier, where all waves are, they and their addresses leave the matrix cores idle.
+template <int PER, int MI, class Ring, class Issue, class Read, class Mac>
+__device__ __forceinline__ void section(Ring& ring, int steps, bool active, Issue issue, Read read, Mac mac) {
+  const int chunks = (steps + PER - 1) / PER;
+  if (!active) {  // uniform
+    for (int i = 0; i < chunks; ++i) {
+      ring.arrive();
+      issue();
+    }
+    return;
+  }
+  auto step = [&](const auto& x, const char* st, int next) {
+    if constexpr (MI == 2) {
+      mac(x, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    auto y = read(st, next);
+    __builtin_amdgcn_sched_barrier(0);
+    mac(x, MI - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    return y;
+  };
+  const char* st = ring.arrive();
+  auto x = read(st, 0);
+  for (int i = 1; i < chunks; ++i) {
+#pragma unroll
+    for (int s = 0; s < PER; ++s) {
+      if (s == PER - 1) st = ring.arrive();
+      x = step(x, st, s == PER - 1 ? 0 : s + 1);
+      if (s == 0) issue();
+    }
+  }
+  const int rest = steps - (chunks - 1) * PER;
+  mac(x, 0);
+  if constexpr (MI == 2) mac(x, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue();
+#pragma unroll
+  for (int s = 1; s < PER; ++s)
+    if (s < rest) {
+      x = read(st, s);
+      mac(x, 0);
+      if constexpr (MI == 2) mac(x, 1);
+    }
+}
+
 // One tile of 32 MI (G') x 64 (G) of the type-factored products on 2 x 4 waves of 16 MI x 16: MI = 2 the 64 x 64
 // blocks of the arrays, MI = 1 the upper or lower half of one.  A lane holds MI neighbouring rows, one for each of
 // its blocks: block i covers the rows of index i modulo MI.  Two waves per SIMD: at MI = 2 nine sums and operands
@@ -105,7 +155,7 @@ struct TypedTile {
   int adj, adj3;
 
   __device__ __forceinline__ TypedTile(const FactCell& cell, const FactK& k, const char* base, char* lds, int block_i,
-                                       int which_half, int block_j, int t0, int t1)
+                           int which_half, int block_j, int t0, int t1)
       : c(cell), kk(k), ws(base), bi(block_i), half(which_half), bj(block_j), t_end(t1), it(t0) {
     const int lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -197,57 +247,6 @@ struct TypedTile {
       }
     }
   }
-  // A section (a type's phases, or its rows) of `steps` 4-row steps, PER of them a chunk: read(stage, s) gives a
-  // step's operands, mac(x) takes the products.  The next step's operands are read ahead of a step's
-  // products, over the barrier too, and the copies of another chunk go out behind the first
-  // step's: right behind the barrier, where all waves are, they and their addresses leave the matrix cores
-  // idle.
-  template <int PER, class Read, class Mac>
-  __device__ __forceinline__ void section(int steps, bool active, Read read, Mac mac) {
-    const int chunks = (steps + PER - 1) / PER;
-    if (!active) {  // uniform
-      for (int i = 0; i < chunks; ++i) {
-        ring.arrive();
-        issue();
-      }
-      return;
-    }
-    // a step's products with the next one's reads behind the first block's (the wait for a step's own
-    // operands is then not one for theirs too)
-    auto step = [&](const auto& x, const char* st, int next) {
-      if constexpr (MI == 2) {
-        mac(x, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      auto y = read(st, next);
-      __builtin_amdgcn_sched_barrier(0);
-      mac(x, MI - 1);
-      __builtin_amdgcn_sched_barrier(0);
-      return y;
-    };
-    const char* st = ring.arrive();
-    auto x = read(st, 0);
-    for (int i = 1; i < chunks; ++i) {
-#pragma unroll
-      for (int s = 0; s < PER; ++s) {
-        if (s == PER - 1) st = ring.arrive();
-        x = step(x, st, s == PER - 1 ? 0 : s + 1);
-        if (s == 0) issue();
-      }
-    }
-    const int rest = steps - (chunks - 1) * PER;
-    mac(x, 0);
-    if constexpr (MI == 2) mac(x, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    issue();
-#pragma unroll
-    for (int s = 1; s < PER; ++s)
-      if (s < rest) {
-        x = read(st, s);
-        mac(x, 0);
-        if constexpr (MI == 2) mac(x, 1);
-      }
-  }
   struct Phases { d2 a[MI], b; };
   __device__ __forceinline__ Phases read_phases(const char* st, int s) const {
     Phases x;
@@ -265,16 +264,17 @@ struct TypedTile {
     clear(p1);
     clear(p2);
     clear(p3);
-    section<RE / 4>((c.nat[t] + 3) / 4, active, [&](const char* st, int s) { return read_phases(st, s); },
-                    [&](const Phases& x, int i) {
-                      p1[i] = MFMA(x.a[i].x, x.b.x, p1[i]);
-                      if constexpr (REAL) {
-                        p1[i] = MFMA(x.a[i].y, x.b.y, p1[i]);
-                      } else {
-                        p2[i] = MFMA(x.a[i].y, x.b.y, p2[i]);
-                        p3[i] = MFMA(x.a[i].x - x.a[i].y, x.b.x + x.b.y, p3[i]);
-                      }
-                    });
+    section<RE / 4, MI>(
+        ring, (c.nat[t] + 3) / 4, active, [&] { issue(); }, [&](const char* st, int s) { return read_phases(st, s); },
+        [&](const Phases& x, int i) {
+          p1[i] = MFMA(x.a[i].x, x.b.x, p1[i]);
+          if constexpr (REAL) {
+            p1[i] = MFMA(x.a[i].y, x.b.y, p1[i]);
+          } else {
+            p2[i] = MFMA(x.a[i].y, x.b.y, p2[i]);
+            p3[i] = MFMA(x.a[i].x - x.a[i].y, x.b.x + x.b.y, p3[i]);
+          }
+        });
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       pR[i] = REAL ? p1[i] : p1[i] + p2[i];
@@ -295,17 +295,18 @@ struct TypedTile {
     clear(m1);
     if constexpr (!REAL) clear(m2);
     clear(F);
-    section<RM / 4>((2 * c.n_l + 3) / 4, active, [&](const char* st, int s) { return read_rows(st, s); },
-                    [&](const Rows& x, int i) {
-                      const double a = DVec<MI>::get(x.a, i);
-                      if constexpr (REAL) {
-                        m1[i] = MFMA(a, x.yr, m1[i]);
-                      } else {
-                        m1[i] = MFMA(a, x.y.x, m1[i]);
-                        m2[i] = MFMA(a, x.y.y, m2[i]);
-                      }
-                      F[i] = MFMA(a, x.l, F[i]);
-                    });
+    section<RM / 4, MI>(
+        ring, (2 * c.n_l + 3) / 4, active, [&] { issue(); }, [&](const char* st, int s) { return read_rows(st, s); },
+        [&](const Rows& x, int i) {
+          const double a = DVec<MI>::get(x.a, i);
+          if constexpr (REAL) {
+            m1[i] = MFMA(a, x.yr, m1[i]);
+          } else {
+            m1[i] = MFMA(a, x.y.x, m1[i]);
+            m2[i] = MFMA(a, x.y.y, m2[i]);
+          }
+          F[i] = MFMA(a, x.l, F[i]);
+        });
   }
 };
 

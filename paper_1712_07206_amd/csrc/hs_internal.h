@@ -258,12 +258,15 @@ struct FactRep {
   int atom, pad;
 };
 // The adjoint's arrays (byte offsets) and splits; Mt = 0: none of it.  RT: R transposed, double
-// [n_act][n_pad][Mt]; ET: the phases transposed, complex [n_pad][et_ld]; UT: complex [types of one
-// pass][n_pad][Mt]; partT: complex [n_act][ngt][Mt][Mt]; partTau: double [nseg][ngb][et_ld][3].
+// [n_act][Mt / 64][n_pad][64]; ET: the phases transposed, complex [blocks of 32 atoms, type t's from etb[t]][n_pad][32];
+// UT: complex [types of one pass][Mt / 64][n_pad][64]; partT: complex [n_act][ngt][Mt][Mt]; partTau: double
+// [nseg][ngb][e_rows][3].
 struct FactAdj {
-  int Mt = 0, et_ld = 0;      // 2 N_L rounded up to 32; phase rows
-  int ngt = 0;                // segments of G in R Z R^T
-  int nseg = 0, ngb = 0;      // segments of G' and blocks of columns in the phase sums
+  int Mt = 0;         // 2 N_L rounded up to 64
+  int ngt = 0;        // segments of G in R Z R^T
+  int nseg = 0;       // segments of G' in the phase sums
+  int ngb = 0;        // 16-column blocks of the phase sums
+  int etb[HSB_MAX_TYPES] = {};
   size_t RT = 0, ET = 0, UT = 0, partT = 0, partTau = 0;
 };
 // Residue form of the factored build.  A, B: residues of R and of Y, a_bytes and b_bytes for every 64 columns; inv:
@@ -315,11 +318,11 @@ int eig_workspace(void* handle, int n, bool vectors, size_t* bytes, std::string&
 // a[i] = conj(a[i]) for i < count.
 hipError_t launch_conj(double2* a, int64_t count, hipStream_t s);
 
-// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1; mi: 16-row blocks per wave side) ----
-// Z, Q: complex [nt][n_pad][n_pad].
+// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1) ----
+// Z, Q: complex, block-major [nt][n_pad / 64][n_pad][64].
 hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s);
-hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, int mi, char* ws,
+hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
                          const double2* Z, const double2* Q, hipStream_t s);
 hipError_t launch_adj_gt(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
                          hipStream_t s);

@@ -189,7 +189,7 @@ struct AdjointPlan {
   FactK f{};
   FactAdj ad;
   size_t consts = 0, Z = 0, Q = 0, end = 0;
-  int mi = 2, pass = 1;
+  int pass = 1;
 };
 
 AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
@@ -205,20 +205,23 @@ AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
   };
   const int64_t np = p.f.n_pad;
   FactAdj& ad = p.ad;
-  ad.Mt = (int)round_up(2 * h.n_l, 32);
-  ad.et_ld = c.e_rows;
-  // waves for twice the SIMDs, where the sizes give them
-  const int64_t waves = 8 * (int64_t)std::max(1, h.num_cus);
+  ad.Mt = (int)round_up(2 * h.n_l, 64);
+  int nab = 0;
+  for (int t = 0; t < c.n_act; ++t) {
+    ad.etb[t] = nab;
+    nab += (c.nat[t] + 31) / 32;
+  }
+  const int cus = std::max(1, h.num_cus);
+  // R Z R^T: waves for twice the SIMDs, where the sizes give them
   const int64_t gt_tiles = (int64_t)(ad.Mt / 32) * (ad.Mt / 32) * c.n_act;
-  ad.ngt = (int)std::min<int64_t>(np / 64, std::max<int64_t>(1, waves / gt_tiles));
-  int64_t c_tiles = 0;
-  for (int t = 0; t < c.n_act; ++t) c_tiles += (c.nat[t] + 15) / 16;
-  ad.ngb = (int)(np / (16 * p.mi));
-  ad.nseg = (int)std::min<int64_t>(np / 64, std::max<int64_t>(1, waves / (c_tiles * ad.ngb)));
+  ad.ngt = (int)std::min<int64_t>(np / 64, std::max<int64_t>(1, 8 * (int64_t)cus / gt_tiles));
+  // phase sums: workgroups for two rounds of the compute units
+  ad.nseg = (int)std::min<int64_t>(np / 64, (2 * (int64_t)cus + np / 64 * nab - 1) / (np / 64 * nab));
+  ad.ngb = (int)(np / 16);
   ad.RT = take((size_t)c.n_act * np * ad.Mt * sizeof(double));
-  ad.ET = take((size_t)np * ad.et_ld * sizeof(double2));
+  ad.ET = take((size_t)nab * np * 32 * sizeof(double2));
   ad.partT = take((size_t)c.n_act * ad.ngt * ad.Mt * ad.Mt * sizeof(double2));
-  ad.partTau = take((size_t)ad.nseg * ad.ngb * ad.et_ld * 3 * sizeof(double));
+  ad.partTau = take((size_t)ad.nseg * ad.ngb * c.e_rows * 3 * sizeof(double));
   const size_t per_type = (2 * (size_t)np * np + (size_t)np * ad.Mt) * sizeof(double2);
   const size_t stacked = (5 * (size_t)stacked_pad(2 * h.n_atoms * h.n_l) * np + 2 * (size_t)np * np) * sizeof(double2);
   p.pass = c.n_act;
@@ -1236,7 +1239,7 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
     const int nt = std::min(p.pass, c.n_act - t0);
     rc = launched(h, launch_adj_zq(c, p.f, t0, nt, h->num_cus, (const double2*)gH, (const double2*)gS, w, Z, Q, s),
                   "k_adj_zq");
-    if (!rc) rc = launched(h, launch_adj_uc(c, p.f, p.ad, t0, nt, p.mi, w, Z, Q, s), "k_adj_uc");
+    if (!rc) rc = launched(h, launch_adj_uc(c, p.f, p.ad, t0, nt, w, Z, Q, s), "k_adj_uc");
     if (!rc) rc = launched(h, launch_adj_gt(c, p.f, p.ad, t0, nt, w, s), "k_adj_gt");
   }
   if (rc) return rc;

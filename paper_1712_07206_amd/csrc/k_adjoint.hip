@@ -17,76 +17,94 @@
 //   k_adj_gt      R Z R^T in segments of G
 //   k_adj_reduce  the segments' sums in order, turned back to complex harmonics; grad tau likewise
 //
-// All on v_mfma_f64_16x16x4f64; k_adj_uc and k_adj_gt read their operands straight into registers, one
-// chunk ahead, and the transposed copies of R and E (k_fact_tables) keep every operand contiguous along
-// the MFMA's row or column index.  Deterministic: fixed orders, no atomics.
+// All on v_mfma_f64_16x16x4f64, the first two through an LDS ring (wave_tile.h); Z, Q, R Z and the
+// transposed copies of R and E (k_fact_tables) are block-major, so that chunks are contiguous runs.
+// Deterministic: fixed orders, no atomics.
+// At N_G = 6000, 64 atoms in two types, l_max = 10 (4.0 ms): k_adj_zq 2.4 ms, 68 % of it the matrix cores' time, the rest
+// the 2.3 GB of Z and Q it writes, the reads of gH and gS and the ring's waits (2.6 ms with one type per workgroup and
+// rows of n_pad); k_adj_uc 1.6 ms, 72 % (the same with operands straight in registers; 67 and 61 us at N_G = 801 in
+// 3 types); k_adj_gt 0.07 ms.
+#include <type_traits>
+
 #include "harmonics.h"
 #include "hs_internal.h"
+#include "tiles.h"
 #include "wave_tile.h"
 
 namespace hsb {
 
 namespace {
 
-// Z_t and Q_t (zeros outside n x n, up to n_pad): 64 x 64 tiles of the square (MI = 2) or their halves (MI = 1,
-// interleaved in blockIdx.y), types over z.
+// Z_t and Q_t (zeros outside n x n, up to n_pad), block-major: [type][64 columns][n_pad rows][64]; 64 x 64 tiles of the
+// square (MI = 2) or their halves (MI = 1, interleaved in blockIdx.y), `per` types each.  Writes 32 bytes per type
+// and element.
 template <int MI>
-__global__ void __launch_bounds__(512, 2) k_adj_zq(FactCell c, FactK kk, int t0, const d2* __restrict__ gH,
+__global__ void __launch_bounds__(512, 2) k_adj_zq(FactCell c, FactK kk, int t0, int per, const d2* __restrict__ gH,
                                                    const d2* __restrict__ gS, const char* __restrict__ ws,
                                                    d2* __restrict__ Z, d2* __restrict__ Q) {
   constexpr int PARTS = 2 / MI;
   __shared__ __align__(16) char lds[TypedTile<MI, false>::lds_bytes];
   const int n = kk.n;
   const int64_t n_pad = kk.n_pad;
-  const int t = t0 + blockIdx.z;
-  TypedTile<MI, false> tile(c, kk, ws, lds, blockIdx.y / PARTS, blockIdx.y % PARTS, blockIdx.x, t, t + 1);
+  const int first = blockIdx.z * per;
+  TypedTile<MI, false> tile(c, kk, ws, lds, blockIdx.y / PARTS, blockIdx.y % PARTS, blockIdx.x, t0 + first,
+                            t0 + first + per);
   const bool active = tile.row0() < n && tile.col0() < n;
   const int col = tile.col();
-  d2* z = Z + (int64_t)blockIdx.z * n_pad * n_pad + col;
-  d2* qq = Q + (int64_t)blockIdx.z * n_pad * n_pad + col;
-  d4 pR[MI], pI[MI], m1[MI], m2[MI], F[MI];
-  tile.phase_sums(t, active, pR, pI);
-  tile.row_sums(active, m1, m2, F);
+  d2 h[MI][4], s[MI][4];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = tile.row(i, q);
-      d2 vz = d2{0.0, 0.0}, vq = d2{0.0, 0.0};  // (the sums of pad columns may hold anything)
+      h[i][q] = s[i][q] = d2{0.0, 0.0};
       if (r < n && col < n) {
-        const d2 h = gH[(int64_t)r * n + col], s = gS[(int64_t)r * n + col];
-        const double a = m1[i][q], b = m2[i][q], d = F[i][q], pr = pR[i][q], pi = pI[i][q];
-        vz = d2{h.x * pr + h.y * pi, h.y * pr - h.x * pi};
-        vq = d2{h.x * a + h.y * b + s.x * d, h.x * b - h.y * a - s.y * d};
+        h[i][q] = gH[(int64_t)r * n + col];
+        s[i][q] = gS[(int64_t)r * n + col];
       }
-      z[(int64_t)r * n_pad] = vz;
-      qq[(int64_t)r * n_pad] = vq;
     }
+  for (int t = first; t < first + per; ++t) {
+    const int64_t o = ((int64_t)t * (n_pad / 64) + blockIdx.x) * n_pad * 64 + col % 64;
+    d4 pR[MI], pI[MI], m1[MI], m2[MI], F[MI];
+    tile.phase_sums(t0 + t, active, pR, pI);
+    tile.row_sums(active, m1, m2, F);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = tile.row(i, q);
+        d2 vz = d2{0.0, 0.0}, vq = d2{0.0, 0.0};  // (the sums of pad columns may hold anything)
+        if (r < n && col < n) {
+          const d2 gh = h[i][q], gs = s[i][q];
+          const double a = m1[i][q], b = m2[i][q], d = F[i][q], pr = pR[i][q], pi = pI[i][q];
+          vz = d2{gh.x * pr + gh.y * pi, gh.y * pr - gh.x * pi};
+          vq = d2{gh.x * a + gh.y * b + gs.x * d, gh.x * b - gh.y * a - gs.y * d};
+        }
+        Z[o + (int64_t)r * 64] = vz;
+        Q[o + (int64_t)r * 64] = vq;
+      }
+  }
 }
 
-// Complex A [k][row], real B [k][col]: re, im += sum over k in [4 k0, 4 k1) (4-row steps), both
-// operands with their leading dimensions, in chunks of KC steps (k1 - k0 a multiple of KC).
+// Complex A [k][64 rows], real B [k][64 columns]: re, im += sum over k in [4 k0, 4 k1) (4-row steps), in chunks of KC
+// steps (k1 - k0 a multiple of KC).
 template <int MI, int NJ, int KC>
-__device__ __forceinline__ void product_cr(const d2* __restrict__ A, int64_t ldA, const double* __restrict__ B,
-                                           int64_t ldB, int k0, int k1, d4 (&re)[MI][NJ], d4 (&im)[MI][NJ]) {
+__device__ __forceinline__ void product_cr(const d2* __restrict__ A, const double* __restrict__ B, int k0, int k1,
+                                           d4 (&re)[MI][NJ], d4 (&im)[MI][NJ]) {
   typedef typename DVec<NJ>::T VB;
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-  const d2* ap = A + (int64_t)lk * ldA + MI * lr;
-  const double* bp = B + (int64_t)lk * ldB + NJ * lr;
+  const d2* ap = A + lk * 64 + MI * lr;
+  const double* bp = B + lk * 64 + NJ * lr;
   struct Chunk { d2 a[KC][MI]; VB b[KC]; };
   auto load = [&](int s, Chunk& x) {
 #pragma unroll
     for (int q = 0; q < KC; ++q) {
       const int64_t k = (int64_t)(s + q) * 4;
 #pragma unroll
-      for (int i = 0; i < MI; ++i) x.a[q][i] = ap[k * ldA + i];
-      x.b[q] = *(const VB*)(bp + k * ldB);
+      for (int i = 0; i < MI; ++i) x.a[q][i] = ap[k * 64 + i];
+      x.b[q] = *(const VB*)(bp + k * 64);
     }
   };
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) re[i][j] = im[i][j] = d4{0.0, 0.0, 0.0, 0.0};
   if (k0 >= k1) return;
   Chunk x;
   load(k0, x);
@@ -107,101 +125,159 @@ __device__ __forceinline__ void product_cr(const d2* __restrict__ A, int64_t ldA
   }
 }
 
-// Workgroups blockIdx.x < nu: tiles of UT[G][k] = sum_G' Z[G'][G] RT[G'][k] (2 x 2 waves, rows G).
-// Past them: the phase sums.  One wave per (16 MI columns G, 16 atoms, segment of G'):
+// Workgroups blockIdx.x < nu: 64 x 64 tiles of UT[G][k] = sum_G' Z[G'][G] RT[G'][k], waves of 32 x 16; nu2 more: the
+// last, partly empty ones in k.  With one or two blocks of 16 k the waves of one column of blocks take every fourth
+// or second step, and their sums are added in the end, so that such a tile takes a quarter or half of the time.
+// Past them: the phase sums of 64 columns G and 32 atoms over a segment of G', waves of 16 x 16:
 // D[G][a] = sum_G' Q[G'][G] conj(ET[G'][a]) (three real products: P1 = q_r e_r, P2 = q_i e_i,
 // P3 = (q_r + q_i)(e_r - e_i), Re = P1 + P2, Im = P3 - P1 + P2), then sum_G K_G Im(E_a(G) D[G][a])
-// over the tile's columns into part[seg][column block][phase row][3].
-template <int MI, int KC>
-__global__ void __launch_bounds__(256, 2) k_adj_uc(FactCell c, FactK kk, FactAdj ad, int t0, int nu, int nab,
+// over the wave's columns into part[seg][16 columns][phase row][3].
+// Types over the slowest index, so the largest tiles come first and the smaller fill up the end.
+// Operands through an LDS ring in chunks of 32 G' (32 KB of Z or Q, 16 KB of RT or ET, each one run); the tiles of one
+// 64 G on one XCD, which then reads that part of Z from memory once.
+__global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj ad, int t0, int nu, int nu2, int nab,
                                                    const char* __restrict__ ws, const d2* __restrict__ Z,
                                                    const d2* __restrict__ Q) {
-  const int64_t n_pad = kk.n_pad;
-  const int t = t0 + blockIdx.y;
+  typedef Ring<3, 48 * 1024> R;
+  __shared__ __align__(16) char lds[R::bytes];
+  const int64_t np = kk.n_pad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int steps = kk.n_pad / 4;
-  if ((int)blockIdx.x < nu) {
-    const int nkb = (ad.Mt + 32 * MI - 1) / (32 * MI);
-    const int row0 = blockIdx.x / nkb * 32 * MI + (wave >> 1) * 16 * MI;
-    const int col0 = blockIdx.x % nkb * 32 * MI + (wave & 1) * 16 * MI;
-    if (row0 >= kk.n_pad || col0 >= ad.Mt) return;
-    d4 re[MI][MI], im[MI][MI];
-    product_cr<MI, MI, KC>(Z + (int64_t)blockIdx.y * n_pad * n_pad + row0, n_pad,
-                           (const double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + col0, ad.Mt, 0, steps, re, im);
-    d2* U = (d2*)(ws + ad.UT) + (int64_t)blockIdx.y * n_pad * ad.Mt;
+  const bool is_u = (int)blockIdx.x < nu + nu2;
+  const int first = (int)blockIdx.x < nu ? 0 : is_u ? nu : nu + nu2;
+  const int num = (int)blockIdx.x < nu ? nu : is_u ? nu2 : (int)gridDim.x - nu - nu2;
+  int start, len;
+  xcd_range((blockIdx.x - first) % kXcds, num, start, len);
+  const int w = start + (blockIdx.x - first) / kXcds;
+  // type (slowest), 64 columns G, segment, block of k or of atoms
+  const int full = c.n_l / 32;  // full 64-wide blocks of the 2 N_L k
+  const int per = !is_u ? nab : (int)blockIdx.x < nu ? full : 1, segs = is_u ? 1 : ad.nseg;
+  const int blk = (int)blockIdx.x >= nu && is_u ? full : w % per;
+  const int seg = w / per % segs, gb = w / per / segs % (kk.n_pad / 64), y = w / per / segs / (kk.n_pad / 64);
+  const int t = t0 + y;
+  if (!is_u && blk * 32 >= c.nat[t]) return;
+  const int nch = kk.n_pad / 32;
+  const int c0 = is_u ? 0 : (int)((int64_t)nch * seg / ad.nseg);
+  const int c1 = is_u ? nch : (int)((int64_t)nch * (seg + 1) / ad.nseg);
+  const char* pa = uniform((const char*)((is_u ? Z : Q) + (((int64_t)y * (np / 64) + gb) * np + c0 * 32) * 64) +
+                           wave * 1024);
+  const char* pb = uniform(ws + (is_u ? ad.RT + ((int64_t)t * (ad.Mt / 64) + blk) * np * 512
+                                      : ad.ET + ((int64_t)(ad.etb[t] + blk) * np + c0 * 32) * 512) +
+                           wave * 1024);
+  R ring{lds, c1 - c0};
+  int issued = c0;
+  auto issue = [&]() {
+    if (issued == c1) return;
+    ++issued;
+    char* st = ring.stage(wave);
+    auto copy = [&](const char* p, int i) {
+      __builtin_amdgcn_global_load_lds((const void*)(p + lane * 16), (lds_ptr)(st + i * 8192), 16, 0, 0);
+    };
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < 4; ++i) copy(pa + i * 8192, i);
+    copy(pb, 4);
+    copy(pb + 8192, 5);
+    pa += 32 * 1024;
+    pb += 16 * 1024;
+  };
+  for (int i = 0; i < R::stages - 1; ++i) issue();
+  if (is_u) {
+    const int k16 = (2 * c.n_l + 15) / 16 - 4 * blk;       // blocks of 16 k left
+    const int cols = k16 == 1 ? 1 : k16 == 2 ? 2 : 4;      // wave columns
+    const int turns = 4 / cols, turn = (wave & 3) / cols;  // this wave's steps: s = turn mod turns
+    const int arow = (wave >> 2) * 32 + 2 * lr, bcol = (wave & 3) % cols * 16 + lr;
+    d4 re[2], im[2];
+    clear(re);
+    clear(im);
+    struct Ops { d2 a[2]; double b; };
+    auto run = [&](auto per) {  // steps of a chunk per wave
+      constexpr int PER = decltype(per)::value, TURNS = 8 / PER;
+      section<PER, 2>(
+          ring, PER * nch, true, issue,
+          [&](const char* st, int s) {
+            const int r = 4 * (s * TURNS + turn) + lk;
+            const d2* A = (const d2*)(st + r * 1024) + arow;
+            return Ops{{A[0], A[1]}, ((const double*)(st + 32 * 1024 + r * 512))[bcol]};
+          },
+          [&](const Ops& o, int i) {
+            re[i] = MFMA(o.a[i].x, o.b, re[i]);
+            im[i] = MFMA(o.a[i].y, o.b, im[i]);
+          });
+    };
+    if (turns == 1) run(std::integral_constant<int, 8>{});
+    else if (turns == 2) run(std::integral_constant<int, 4>{});
+    else run(std::integral_constant<int, 2>{});
+    if (turns > 1) {  // all copies have landed: the ring's memory is free once everyone is here
+      __syncthreads();
+      double* mine = (double*)lds + wave * 1024 + lane;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < MI; ++j)
-          U[(int64_t)(row0 + MI * (lk + 4 * q) + i) * ad.Mt + col0 + MI * lr + j] = d2{re[i][j][q], im[i][j][q]};
+        for (int q = 0; q < 4; ++q) {
+          mine[(i * 4 + q) * 64] = re[i][q];
+          mine[(8 + i * 4 + q) * 64] = im[i][q];
+        }
+      __syncthreads();
+      if (turn > 0) return;
+      for (int o = 1; o < turns; ++o) {
+        const double* other = mine + o * cols * 1024;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            re[i][q] += other[(i * 4 + q) * 64];
+            im[i][q] += other[(8 + i * 4 + q) * 64];
+          }
+      }
+    }
+    d2* U = (d2*)(ws + ad.UT) +
+            (((int64_t)y * (ad.Mt / 64) + blk) * np + gb * 64 + (wave >> 2) * 32) * 64 + bcol;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) U[(2 * (lk + 4 * q) + i) * 64] = d2{re[i][q], im[i][q]};
     return;
   }
-  const int w = ((int)blockIdx.x - nu) * 4 + wave;  // (column block, atom block, segment), segment fastest
-  const int seg = w % ad.nseg, ab = w / ad.nseg % nab, gb = w / ad.nseg / nab;
-  const int row0 = gb * 16 * MI, a0 = ab * 16;
-  if (row0 >= kk.n_pad || a0 >= c.nat[t]) return;
-  const int nch = steps / KC;
-  const int k0 = (int)((int64_t)nch * seg / ad.nseg) * KC, k1 = (int)((int64_t)nch * (seg + 1) / ad.nseg) * KC;
-  const d2* ET = (const d2*)(ws + ad.ET) + c.eoff[t] + a0;
-  const d2* qp = Q + (int64_t)blockIdx.y * n_pad * n_pad + (int64_t)lk * n_pad + row0 + MI * lr;
-  const d2* ep = ET + (int64_t)lk * ad.et_ld + lr;
-  struct Chunk { d2 a[KC][MI], b[KC]; };
-  auto load = [&](int s, Chunk& x) {
-#pragma unroll
-    for (int q = 0; q < KC; ++q) {
-      const int64_t k = (int64_t)(s + q) * 4;
-#pragma unroll
-      for (int i = 0; i < MI; ++i) x.a[q][i] = qp[k * n_pad + i];
-      x.b[q] = ep[k * ad.et_ld];
-    }
-  };
-  d4 p1[MI], p2[MI], p3[MI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i) p1[i] = p2[i] = p3[i] = d4{0.0, 0.0, 0.0, 0.0};
-  if (k0 < k1) {
-    Chunk x;
-    load(k0, x);
-    for (int s = k0; s < k1; s += KC) {
-      Chunk y;
-      load(s + KC < k1 ? s + KC : s, y);
-#pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        const double es = x.b[q].x - x.b[q].y;
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          p1[i] = MFMA(x.a[q][i].x, x.b[q].x, p1[i]);
-          p2[i] = MFMA(x.a[q][i].y, x.b[q].y, p2[i]);
-          p3[i] = MFMA(x.a[q][i].x + x.a[q][i].y, es, p3[i]);
-        }
-      }
-      x = y;
-    }
-  }
-  // lane: atom a0 + lr, columns G = row0 + MI (lk + 4 q) + i; pads of E are zero
+  const int row = (wave >> 1) * 16, col = (wave & 1) * 16 + lr;
+  d4 p1[1], p2[1], p3[1];
+  clear(p1);
+  clear(p2);
+  clear(p3);
+  struct Ops { d2 a, b; };
+  section<8, 1>(
+      ring, 8 * (c1 - c0), true, issue,
+      [&](const char* st, int s) {
+        return Ops{((const d2*)(st + (4 * s + lk) * 1024))[row + lr],
+                   ((const d2*)(st + 32 * 1024 + (4 * s + lk) * 512))[col]};
+      },
+      [&](const Ops& o, int) {
+        p1[0] = MFMA(o.a.x, o.b.x, p1[0]);
+        p2[0] = MFMA(o.a.y, o.b.y, p2[0]);
+        p3[0] = MFMA(o.a.x + o.a.y, o.b.x - o.b.y, p3[0]);
+      });
+  // lane: atom 32 blk + col, columns G = 64 gb + row + lk + 4 q; pads of E are zero
   const double* kv = (const double*)(ws + kk.kv);
+  const d2* ET = (const d2*)(ws + ad.ET) + (int64_t)(ad.etb[t] + blk) * np * 32 + col;
   double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int G = row0 + MI * (lk + 4 * q) + i;
-      const d2 e = ET[(int64_t)G * ad.et_ld + lr];
-      const double re = p1[i][q] + p2[i][q], im = p3[i][q] - p1[i][q] + p2[i][q];
-      const double s = e.x * im + e.y * re;
-      v[0] += s * kv[4 * G + 0];
-      v[1] += s * kv[4 * G + 1];
-      v[2] += s * kv[4 * G + 2];
-    }
+  for (int q = 0; q < 4; ++q) {
+    const int64_t G = gb * 64 + row + lk + 4 * q;
+    const d2 e = ET[G * 32];
+    const double re = p1[0][q] + p2[0][q], im = p3[0][q] - p1[0][q] + p2[0][q];
+    const double s = e.x * im + e.y * re;
+    v[0] += s * kv[4 * G + 0];
+    v[1] += s * kv[4 * G + 1];
+    v[2] += s * kv[4 * G + 2];
+  }
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     v[d] += __shfl_xor(v[d], 16, 64);
     v[d] += __shfl_xor(v[d], 32, 64);
   }
-  if (lk == 0 && a0 + lr < c.nat[t]) {
-    double* part = (double*)(ws + ad.partTau) + (((int64_t)seg * ad.ngb + gb) * ad.et_ld + c.eoff[t] + a0 + lr) * 3;
+  const int a = blk * 32 + col;
+  if (lk == 0 && a < c.nat[t]) {
+    double* part =
+        (double*)(ws + ad.partTau) + (((int64_t)seg * ad.ngb + gb * 4 + (wave >> 1)) * c.e_rows + c.eoff[t] + a) * 3;
     part[0] = v[0];
     part[1] = v[1];
     part[2] = v[2];
@@ -216,15 +292,17 @@ __global__ void __launch_bounds__(256, 2) k_adj_gt(FactCell c, FactK kk, FactAdj
   const int t = t0 + blockIdx.y, seg = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int nkb = (ad.Mt + 32 * MI - 1) / (32 * MI);
+  const int nkb = ad.Mt / (32 * MI);
   const int row0 = blockIdx.x / nkb * 32 * MI + (wave >> 1) * 16 * MI;
   const int col0 = blockIdx.x % nkb * 32 * MI + (wave & 1) * 16 * MI;
-  if (row0 >= ad.Mt || col0 >= ad.Mt) return;
   const int nch = kk.n_pad / 4 / KC;
   const int k0 = (int)((int64_t)nch * seg / ad.ngt) * KC, k1 = (int)((int64_t)nch * (seg + 1) / ad.ngt) * KC;
   d4 re[MI][MI], im[MI][MI];
-  product_cr<MI, MI, KC>((const d2*)(ws + ad.UT) + (int64_t)blockIdx.y * n_pad * ad.Mt + row0, ad.Mt,
-                         (const double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + col0, ad.Mt, k0, k1, re, im);
+  clear(re);
+  clear(im);
+  product_cr<MI, MI, KC>(
+      (const d2*)(ws + ad.UT) + ((int64_t)blockIdx.y * nkb + row0 / 64) * n_pad * 64 + row0 % 64,
+      (const double*)(ws + ad.RT) + ((int64_t)t * nkb + col0 / 64) * n_pad * 64 + col0 % 64, k0, k1, re, im);
   d2* out = (d2*)(ws + ad.partT) + ((int64_t)t * ad.ngt + seg) * ad.Mt * ad.Mt;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -247,7 +325,7 @@ __global__ void __launch_bounds__(256) k_adj_reduce(FactCell c, FactAdj ad, int 
     if (t >= c.n_act || blockIdx.y > 0) return;
     const double* part = (const double*)(ws + ad.partTau) + (int64_t)(c.eoff[t] + a) * 3 + i % 3;
     double s = 0.0;
-    for (int b = lane; b < ad.nseg * ad.ngb; b += 64) s += part[(int64_t)b * ad.et_ld * 3];
+    for (int b = lane; b < ad.nseg * ad.ngb; b += 64) s += part[(int64_t)b * c.e_rows * 3];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if (lane == 0) gtau[(c.atom0[t] + a) * 3 + i % 3] = -2.0 * s;
@@ -287,32 +365,30 @@ hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s) {
   const int nb = kk.n_pad / 64;
   const bool halves = 2 * nb * nb * nt <= num_cus;  // as in launch_fact_hs
+  // gH and gS are read once for all types where the tiles alone fill the compute units several times over
+  const int per = nb * nb >= 4 * num_cus ? nt : 1;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nb, halves ? 2 * nb : nb, nt), dim3(512), 0, s, c, kk, t0, (const d2*)gH,
-                       (const d2*)gS, ws, (d2*)Z, (d2*)Q);
+    hipLaunchKernelGGL(kernel, dim3(nb, halves ? 2 * nb : nb, nt / per), dim3(512), 0, s, c, kk, t0, per,
+                       (const d2*)gH, (const d2*)gS, ws, (d2*)Z, (d2*)Q);
   };
   halves ? go(k_adj_zq<1>) : go(k_adj_zq<2>);
   return hipGetLastError();
 }
 
-hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, int mi, char* ws,
+hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
                          const double2* Z, const double2* Q, hipStream_t s) {
-  const int nkb = (ad.Mt + 32 * mi - 1) / (32 * mi);
-  const int nu = kk.n_pad / (32 * mi) * nkb;
+  const int nb = kk.n_pad / 64;
   int nab = 0;
-  for (int t = t0; t < t0 + nt; ++t) nab = nab > (c.nat[t] + 15) / 16 ? nab : (c.nat[t] + 15) / 16;
-  const int nc = (kk.n_pad / (16 * mi) * nab * ad.nseg + 3) / 4;
-  const dim3 grid(nu + nc, nt);
-  if (mi == 2)
-    hipLaunchKernelGGL((k_adj_uc<2, 4>), grid, dim3(256), 0, s, c, kk, ad, t0, nu, nab, ws, (const d2*)Z, (const d2*)Q);
-  else
-    hipLaunchKernelGGL((k_adj_uc<1, 4>), grid, dim3(256), 0, s, c, kk, ad, t0, nu, nab, ws, (const d2*)Z, (const d2*)Q);
+  for (int t = t0; t < t0 + nt; ++t) nab = nab > (c.nat[t] + 31) / 32 ? nab : (c.nat[t] + 31) / 32;
+  const int nu = nt * nb * (c.n_l / 32), nu2 = c.n_l % 32 ? nt * nb : 0;
+  hipLaunchKernelGGL(k_adj_uc, dim3(nu + nu2 + nt * nb * ad.nseg * nab), dim3(512), 0, s, c, kk, ad, t0, nu, nu2, nab, ws,
+                     (const d2*)Z, (const d2*)Q);
   return hipGetLastError();
 }
 
 hipError_t launch_adj_gt(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
                          hipStream_t s) {
-  const int nkb = (ad.Mt + 63) / 64;
+  const int nkb = ad.Mt / 64;
   hipLaunchKernelGGL((k_adj_gt<2, 4>), dim3(nkb * nkb, nt, ad.ngt), dim3(256), 0, s, c, kk, ad, t0, ws);
   return hipGetLastError();
 }

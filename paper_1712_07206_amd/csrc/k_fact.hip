@@ -200,12 +200,14 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     }
     E[a * 64] = v;
     if (rep) EW[a * 64] = make_double2(wt * v.x, wt * v.y);
-    if (ad.Mt) ((double2*)(ws + ad.ET))[(int64_t)G * ad.et_ld + c.eoff[t] + a] = v;
   }
   if (!ad.Mt) return;
+  double2* ET = (double2*)(ws + ad.ET) + ((int64_t)ad.etb[t] * n_pad + G) * 32;
+  for (int a = wave; a < (nt + 31) / 32 * 32; a += 4)
+    ET[(int64_t)(a / 32) * n_pad * 32 + a % 32] = a < nt ? E[a * 64] : make_double2(0.0, 0.0);
   // transposed copy of R: lanes along the rows
   const int G0 = (blockIdx.x - kk.gblk0) * kTabG;
-  double* RT = (double*)(ws + ad.RT) + ((int64_t)t * n_pad + G0) * ad.Mt;
+  double* RT = (double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + G0 * 64;
   for (int e = tid; e < kTabG * ad.Mt; e += 256) {
     const int q = e / ad.Mt, r = e - q * ad.Mt;
     double v = 0.0;
@@ -215,7 +217,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
       lm_of(L, l, m);
       v = ang[L * kTabS + q] * ab[(x2 * nl1 + l) * kTabS + q];
     }
-    RT[(int64_t)q * ad.Mt + r] = v;
+    RT[(int64_t)(r / 64) * n_pad * 64 + q * 64 + r % 64] = v;
   }
 }
 

@@ -134,7 +134,9 @@ def test_batch_uploads_radial_data_past_the_by_value_limit():
 
 @pytest.mark.parametrize("atoms,l_max,n_g", [((1,), 0, 1), ((2,), 4, 33), ((3, 1, 2), 3, 64), ((17, 16), 2, 65),
                                              ((1, 1, 1), 1, 300),  # one type per pass: its Z and Q fill the workspace
-                                             ((2, 0, 1), 5, 129), ((1,) * 9, 7, 80)])
+                                             ((2, 0, 1), 5, 129), ((1,) * 9, 7, 80),
+                                             ((2, 33), 8, 70),  # 162 rows: 3 of the last 4 blocks; two blocks of atoms
+                                             ((2, 1), 1, 2050)])  # all types in one workgroup of k_adj_zq
 def test_adjoint_of_general_matrices(atoms, l_max, n_g):
     """hsbuild_backward against the stacked formulas grad T_t = sum_a W_a gH W_a^H and
     c_a = conj(W_a gH) . (T W_a) + conj(W_a gS) . (lam W_a), with T, gH and gS none of them

@@ -237,6 +237,15 @@ int hsbuild_eigensolve(hsbuild_t h, int32_t ng, void* H, void* S, double* w, int
 int hsbuild_forward_coefficients(hsbuild_t h, int32_t ng, const void* coef, const void* T, void* H, void* S,
                                  void* ws, size_t ws_bytes, void* stream);
 
+/* The lower triangles of H and S (device complex128 [ng][ng]) from the upper
+ * ones, as conjugates: full Hermitian matrices, in place. */
+int hsbuild_mirror(hsbuild_t h, int32_t ng, void* H, void* S, void* stream);
+
+/* oH = (gH + gH^H) / 2 and oS likewise, device complex128 [ng][ng]: the gradients
+ * hsbuild_backward takes, for a loss of the mirrored matrices.  gH or gS may be
+ * NULL (its output is zero); the outputs overlap neither each other nor an input. */
+int hsbuild_hermitian_part(hsbuild_t h, int32_t ng, const void* gH, const void* gS, void* oH, void* oS, void* stream);
+
 /* Adjoint of hsbuild_forward for a real loss L(H, S).  gH, gS: device
  * complex128 [ng][ng], the full Hermitian gradients dL/dRe H + i dL/dIm H
  * (likewise S).  Outputs: gT device complex128 [n_types][2N_L][2N_L] =

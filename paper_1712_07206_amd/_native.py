@@ -44,7 +44,7 @@ HSB_MODE_EIGEN = 7
 EXPORTS = ("hsbuild_create", "hsbuild_destroy", "hsbuild_workspace_bytes", "hsbuild_coefficients",
            "hsbuild_forward", "hsbuild_forward_factored", "hsbuild_forward_hsdla", "hsbuild_forward_real", "hsbuild_eigensolve",
            "hsbuild_forward_coefficients",
-           "hsbuild_backward",
+           "hsbuild_backward", "hsbuild_mirror", "hsbuild_hermitian_part",
            "hsbuild_batch", "hsbuild_last_error",
            "hsbuild_host_bessel", "hsbuild_host_angular", "hsbuild_set_timing", "hsbuild_stage_times",
            "hsbuild_set_option", "hsbuild_get_option", "hsbuild_mfma_probe", "hsbuild_forward_static")
@@ -118,6 +118,10 @@ def lib():
     L.hsbuild_backward.argtypes = [c_void_p, POINTER(c_double), c_int32, c_void_p, c_void_p, c_void_p, c_void_p,
                                    c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
     L.hsbuild_backward.restype = c_int
+    L.hsbuild_mirror.argtypes = [c_void_p, c_int32, c_void_p, c_void_p, c_void_p]
+    L.hsbuild_mirror.restype = c_int
+    L.hsbuild_hermitian_part.argtypes = [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
+    L.hsbuild_hermitian_part.restype = c_int
     L.hsbuild_batch.argtypes = [c_void_p, c_int32, POINTER(c_double), POINTER(c_int32), c_void_p,
                                 POINTER(c_int64), c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t,
                                 c_void_p]

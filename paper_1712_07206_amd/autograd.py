@@ -10,7 +10,7 @@ from __future__ import annotations
 
 import torch
 
-from .hsbuild import HSBuilder, hermitian_full
+from .hsbuild import HSBuilder
 
 
 class HSBuildFunction(torch.autograd.Function):
@@ -20,18 +20,13 @@ class HSBuildFunction(torch.autograd.Function):
         ctx.builder = builder
         ctx.k_frac = tuple(float(x) for x in k_frac)
         ctx.save_for_backward(tau.detach(), T.detach(), g)
-        return hermitian_full(H), hermitian_full(S)
+        return builder.mirror(H, S)
 
     @staticmethod
     def backward(ctx, gH, gS):
         tau, T, g = ctx.saved_tensors
-        n = g.shape[0]
-        zeros = None
-        if gH is None or gS is None:
-            zeros = torch.zeros((n, n), dtype=torch.complex128, device=tau.device)
-        gH = zeros if gH is None else 0.5 * (gH + gH.conj().transpose(0, 1))
-        gS = zeros if gS is None else 0.5 * (gS + gS.conj().transpose(0, 1))
-        gT, gtau = ctx.builder.backward(ctx.k_frac, g, tau, T, gH.contiguous(), gS.contiguous())
+        gH, gS = ctx.builder.hermitian_part(int(g.shape[0]), gH, gS)
+        gT, gtau = ctx.builder.backward(ctx.k_frac, g, tau, T, gH, gS)
         return gtau, gT, None, None, None
 
 

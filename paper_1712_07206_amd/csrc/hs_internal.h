@@ -318,6 +318,11 @@ int eig_workspace(void* handle, int n, bool vectors, size_t* bytes, std::string&
 // a[i] = conj(a[i]) for i < count.
 hipError_t launch_conj(double2* a, int64_t count, hipStream_t s);
 
+// ---- full matrices (k_herm.hip) ----
+// Lower triangles of H and S from the upper ones; out = (g + g^H) / 2 of gH and gS (zero for a null one).
+hipError_t launch_mirror(int n, double2* H, double2* S, hipStream_t s);
+hipError_t launch_hermitian_part(int n, const double2* gH, const double2* gS, double2* oH, double2* oS, hipStream_t s);
+
 // ---- adjoint (one k-point; active types t0 .. t0 + nt - 1) ----
 // Z, Q: complex, block-major [nt][n_pad / 64][n_pad][64].
 hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,

@@ -1205,6 +1205,31 @@ int hsbuild_forward_coefficients(hsbuild_t h, int32_t ng, const void* coef, cons
   return enqueue_split(h, L, w, (double2*)H, (double2*)S, s);
 }
 
+int hsbuild_mirror(hsbuild_t h, int32_t ng, void* H, void* S, void* stream) {
+  if (!h) return HSB_ERR_ARG;
+  h->err.clear();
+  if (!H || !S) return fail(h, HSB_ERR_ARG, "null H or S");
+  if (H == S) return fail(h, HSB_ERR_ARG, "H and S must be distinct buffers");
+  int rc = check_ng(h, ng);
+  if (rc) return rc;
+  if ((rc = check_device(h))) return rc;
+  return launched(h, launch_mirror(ng, (double2*)H, (double2*)S, (hipStream_t)stream), "k_mirror");
+}
+
+int hsbuild_hermitian_part(hsbuild_t h, int32_t ng, const void* gH, const void* gS, void* oH, void* oS, void* stream) {
+  if (!h) return HSB_ERR_ARG;
+  h->err.clear();
+  if (!oH || !oS) return fail(h, HSB_ERR_ARG, "null oH or oS");
+  if (oH == oS || oH == gH || oH == gS || oS == gH || oS == gS)
+    return fail(h, HSB_ERR_ARG, "the outputs must be distinct from each other and from the inputs");
+  int rc = check_ng(h, ng);
+  if (rc) return rc;
+  if ((rc = check_device(h))) return rc;
+  return launched(h, launch_hermitian_part(ng, (const double2*)gH, (const double2*)gS, (double2*)oH, (double2*)oS,
+                                           (hipStream_t)stream),
+                  "k_hermitian_part");
+}
+
 int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
                      const void* T, const void* gH, const void* gS, void* gT, double* gtau, void* ws,
                      size_t ws_bytes, void* stream) {

@@ -272,6 +272,25 @@ class HSBuilder:
                                          _ptr(gT), _ptr(gtau), _ptr(ws), ws.numel(), _stream()), self._h)
         return gT, gtau
 
+    def mirror(self, H: torch.Tensor, S: torch.Tensor):
+        """Full Hermitian H and S from the upper triangles of a forward call, in
+        place (hsbuild_mirror)."""
+        ng = int(H.shape[0])
+        for name, M in (("H", H), ("S", S)):
+            if not _dev(M, torch.complex128, name, (ng, ng)).data_ptr() == M.data_ptr() or M.is_conj():
+                raise ValueError("%s must be contiguous" % name)
+        N.check(N.lib().hsbuild_mirror(self._h, ng, _ptr(H), _ptr(S), _stream()), self._h)
+        return H, S
+
+    def hermitian_part(self, ng: int, gH: Optional[torch.Tensor], gS: Optional[torch.Tensor]):
+        """(g + g^H) / 2 of gH and gS, zero for None (hsbuild_hermitian_part)."""
+        ins = [None if x is None else _dev(x.resolve_conj().resolve_neg(), torch.complex128, name, (ng, ng))
+               for name, x in (("gH", gH), ("gS", gS))]
+        outs = [torch.empty((ng, ng), dtype=torch.complex128, device="cuda") for _ in range(2)]
+        N.check(N.lib().hsbuild_hermitian_part(self._h, ng, *[None if x is None else _ptr(x) for x in ins],
+                                               *[_ptr(x) for x in outs], _stream()), self._h)
+        return outs
+
     def batch(self, k_frac, g_list: Sequence[torch.Tensor], tau: torch.Tensor, T: torch.Tensor,
               H: Optional[torch.Tensor] = None, S: Optional[torch.Tensor] = None, out_off=None,
               ws: Optional[torch.Tensor] = None):

@@ -233,10 +233,11 @@ AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
   return p;
 }
 
-// Blocks per wave side of Y = T' R over `cols` columns: 64 x 64 workgroups where they are enough for
-// every compute unit, else 32 x 32.
+// Blocks per wave side of Y = T' R over `cols` columns: 64 x 64 workgroups where they are two for every
+// compute unit, else 32 x 32 (282 of the larger, N_G = 3000: 21.7 us against 29.6; 752, N_G = 6000, real: 59 against
+// 35).
 int y_block(const FactCell& c, int64_t cols, int num_cus) {
-  return cols / 64 * ((c.Mr + 63) / 64) * c.n_act < num_cus ? 1 : 2;
+  return cols / 64 * ((c.Mr + 63) / 64) * c.n_act < 2 * num_cus ? 1 : 2;
 }
 
 // The radial data by value; false if the types need more entries than RadialArgs holds.

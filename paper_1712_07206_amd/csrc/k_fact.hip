@@ -50,15 +50,17 @@ __device__ inline int find_block(const FactK* ks, int nk, int b, int FactK::*fir
 }
 
 constexpr int kTabG = 64;          // columns per workgroup of k_fact_tables
+constexpr int kTabWaves = 16;
 constexpr int kTabS = kTabG + 1;  // their stride in LDS: the transposed copies read along the rows
 
 // Blocks x < ngb: type blockIdx.y's R rows and phases (and, for the first type, the K vectors) of 64
-// columns; blocks past them: T'.  Latency-bound (a few hundred workgroups of short serial
-// recurrences), so the recurrences are spread over the workgroup: wave 0 runs the backward Bessel
-// recurrence of its 64 columns while waves 1 to 3 run the power series (columns with x < 2; l
-// dealt over the waves) and the Legendre recurrences (m dealt over the waves), whose coefficients
-// are compile-time tables.
-__global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, const TypeConsts* __restrict__ consts,
+// columns; blocks past them: T'.  Latency-bound at small bases (a few hundred workgroups of short serial
+// recurrences), bandwidth-bound on its writes at large ones, so the work is spread over the workgroup:
+// wave 0 runs the backward Bessel recurrence of its 64 columns while the others run the power series (columns
+// with x < 2; l dealt over the waves) and the Legendre recurrences (m dealt over the waves), whose
+// coefficients are compile-time tables.  16 waves: 14.5 us at N_G = 1237 in 3 types, 44 us at 12000 in 4; with 4 waves
+// 18.9 and 62.
+__global__ void __launch_bounds__(64 * kTabWaves) k_fact_tables(FactCell c, RadialArgs ra, const TypeConsts* __restrict__ consts,
                                                      FactK one, const FactK* __restrict__ many, int nk, int ngb,
                                                      const int32_t* __restrict__ g, const double* __restrict__ tau,
                                                      const FactRep* __restrict__ rep, FactAdj ad,
@@ -68,7 +70,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
   const int tid = threadIdx.x;
   const int lmax = c.l_max, nl1 = lmax + 1;
   if ((int)blockIdx.x >= ngb) {  // T'[r][k], stored [k][r] zero-padded
-    const int64_t e = (int64_t)(blockIdx.x - ngb) * 256 + tid;
+    const int64_t e = (int64_t)(blockIdx.x - ngb) * (64 * kTabWaves) + tid;
     const int k = (int)(e / c.Mc), r = (int)(e % c.Mc);
     if (k >= c.Mr) return;
     const int M = 2 * c.n_l;
@@ -123,7 +125,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     if (!(x < 2.0)) sph_bessel_back(lmax + 1, x, jl + lane, kTabS);
   } else {
     if (x < 2.0) {
-      for (int l = wave - 1; l <= lmax + 1; l += 3) jl[l * kTabS + lane] = sph_bessel_series(l, x);
+      for (int l = wave - 1; l <= lmax + 1; l += kTabWaves - 1) jl[l * kTabS + lane] = sph_bessel_series(l, x);
     }
     double ct = 1.0, wr = 0.0, wi = 0.0;
     if (!(kn < 1e-12)) {
@@ -132,7 +134,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     }
     double pr = c.pre, pi = 0.0;  // pre w^m
     int mp = 0;
-    for (int m = wave - 1; m <= lmax; m += 3) {
+    for (int m = wave - 1; m <= lmax; m += kTabWaves - 1) {
       for (; mp < m; ++mp) {
         const double q = pr * wr - pi * wi;
         pi = pr * wi + pi * wr;
@@ -153,7 +155,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     }
   }
   __syncthreads();
-  for (int l = wave; l <= lmax; l += 4) {
+  for (int l = wave; l <= lmax; l += kTabWaves) {
     double u, du, ud, dud;
     if (consts) {
       const double* q = consts->radial[c.type[t]][l];
@@ -174,7 +176,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
   const int blk = blockIdx.x - kk.gblk0;
   double* R = (double*)(ws + kk.R) + ((int64_t)blk * c.n_act + t) * c.Mr * 64 + lane;
   double* LR = (double*)(ws + kk.LR) + ((int64_t)blk * c.n_act + t) * c.Mr * 64 + lane;
-  for (int L = wave; L < c.n_l; L += 4) {
+  for (int L = wave; L < c.n_l; L += kTabWaves) {
     int l, m;
     lm_of(L, l, m);
     const double s = ang[L * kTabS + lane];
@@ -184,11 +186,11 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
     R[(c.n_l + L) * 64] = xb;
     LR[(c.n_l + L) * 64] = (consts ? consts->udot2[c.type[t]][l] : ra.v[t * nl1 + l][4]) * xb;
   }
-  for (int r = 2 * c.n_l + wave; r < c.Mr; r += 4) R[r * 64] = LR[r * 64] = 0.0;
+  for (int r = 2 * c.n_l + wave; r < c.Mr; r += kTabWaves) R[r * 64] = LR[r * 64] = 0.0;
   double2* E = (double2*)(ws + kk.E) + ((int64_t)blk * c.e_rows + c.eoff[t]) * 64 + lane;
   double2* EW = (double2*)(ws + kk.EW) + ((int64_t)blk * c.e_rows + c.eoff[t]) * 64 + lane;
   const int nt = c.nat[t], erows = (nt + kFactRows - 1) / kFactRows * kFactRows;
-  for (int a = wave; a < erows; a += 4) {
+  for (int a = wave; a < erows; a += kTabWaves) {
     double2 v = make_double2(0.0, 0.0);
     double wt = 1.0;
     if (a < nt && valid) {
@@ -203,12 +205,12 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
   }
   if (!ad.Mt) return;
   double2* ET = (double2*)(ws + ad.ET) + ((int64_t)ad.etb[t] * n_pad + G) * 32;
-  for (int a = wave; a < (nt + 31) / 32 * 32; a += 4)
+  for (int a = wave; a < (nt + 31) / 32 * 32; a += kTabWaves)
     ET[(int64_t)(a / 32) * n_pad * 32 + a % 32] = a < nt ? E[a * 64] : make_double2(0.0, 0.0);
   // transposed copy of R: lanes along the rows
   const int G0 = (blockIdx.x - kk.gblk0) * kTabG;
   double* RT = (double*)(ws + ad.RT) + (int64_t)t * n_pad * ad.Mt + G0 * 64;
-  for (int e = tid; e < kTabG * ad.Mt; e += 256) {
+  for (int e = tid; e < kTabG * ad.Mt; e += 64 * kTabWaves) {
     const int q = e / ad.Mt, r = e - q * ad.Mt;
     double v = 0.0;
     if (r < 2 * c.n_l && G0 + q < kk.n) {
@@ -226,7 +228,7 @@ __global__ void __launch_bounds__(256) k_fact_tables(FactCell c, RadialArgs ra, 
 template <int MI, int NJ, bool REAL>
 __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
                                                    char* __restrict__ ws) {
-  constexpr int KC = 2;
+  constexpr int KC = 4;
   const FactK& kk = many ? many[find_block(many, nk, blockIdx.x, &FactK::yblk0)] : one;
   const int t = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -373,8 +375,8 @@ hipError_t launch_fact_tables(const FactCell& c, const RadialArgs& ra, const Typ
                               const FactK* many, int nk, int ngb, const int32_t* g, const double* tau,
                               const FactRep* rep, const FactAdj& ad, const double2* T, char* ws, hipStream_t s) {
   const size_t lds = (size_t)(c.n_l + c.l_max + 2 + 2 * (c.l_max + 1)) * kTabS * sizeof(double);
-  const int ntb = (int)(((int64_t)c.Mr * c.Mc + 255) / 256);
-  hipLaunchKernelGGL(k_fact_tables, dim3(ngb + ntb, c.n_act), dim3(256), lds, s, c, ra, consts, one, many, nk, ngb, g,
+  const int ntb = (int)(((int64_t)c.Mr * c.Mc + 64 * kTabWaves - 1) / (64 * kTabWaves));
+  hipLaunchKernelGGL(k_fact_tables, dim3(ngb + ntb, c.n_act), dim3(64 * kTabWaves), lds, s, c, ra, consts, one, many, nk, ngb, g,
                      tau, rep, ad, T, ws);
   return hipGetLastError();
 }

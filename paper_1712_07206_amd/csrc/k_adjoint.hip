@@ -20,7 +20,7 @@
 // All on v_mfma_f64_16x16x4f64, the first two through an LDS ring (wave_tile.h); Z, Q, R Z and the
 // transposed copies of R and E (k_fact_tables) are block-major, so that chunks are contiguous runs.
 // Deterministic: fixed orders, no atomics.
-// At N_G = 6000, 64 atoms in two types, l_max = 10 (4.0 ms): k_adj_zq 2.4 ms, 68 % of it the matrix cores' time, the rest
+// At N_G = 6000, 64 atoms in two types, l_max = 10 (3.9 ms): k_adj_zq 2.3 ms, 71 % of it the matrix cores' time, the rest
 // the 2.3 GB of Z and Q it writes, the reads of gH and gS and the ring's waits (2.6 ms with one type per workgroup and
 // rows of n_pad); k_adj_uc 1.6 ms, 72 % (the same with operands straight in registers; 67 and 61 us at N_G = 801 in
 // 3 types); k_adj_gt 0.07 ms.
@@ -35,20 +35,21 @@ namespace hsb {
 
 namespace {
 
-// Z_t and Q_t (zeros outside n x n, up to n_pad), block-major: [type][64 columns][n_pad rows][64]; 64 x 64 tiles of the
-// square (MI = 2) or their halves (MI = 1, interleaved in blockIdx.y), `per` types each.  Writes 32 bytes per type
-// and element.
+// Z_t and Q_t (zeros outside n x n, up to n_pad), block-major: [type][64 columns][n_pad rows][64]; 64 x 32 tiles of the
+// square (MI = 2) or 32 x 32 ones (MI = 1), column halves interleaved in blockIdx.x and row halves in blockIdx.y, `per`
+// types each.  Writes 32 bytes per type and element.
 template <int MI>
-__global__ void __launch_bounds__(512, 2) k_adj_zq(FactCell c, FactK kk, int t0, int per, const d2* __restrict__ gH,
+__global__ void __launch_bounds__(256, 2) k_adj_zq(FactCell c, FactK kk, int t0, int per, const d2* __restrict__ gH,
                                                    const d2* __restrict__ gS, const char* __restrict__ ws,
                                                    d2* __restrict__ Z, d2* __restrict__ Q) {
   constexpr int PARTS = 2 / MI;
+  const int bj = blockIdx.x / 2;
   __shared__ __align__(16) char lds[TypedTile<MI, false>::lds_bytes];
   const int n = kk.n;
   const int64_t n_pad = kk.n_pad;
   const int first = blockIdx.z * per;
-  TypedTile<MI, false> tile(c, kk, ws, lds, blockIdx.y / PARTS, blockIdx.y % PARTS, blockIdx.x, t0 + first,
-                            t0 + first + per);
+  TypedTile<MI, false> tile(c, kk, ws, lds, blockIdx.y / PARTS, blockIdx.y % PARTS, bj, blockIdx.x % 2,
+                            t0 + first, t0 + first + per);
   const bool active = tile.row0() < n && tile.col0() < n;
   const int col = tile.col();
   d2 h[MI][4], s[MI][4];
@@ -64,7 +65,7 @@ __global__ void __launch_bounds__(512, 2) k_adj_zq(FactCell c, FactK kk, int t0,
       }
     }
   for (int t = first; t < first + per; ++t) {
-    const int64_t o = ((int64_t)t * (n_pad / 64) + blockIdx.x) * n_pad * 64 + col % 64;
+    const int64_t o = ((int64_t)t * (n_pad / 64) + bj) * n_pad * 64 + col % 64;
     d4 pR[MI], pI[MI], m1[MI], m2[MI], F[MI];
     tile.phase_sums(t0 + t, active, pR, pI);
     tile.row_sums(active, m1, m2, F);
@@ -364,14 +365,14 @@ __global__ void __launch_bounds__(256) k_adj_reduce(FactCell c, FactAdj ad, int 
 hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s) {
   const int nb = kk.n_pad / 64;
-  const bool halves = 2 * nb * nb * nt <= num_cus;  // as in launch_fact_hs
+  const bool quarters = 4 * nb * nb * nt <= num_cus;  // as in launch_fact_hs
   // gH and gS are read once for all types where the tiles alone fill the compute units several times over
   const int per = nb * nb >= 4 * num_cus ? nt : 1;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nb, halves ? 2 * nb : nb, nt / per), dim3(512), 0, s, c, kk, t0, per,
+    hipLaunchKernelGGL(kernel, dim3(2 * nb, quarters ? 2 * nb : nb, nt / per), dim3(256), 0, s, c, kk, t0, per,
                        (const d2*)gH, (const d2*)gS, ws, (d2*)Z, (d2*)Q);
   };
-  halves ? go(k_adj_zq<1>) : go(k_adj_zq<2>);
+  quarters ? go(k_adj_zq<1>) : go(k_adj_zq<2>);
   return hipGetLastError();
 }
 

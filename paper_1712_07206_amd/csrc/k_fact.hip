@@ -20,15 +20,16 @@
 //   k_fact_y       Y_t = T'_t R_t
 //   k_fact_hs      the upper triangles of H and S
 //
-// k_fact_hs runs on v_mfma_f64_16x16x4f64 with its operands fed through LDS (TypedTile in wave_tile.h), one 64 x 64
-// tile per workgroup of 8 waves; R, lam R, Y and E are block-major so that a tile reads contiguous runs.
-// Bound by the FP64 matrix cores: at N_G = 12000, 128 atoms, l_max = 10 they are busy for 76 % of its 8.3 ms (at
-// 2.3 GHz); the rest is waits at the ring's barriers and the copies.  The same tile on 2 x 2 waves with operands read
-// straight from global memory into registers, no barriers, took 9.2 ms; with the copies and their address
-// arithmetic right behind the barrier 8.9; with a wave's row and column not known to be uniform, so that the ring
-// ran on vector registers, 9.9.  The FP64 vector units share the matrix cores' pipe: the addition theorem's sum over l in
-// place of the S product has fewer operations and was slower in every form tried (8.3 with the tile of 64 x 32 its
-// registers allow and S apart).
+// k_fact_hs runs on v_mfma_f64_16x16x4f64 with its operands fed through LDS (TypedTile in wave_tile.h), two
+// workgroups of 64 x 32 outputs to a compute unit; R, lam R, Y and E are block-major, so that what a tile reads of an
+// array lies together.
+// Bound by the FP64 matrix cores: at N_G = 12000, 128 atoms, l_max = 10 they are busy for 81 % of its 7.8 ms (at
+// 2.3 GHz); the rest is waits at the ring's barriers and the copies.  One workgroup of 64 x 64 on eight waves took 8.3 ms;
+// with its copies and their address arithmetic right behind the barrier 8.9; with a wave's row and column not
+// known to be uniform, so that the ring ran on vector registers, 9.9; and 64 x 64 on 2 x 2 waves with operands read
+// straight from global memory into registers, no barriers, 9.2.  The FP64 vector units share the matrix cores' pipe:
+// the addition theorem's sum over l in place of the S product has fewer operations and was slower in every form
+// tried.
 #include "harmonics.h"
 #include "hs_internal.h"
 #include "special.h"
@@ -294,12 +295,12 @@ __global__ void __launch_bounds__(256, 2) k_fact_y(FactCell c, FactK one, const 
 }
 
 // Upper triangles of H and S: per type P_t times the sums over its R rows (TypedTile), into the running H and S.
-// 64 x 64 tiles (MI = 2), or two halves of each (MI = 1).
+// 64 x 32 tiles, the halves of 64 x 64 ones (MI = 2), or quarters of those (MI = 1).
 template <int MI, bool REAL>
-__global__ void __launch_bounds__(512, 2) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
+__global__ void __launch_bounds__(256, 2) k_fact_hs(FactCell c, FactK one, const FactK* __restrict__ many, int nk,
                                                     int num_wg, int gr, const char* __restrict__ ws,
                                                     void* __restrict__ H, void* __restrict__ S) {
-  constexpr int PARTS = 2 / MI;
+  constexpr int PARTS = 4 / MI;
   __shared__ __align__(16) char lds[TypedTile<MI, REAL>::lds_bytes];
   int start, len;
   xcd_range(blockIdx.x % kXcds, num_wg, start, len);
@@ -310,8 +311,10 @@ __global__ void __launch_bounds__(512, 2) k_fact_hs(FactCell c, FactK one, const
   int bi, bj;
   if (gr > 0) grouped_decode(w / PARTS - kk.tile0, nb, gr, bi, bj);
   else tri_decode(w / PARTS - kk.tile0, nb, bi, bj);
-  if (bi * 64 + w % PARTS * 32 >= n) return;
-  TypedTile<MI, REAL> tile(c, kk, ws, lds, bi, w % PARTS, bj, 0, c.n_act);
+  const int part = w % PARTS;
+  if (bi * 64 + part / 2 * 32 >= n || bj * 64 + part % 2 * 32 >= n) return;
+  if (bi == bj && part == 2) return;  // below the diagonal
+  TypedTile<MI, REAL> tile(c, kk, ws, lds, bi, part / 2, bj, part % 2, 0, c.n_act);
   const int r0 = tile.row0(), c0 = tile.col0();
   const bool active = r0 < n && c0 < n && c0 + 16 > r0;
   d4 hR[MI], hI[MI], sR[MI], sI[MI];
@@ -393,15 +396,15 @@ hipError_t launch_fact_y(const FactCell& c, const FactK& one, const FactK* many,
 
 hipError_t launch_fact_hs(const FactCell& c, const FactK& one, const FactK* many, int nk, int tiles, bool real, int gr,
                           int num_cus, const char* ws, void* H, void* S, hipStream_t s) {
-  // Halves of tiles while all of them run at once: half the products per workgroup, but each operand read for
-  // half as many, so a half takes 0.73 of a tile's time (5-type cell of l_max 8: 120 tiles 67 us as halves, 81 whole;
-  // 136 tiles, 272 halves on 256 compute units, 96 and 84; 1128 tiles of another 289 and 253).
-  const bool halves = 2 * tiles <= num_cus;
-  const int num_wg = halves ? 2 * tiles : tiles;
+  // Quarters while there is one for every compute unit at most: half the products per workgroup, but each operand
+  // read for half as many (3-type cell of l_max 7: 28 tiles 44 us as quarters, 51 as halves; 66 tiles 59 and 57; 1128 tiles
+  // of a 2-type cell 253 and 224).
+  const bool quarters = 4 * tiles <= num_cus;
+  const int num_wg = (quarters ? 4 : 2) * tiles;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(num_wg), dim3(512), 0, s, c, one, many, nk, num_wg, gr, ws, H, S);
+    hipLaunchKernelGGL(kernel, dim3(num_wg), dim3(256), 0, s, c, one, many, nk, num_wg, gr, ws, H, S);
   };
-  if (halves) real ? go(k_fact_hs<1, true>) : go(k_fact_hs<1, false>);
+  if (quarters) real ? go(k_fact_hs<1, true>) : go(k_fact_hs<1, false>);
   else real ? go(k_fact_hs<2, true>) : go(k_fact_hs<2, false>);
   return hipGetLastError();
 }

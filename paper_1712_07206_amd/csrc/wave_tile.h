@@ -42,13 +42,13 @@ __device__ __forceinline__ const char* uniform(const char* p) {
   return (const char*)(((uintptr_t)hi << 32) | lo);
 }
 
-// LDS ring of a workgroup of eight waves: chunks of BYTES, copied straight there (global_load_lds_dwordx4) as
-// copies of 1 KB, copy 8 i + w of a chunk by wave w; STAGES - 1 chunks ahead, one barrier per chunk.
+// LDS ring of a workgroup: chunks of BYTES, copied straight there (global_load_lds_dwordx4) as copies of 1 KB, copy
+// WAVES i + w of a chunk by wave w; STAGES - 1 chunks ahead, one barrier per chunk.
 // The ring has to be the kernel's only __shared__ array: with several the compiler waits for every pending
 // copy before each read of one.
-template <int STAGES, int BYTES>
+template <int STAGES, int BYTES, int WAVES = 8>
 struct Ring {
-  static constexpr int stages = STAGES, chunk = BYTES, copies = BYTES / 8192, bytes = STAGES * BYTES;
+  static constexpr int stages = STAGES, chunk = BYTES, copies = BYTES / 1024 / WAVES, bytes = STAGES * BYTES;
   char* lds;
   int left;  // chunks not yet waited for
   int istage = 0, cstage = 0;
@@ -126,43 +126,49 @@ __device__ __forceinline__ void section(Ring& ring, int steps, bool active, Issu
     }
 }
 
-// One tile of 32 MI (G') x 64 (G) of the type-factored products on 2 x 4 waves of 16 MI x 16: MI = 2 the 64 x 64
-// blocks of the arrays, MI = 1 the upper or lower half of one.  A lane holds MI neighbouring rows, one for each of
-// its blocks: block i covers the rows of index i modulo MI.  Two waves per SIMD: at MI = 2 nine sums and operands
-// take 206 registers.
+// One tile of 32 MI (G') x 32 (G) of the type-factored products on 2 x 2 waves of 16 MI x 16: one half of the columns
+// and (MI = 1) one half of the rows of a 64 x 64 block of the arrays.  A lane holds MI neighbouring rows, one for
+// each of its blocks: block i covers the rows of index i modulo MI.  Two workgroups to a compute unit, one wave
+// of each per SIMD, so that one's waits at its barriers are the other's time.
 //
-// Chunks of 48 KB are 24 phase rows (E at G', EW at G), then 24 of the type's R rows (R at G'; lam R and Y at G; the
-// real form 32), contiguous runs of the block-major arrays; rows past a type's are copied but not used.
-// (Chunks of half that in twice the stages: the same at N_G = 12000, 3 to 15 % more where a type has fewer chunks.)
+// Chunks of 20 KB are 12 phase rows (E at G', EW at G), then 16 of the type's R rows (R at G'; lam R and Y at G; the
+// real form 20) out of the block-major arrays; rows past a type's are copied but not used.
 template <int MI, bool REAL>
 struct TypedTile {
-  static constexpr int RE = 24, RM = REAL ? 32 : 24;
-  typedef Ring<3, 48 * 1024> R;
+  static constexpr int RE = 12, RM = REAL ? 20 : 16;
+  typedef Ring<4, 20 * 1024, 4> R;
   static constexpr int lds_bytes = R::bytes;
+  // offsets in a stage: EW; lam R and Y, and the latter's row
+  static constexpr int at_b = RE * 1024, at_l = RM * 512, at_y = RM * 768, y_row = REAL ? 256 : 512;
   typedef typename DVec<MI>::T VA;
   const FactCell& c;
   const FactK& kk;
   const char* ws;
   R ring;
-  int bi, half, bj, t_end;
+  int bi, bj, part_i, part_j, t_end;
   int wave, lr, lk, arow, bcol;
-  // The next chunk to issue: its type, chunks left of the type's phases or rows; this wave's three copies of it: the
-  // phases' and rows' next sources, the rows' step per chunk and what it takes from the last to the next type's first.
+  // The next chunk to issue: its type, chunks left of the type's phases or rows; this wave's next sources: of E and EW;
+  // of R, lam R and Y (the real form's wave takes R or lam R in p1, lam R or Y in p2), and what takes them from the
+  // last chunk of a type to the next type's first.
   int it, n_left;
   bool irows = false;
-  const char *pa, *pb;               // E, EW
+  const char *pa, *pb;
   const char *p0, *p1, *p2, *p3;
+  unsigned off, off2, off4;  // a lane's offset in a copy: of whole rows of 1 KB, of halves of those, of halves of 512 bytes
   int adj, adj3;
 
   __device__ __forceinline__ TypedTile(const FactCell& cell, const FactK& k, const char* base, char* lds, int block_i,
-                           int which_half, int block_j, int t0, int t1)
-      : c(cell), kk(k), ws(base), bi(block_i), half(which_half), bj(block_j), t_end(t1), it(t0) {
+                                       int half_i, int block_j, int half_j, int t0, int t1)
+      : c(cell), kk(k), ws(base), bi(block_i), bj(block_j), part_i(half_i), part_j(half_j), t_end(t1), it(t0) {
     const int lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lr = lane & 15;
     lk = lane >> 4;
-    arow = half * 32 + (wave >> 2) * 16 * MI + MI * lr;
-    bcol = (wave & 3) * 16 + lr;
+    arow = part_i * 32 + (wave >> 1) * 16 * MI + MI * lr;
+    bcol = (wave & 1) * 16 + lr;
+    off = lane * 16;
+    off2 = (lane >> 5) * 1024 + (lane & 31) * 16;
+    off4 = (lane >> 4) * 512 + (lane & 15) * 16;
     ring.lds = lds;
     ring.left = 0;
     for (int t = t0; t < t1; ++t) ring.left += (c.nat[t] + RE - 1) / RE + (2 * c.n_l + RM - 1) / RM;
@@ -170,41 +176,44 @@ struct TypedTile {
     const int n_f = (2 * c.n_l + RM - 1) / RM;
     const int64_t ra = ((int64_t)bi * c.n_act + it) * c.Mr, rb = ((int64_t)bj * c.n_act + it) * c.Mr;
     const char* r = ws + kk.R + ra * 512;
-    const char* l = ws + kk.LR + rb * 512;
-    const char* y = ws + kk.Y + rb * (REAL ? 512 : 1024);
+    const char* l = ws + kk.LR + rb * 512 + part_j * 256;
+    const char* y = ws + kk.Y + rb * (REAL ? 512 : 1024) + part_j * y_row;
     p0 = uniform(r + wave * 1024);
-    p1 = REAL ? p0 : uniform(wave < 4 ? r + (wave + 8) * 1024 : l + (wave - 4) * 1024);
-    p2 = uniform(l + (REAL ? wave : wave + 4) * 1024);
-    p3 = uniform(y + wave * 1024);
+    if constexpr (REAL) {  // copies 0-9 of R (2 rows each), 10-14 of lam R, 15-19 of Y (4 rows each)
+      p1 = uniform(wave < 2 ? r + (8 + wave) * 1024 : l + (wave - 2) * 2048);
+      p2 = uniform(wave < 3 ? l + (2 + wave) * 2048 : y);
+      p3 = uniform(y + (1 + wave) * 2048);
+    } else {  // copies 0-7 of R, 8-11 of lam R (4 rows), 12-19 of Y (2 rows)
+      p2 = p1 = uniform(l + wave * 2048);
+      p3 = uniform(y + wave * 2048);
+    }
     adj = (c.Mr - n_f * RM) * 512;
     adj3 = adj * (REAL ? 1 : 2);
     phase_source();
     for (int i = 0; i < R::stages - 1; ++i) issue();
   }
   // First row and column of this wave's part (uniform).
-  __device__ __forceinline__ int row0() const { return bi * 64 + half * 32 + (wave >> 2) * 16 * MI; }
-  __device__ __forceinline__ int col0() const { return bj * 64 + (wave & 3) * 16; }
+  __device__ __forceinline__ int row0() const { return bi * 64 + part_i * 32 + (wave >> 1) * 16 * MI; }
+  __device__ __forceinline__ int col0() const { return bj * 64 + part_j * 32 + (wave & 1) * 16; }
   // Row of element q of block i, and the column, of this lane's sums.
   __device__ __forceinline__ int row(int i, int q) const { return row0() + MI * (lk + 4 * q) + i; }
-  __device__ __forceinline__ int col() const { return bj * 64 + bcol; }
+  __device__ __forceinline__ int col() const { return col0() + lr; }
 
   __device__ __forceinline__ void phase_source() {
     pa = uniform(ws + kk.E + ((int64_t)bi * c.e_rows + c.eoff[it]) * 1024 + wave * 1024);
-    pb = uniform(ws + kk.EW + ((int64_t)bj * c.e_rows + c.eoff[it]) * 1024 + wave * 1024);
+    pb = uniform(ws + kk.EW + ((int64_t)bj * c.e_rows + c.eoff[it]) * 1024 + part_j * 512 + wave * 2048);
   }
   __device__ __forceinline__ void issue() {
     if (it >= t_end) return;
     char* st = ring.stage(wave);
-    const unsigned off = (threadIdx.x & 63) * 16;
-    auto copy = [&](const char* p, int i) {
-      __builtin_amdgcn_global_load_lds((const void*)(p + off), (lds_ptr)(st + i * 8192), 16, 0, 0);
+    auto copy = [&](const char* p, unsigned o, int i) {
+      __builtin_amdgcn_global_load_lds((const void*)(p + o), (lds_ptr)(st + i * 4096), 16, 0, 0);
     };
     if (!irows) {
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        copy(pa + i * 8192, i);
-        copy(pb + i * 8192, i + 3);
-      }
+      for (int i = 0; i < 3; ++i) copy(pa + i * 4096, off, i);
+      copy(pb, off2, 3);
+      copy(pb + 8192, off2, 4);  // waves 2 and 3: two rows past the chunk's, to memory not read
       pa += RE * 1024;
       pb += RE * 1024;
       if (--n_left == 0) {
@@ -212,28 +221,22 @@ struct TypedTile {
         n_left = (2 * c.n_l + RM - 1) / RM;
       }
     } else {
+      copy(p0, off, 0);
+      copy(p0 + 4096, off, 1);
       if constexpr (REAL) {
-        copy(p0, 0);
-        copy(p0 + 8192, 1);
-        copy(p2, 2);
-        copy(p2 + 8192, 3);
-        copy(p3, 4);
-        copy(p3 + 8192, 5);
-        p0 += RM * 512;
-        p2 += RM * 512;
+        copy(p1, wave < 2 ? off : off4, 2);
+        copy(p2, off4, 3);
+        copy(p3, off4, 4);
+        p1 += RM * 512;
         p3 += RM * 512;
       } else {
-        copy(p0, 0);
-        copy(p1, 1);
-        copy(p2, 2);
-        copy(p3, 3);
-        copy(p3 + 8192, 4);
-        copy(p3 + 16384, 5);
-        p0 += RM * 512;
-        p1 += RM * 512;
-        p2 += RM * 512;
+        copy(p2, off4, 2);
+        copy(p3, off2, 3);
+        copy(p3 + 8192, off2, 4);
         p3 += RM * 1024;
       }
+      p0 += RM * 512;
+      p2 += RM * 512;
       if (--n_left == 0) {
         irows = false;
         if (++it < t_end) {
@@ -253,7 +256,7 @@ struct TypedTile {
     const d2* A = (const d2*)(st + (4 * s + lk) * 1024) + arow;
 #pragma unroll
     for (int i = 0; i < MI; ++i) x.a[i] = A[i];
-    x.b = ((const d2*)(st + (RE + 4 * s + lk) * 1024))[bcol];
+    x.b = ((const d2*)(st + at_b + (4 * s + lk) * 512))[bcol];
     return x;
   }
   // P_t = E_t^H E_t: three real products per complex one (P1 = a_r b_r, P2 = a_i b_i,
@@ -285,9 +288,9 @@ struct TypedTile {
   __device__ __forceinline__ Rows read_rows(const char* st, int s) const {
     Rows x;
     x.a = *(const VA*)((const double*)(st + (4 * s + lk) * 512) + arow);
-    x.l = ((const double*)(st + RM * 512 + (4 * s + lk) * 512))[bcol];
-    if constexpr (REAL) x.yr = ((const double*)(st + 2 * RM * 512 + (4 * s + lk) * 512))[bcol];
-    else x.y = ((const d2*)(st + 2 * RM * 512 + (4 * s + lk) * 1024))[bcol];
+    x.l = ((const double*)(st + at_l + (4 * s + lk) * 256))[bcol];
+    if constexpr (REAL) x.yr = ((const double*)(st + at_y + (4 * s + lk) * y_row))[bcol];
+    else x.y = ((const d2*)(st + at_y + (4 * s + lk) * y_row))[bcol];
     return x;
   }
   // m1 + i m2 = R_t^T Y_t (the real form: m1 only), F = R_t^T Lam_t R_t.

@@ -68,7 +68,7 @@ def test_basis_around_the_blocks(n_g):
     _check(_case((3, 1), 2, n_g))
 
 
-@pytest.mark.parametrize("n_g", [960, 961])  # 120 and 136 tiles: on both sides of the rule that halves them
+@pytest.mark.parametrize("n_g", [640, 641])  # 55 and 66 tiles: on both sides of the rule that cuts them in four
 def test_basis_around_the_tile_choice(n_g):
     _check(_case((2, 1), 2, n_g))
 

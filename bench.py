@@ -1,12 +1,14 @@
 #!/usr/bin/env python3
 """Throughput of the muffin-tin H+S build on one MI355X.
 
-One step = one hsbuild_forward call (matching coefficients, per-atom T
-products and the fused Hermitian H/S contraction) over the full-size
-synthetic cell: 4 atom types x 32 atoms, l_max = 10 (N_L = 121), N_G = 12000,
+One step = one hsbuild_forward call (radial and angular tables and phases, T
+products per atom type and the Hermitian H/S contraction, in the type-factored
+form the library runs by default) over the full-size synthetic cell: 4 atom types x 32 atoms, l_max = 10 (N_L = 121), N_G = 12000,
 complex128.  Inputs are resident in HBM before the timed region.  The value
-is FP64-equivalent TFLOP/s with the algorithmic flop count
-F = 16 k_c N_G (N_G + 1) + 32 N_atoms N_L^2 N_G  (k_c = N_atoms N_L).
+is FP64-equivalent TFLOP/s with the conventional flop count of the contraction
+over all atoms, F = 16 k_c N_G (N_G + 1) + 32 N_atoms N_L^2 N_G  (k_c =
+N_atoms N_L); the type-factored form executes fewer, and its own rate is the
+roofline's.
 
 Prints one JSON line on stdout; progress goes to stderr.
 """
@@ -153,12 +155,13 @@ def split_leg(args, case, b64, g, tau, T, H, S, ws, ms_fp64, flops) -> dict:
         eh = (torch.linalg.norm(hermitian_full(H) - H64) / torch.linalg.norm(H64)).item()
         es = (torch.linalg.norm(hermitian_full(S) - S64) / torch.linalg.norm(S64)).item()
         if precision in (HSB_SPLIT_CRT, HSB_SPLIT_CRT_BF16, HSB_SPLIT_CRT_FP16):
-            # residue-MFMA work of the two contraction launches (S and H): every 256 x 256 block of the
-            # upper triangle, the stacked rows padded to 64, per modulus two int8 products (P and Q,
-            # one workgroup each) x 2 operations
-            nbs = -(-n // 256)
-            k64 = -(-2 * case["n_atoms"] * case["n_l"] // 64) * 64
-            mfma_ops = 2.0 * nbs * (nbs + 1) * 256 * 128 * k64 * slices * 2 * 2
+            # residue-MFMA work of H: every 64 x 64 tile of the upper triangle and type, the type's 2 N_L
+            # rows padded to a matrix-core step, per modulus two products (real by complex) x 2
+            # operations; the phases and S run on the FP64 matrix cores in the same kernel
+            nb = -(-n // 64)
+            rows = 64 if precision == HSB_SPLIT_CRT else 32
+            k_t = -(-2 * case["n_l"] // rows) * rows
+            mfma_ops = nb * (nb + 1) / 2 * 64.0 * 64.0 * case["n_types"] * k_t * slices * 2 * 2
         else:
             # slice-MFMA work executed by the two contraction launches (S and H): every 128 x 64 tile
             # of the upper triangle, the stacked rows padded to 32, S(S+1)/2 slice pairs x 4 real
@@ -187,10 +190,10 @@ def split_leg(args, case, b64, g, tau, T, H, S, ws, ms_fp64, flops) -> dict:
 
     forms = []
     if args.crt_moduli > 0:  # "slices" of the residue form: its moduli; "slice_bits": bits per residue byte
-        forms.append(one("crt", HSB_SPLIT_CRT, args.crt_moduli, 8, 5000.0, "TOP/s", "k_hs_crt"))
+        forms.append(one("crt", HSB_SPLIT_CRT, args.crt_moduli, 8, 5000.0, "TOP/s", "k_fact_crt"))
     if args.crt16_moduli > 0:  # the residues as bfloat16 / half integers on the 16-bit matrix cores
-        forms.append(one("crt_bf16", HSB_SPLIT_CRT_BF16, args.crt16_moduli, 8, 2500.0, "TFLOP/s", "k_hs_crt"))
-        forms.append(one("crt_fp16", HSB_SPLIT_CRT_FP16, args.crt16_moduli, 8, 2500.0, "TFLOP/s", "k_hs_crt"))
+        forms.append(one("crt_bf16", HSB_SPLIT_CRT_BF16, args.crt16_moduli, 8, 2500.0, "TFLOP/s", "k_fact_crt"))
+        forms.append(one("crt_fp16", HSB_SPLIT_CRT_FP16, args.crt16_moduli, 8, 2500.0, "TFLOP/s", "k_fact_crt"))
     if args.int8_slices > 0:
         forms.append(one("int8", HSB_SPLIT_INT8, args.int8_slices, 7, 5000.0, "TOP/s", "k_hs_split8"))
     if args.split_slices > 0:
@@ -207,70 +210,75 @@ def split_leg(args, case, b64, g, tau, T, H, S, ws, ms_fp64, flops) -> dict:
     return out
 
 
-def factored_flops(case, mac_flops=8.0) -> tuple:
-    """Algorithmic flops of the type-factored forward: per upper-triangle entry and
-    type, N_t + 4 N_L complex multiply-adds (phases, H and S slots; mac_flops each:
-    8 in the conventional count, 6 as the 3M form executes them) and two complex
-    products folded in; plus the per-type T products.  Returns (contraction, total)."""
+def factored_flops(case, executed: bool = False) -> tuple:
+    """Flops of the type-factored forward.  Conventional: per upper-triangle entry and
+    type, N_t + 4 N_L complex multiply-adds (phases, H and S slots; 8 flops each) and two
+    complex products folded in; plus the per-type T products.  Executed: three real
+    multiply-adds per atom (the phases, 3M), three per row (H two, S one: the rows
+    are real) and 15 flops folded in.  Returns (contraction, total)."""
     n, n_l = case["n_g"], case["n_l"]
-    counts = [int((case["atom_type"] == t).sum()) for t in range(case["n_types"])]
-    per_entry = sum(mac_flops * (nt + 4 * n_l) + 16.0 for nt in counts if nt > 0)
-    contraction = per_entry * n * (n + 1) / 2.0
-    return contraction, contraction + 32.0 * sum(1 for nt in counts if nt > 0) * n_l * n_l * n
+    counts = [c for c in (int((case["atom_type"] == t).sum()) for t in range(case["n_types"])) if c > 0]
+    if executed:
+        contraction = sum(6.0 * nt + 12.0 * n_l + 15.0 for nt in counts) * n * (n + 1) / 2.0
+        return contraction, contraction + 16.0 * len(counts) * n_l * n_l * n
+    contraction = sum(8.0 * (nt + 4 * n_l) + 16.0 for nt in counts) * n * (n + 1) / 2.0
+    return contraction, contraction + 32.0 * len(counts) * n_l * n_l * n
 
 
-def factored_leg(args, case, g, tau, T, H, S, ms_fp64) -> dict:
-    """The type-factored forward (hsbuild_forward_factored) on the same workload:
-    time to solution, speedup over the stacked FP64 path and the relative
-    Frobenius error against its H and S (upper triangles)."""
+def stacked_leg(args, case, g, tau, T, H, S, ms_fp64) -> dict:
+    """The stacked FP64 contraction over all atoms (HSB_OPT_SPLIT_K = 0) on the same
+    workload: time per step, the default form's speedup over it and the relative
+    Frobenius error of the default form's H and S against it (upper triangles)."""
     import torch
 
     from paper_1712_07206_amd import _native as N
     from paper_1712_07206_amd.hsbuild import HSBuilder
     n = case["n_g"]
-    bf = HSBuilder.from_case(case)
-    wsb = bf.workspace_bytes(N.HSB_MODE_FACTORED, [n])
+    bs = HSBuilder.from_case(case)
+    bs.set_option(N.HSB_OPT_SPLIT_K, 0)
+    wsb = bs.workspace_bytes(N.HSB_MODE_FORWARD, [n])
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     H2 = torch.empty_like(H)
     S2 = torch.empty_like(S)
-    log("factored path: workspace %.2f GB" % (wsb / 1e9))
-    kf = case["k_frac"]
+    log("stacked path: workspace %.2f GB" % (wsb / 1e9))
 
-    for _ in range(max(1, args.warmup)):
-        bf.forward_factored(kf, g, tau, T, H2, S2, ws=ws)
+    def step():
+        code = bs.forward_raw(case["k_frac"], n, g, tau, T, H2, S2, ws, wsb)
+        if code != N.HSB_OK:
+            raise N.HSBuildError(code, N.last_error(bs._h))
+
+    step()
     torch.cuda.synchronize()
-    bf.set_timing(True)
+    bs.set_timing(True)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    reps = max(args.steps, 10)
+    reps = 3
     e0.record()
     for _ in range(reps):
-        bf.forward_factored(kf, g, tau, T, H2, S2, ws=ws)
+        step()
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
-    stage_ms, _ = bf.stage_times()
-    bf.set_timing(False)
-    Hu, Su = torch.triu(H), torch.triu(S)
-    eh = (torch.linalg.norm(torch.triu(H2) - Hu) / torch.linalg.norm(Hu)).item()
-    es = (torch.linalg.norm(torch.triu(S2) - Su) / torch.linalg.norm(Su)).item()
+    stage_ms, _ = bs.stage_times()
+    bs.set_timing(False)
+    Hu, Su = torch.triu(H2), torch.triu(S2)
+    eh = (torch.linalg.norm(torch.triu(H) - Hu) / torch.linalg.norm(Hu)).item()
+    es = (torch.linalg.norm(torch.triu(S) - Su) / torch.linalg.norm(Su)).item()
     del Hu, Su, H2, S2, ws
-    bf.close()
+    bs.close()
     torch.cuda.empty_cache()
-    fc, ft = factored_flops(case)
-    fx, _ = factored_flops(case, 6.0)  # as executed (3M form)
-    kt = fc / (stage_ms[2] * 1e-3) / 1e12
-    kx = fx / (stage_ms[2] * 1e-3) / 1e12
-    log("factored: %.3f ms/step (contraction %.3f ms, %.2f TFLOP/s on its own %.4g TFLOP), %.1fx faster than the "
-        "stacked FP64 path, rel err vs it H %.2e S %.2e" % (ms, stage_ms[2], kt, fc / 1e12, ms_fp64 / ms, eh, es))
-    return {"ms_per_step": round(ms, 4), "steps": reps, "speedup_vs_fp64": round(ms_fp64 / ms, 3),
-            "own_flops_per_step": ft, "own_tflops": round(ft / (ms * 1e-3) / 1e12, 4),
+    # three real products per complex one: 12 instead of 16 flops per stacked row and entry pair
+    fx = 12.0 * case["n_atoms"] * case["n_l"] * n * (n + 1)
+    rate = fx / (stage_ms[2] * 1e-3) / 1e12
+    log("stacked: %.3f ms/step (contraction %.3f ms, %.2f TFLOP/s executed); the default form %.1fx faster, its rel "
+        "err vs it H %.2e S %.2e" % (ms, stage_ms[2], rate, ms / ms_fp64, eh, es))
+    return {"ms_per_step": round(ms, 4), "steps": reps, "speedup_of_default": round(ms / ms_fp64, 3),
             "stages_ms": {"coefficients": round(stage_ms[0], 4), "t_products": round(stage_ms[1], 4),
-                          "fact_contraction": round(stage_ms[2], 4)},
-            "roofline": {"kernel": "k_hs_fact", "bound": "mfma", "achieved": round(kx, 4),
+                          "hs_contraction": round(stage_ms[2], 4)},
+            "roofline": {"kernel": "k_hs_fp64", "bound": "mfma", "achieved": round(rate, 4),
                          "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": round(kx / FP64_MFMA_PEAK_TFLOPS, 4), "algorithmic_flops_per_launch": fx,
-                         "complex_form": "3M", "fp64_equiv_tflops": round(kt, 4)},
-            "rel_err_vs_fp64": {"H": eh, "S": es}}
+                         "frac": round(rate / FP64_MFMA_PEAK_TFLOPS, 4), "algorithmic_flops_per_launch": fx,
+                         "complex_form": "3M"},
+            "rel_err_of_default": {"H": eh, "S": es}}
 
 
 def hsdla_leg(args, case, g, tau, T, H, S, ms_fp64) -> dict:
@@ -401,9 +409,9 @@ def real_leg(args) -> dict:
 
 def small_leg(args) -> dict:
     """One k-point of the 16-atom l_max 8 cell at N_G = 3000 (k_c = 1296): the whole
-    forward, its contraction against the FP64 MFMA roofline (executed 3M flops), in the
-    library's default stream-K form (600 tiles: fewer than 4 per compute unit), with the
-    stacked index in two segments, and in one pass."""
+    forward, its contraction against the FP64 MFMA roofline (executed flops), in the
+    library's default (type-factored) form, and in the stacked form with the
+    stacked index in two segments and in one pass."""
     import torch
 
     from flapw_cells import make_case
@@ -413,17 +421,15 @@ def small_leg(args) -> dict:
     n, n_at, n_l = case["n_g"], case["n_atoms"], case["n_l"]
     k_c = n_at * n_l
     flops = 16.0 * k_c * n * (n + 1) + 32.0 * n_at * n_l * n_l * n
-    flops_exec = 12.0 * k_c * n * (n + 1)
     b = HSBuilder.from_case(case)
     g, tau, T = case_tensors(case)
     H = torch.empty((n, n), dtype=torch.complex128, device="cuda")
     S = torch.empty_like(H)
     reps = max(10, 4 * args.steps)
-    out = {"workload": case["name"], "n_g": n, "k_c": k_c, "flops_per_step": flops,
-           "algorithmic_flops_per_launch": flops_exec}
-    # auto: the stream-K contraction (equal shares of (tile, chunk) units per workgroup); 2: the
-    # stacked index in two segments; 0: one pass
-    for mode, key in ((1, "split_k_auto"), (2, "segments_2"), (0, "one_pass")):
+    out = {"workload": case["name"], "n_g": n, "k_c": k_c, "flops_per_step": flops}
+    # 1: the type-factored form; stacked, 2: the stacked index in two segments; 0: one pass
+    for mode, key in ((1, "default"), (2, "segments_2"), (0, "one_pass")):
+        flops_exec = factored_flops(case, executed=True)[0] if mode == 1 else 12.0 * k_c * n * (n + 1)
         b.set_option(N.HSB_OPT_SPLIT_K, mode)
         wsb = b.workspace_bytes(N.HSB_MODE_FORWARD, [n])
         ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
@@ -449,8 +455,8 @@ def small_leg(args) -> dict:
         out[key] = {"ms_per_step": round(ms, 4), "tflops": round(flops / (ms * 1e-3) / 1e12, 4),
                     "stages_ms": {"coefficients": round(st[0], 4), "t_products": round(st[1], 4),
                                   "hs_contraction": round(st[2], 4), "segment_sum": round(st[3], 4)},
-                    "roofline": {"kernel": {1: "k_hs_fp64_stream", 2: "k_hs_fp64_sk", 0: "k_hs_fp64"}[mode],
-                                 "bound": "mfma",
+                    "roofline": {"kernel": {1: "k_fact_hs", 2: "k_hs_fp64_sk", 0: "k_hs_fp64"}[mode],
+                                 "bound": "mfma", "algorithmic_flops_per_launch": flops_exec,
                                  "achieved": round(achieved, 4), "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                                  "frac": round(achieved / FP64_MFMA_PEAK_TFLOPS, 4)}}
         log("N_G 3000 cell (%s): %.3f ms per forward, contraction %.3f ms = %.1f TFLOP/s executed (%.3f of peak), "
@@ -527,11 +533,11 @@ def batch_leg(args) -> dict:
     torch.cuda.synchronize()
     ms_graph = e0.elapsed_time(e1) / reps
     # sequential: one forward per k on the same stream, outputs written in place, with the
-    # library's default (stream-K on these small bases) and with the one-pass form
+    # library's default (type-factored) and with the stacked one-pass form
     outs = [(H[int(off[k]): int(off[k]) + ng[k] ** 2].view(ng[k], ng[k]),
              S[int(off[k]): int(off[k]) + ng[k] ** 2].view(ng[k], ng[k])) for k in range(n_k)]
     seq = {}
-    for mode, key in ((1, "split_k_auto"), (0, "one_pass")):
+    for mode, key in ((1, "default"), (0, "one_pass")):
         b.set_option(N.HSB_OPT_SPLIT_K, mode)
         wsb = max(b.workspace_bytes(N.HSB_MODE_FORWARD, [n]) for n in ng)  # the split's partials vary with n
         ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
@@ -551,7 +557,7 @@ def batch_leg(args) -> dict:
         torch.cuda.synchronize()
         seq[key] = e0.elapsed_time(e1) / reps
         del ws
-    ms_seq = seq["split_k_auto"]
+    ms_seq = seq["default"]
     log("batch %d k-points: graph %.3f ms, sequential %.3f ms (one-pass %.3f ms), speedup %.3f (%.3f), %.2f TFLOP/s"
         % (n_k, ms_graph, ms_seq, seq["one_pass"], ms_seq / ms_graph, seq["one_pass"] / ms_graph,
            flops / (ms_graph * 1e-3) / 1e12))
@@ -600,18 +606,32 @@ def adjoint_leg(args) -> dict:
     torch.cuda.empty_cache()
     return {"workload": case["name"], "n_g": n, "ms_per_backward": round(ms, 4), "flops": flops,
             "fp64_equiv_tflops": round(flops / (ms * 1e-3) / 1e12, 4),
-            "note": "conventional flop count; the products P_H, P_S run in the 3M form (6 flops per complex "
-                    "multiply-add)"}
+            "note": "conventional flop count of the products over all atoms; the type-factored form executes fewer"}
 
 
-def coefficient_leg(case, ms_coef: float) -> dict:
-    """The coefficient build (a1-a5, ending in the W write) as an HBM-bound
-    stage: algorithmic bytes 2 k_c N_G x 16 (the coefficients written once)
-    over the forward's coefficient stage time, against 8 TB/s and against a
+def coefficient_leg(case, g, tau) -> dict:
+    """The coefficient build (hsbuild_coefficients: tables and k_assemble, ending in the
+    write of A and B) as an HBM-bound call: algorithmic bytes 2 k_c N_G x 16 (the
+    coefficients written once) over its time, against 8 TB/s and against a
     timed 2 GiB device-to-device copy (its read and its write both counted)."""
     import torch
+
+    from paper_1712_07206_amd.hsbuild import HSBuilder
     k_c = case["n_atoms"] * case["n_l"]
     alg = 2.0 * k_c * case["n_g"] * 16
+    b = HSBuilder.from_case(case)
+    out = b.coefficients(case["k_frac"], g, tau)
+    torch.cuda.synchronize()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(5):
+        b.coefficients(case["k_frac"], g, tau, out)
+    e1.record()
+    torch.cuda.synchronize()
+    ms_coef = e0.elapsed_time(e1) / 5
+    del out
+    b.close()
+    torch.cuda.empty_cache()
     size = 2 << 30
     src = torch.empty(size, dtype=torch.uint8, device="cuda")
     src.fill_(1)
@@ -633,7 +653,7 @@ def coefficient_leg(case, ms_coef: float) -> dict:
     ach = alg / (ms_coef * 1e-3) / 1e9
     log("coefficient build: %.3f ms, %.0f GB/s (%.1f %% of 8 TB/s, %.1f %% of a %.0f GB/s copy)"
         % (ms_coef, ach, 100 * ach / 8000.0, 100 * ach / copy_gbs, copy_gbs))
-    return {"stage": "a1-a5: tables, lambda and k_assemble (the W write)", "ms": round(ms_coef, 4),
+    return {"stage": "hsbuild_coefficients: tables and k_assemble (the write of A and B)", "ms": round(ms_coef, 4),
             "algorithmic_bytes": alg, "achieved_gbs": round(ach, 1), "peak_gbs": 8000.0,
             "frac": round(ach / 8000.0, 4), "copy_gbs": round(copy_gbs, 1), "frac_of_copy": round(ach / copy_gbs, 4),
             "copy": "2 GiB device-to-device, read and write both counted"}
@@ -776,7 +796,8 @@ def main() -> int:
                     help="run the autotuner before timing (default: the library's default options)")
     ap.add_argument("--waves", type=int, default=0, help="contraction waves per workgroup (4 or 8; skips tuning)")
     ap.add_argument("--tile-group", type=int, default=None, help="contraction tile order (skips tuning)")
-    ap.add_argument("--no-factored", action="store_true", help="skip the type-factored leg")
+    ap.add_argument("--no-stacked", "--no-factored", action="store_true",
+                    help="skip the comparison with the stacked FP64 contraction")
     ap.add_argument("--no-hsdla", action="store_true", help="skip the rocBLAS HSDLA baseline leg")
     ap.add_argument("--no-real", action="store_true", help="skip the real-symmetric (inversion) leg")
     ap.add_argument("--no-small", action="store_true", help="skip the one-k-point N_G 3000 leg (16-atom cell)")
@@ -876,11 +897,11 @@ def main() -> int:
     log("timed %d steps: %.3f ms/step (wall %.3f s); stages ms: coef %.3f, tprod %.3f, hs %.3f over %d calls"
         % (args.steps, ms_step, wall, stage_ms[0], stage_ms[1], stage_ms[2], calls))
     tflops = flops / (ms_step * 1e-3) / 1e12
-    # The 8-wave contraction forms each complex product from three real ones
-    # (12 instead of 16 flops per stacked row and upper-triangle entry pair), the
-    # 4-wave one from four: the roofline prices the kernel on the products it
-    # has to execute, the headline on the conventional count.
-    flops_hs_exec = (12.0 if options["waves"] == 8 else 16.0) * k_c * n * (n + 1)
+    # The roofline prices the kernel on the operations it has to execute, the headline on the
+    # conventional count of the contraction over all atoms.  HSB_OPT_HS_WAVES = 4 pins the stacked
+    # contraction (four real products per complex one).
+    factored = options["waves"] == 8
+    flops_hs_exec = factored_flops(case, executed=True)[0] if factored else 16.0 * k_c * n * (n + 1)
     hs_tflops = flops_hs_exec / (stage_ms[2] * 1e-3) / 1e12
     hs_equiv = flops_hs / (stage_ms[2] * 1e-3) / 1e12
 
@@ -901,17 +922,19 @@ def main() -> int:
         "config": {"workload": case["name"], "n_atoms": n_at, "n_types": case["n_types"], "l_max": case["l_max"],
                    "n_l": n_l, "n_g": n, "k_c": k_c, "precision": "fp64", "flops_per_step": flops},
         "pct_fp64_mfma_peak": round(100.0 * tflops / FP64_MFMA_PEAK_TFLOPS, 2),
-        "pct_note": "FP64-equivalent rate (conventional 8-flop complex multiply-add count) over the FP64 MFMA "
-                    "peak; the 3-product complex form lets it pass 100%",
+        "pct_note": "FP64-equivalent rate (conventional count of the contraction over all atoms, 8 flops per complex "
+                    "multiply-add) over the FP64 MFMA peak; the type-factored form executes about 1/70 of "
+                    "those operations, at the rate under roofline",
         "contraction_options": options,
         "stages_ms": {"coefficients": round(stage_ms[0], 4), "t_products": round(stage_ms[1], 4),
                       "hs_contraction": round(stage_ms[2], 4), "segment_sum": round(stage_ms[3], 4)},
-        "roofline": {"kernel": "k_hs_fp64", "bound": "mfma", "achieved": round(hs_tflops, 4),
+        "roofline": {"kernel": "k_fact_hs" if factored else "k_hs_fp64", "bound": "mfma",
+                     "achieved": round(hs_tflops, 4),
                      "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(hs_tflops / FP64_MFMA_PEAK_TFLOPS, 4),
                      "traffic": recorded_traffic(case["name"], options),
                      "algorithmic_flops_per_launch": flops_hs_exec,
-                     "complex_form": "3M" if options["waves"] == 8 else "4M",
+                     "complex_form": "type-factored" if factored else "4M",
                      "fp64_equiv_tflops": round(hs_equiv, 4)},
         "split_speedup": None,
         "paper_context": {
@@ -922,9 +945,9 @@ def main() -> int:
                                "TiO2 (61%), whole H/S build",
         },
     }
-    result["coefficient_build"] = coefficient_leg(case, stage_ms[0])
-    if not args.no_factored:
-        result["factored"] = factored_leg(args, case, g, tau, T, H, S, ms_step)
+    result["coefficient_build"] = coefficient_leg(case, g, tau)
+    if not args.no_stacked:
+        result["stacked"] = stacked_leg(args, case, g, tau, T, H, S, ms_step)
     if not args.no_hsdla:
         result["hsdla_rocblas"] = hsdla_leg(args, case, g, tau, T, H, S, ms_step)
     if args.split_slices > 0 or args.int8_slices > 0 or args.fp16_slices > 0 or args.crt_moduli > 0 or \

@@ -23,7 +23,7 @@
 // k_fact_hs runs on v_mfma_f64_16x16x4f64 with its operands fed through LDS (TypedTile in wave_tile.h), two
 // workgroups of 64 x 32 outputs to a compute unit; R, lam R, Y and E are block-major, so that what a tile reads of an
 // array lies together.
-// Bound by the FP64 matrix cores: at N_G = 12000, 128 atoms, l_max = 10 they are busy for 81 % of its 7.8 ms (at
+// Bound by the FP64 matrix cores: at N_G = 12000, 128 atoms, l_max = 10 they are busy for 80 % of its 7.8 ms (at
 // 2.3 GHz); the rest is waits at the ring's barriers and the copies.  One workgroup of 64 x 64 on eight waves took 8.3 ms;
 // with its copies and their address arithmetic right behind the barrier 8.9; with a wave's row and column not
 // known to be uniform, so that the ring ran on vector registers, 9.9; and 64 x 64 on 2 x 2 waves with operands read

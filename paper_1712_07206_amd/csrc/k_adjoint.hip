@@ -22,8 +22,9 @@
 // Deterministic: fixed orders, no atomics.
 // At N_G = 6000, 64 atoms in two types, l_max = 10 (3.9 ms): k_adj_zq 2.3 ms, 71 % of it the matrix cores' time, the rest
 // the 2.3 GB of Z and Q it writes, the reads of gH and gS and the ring's waits (2.6 ms with one type per workgroup and
-// rows of n_pad); k_adj_uc 1.6 ms, 72 % (the same with operands straight in registers; 67 and 61 us at N_G = 801 in
-// 3 types); k_adj_gt 0.07 ms.
+// rows of n_pad); k_adj_uc 1.55 ms, of which its products take 1.15 at a large matrix product's rate (1.73 ms with one
+// workgroup of 64 columns G on eight waves to a compute unit; at N_G = 801 in 3 types, where the tiles are fewer than
+// the compute units, 37 and 61 us); k_adj_gt 0.07 ms.
 #include <type_traits>
 
 #include "harmonics.h"
@@ -126,20 +127,22 @@ __device__ __forceinline__ void product_cr(const d2* __restrict__ A, const doubl
   }
 }
 
-// Workgroups blockIdx.x < nu: 64 x 64 tiles of UT[G][k] = sum_G' Z[G'][G] RT[G'][k], waves of 32 x 16; nu2 more: the
+// Workgroups blockIdx.x < nu: 32 (G) x 64 tiles of UT[G][k] = sum_G' Z[G'][G] RT[G'][k], waves of 32 x 16; nu2 more: the
 // last, partly empty ones in k.  With one or two blocks of 16 k the waves of one column of blocks take every fourth
 // or second step, and their sums are added in the end, so that such a tile takes a quarter or half of the time.
-// Past them: the phase sums of 64 columns G and 32 atoms over a segment of G', waves of 16 x 16:
+// Past them: the phase sums of 32 columns G and 32 atoms over a segment of G', waves of 16 x 16:
 // D[G][a] = sum_G' Q[G'][G] conj(ET[G'][a]) (three real products: P1 = q_r e_r, P2 = q_i e_i,
 // P3 = (q_r + q_i)(e_r - e_i), Re = P1 + P2, Im = P3 - P1 + P2), then sum_G K_G Im(E_a(G) D[G][a])
 // over the wave's columns into part[seg][16 columns][phase row][3].
 // Types over the slowest index, so the largest tiles come first and the smaller fill up the end.
-// Operands through an LDS ring in chunks of 32 G' (32 KB of Z or Q, 16 KB of RT or ET, each one run); the tiles of one
-// 64 G on one XCD, which then reads that part of Z from memory once.
-__global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj ad, int t0, int nu, int nu2, int nab,
+// Operands through an LDS ring in chunks of 16 G' (8 KB of Z or Q, half of each row of a block; 8 KB of RT or ET, one
+// run); two workgroups to a compute unit, one's waits being the other's time.  32 columns G rather than 32 k, since Z has
+// twice the bytes.  Three workgroups with three stages: the same.  The tiles of one 32 G on one XCD, which then reads
+// that part of Z from memory once.
+__global__ void __launch_bounds__(256, 2) k_adj_uc(FactCell c, FactK kk, FactAdj ad, int t0, int nu, int nu2, int nab,
                                                    const char* __restrict__ ws, const d2* __restrict__ Z,
                                                    const d2* __restrict__ Q) {
-  typedef Ring<3, 48 * 1024> R;
+  typedef Ring<4, 16 * 1024, 4> R;
   __shared__ __align__(16) char lds[R::bytes];
   const int64_t np = kk.n_pad;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -150,64 +153,65 @@ __global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj
   int start, len;
   xcd_range((blockIdx.x - first) % kXcds, num, start, len);
   const int w = start + (blockIdx.x - first) / kXcds;
-  // type (slowest), 64 columns G, segment, block of k or of atoms
+  // type (slowest), 32 columns G, segment, block of k or of atoms
   const int full = c.n_l / 32;  // full 64-wide blocks of the 2 N_L k
   const int per = !is_u ? nab : (int)blockIdx.x < nu ? full : 1, segs = is_u ? 1 : ad.nseg;
   const int blk = (int)blockIdx.x >= nu && is_u ? full : w % per;
-  const int seg = w / per % segs, gb = w / per / segs % (kk.n_pad / 64), y = w / per / segs / (kk.n_pad / 64);
+  const int seg = w / per % segs, gb = w / per / segs % (kk.n_pad / 32), y = w / per / segs / (kk.n_pad / 32);
   const int t = t0 + y;
   if (!is_u && blk * 32 >= c.nat[t]) return;
-  const int nch = kk.n_pad / 32;
+  const int nch = kk.n_pad / 16;
   const int c0 = is_u ? 0 : (int)((int64_t)nch * seg / ad.nseg);
   const int c1 = is_u ? nch : (int)((int64_t)nch * (seg + 1) / ad.nseg);
-  const char* pa = uniform((const char*)((is_u ? Z : Q) + (((int64_t)y * (np / 64) + gb) * np + c0 * 32) * 64) +
-                           wave * 1024);
+  const char* pa = uniform((const char*)((is_u ? Z : Q) + (((int64_t)y * (np / 64) + gb / 2) * np + c0 * 16) * 64 +
+                                         gb % 2 * 32) + wave * 2048);
   const char* pb = uniform(ws + (is_u ? ad.RT + ((int64_t)t * (ad.Mt / 64) + blk) * np * 512
-                                      : ad.ET + ((int64_t)(ad.etb[t] + blk) * np + c0 * 32) * 512) +
+                                      : ad.ET + ((int64_t)(ad.etb[t] + blk) * np + c0 * 16) * 512) +
                            wave * 1024);
   R ring{lds, c1 - c0};
+  const unsigned half = (lane >> 5) * 1024 + (lane & 31) * 16;  // of two rows of 512 bytes in rows of 1 KB
   int issued = c0;
   auto issue = [&]() {
     if (issued == c1) return;
     ++issued;
     char* st = ring.stage(wave);
-    auto copy = [&](const char* p, int i) {
-      __builtin_amdgcn_global_load_lds((const void*)(p + lane * 16), (lds_ptr)(st + i * 8192), 16, 0, 0);
+    auto copy = [&](const char* p, unsigned off, int i) {
+      __builtin_amdgcn_global_load_lds((const void*)(p + off), (lds_ptr)(st + i * 4096), 16, 0, 0);
     };
-#pragma unroll
-    for (int i = 0; i < 4; ++i) copy(pa + i * 8192, i);
-    copy(pb, 4);
-    copy(pb + 8192, 5);
-    pa += 32 * 1024;
-    pb += 16 * 1024;
+    copy(pa, half, 0);
+    copy(pa + 8192, half, 1);
+    copy(pb, lane * 16, 2);
+    copy(pb + 4096, lane * 16, 3);
+    pa += 16 * 1024;
+    pb += 8 * 1024;
   };
   for (int i = 0; i < R::stages - 1; ++i) issue();
   if (is_u) {
     const int k16 = (2 * c.n_l + 15) / 16 - 4 * blk;       // blocks of 16 k left
     const int cols = k16 == 1 ? 1 : k16 == 2 ? 2 : 4;      // wave columns
-    const int turns = 4 / cols, turn = (wave & 3) / cols;  // this wave's steps: s = turn mod turns
-    const int arow = (wave >> 2) * 32 + 2 * lr, bcol = (wave & 3) % cols * 16 + lr;
+    const int turns = 4 / cols, turn = wave / cols;  // this wave's steps: s = turn mod turns
+    const int bcol = wave % cols * 16 + lr;
     d4 re[2], im[2];
     clear(re);
     clear(im);
     struct Ops { d2 a[2]; double b; };
     auto run = [&](auto per) {  // steps of a chunk per wave
-      constexpr int PER = decltype(per)::value, TURNS = 8 / PER;
+      constexpr int PER = decltype(per)::value, TURNS = 4 / PER;
       section<PER, 2>(
           ring, PER * nch, true, issue,
           [&](const char* st, int s) {
             const int r = 4 * (s * TURNS + turn) + lk;
-            const d2* A = (const d2*)(st + r * 1024) + arow;
-            return Ops{{A[0], A[1]}, ((const double*)(st + 32 * 1024 + r * 512))[bcol]};
+            const d2* A = (const d2*)(st + r * 512) + lr;
+            return Ops{{A[0], A[16]}, ((const double*)(st + 8 * 1024 + r * 512))[bcol]};
           },
           [&](const Ops& o, int i) {
             re[i] = MFMA(o.a[i].x, o.b, re[i]);
             im[i] = MFMA(o.a[i].y, o.b, im[i]);
           });
     };
-    if (turns == 1) run(std::integral_constant<int, 8>{});
-    else if (turns == 2) run(std::integral_constant<int, 4>{});
-    else run(std::integral_constant<int, 2>{});
+    if (turns == 1) run(std::integral_constant<int, 4>{});
+    else if (turns == 2) run(std::integral_constant<int, 2>{});
+    else run(std::integral_constant<int, 1>{});
     if (turns > 1) {  // all copies have landed: the ring's memory is free once everyone is here
       __syncthreads();
       double* mine = (double*)lds + wave * 1024 + lane;
@@ -231,12 +235,11 @@ __global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj
           }
       }
     }
-    d2* U = (d2*)(ws + ad.UT) +
-            (((int64_t)y * (ad.Mt / 64) + blk) * np + gb * 64 + (wave >> 2) * 32) * 64 + bcol;
+    d2* U = (d2*)(ws + ad.UT) + (((int64_t)y * (ad.Mt / 64) + blk) * np + gb * 32) * 64 + bcol;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) U[(2 * (lk + 4 * q) + i) * 64] = d2{re[i][q], im[i][q]};
+      for (int q = 0; q < 4; ++q) U[(16 * i + lk + 4 * q) * 64] = d2{re[i][q], im[i][q]};
     return;
   }
   const int row = (wave >> 1) * 16, col = (wave & 1) * 16 + lr;
@@ -245,24 +248,24 @@ __global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj
   clear(p2);
   clear(p3);
   struct Ops { d2 a, b; };
-  section<8, 1>(
-      ring, 8 * (c1 - c0), true, issue,
+  section<4, 1>(
+      ring, 4 * (c1 - c0), true, issue,
       [&](const char* st, int s) {
-        return Ops{((const d2*)(st + (4 * s + lk) * 1024))[row + lr],
-                   ((const d2*)(st + 32 * 1024 + (4 * s + lk) * 512))[col]};
+        return Ops{((const d2*)(st + (4 * s + lk) * 512))[row + lr],
+                   ((const d2*)(st + 8 * 1024 + (4 * s + lk) * 512))[col]};
       },
       [&](const Ops& o, int) {
         p1[0] = MFMA(o.a.x, o.b.x, p1[0]);
         p2[0] = MFMA(o.a.y, o.b.y, p2[0]);
         p3[0] = MFMA(o.a.x + o.a.y, o.b.x - o.b.y, p3[0]);
       });
-  // lane: atom 32 blk + col, columns G = 64 gb + row + lk + 4 q; pads of E are zero
+  // lane: atom 32 blk + col, columns G = 32 gb + row + lk + 4 q; pads of E are zero
   const double* kv = (const double*)(ws + kk.kv);
   const d2* ET = (const d2*)(ws + ad.ET) + (int64_t)(ad.etb[t] + blk) * np * 32 + col;
   double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int64_t G = gb * 64 + row + lk + 4 * q;
+    const int64_t G = gb * 32 + row + lk + 4 * q;
     const d2 e = ET[G * 32];
     const double re = p1[0][q] + p2[0][q], im = p3[0][q] - p1[0][q] + p2[0][q];
     const double s = e.x * im + e.y * re;
@@ -278,7 +281,7 @@ __global__ void __launch_bounds__(512, 2) k_adj_uc(FactCell c, FactK kk, FactAdj
   const int a = blk * 32 + col;
   if (lk == 0 && a < c.nat[t]) {
     double* part =
-        (double*)(ws + ad.partTau) + (((int64_t)seg * ad.ngb + gb * 4 + (wave >> 1)) * c.e_rows + c.eoff[t] + a) * 3;
+        (double*)(ws + ad.partTau) + (((int64_t)seg * ad.ngb + gb * 2 + (wave >> 1)) * c.e_rows + c.eoff[t] + a) * 3;
     part[0] = v[0];
     part[1] = v[1];
     part[2] = v[2];
@@ -378,11 +381,11 @@ hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int
 
 hipError_t launch_adj_uc(const FactCell& c, const FactK& kk, const FactAdj& ad, int t0, int nt, char* ws,
                          const double2* Z, const double2* Q, hipStream_t s) {
-  const int nb = kk.n_pad / 64;
+  const int nb = kk.n_pad / 32;
   int nab = 0;
   for (int t = t0; t < t0 + nt; ++t) nab = nab > (c.nat[t] + 31) / 32 ? nab : (c.nat[t] + 31) / 32;
   const int nu = nt * nb * (c.n_l / 32), nu2 = c.n_l % 32 ? nt * nb : 0;
-  hipLaunchKernelGGL(k_adj_uc, dim3(nu + nu2 + nt * nb * ad.nseg * nab), dim3(512), 0, s, c, kk, ad, t0, nu, nu2, nab, ws,
+  hipLaunchKernelGGL(k_adj_uc, dim3(nu + nu2 + nt * nb * ad.nseg * nab), dim3(256), 0, s, c, kk, ad, t0, nu, nu2, nab, ws,
                      (const d2*)Z, (const d2*)Q);
   return hipGetLastError();
 }

@@ -107,9 +107,10 @@ __device__ __forceinline__ void section(Ring& ring, int steps, bool active, Issu
   for (int i = 1; i < chunks; ++i) {
 #pragma unroll
     for (int s = 0; s < PER; ++s) {
+      if (PER == 1) issue();  // arrive() counts on one issue before it
       if (s == PER - 1) st = ring.arrive();
       x = step(x, st, s == PER - 1 ? 0 : s + 1);
-      if (s == 0) issue();
+      if (PER > 1 && s == 0) issue();
     }
   }
   const int rest = steps - (chunks - 1) * PER;

@@ -295,7 +295,7 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
 /* Tuning options (performance only).
  * HSB_OPT_TILE_GROUP: order in which the upper-triangle tiles of every
  * contraction are dealt to the compute units: 0 = row-major, g > 0 = super-rows
- * (128 rows; 64 or 32 for the factored kernel) taken g at a time, column by column
+ * (128 rows; 64 in the type-factored form) taken g at a time, column by column
  * (0..64; default 8, or 4 on a handle with a split precision).  Results are
  * bitwise independent of it.
  * HSB_OPT_HS_WAVES: waves per workgroup of the stacked FP64 contraction, 4 (64 x 32

@@ -17,7 +17,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libhsbuild.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-SOURCES = ["hsbuild.cpp", "k_coef.hip", "k_tprod.hip", "k_hs.hip", "k_adjoint.hip", "k_split.hip", "k_fact.hip",
+SOURCES = ["hsbuild.cpp", "k_coef.hip", "k_tprod.hip", "k_hs.hip", "k_adjoint.hip", "k_adjoint_stacked.hip", "k_split.hip", "k_fact.hip",
            "k_fact_crt.hip", "hsdla_blas.cpp", "k_probe.hip", "k_crt.hip", "k_herm.hip"]
 ARCH = "gfx950"
 FLAGS = [

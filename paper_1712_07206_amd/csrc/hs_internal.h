@@ -51,12 +51,15 @@ struct Layout {
   int n = 0, n_pad = 0, K = 0, K_pad = 0;
   size_t W = 0, Y = 0, ang = 0, ab = 0, kv = 0, lam = 0, consts = 0, end = 0;
   size_t stacked_end = 0;  // forward: the stacked form's part of `end`
-  bool factored = false;   // forward: run the type-factored form
+  bool factored = false;   // forward, backward: run the type-factored form
   size_t WL = 0;  // lam W (the FP64 contraction's S operand), forward in FP64 only
   int ns = 1;              // FP64 forward: segments of the stacked index (split contraction when > 1)
   int nsh = 0;             // FP64 forward: workgroups of the stream-K contraction (0: not used)
   size_t skH = 0, skS = 0;  // partial H and S: per segment (ns > 1), or the stream-K slots (nsh > 0)
+  size_t PH = 0, PS = 0, partT = 0, partTau = 0;  // stacked adjoint only
+  size_t WT = 0, gHp = 0, gSp = 0;                // stacked adjoint: operands of the 3M products
   size_t TT = 0;                                  // T^T per type, zero-padded (T products)
+  int Kt = 0;                                     // stacked adjoint: K_pad rounded up to 128
   int K_pad2 = 0;                                  // split only: stacked rows padded to 32
   size_t mx = 0, scale = 0, slL = 0, slS = 0, slY = 0;  // split only (slL, slS, slY: residue planes in the CRT form)
   int K64 = 0, n_res = 0;                              // residue form: rows padded to 64, columns to 256
@@ -323,7 +326,25 @@ hipError_t launch_conj(double2* a, int64_t count, hipStream_t s);
 hipError_t launch_mirror(int n, double2* H, double2* S, hipStream_t s);
 hipError_t launch_hermitian_part(int n, const double2* gH, const double2* gS, double2* oH, double2* oS, hipStream_t s);
 
-// ---- adjoint (one k-point; active types t0 .. t0 + nt - 1) ----
+// ---- stacked adjoint (k_adjoint_stacked.hip) ----
+int gradtau_blocks(int n);
+// P_H = W gH and P_S = W gS ([K_pad][n_pad]) in the 3M form from W^T ([n_pad][Kt], Kt a multiple
+// of 128, zeros past K_pad) and gS, gH zero-padded to [n_pad][n_pad].
+hipError_t launch_pgemm3m(const double2* WT, const double2* gSp, const double2* gHp, int Kt, int K_pad, int n_pad,
+                          double2* PH, double2* PS, hipStream_t s);
+// WT[G][k] = W[k][G] (k < K_pad), 0 for K_pad <= k < Kt.
+hipError_t launch_transpose(const double2* W, int K_pad, int n_pad, int Kt, double2* WT, hipStream_t s);
+// gp = g ([n][n]) zero-padded to [n_pad][n_pad].
+hipError_t launch_pad_square(const double2* g, int n, int n_pad, double2* gp, hipStream_t s);
+// gT[t] = sum over atoms of type t of P_H,a W_a^H (part: [n_atoms][2N_L][2N_L] scratch).
+hipError_t launch_gradT(const CellArgs& c, const double2* PH, const double2* W, int n_pad, double2* part,
+                        double2* gT, hipStream_t s);
+// gtau[a] = -2 sum_G K_G Im c_a(G) (part: [n_atoms][gradtau_blocks(n)][3] scratch).
+hipError_t launch_gradtau(const CellArgs& c, const double2* PH, const double2* PS, const double2* Y,
+                          const double2* W, const double* lam, const double* kv, int n, int n_pad, double* part,
+                          double* gtau, hipStream_t s);
+
+// ---- type-factored adjoint (one k-point; active types t0 .. t0 + nt - 1) ----
 // Z, Q: complex, block-major [nt][n_pad / 64][n_pad][64].
 hipError_t launch_adj_zq(const FactCell& c, const FactK& kk, int t0, int nt, int num_cus, const double2* gH,
                          const double2* gS, const char* ws, double2* Z, double2* Q, hipStream_t s);

@@ -233,6 +233,33 @@ AdjointPlan adjoint_plan(const hsbuild_s& h, int ng) {
   return p;
 }
 
+// Whether the stacked adjoint (k_adjoint_stacked.hip) takes less time than the type-factored one: a product with the rows of
+// all atoms against, for every type, two N_G x N_G matrices to and from memory and several kernels one after the other.
+// The estimates (microseconds) are fits to both on 462 cells of 2 to 16 types of 1, 2 and 4 atoms, l_max 0 to 10, N_G 100 to
+// 5000, within 25 and 35 % of the measurements, 5 and 10 % in the mean.  Stacked: a round of its 128 x 64 tiles over the
+// compute units is a pass over N_G.  Factored: the launches and the chunks of rows of each pass over the types (`rounds`
+// of its tiles over the compute units), Z and Q of every type, and the products with them.  The smaller one was the
+// faster, or within 5 % of it, in all cells but 7, and there up to 25 % slower.  16 types of one atom, l_max = 4, N_G = 100 /
+// 1500 / 5000: stacked 0.21 / 1.06 / 7.6 ms, factored 0.38 / 1.59 / 11.0; 4 types of one atom, l_max = 8, N_G = 4000: 4.5 and
+// 2.7.
+bool adjoint_stacked(const hsbuild_s& h, int ng, const AdjointPlan& p) {
+  const double cus = std::max(1, h.num_cus), m = 2.0 * h.n_l;
+  const double k = (double)h.n_atoms * m;
+  const double n128 = (double)round_up(ng, 128), kt = (double)round_up(stacked_pad((int)k), 128);
+  const double stacked =
+      39.0 + 0.169 * n128 + 0.386 * std::ceil(n128 / 64.0 * (kt / 128.0) / cus) * n128 + 1.49 * m + 5.94e-5 * k * n128;
+  const double n = p.f.n_pad, nb = n / 64.0;
+  double factored = 26.4;
+  for (int t0 = 0; t0 < p.c.n_act; t0 += p.pass) {
+    const int nt = std::min(p.pass, p.c.n_act - t0);
+    double chunks = p.c.Mr / 16.0;  // and the phases' past the first
+    for (int t = t0; t < t0 + nt; ++t) chunks = std::max(chunks, p.c.Mr / 16.0 + (p.c.nat[t] - 1) / 12);
+    const double rounds = std::max(1.0, 4.0 * nb * nb * nt / (4.0 * cus));
+    factored += 14.2 + 1.50 * rounds * chunks + 0.0108 * n + nt * n * n * (1.13e-5 + 7.54e-8 * p.ad.Mt);
+  }
+  return stacked < factored;
+}
+
 // Blocks per wave side of Y = T' R over `cols` columns: 64 x 64 workgroups where they are two for every
 // compute unit, else 32 x 32 (282 of the larger, N_G = 3000: 21.7 us against 29.6; 752, N_G = 6000, real: 59 against
 // 35).
@@ -287,8 +314,12 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     return L;
   }
   if (mode == HSB_MODE_BACKWARD) {
-    L.end = adjoint_plan(h, ng).end;
-    return L;
+    const AdjointPlan p = adjoint_plan(h, ng);
+    if (!adjoint_stacked(h, ng, p)) {
+      L.factored = true;
+      L.end = p.end;
+      return L;
+    }
   }
   if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && (h.precision == HSB_FP64 || is_crt(h.precision)))) {
     L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL, mode == HSB_MODE_REAL && is_crt(h.precision));
@@ -344,6 +375,17 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.rep = take((size_t)h.n_atoms * sizeof(FactRep));
     L.tau_rep = take((size_t)h.n_atoms * 3 * sizeof(double));
     L.wrow = take((size_t)L.K_pad * sizeof(double));
+  }
+  if (mode == HSB_MODE_BACKWARD) {  // stacked
+    const size_t M = 2 * (size_t)h.n_l;
+    L.PH = take((size_t)L.K_pad * np * sizeof(double2));
+    L.PS = take((size_t)L.K_pad * np * sizeof(double2));
+    L.Kt = (int)round_up(L.K_pad, 128);
+    L.WT = take((size_t)np * L.Kt * sizeof(double2));
+    L.gHp = take((size_t)np * np * sizeof(double2));
+    L.gSp = take((size_t)np * np * sizeof(double2));
+    L.partT = take((size_t)h.n_atoms * M * M * sizeof(double2));
+    L.partTau = take((size_t)h.n_atoms * gradtau_blocks(ng) * 3 * sizeof(double));
   }
   L.end = off;
   // the factored form runs in the same memory (the stacked one keeps its place in it: an option or
@@ -1231,20 +1273,13 @@ int hsbuild_hermitian_part(hsbuild_t h, int32_t ng, const void* gH, const void* 
                   "k_hermitian_part");
 }
 
-int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
-                     const void* T, const void* gH, const void* gS, void* gT, double* gtau, void* ws,
-                     size_t ws_bytes, void* stream) {
-  if (!h) return HSB_ERR_ARG;
-  h->err.clear();
-  if (!k_frac || !g || !tau || !T || !gH || !gS || !gT || !gtau)
-    return fail(h, HSB_ERR_ARG, "null k_frac, g, tau, T, gH, gS, gT or gtau");
-  int rc = check_ng(h, ng);
-  if (rc) return rc;
-  const Layout L = make_layout(*h, ng, HSB_MODE_BACKWARD);
-  if ((rc = check_ws(h, L, ws, ws_bytes))) return rc;
-  if ((rc = check_device(h))) return rc;
-  hipStream_t s = (hipStream_t)stream;
-  char* w = (char*)ws;
+}  // extern "C"
+
+namespace {
+
+int factored_adjoint(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
+                     const void* T, const void* gH, const void* gS, void* gT, double* gtau, char* w, hipStream_t s) {
+  int rc;
   AdjointPlan p = adjoint_plan(*h, ng);
   const FactCell& c = p.c;
   for (int i = 0; i < 3; ++i) p.f.kfrac[i] = k_frac[i];
@@ -1270,6 +1305,51 @@ int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int3
   }
   if (rc) return rc;
   return launched(h, launch_adj_reduce(c, p.ad, h->n_types, h->n_atoms, w, (double2*)gT, gtau, s), "k_adj_reduce");
+}
+
+int stacked_adjoint(hsbuild_t h, const Layout& L, const double k_frac[3], const int32_t* g, const double* tau,
+                    const void* T, const void* gH, const void* gS, void* gT, double* gtau, char* w, hipStream_t s) {
+  int rc;
+  if ((rc = enqueue_operands(h, L, k_frac, g, tau, T, w, s))) return rc;
+  const CellArgs& c = h->cell;
+  const double2* W = (const double2*)(w + L.W);
+  double2* PH = (double2*)(w + L.PH);
+  double2* PS = (double2*)(w + L.PS);
+  // P_H = W gH, P_S = W gS in the 3M form, from W^T and zero-padded gH, gS
+  double2* WT = (double2*)(w + L.WT);
+  double2* gHp = (double2*)(w + L.gHp);
+  double2* gSp = (double2*)(w + L.gSp);
+  rc = launched(h, launch_transpose(W, L.K_pad, L.n_pad, L.Kt, WT, s), "k_transpose");
+  if (!rc) rc = launched(h, launch_pad_square((const double2*)gH, L.n, L.n_pad, gHp, s), "k_pad_square");
+  if (!rc) rc = launched(h, launch_pad_square((const double2*)gS, L.n, L.n_pad, gSp, s), "k_pad_square");
+  if (!rc) rc = launched(h, launch_pgemm3m(WT, gSp, gHp, L.Kt, L.K_pad, L.n_pad, PH, PS, s), "k_pgemm3m");
+  if (!rc) rc = launched(h, launch_gradT(c, PH, W, L.n_pad, (double2*)(w + L.partT), (double2*)gT, s), "k_gradT");
+  if (rc) return rc;
+  return launched(h, launch_gradtau(c, PH, PS, (const double2*)(w + L.Y), W, (const double*)(w + L.lam),
+                                    (const double*)(w + L.kv), L.n, L.n_pad, (double*)(w + L.partTau), gtau, s),
+                  "k_gradtau");
+}
+
+}  // namespace
+
+extern "C" {
+
+int hsbuild_backward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
+                     const void* T, const void* gH, const void* gS, void* gT, double* gtau, void* ws,
+                     size_t ws_bytes, void* stream) {
+  if (!h) return HSB_ERR_ARG;
+  h->err.clear();
+  if (!k_frac || !g || !tau || !T || !gH || !gS || !gT || !gtau)
+    return fail(h, HSB_ERR_ARG, "null k_frac, g, tau, T, gH, gS, gT or gtau");
+  int rc = check_ng(h, ng);
+  if (rc) return rc;
+  const Layout L = make_layout(*h, ng, HSB_MODE_BACKWARD);
+  if ((rc = check_ws(h, L, ws, ws_bytes))) return rc;
+  if ((rc = check_device(h))) return rc;
+  hipStream_t s = (hipStream_t)stream;
+  char* w = (char*)ws;
+  return L.factored ? factored_adjoint(h, k_frac, ng, g, tau, T, gH, gS, gT, gtau, w, s)
+                    : stacked_adjoint(h, L, k_frac, g, tau, T, gH, gS, gT, gtau, w, s);
 }
 
 }  // extern "C"

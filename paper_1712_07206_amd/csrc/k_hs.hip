@@ -21,8 +21,8 @@
 // that touch the upper triangle are computed; they are numbered over 128 x 128
 // super-tiles (grouped order, tiles.h) and the numbering is dealt to the eight
 // XCDs in contiguous ranges so tiles sharing a row strip share an L2.  The 3M
-// tile routine also serves the per-atom T products (k_tprod3m), with the plain
-// complex product.
+// tile routine also serves the per-atom T products (k_tprod3m) and the stacked
+// adjoint's products (k_pgemm3m), with the plain complex product.
 //
 // k_hs_fp64 computes one k-point, one workgroup per tile.  k_hs_fp64_batch is
 // the persistent form for many k-points: a fixed grid (one workgroup per CU)
@@ -496,6 +496,24 @@ __global__ void __launch_bounds__(128 * WR, 1) k_hs_fp64_batch(const d2* __restr
   }
 }
 
+// Adjoint products P_H = W gH and P_S = W gS ([K_pad][n_pad]) with the same tile
+// routine: tile rows k (128), columns G (64), contraction over G'.  The left operand
+// is W^T (rows G', k contiguous, Kt = K_pad rounded to 128, zeros past K_pad), the
+// right ones gS and gH zero-padded to n_pad x n_pad, so every copy is in bounds and
+// the pads add nothing.  Full tiles, row-major tile order dealt to the XCDs in
+// contiguous ranges (the tiles an XCD runs together share their W^T strip).
+__global__ void __launch_bounds__(512, 1) k_pgemm3m(const d2* __restrict__ WT, const d2* __restrict__ gSp,
+                                                  const d2* __restrict__ gHp, int Kt, int K_pad, int n_pad, int ncb,
+                                                  int num_wg, d2* __restrict__ PH, d2* __restrict__ PS) {
+  __shared__ Smem sm;
+  const int x = blockIdx.x % kXcds;
+  int start, len;
+  xcd_range(x, num_wg, start, len);
+  const int w = start + blockIdx.x / kXcds;
+  const int rb = w / ncb, cb = w % ncb;
+  hs_tile3m<4, false>(sm, WT, gSp, gHp, n_pad, Kt, n_pad, rb * BM, cb * BN, K_pad, n_pad, false, PH, PS, n_pad);
+}
+
 // Per-atom T products Y_a = T_t W_a on the same tile routine (plain products): tile
 // rows r of Y_a (128), the routine's two outputs are two adjacent 64-column halves of
 // a 128-column block (both share the staged T), contraction over the atom's rows k in
@@ -530,6 +548,15 @@ hipError_t launch_tprod3m(const CellArgs& c, const double2* TT, const double2* W
   dim3 grid(n_pad / (2 * BN), tprod_mp(M) / BM, c.n_atoms);
   hipLaunchKernelGGL(k_tprod3m, grid, dim3(512), 0, s, c, (const d2*)TT, (const d2*)W, (d2*)Y, n_pad, tprod_kc(M),
                      tprod_mp(M));
+  return hipGetLastError();
+}
+
+hipError_t launch_pgemm3m(const double2* WT, const double2* gSp, const double2* gHp, int Kt, int K_pad, int n_pad,
+                          double2* PH, double2* PS, hipStream_t s) {
+  if (Kt % BM || n_pad % BN) return hipErrorInvalidValue;
+  const int ncb = n_pad / BN, num_wg = ncb * (Kt / BM);
+  hipLaunchKernelGGL(k_pgemm3m, dim3(num_wg), dim3(512), 0, s, (const d2*)WT, (const d2*)gSp, (const d2*)gHp, Kt,
+                     K_pad, n_pad, ncb, num_wg, (d2*)PH, (d2*)PS);
   return hipGetLastError();
 }
 

@@ -139,8 +139,9 @@ int hsbuild_coefficients(hsbuild_t h, const double k_frac[3], int32_t ng, const 
  * H, S: device complex128 [ng][ng]; upper triangle written.
  * The handle's precision selects FP64 or the split-precision contraction.  In
  * FP64 the call runs the type-factored form (see hsbuild_forward_factored)
- * unless an option pins the stacked contraction: HSB_OPT_SPLIT_K other than 1,
- * or HSB_OPT_HS_WAVES = 4. */
+ * unless an option pins the stacked contraction (HSB_OPT_SPLIT_K other than 1,
+ * or HSB_OPT_HS_WAVES = 4) or that is the faster one for the cell at max_ng: many
+ * types of one or two atoms with l_max = 0 or 1, at thousands of plane waves. */
 int hsbuild_forward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32_t* g, const double* tau,
                     const void* T, void* H, void* S, void* ws, size_t ws_bytes, void* stream);
 
@@ -189,7 +190,7 @@ int hsbuild_forward_factored(hsbuild_t h, const double k_frac[3], int32_t ng, co
  * upper triangle written; equal to the real parts of hsbuild_forward's
  * outputs up to FP64 rounding (undefined if the symmetry does not hold).
  * Other arguments as hsbuild_forward.  A handle created with HSB_FP64 runs
- * the type-factored form on real parts, as does one with a residue form
+ * the type-factored form on real parts (or the stacked one, as hsbuild_forward does), as does one with a residue form
  * (HSB_SPLIT_CRT*), with H by residues; HSB_SPLIT_INT8 runs its split contraction (the real
  * parts of the split products); both to the split path's error; HSB_SPLIT_BF16 and HSB_SPLIT_FP16 handles get
  * HSB_ERR_UNSUPPORTED before anything is enqueued.
@@ -314,8 +315,9 @@ int hsbuild_stage_times(hsbuild_t h, double* ms_avg, int32_t* n_calls);
  * give bitwise the same H and S.
  * HSB_OPT_SPLIT_K: 1 (default) leaves the form of the FP64 builds to the library:
  * with HSB_OPT_HS_WAVES = 8 hsbuild_forward and hsbuild_batch run the
- * type-factored form.  Where the stacked contraction runs
- * (hsbuild_forward_coefficients), it runs in stream-K
+ * type-factored form, or the stacked one where that is faster (see
+ * hsbuild_forward).  Where the stacked contraction runs
+ * (hsbuild_forward_coefficients among others), it runs in stream-K
  * form when the upper triangle has fewer than 4 tiles per compute unit and a
  * time model puts it ahead of one pass: the units (128 x 64 tile, 16 stacked
  * rows) are dealt to at most one workgroup per compute unit in equal

@@ -51,8 +51,8 @@ struct Layout {
   int n = 0, n_pad = 0, K = 0, K_pad = 0;
   size_t W = 0, Y = 0, ang = 0, ab = 0, kv = 0, lam = 0, consts = 0, end = 0;
   size_t stacked_end = 0;  // forward: the stacked form's part of `end`
-  bool factored = false;   // forward, backward: run the type-factored form
-  size_t WL = 0;  // lam W (the FP64 contraction's S operand), forward in FP64 only
+  bool factored = false;   // forward, real, backward: run the type-factored form
+  size_t WL = 0;  // lam W (the FP64 contraction's S operand), forward and real in FP64 only
   int ns = 1;              // FP64 forward: segments of the stacked index (split contraction when > 1)
   int nsh = 0;             // FP64 forward: workgroups of the stream-K contraction (0: not used)
   size_t skH = 0, skS = 0;  // partial H and S: per segment (ns > 1), or the stream-K slots (nsh > 0)
@@ -144,6 +144,10 @@ hipError_t launch_hs_fp64_sk(const double2* W, const double2* WL, const double2*
                              int n_pad, int gr, double2* Hp, double2* Sp, hipStream_t s);
 hipError_t launch_sk_reduce(const double2* Hp, const double2* Sp, int ns, int n, int n_pad, double2* H, double2* S,
                             int64_t ldh, hipStream_t s);
+
+// The same contraction keeping only the real parts, Re(W^H Y) and Re(W^H lam W), as doubles.
+hipError_t launch_hs_fp64_real(const double2* W, const double2* WL, const double2* Y, int K_pad, int n, int n_pad, int gr,
+                               double* H, double* S, int64_t ldh, hipStream_t s);
 
 // Number of 128 x 64 tiles the contraction covers for a padded basis size.
 int hs_tiles(int n_pad);

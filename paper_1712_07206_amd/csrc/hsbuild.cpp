@@ -105,10 +105,30 @@ hipError_t static_scratch(int dev, void** out) {
 
 // ---- type-factored form ----
 
-// The forward runs the type-factored form in FP64, unless an option pins the stacked contraction, and in
-// the residue forms.
+// Whether the stacked contraction is the faster one for the handle's cell at its largest basis: many types of one or two
+// atoms and l_max = 0 or 1, whose 4-row steps of the matrix cores and sums per type outweigh a product over the few
+// rows of all atoms.  By the handle's max_ng, not the call's basis, so that the forward and the batch agree.  The estimates
+// (microseconds; steps: 4 rows of a type's phases or R rows) come from 5 to 16 types, N_G 1000 to 9000: 16 types of one atom,
+// l_max = 0, N_G = 1500 / 5000 / 9000: stacked 75 / 245 / 594 us, factored 75 / 436 / 1314; of four, l_max = 0, 4000:
+// 408 and 285; the real form's pairs, 16 types of one, 5000: 216 and 359.
+bool stacked_cell(const hsbuild_s& h, bool real) {
+  const double n2 = 1e-6 * h.max_ng * (double)h.max_ng, rows = stacked_pad((real ? 1 : 2) * h.n_atoms * h.n_l);
+  double factored = 0.0;
+  for (int t = 0; t < h.n_types; ++t) {
+    int atoms = h.cell.type_start[t + 1] - h.cell.type_start[t];
+    if (real) atoms = (atoms + 1) / 2;
+    const int steps = (atoms + 3) / 4 + (2 * h.n_l + 3) / 4;
+    if (atoms) factored += real ? 0.5 + 0.125 * steps : 0.45 + 0.2 * steps;
+  }
+  if (real) return 60.0 + 0.3 * rows + n2 * (1.1 + 0.0875 * rows) < 30.0 + n2 * (1.1 + factored);
+  return 50.0 + 0.3 * rows + n2 * (2.65 + 0.0975 * rows) < 22.0 + n2 * (2.6 + factored);
+}
+
+// The forward runs the type-factored form in FP64, unless an option pins the stacked contraction or that is the faster one,
+// and in the residue forms.
 bool use_factored(const hsbuild_s& h) {
-  return is_crt(h.precision) || (h.precision == HSB_FP64 && h.split_k == 1 && h.hs_waves == 8);
+  return is_crt(h.precision) ||
+         (h.precision == HSB_FP64 && h.split_k == 1 && h.hs_waves == 8 && !stacked_cell(h, false));
 }
 
 // The types of `cell` with atoms (the real form's cell holds the representatives).
@@ -321,7 +341,9 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
       return L;
     }
   }
-  if (mode == HSB_MODE_FACTORED || (mode == HSB_MODE_REAL && (h.precision == HSB_FP64 || is_crt(h.precision)))) {
+  if (mode == HSB_MODE_FACTORED ||
+      (mode == HSB_MODE_REAL && (is_crt(h.precision) || (h.precision == HSB_FP64 && !stacked_cell(h, true))))) {
+    L.factored = true;
     L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL, mode == HSB_MODE_REAL && is_crt(h.precision));
     return L;
   }
@@ -331,7 +353,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
     L.W = take((size_t)L.K_pad * np * sizeof(double2));
     L.Y = take((size_t)L.K_pad * np * sizeof(double2));
   }
-  if (mode == HSB_MODE_FORWARD && h.precision == HSB_FP64)
+  if ((mode == HSB_MODE_FORWARD || mode == HSB_MODE_REAL) && h.precision == HSB_FP64)
     L.WL = take((size_t)L.K_pad * np * sizeof(double2));
   if (mode == HSB_MODE_FORWARD && h.precision == HSB_FP64 && h.hs_waves == 8 && h.split_k == 1) {
     L.nsh = hs_stream_shares(L.n_pad, L.K_pad, h.num_cus);
@@ -1112,10 +1134,11 @@ int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const 
   Layout Lr = L;  // the stacked rows of the representatives only
   Lr.K = 2 * n_rep * h->n_l;
   Lr.K_pad = stacked_pad(Lr.K);
+  Lr.WL = 0;  // lam W is formed below, after the pair weights are folded into lam
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
   if ((rc = stage_reps(h, rep, wt))) return rc;
-  if (h->precision == HSB_FP64 || is_crt(h->precision))
+  if (L.factored)
     return factored_enqueue(h, crep, true, is_crt(h->precision), k_frac, ng, g, tau, T, H, S, w, s);
   mark(h, 0, s);
   if ((rc = upload_reps(h, w + L.rep, n_rep, s))) return rc;
@@ -1135,7 +1158,15 @@ int hsbuild_forward_real(hsbuild_t h, const double k_frac[3], int32_t ng, const 
                                     tau_rep, wrow, lam, s),
                 "k_rep_setup");
   if (!rc) rc = launched(h, launch_scale_rows(Y, wrow, Lr.K_pad, L.n_pad, Y, s), "k_scale_rows");
-  if (!rc) rc = enqueue_split_real(h, Lr, w, H, S, s);
+  if (rc) return rc;
+  if (h->precision != HSB_FP64) return enqueue_split_real(h, Lr, w, H, S, s);
+  const double2* W = (const double2*)(w + L.W);
+  double2* WL = (double2*)(w + L.WL);  // S's right operand, lam W (lam with the pair weights)
+  rc = launched(h, launch_scale_rows(W, lam, Lr.K_pad, L.n_pad, WL, s), "k_scale_rows");
+  if (!rc)
+    rc = launched(h, launch_hs_fp64_real(W, WL, Y, Lr.K_pad, ng, L.n_pad, h->tile_group, H, S, ng, s), "k_hs_real");
+  mark(h, 3, s);
+  mark(h, 4, s);
   return rc;
 }
 

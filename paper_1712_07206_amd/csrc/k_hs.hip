@@ -534,6 +534,131 @@ __global__ void __launch_bounds__(512, 1) k_tprod3m(CellArgs c, const d2* __rest
                       Ya, n_pad);
 }
 
+// Real-symmetric contraction on whole 128 x 128 super-tiles: Re(W^H Y) and
+// Re(W^H lam W) keep two of the four real MFMAs per complex multiply-add, so
+// with the 128 x 64 tile above a wave would read twice the LDS per MFMA.
+// Here the tile is 128 x 128 and 8 rows are staged per chunk, copied straight
+// into double-buffered LDS: 8 waves of 32 x 64 (2 x 4 MFMA blocks), the same
+// MFMA work and LDS reads per chunk as the complex kernel.
+constexpr int RN = 128, RK = 8;
+
+struct RSmem {
+  d2 L[2][RK][BM];
+  d2 R[2][RK][RN];
+  d2 Y[2][RK][RN];
+};
+
+__global__ void __launch_bounds__(512, 1) k_hs_real(const d2* __restrict__ W, const d2* __restrict__ WL,
+                                                    const d2* __restrict__ Y, int K_pad, int n, int n_pad, int nbr,
+                                                    int num_wg, int gr, double* __restrict__ H,
+                                                    double* __restrict__ S, int64_t ldh) {
+  __shared__ RSmem sm;
+  const int x = blockIdx.x % kXcds;
+  int start, len;
+  xcd_range(x, num_wg, start, len);
+  const int w = start + blockIdx.x / kXcds;
+  int bi, bj;
+  if (gr > 0) grouped_decode(w, nbr, gr, bi, bj);
+  else tri_decode(w, nbr, bi, bj);
+  const int row0 = bi * BM, col0 = bj * RN;
+  if (col0 >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = wave >> 1, wc = wave & 1;  // rows wr*32, columns wc*64
+
+  // Staging straight into LDS: 48 copies of 1 KB (64 elements) per 8-row chunk, wave w
+  // takes j = w + 8 i: copies 0..15 are W at the tile rows, 16..31 lam W (prepared in
+  // HBM) and 32..47 Y at the tile columns; copy j covers row (j % 16) / 2, half j % 2.
+  const d2* src0[6];
+  int dst[6];  // d2 offset in buffer 0 of sm (L, R, Y are consecutive members)
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const int j = wave + 8 * i, r = (j & 15) >> 1, half = j & 1;
+    if (i < 2) {
+      src0[i] = W + (int64_t)r * n_pad + row0 + half * 64;
+      dst[i] = r * BM + half * 64;
+    } else if (i < 4) {
+      src0[i] = WL + (int64_t)r * n_pad + col0 + half * 64;
+      dst[i] = 2 * RK * BM + r * RN + half * 64;
+    } else {
+      src0[i] = Y + (int64_t)r * n_pad + col0 + half * 64;
+      dst[i] = 2 * RK * BM + 2 * RK * RN + r * RN + half * 64;
+    }
+  }
+  d2* base = &sm.L[0][0][0];
+  auto issue = [&](int c, int buf) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      const int off = dst[i] + buf * (i < 2 ? RK * BM : RK * RN);
+      __builtin_amdgcn_global_load_lds((const void*)(src0[i] + (int64_t)c * RK * n_pad + lane),
+                                       (lds_ptr)(base + off), 16, 0, 0);
+    }
+  };
+
+  d4 hr[2][4], sr[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hr[i][j] = sr[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+
+  const int nchunks = K_pad / RK;
+  issue(0, 0);
+  for (int c = 0; c < nchunks; ++c) {
+    const int b = c & 1;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of chunk c have landed
+    __syncthreads();                // everyone's have, and buffer b^1 is free
+    if (c + 1 < nchunks) issue(c + 1, b ^ 1);
+#pragma unroll
+    for (int ks = 0; ks < RK / 4; ++ks) {
+      const int kk = ks * 4 + (lane >> 4);
+      double ar[2], ai[2], yre[4], yim[4], wre[4], wim[4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const d2 a = sm.L[b][kk][wr * 32 + i * 16 + (lane & 15)];
+        ar[i] = a.x; ai[i] = a.y;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const d2 yv = sm.Y[b][kk][wc * 64 + j * 16 + (lane & 15)];
+        const d2 wv = sm.R[b][kk][wc * 64 + j * 16 + (lane & 15)];
+        yre[j] = yv.x; yim[j] = yv.y; wre[j] = wv.x; wim[j] = wv.y;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hr[i][j] = MFMA(ar[i], yre[j], hr[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sr[i][j] = MFMA(ar[i], wre[j], sr[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hr[i][j] = MFMA(ai[i], yim[j], hr[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sr[i][j] = MFMA(ai[i], wim[j], sr[i][j]);
+    }
+  }
+
+  // D layout of the 16x16 f64 MFMA: lane l, element q -> row l/16 + 4q, column l%16
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = row0 + wr * 32 + i * 16 + (lane >> 4) + 4 * q;
+        const int col = col0 + wc * 64 + j * 16 + (lane & 15);
+        if (row < n && col < n && col >= row) {
+          const int64_t o = (int64_t)row * ldh + col;
+          H[o] = hr[i][j][q];
+          S[o] = sr[i][j][q];
+        }
+      }
+}
+
 }  // namespace
 
 int hs_tiles(int n_pad) {
@@ -634,6 +759,16 @@ hipError_t launch_sk_reduce(const double2* Hp, const double2* Sp, int ns, int n,
                             int64_t ldh, hipStream_t s) {
   hipLaunchKernelGGL(k_sk_reduce, dim3((n + 255) / 256, n), dim3(256), 0, s, (const d2*)Hp, (const d2*)Sp, ns, n,
                      n_pad, (d2*)H, (d2*)S, ldh);
+  return hipGetLastError();
+}
+
+hipError_t launch_hs_fp64_real(const double2* W, const double2* WL, const double2* Y, int K_pad, int n, int n_pad, int gr,
+                               double* H, double* S, int64_t ldh, hipStream_t s) {
+  const int nbr = n_pad / BM;
+  const int num_wg = hs_tiles(n_pad) / 2;  // whole 128 x 128 super-tiles
+  if (K_pad % RK) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_hs_real, dim3(num_wg), dim3(512), 0, s, (const d2*)W, (const d2*)WL, (const d2*)Y, K_pad, n, n_pad,
+                     nbr, num_wg, gr, H, S, ldh);
   return hipGetLastError();
 }
 

@@ -48,3 +48,83 @@ def test_adjoint_workspace_is_no_larger_than_the_stacked_operands(atoms, l_max):
                                              ((12, 1) * 6, 6, 70), ((1,) * 6, 3, 300)])
 def test_adjoint_of_general_matrices(atoms, l_max, n_g):
     typed.test_adjoint_of_general_matrices(atoms, l_max, n_g)
+
+
+
+def _run(case, max_ng, real=False):
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    n = case["n_g"]
+    print("atoms", np.bincount(case["atom_type"]), "l_max", case["l_max"], "N_G", n, "max N_G", max_ng, flush=True)
+    b = HSBuilder.from_case(case, max_ng=max_ng)
+    g, tau, T = case_tensors(case)
+    H = torch.full((n, n), float("nan"), dtype=torch.float64 if real else torch.complex128, device="cuda")
+    S = H.clone()
+    if real:
+        b.forward_real(case["k_frac"], g, tau, case["partner"], T, H, S)
+    else:
+        b.forward(case["k_frac"], g, tau, T, H, S)
+    return b, H, S
+
+
+# the stacked builds that a handle of many types with few rows takes at a large max_ng, l_max 0 and 1, a type without atoms;
+# edges of their 128 x 64 tiles (the real form's: 128 x 128)
+@pytest.mark.parametrize("atoms,l_max,n_g", [((1,) * 16, 0, 1), ((1,) * 16, 1, 129), ((1,) * 5 + (0,) + (1,) * 3, 0, 65),
+                                             ((2,) * 12, 0, 300)])
+def test_build_of_few_rows_at_a_large_max_ng(atoms, l_max, n_g):
+    """Against the oracle, forward_static and the batch bitwise equal."""
+    case = typed._case(atoms, l_max, n_g)
+    b, H, S = _run(case, 9000)
+    Hr, Sr = typed.o.hs(case)
+    il, iu = np.tril_indices(n_g, -1), torch.triu_indices(n_g, n_g, device="cuda")
+    for M, R in ((H.cpu().numpy(), Hr), (S.cpu().numpy(), Sr)):
+        assert np.all(np.isnan(M[il])), "strict lower triangle was written"
+        assert typed._rel(typed._full(M), R) <= typed.TOL
+    from paper_1712_07206_amd.hsbuild import case_tensors
+    g, tau, T = case_tensors(case)
+    k = np.asarray(case["k_frac"])
+    Hb, Sb, off = b.batch(np.stack([-k, k]), [g, g], tau, T)
+    for got in (b.forward_static(k, g, tau, T), [M[int(off[1]):].view(n_g, n_g) for M in (Hb, Sb)]):
+        assert all(torch.equal(x[iu[0], iu[1]], r[iu[0], iu[1]]) for x, r in zip(got, (H, S)))
+
+
+@pytest.mark.parametrize("atoms,l_max,n_g", [((2,) * 16, 0, 1), ((2,) * 15 + (1,), 0, 127), ((2,) * 8, 0, 129),
+                                             ((4,) * 16, 0, 257)])
+def test_real_build_of_few_rows_at_a_large_max_ng(atoms, l_max, n_g):
+    case = typed._case(atoms, l_max, n_g, inversion=True)
+    _, H, S = _run(case, 9000, real=True)
+    Hr, Sr = typed.o.hs(case)
+    for M, R in ((H.cpu().numpy(), Hr.real), (S.cpu().numpy(), Sr.real)):
+        assert np.all(np.isnan(M[np.tril_indices(n_g, -1)])), "strict lower triangle was written"
+        assert typed._rel(np.triu(M) + np.triu(M, 1).T, R) <= typed.TOL
+
+
+def _time(f):
+    f()
+    best = float("inf")
+    for _ in range(5):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(10):
+            f()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best
+
+
+def test_default_forward_is_not_slower_than_the_stacked_one():
+    """16 types of one atom with one (A, B) pair each: the type-factored form takes 1.75 times the stacked contraction's
+    time.  Bar: 1.2 times, for the clock's noise."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = typed._case((1,) * 16, 0, 5000)
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    H = torch.empty((5000, 5000), dtype=torch.complex128, device="cuda")
+    S = torch.empty_like(H)
+    t = {}
+    for mode in (1, 0):
+        b.set_option(N.HSB_OPT_SPLIT_K, mode)
+        t[mode] = _time(lambda: b.forward(case["k_frac"], g, tau, T, H, S))
+    print("default %.3f ms, stacked %.3f ms" % (t[1] / 10, t[0] / 10))
+    assert t[1] <= 1.2 * t[0]

@@ -156,6 +156,17 @@ FactCell fact_cell(const CellArgs& cell) {
   return c;
 }
 
+// Whether a residue handle runs the FP64 products for `cell`: eight types or more with fewer than 256 rows of all atoms
+// each.  k_fact_crt's chunks, its recombination of the residues (4 FP64 operations per modulus, entry and type) and the
+// phase and S products are per type, and there more than the FP64 products it saves: over 8 to 16 types of 1 to 4 atoms,
+// l_max 0 to 10, N_G 100 to 5000 the FP64 build took 0.2 to 0.93 of its time.  (The stacked residues had taken 0.45 to 5 of it: 16
+// types of one atom, l_max = 2, N_G = 5000: bytes 994 us stacked, 1762 by types, FP64 744; l_max = 8: 3059, 4007, 3673.)
+bool crt_in_fp64(const CellArgs& cell) {
+  int n_act = 0;
+  for (int t = 0; t < cell.n_types; ++t) n_act += cell.type_start[t + 1] > cell.type_start[t];
+  return n_act >= 8 && 2LL * cell.n_atoms * cell.n_l < 256LL * n_act;
+}
+
 // Workspace of the factored form: what the k-points share, then each one's arrays.  Returns the end.
 // consts: offset of the uploaded type constants; ks[k].n is given.  cr: the residue form (one k-point).
 size_t fact_layout(const hsbuild_s& h, FactCell& c, FactK* ks, int n_k, bool real, size_t* consts, size_t* many,
@@ -344,7 +355,9 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
   if (mode == HSB_MODE_FACTORED ||
       (mode == HSB_MODE_REAL && (is_crt(h.precision) || (h.precision == HSB_FP64 && !stacked_cell(h, true))))) {
     L.factored = true;
-    L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL, mode == HSB_MODE_REAL && is_crt(h.precision));
+    // (the real form decides on the representatives, at most all atoms)
+    const bool crt = mode == HSB_MODE_REAL && is_crt(h.precision) && !crt_in_fp64(h.cell);
+    L.end = fact_bytes(h, ng, mode == HSB_MODE_REAL, crt);
     return L;
   }
   if (mode != HSB_MODE_COEFFICIENTS) {
@@ -415,7 +428,7 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
   L.stacked_end = off;
   if (mode == HSB_MODE_FORWARD && use_factored(h)) {
     L.factored = true;
-    L.end = std::max(L.end, fact_bytes(h, ng, false, is_crt(h.precision)));
+    L.end = std::max(L.end, fact_bytes(h, ng, false, is_crt(h.precision) && !crt_in_fp64(h.cell)));
   }
   return L;
 }
@@ -977,6 +990,7 @@ int upload_reps(hsbuild_t h, void* dst, int n_rep, hipStream_t s) {
 // atoms and multiplicities are uploaded from the handle's pinned list.
 int factored_enqueue(hsbuild_t h, const CellArgs& cell, bool real, bool crt, const double k_frac[3], int32_t ng,
                      const int32_t* g, const double* tau, const void* T, void* H, void* S, char* w, hipStream_t s) {
+  crt = crt && !crt_in_fp64(cell);
   FactCell c = fact_cell(cell);
   FactK f{};
   RadialArgs ra;

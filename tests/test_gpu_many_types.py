@@ -128,3 +128,37 @@ def test_default_forward_is_not_slower_than_the_stacked_one():
         t[mode] = _time(lambda: b.forward(case["k_frac"], g, tau, T, H, S))
     print("default %.3f ms, stacked %.3f ms" % (t[1] / 10, t[0] / 10))
     assert t[1] <= 1.2 * t[0]
+
+
+@pytest.mark.parametrize("real", [False, True])
+def test_residue_handles_of_many_types(real):
+    """16 types of one atom (pair), l_max = 2: a residue handle runs the FP64 products (bitwise an FP64 handle's) in their time;
+    by residues per type it took 2.6 (real form: 2.4) times that.  Bar: 1.2 times, for the clock's noise."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    n = 1500
+    case = typed._case((1 + real,) * 16, 2, n, inversion=real)
+    g, tau, T = case_tensors(case)
+    iu = torch.triu_indices(n, n, device="cuda")
+    t, out = {}, {}
+    for prec in (N.HSB_FP64, N.HSB_SPLIT_CRT, N.HSB_SPLIT_CRT_FP16):
+        b = HSBuilder.from_case(case, precision=prec, n_slices=11)
+        H = torch.empty((n, n), dtype=torch.float64 if real else torch.complex128, device="cuda")
+        S = torch.empty_like(H)
+        if real:
+            t[prec] = _time(lambda: b.forward_real(case["k_frac"], g, tau, case["partner"], T, H, S))
+        else:
+            t[prec] = _time(lambda: b.forward(case["k_frac"], g, tau, T, H, S))
+        out[prec] = H[iu[0], iu[1]], S[iu[0], iu[1]]
+        b.close()
+    print("ms", {p: v / 10 for p, v in t.items()}, flush=True)
+    for prec in (N.HSB_SPLIT_CRT, N.HSB_SPLIT_CRT_FP16):
+        assert all(torch.equal(x, y) for x, y in zip(out[prec], out[N.HSB_FP64]))
+        assert t[prec] <= 1.2 * t[N.HSB_FP64]
+
+
+@pytest.mark.parametrize("real", [False, True])
+def test_residues_of_the_most_types(real):
+    """The residue kernels on the largest number of types, with the rows (338 a type) that keep them."""
+    import test_gpu_crt_typed
+    test_gpu_crt_typed._check(typed._case((1 + real,) * 16, 12, 70, inversion=real), real=real)

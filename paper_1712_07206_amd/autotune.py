@@ -1,12 +1,15 @@
 """Autotuner for the performance options of the H/S build.
 
 The tile order changes only the order in which work is dealt to the compute
-units, never the arithmetic (bitwise the same H and S); the wave count of the
-FP64 contraction also selects its complex form (three real products per
-complex one with 8 waves, four with 4), whose results agree to FP64 rounding.
-`tune` times the candidates on the caller's inputs with HIP events and
-returns the fastest; `cached_options` / `apply` keep the choice in a JSON
-cache keyed by device, precision and problem size so later runs reuse it.
+units, never the arithmetic (bitwise the same H and S).  The wave count is left
+alone unless the caller names candidates: on an FP64 handle 8 leaves the form of
+the build to the library and 4 pins the stacked contraction (four real products
+per complex one; results agree to FP64 rounding), tens of times slower on most
+cells; on a residue handle it is the layout of hsbuild_forward_coefficients,
+which the builds timed here don't run.  `tune` times the candidates on the
+caller's inputs with HIP events and returns the fastest; `cached_options` /
+`apply` keep the choice in a JSON cache keyed by device, precision and problem
+size so later runs reuse it.
 """
 from __future__ import annotations
 
@@ -20,7 +23,9 @@ from . import _native as N
 
 DEFAULT_CACHE = os.environ.get("HSB_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "hsbuild_tune.json"))
 TILE_GROUPS = (0, 4, 8)
-WAVES = (4, 8)
+# What the options mean for the builds: entries of another meaning are not reused (in the first, 4 waves were a layout of
+# the one contraction there was).
+FORM = 2
 
 
 def _key(builder, n_g: int, precision: int) -> str:
@@ -28,8 +33,15 @@ def _key(builder, n_g: int, precision: int) -> str:
     arch = getattr(prop, "gcnArchName", "gpu").split(":")[0]
     k_c = builder.n_atoms * builder.n_l
     # problem-size buckets: the stacked width and the basis size to the next power of two
-    return "%s/cu%d/p%d/nl%d/kc%d/ng%d" % (arch, prop.multi_processor_count, precision, builder.n_l,
-                                          1 << max(0, (k_c - 1).bit_length()), 1 << max(0, (n_g - 1).bit_length()))
+    return "f%d/%s/cu%d/p%d/nl%d/kc%d/ng%d" % (FORM, arch, prop.multi_processor_count, precision, builder.n_l,
+                                               1 << max(0, (k_c - 1).bit_length()),
+                                               1 << max(0, (n_g - 1).bit_length()))
+
+
+def _waves(builder, waves: Optional[Iterable[int]]):
+    if waves is not None:
+        return list(waves)
+    return [8] if builder.precision == N.HSB_FP64 else [builder.get_option(N.HSB_OPT_HS_WAVES)]
 
 
 def _load(path: str) -> Dict[str, dict]:
@@ -52,15 +64,16 @@ def apply(builder, options: dict) -> None:
 
 
 def tune(builder, k_frac, g, tau, T, precision: int = N.HSB_FP64, groups: Iterable[int] = TILE_GROUPS,
-         waves: Iterable[int] = WAVES, reps: int = 2, path: Optional[str] = DEFAULT_CACHE) -> dict:
+         waves: Optional[Iterable[int]] = None, reps: int = 2, path: Optional[str] = DEFAULT_CACHE) -> dict:
     """Times hsbuild_forward for each (waves, tile order) and keeps the fastest
-    (and stores it in the cache when `path` is given)."""
+    (and stores it in the cache when `path` is given).  waves: the default form's 8
+    on an FP64 handle, the handle's own value on the others, unless given."""
     n = int(g.shape[0])
     H = torch.empty((n, n), dtype=torch.complex128, device="cuda")
     S = torch.empty((n, n), dtype=torch.complex128, device="cuda")
-    waves = list(waves)
+    waves = _waves(builder, waves)
     wsb = 0
-    for wv in waves:  # the workspace depends on the wave count (the 8-wave form may split its stacked index)
+    for wv in waves:  # the workspace depends on the wave count
         builder.set_option(N.HSB_OPT_HS_WAVES, wv)
         wsb = max(wsb, builder.workspace_bytes(N.HSB_MODE_FORWARD, [n]))
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
@@ -98,12 +111,13 @@ def tune(builder, k_frac, g, tau, T, precision: int = N.HSB_FP64, groups: Iterab
     return result
 
 
-def tune_batch(builder, k_frac, g_list, tau, T, groups: Iterable[int] = (8, 4), waves: Iterable[int] = (8, 4),
-               reps: int = 1) -> dict:
-    """Times hsbuild_batch (one captured graph, one persistent contraction over
-    every k-point's tiles) for each (waves, tile order) and keeps the fastest.
+def tune_batch(builder, k_frac, g_list, tau, T, groups: Iterable[int] = (8, 4),
+               waves: Optional[Iterable[int]] = None, reps: int = 1) -> dict:
+    """Times hsbuild_batch (one captured graph, each kernel over every k-point's
+    tiles) for each (waves, tile order) and keeps the fastest; waves as in `tune`.
     Each candidate re-captures the graph once, untimed."""
     times = {}
+    waves = _waves(builder, waves)
     H = S = None
     for wv in waves:
         for gr in groups:

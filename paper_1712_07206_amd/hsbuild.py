@@ -53,6 +53,7 @@ class HSBuilder:
         self.l_max = int(l_max)
         self.n_l = (self.l_max + 1) ** 2
         self.max_ng = int(max_ng)
+        self.precision = int(precision)
         cfg = N.HsbConfig()
         cfg.n_types = self.n_types
         cfg.n_atoms = self.n_atoms

@@ -73,3 +73,40 @@ def test_stream_k_and_segments_match_one_pass(idx, n_g):
             assert np.array_equal(x, y), mode
             assert np.linalg.norm(x - r) <= 1e-14 * np.linalg.norm(r), mode
             assert np.abs(x - r).max() <= 1e-13 * np.abs(r).max(), mode
+
+
+def _one_atom():
+    case = dict(make_case(0))
+    case["atom_type"], case["tau"], case["n_atoms"] = case["atom_type"][:1], case["tau"][:1], 1
+    return case
+
+
+# stacked widths of one, two and three 64-row chunks (50, 100, 160 rows), fewer than the copy ring's four stages; one block of
+# 256 columns; and 12 of them a side at 30976 rows
+@pytest.mark.parametrize("which", ["one atom", "two atoms", "five atoms", "16 atoms, N_G 129", "128 atoms, N_G 3000"])
+def test_residue_layouts_match_the_oracle_and_each_other(which):
+    """Bytes in 4 and 8 waves, and the 16-bit kinds: bitwise the same H and S, at the split path's 1e-10."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = {"one atom": _one_atom, "two atoms": lambda: make_case(0), "five atoms": lambda: make_case(8),
+            "16 atoms, N_G 129": lambda: make_case(1, n_g=129),
+            "128 atoms, N_G 3000": lambda: make_case(2, n_g=3000)}[which]()
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    coef = b.coefficients(case["k_frac"], g, tau)
+    b.close()
+    Hr, Sr = o.hs(case)
+    iu = np.triu_indices(case["n_g"])
+    first = None
+    for prec, waves in ((N.HSB_SPLIT_CRT, 4), (N.HSB_SPLIT_CRT, 8), (N.HSB_SPLIT_CRT_BF16, 8), (N.HSB_SPLIT_CRT_FP16, 8)):
+        print(which, "precision", prec, "waves", waves, flush=True)
+        b = HSBuilder.from_case(case, precision=prec, n_slices=11)
+        b.set_option(N.HSB_OPT_HS_WAVES, waves)
+        H, S = _from_coefficients(b, coef, T)
+        b.close()
+        if first is None:
+            first = H, S
+            eh, es = _rel(_full(H), Hr), _rel(_full(S), Sr)
+            print("rel err H %.3e S %.3e" % (eh, es), flush=True)
+            assert eh <= 1e-10 and es <= 1e-10
+        assert np.array_equal(H[iu], first[0][iu]) and np.array_equal(S[iu], first[1][iu])

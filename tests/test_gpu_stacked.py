@@ -110,3 +110,29 @@ def test_residue_layouts_match_the_oracle_and_each_other(which):
             print("rel err H %.3e S %.3e" % (eh, es), flush=True)
             assert eh <= 1e-10 and es <= 1e-10
         assert np.array_equal(H[iu], first[0][iu]) and np.array_equal(S[iu], first[1][iu])
+
+
+def test_type_factored_builds_against_the_stacked_contraction_at_full_size():
+    """N_G = 12000, 128 atoms, l_max = 10: the FP64 and byte-residue builds against the one-pass stacked contraction of
+    the same call, over the upper triangles; FP64's 1e-12 (S of the residue form too), the split path's 1e-10 for H."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    case = make_case(2)
+    n = case["n_g"]
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    b.set_option(N.HSB_OPT_SPLIT_K, 0)
+    ref = [torch.triu(M) for M in b.forward(case["k_frac"], g, tau, T)]
+    b.close()
+    del b
+    torch.cuda.empty_cache()
+    for prec, bars in ((N.HSB_FP64, (1e-12, 1e-12)), (N.HSB_SPLIT_CRT, (1e-10, 1e-12))):
+        print("N_G", n, "precision", prec, flush=True)
+        b = HSBuilder.from_case(case, precision=prec, n_slices=11)
+        for M, R, bar in zip(b.forward(case["k_frac"], g, tau, T), ref, bars):
+            e = (torch.linalg.norm(torch.triu(M) - R) / torch.linalg.norm(R)).item()
+            print("rel %.3e" % e, flush=True)
+            assert e <= bar
+        b.close()
+        del b
+        torch.cuda.empty_cache()

@@ -160,7 +160,9 @@ int hsbuild_forward(hsbuild_t h, const double k_frac[3], int32_t ng, const int32
  * call allocates nothing (no hipMalloc, hipFree or allocating library call).
  * A problem whose hsbuild_workspace_bytes(h, HSB_MODE_FORWARD, 1, &ng) exceeds
  * HSB_STATIC_SCRATCH_BYTES gets HSB_ERR_WORKSPACE before anything is enqueued
- * (use hsbuild_forward with a caller workspace for it).  Every call on one GPU
+ * (use hsbuild_forward with a caller workspace for it), unless the stacked form
+ * fits (many types of one atom, l_max = 2, N_G of 13000 to 17000): the call runs
+ * that, equal to hsbuild_forward up to FP64 rounding.  Every call on one GPU
  * uses that GPU's one array, whose contents stay from the last call (each call
  * overwrites every byte it reads first): calls that may overlap on one GPU --
  * on different streams, from different handles or threads without ordering --

@@ -136,3 +136,29 @@ def test_type_factored_builds_against_the_stacked_contraction_at_full_size():
         b.close()
         del b
         torch.cuda.empty_cache()
+
+
+def test_static_forward_in_the_stacked_form():
+    """16 types of one atom, l_max = 2, N_G = 14000: the padded rows of the type-factored form need more than the static
+    scratch, the stacked ones less; the call runs these, and agrees with hsbuild_forward to FP64 rounding."""
+    from paper_1712_07206_amd import _native as N
+    from paper_1712_07206_amd.hsbuild import HSBuilder, case_tensors
+    from test_gpu_typed import _case
+    n = 14000
+    case = _case((1,) * 16, 2, n)
+    g, tau, T = case_tensors(case)
+    b = HSBuilder.from_case(case)
+    need = b.workspace_bytes(N.HSB_MODE_FORWARD, [n])
+    b.set_option(N.HSB_OPT_SPLIT_K, 0)
+    stacked = b.workspace_bytes(N.HSB_MODE_FORWARD, [n])
+    b.set_option(N.HSB_OPT_SPLIT_K, 1)
+    print("workspace", need, "stacked", stacked, flush=True)
+    assert stacked <= 256 << 20 < need
+    ref = b.forward(case["k_frac"], g, tau, T)
+    H, S = _nan(n), _nan(n)
+    b.forward_static(case["k_frac"], g, tau, T, H, S)
+    low = torch.ones((n, n), dtype=torch.bool, device="cuda").tril_(-1)
+    for M, R in zip((H, S), ref):
+        assert bool(torch.isnan(M.real[low]).all()), "strict lower triangle written"
+        R = R.masked_fill(low, 0.0)
+        assert (torch.linalg.norm(M.masked_fill(low, 0.0) - R) / torch.linalg.norm(R)).item() <= 1e-12

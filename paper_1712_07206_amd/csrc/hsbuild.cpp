@@ -369,7 +369,8 @@ Layout make_layout(const hsbuild_s& h, int ng, int mode) {
   if ((mode == HSB_MODE_FORWARD || mode == HSB_MODE_REAL) && h.precision == HSB_FP64)
     L.WL = take((size_t)L.K_pad * np * sizeof(double2));
   if (mode == HSB_MODE_FORWARD && h.precision == HSB_FP64 && h.hs_waves == 8 && h.split_k == 1) {
-    L.nsh = hs_stream_shares(L.n_pad, L.K_pad, h.num_cus);
+    // (where the builds themselves run stacked, in one pass: the batch's blocks equal the forward's bitwise)
+    L.nsh = stacked_cell(h, false) ? 0 : hs_stream_shares(L.n_pad, L.K_pad, h.num_cus);
     if (L.nsh > 0) {
       L.skH = take(hs_stream_slot_elems(L.nsh) * sizeof(double2));
       L.skS = take(hs_stream_slot_elems(L.nsh) * sizeof(double2));

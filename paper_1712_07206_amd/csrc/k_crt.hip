@@ -21,7 +21,7 @@
 // the residues, and H and S, are the same).  The column scaling keeps |Re|, |Im| of the integer
 // product below M/2 (M = prod m_i) by Cauchy-Schwarz, so the residues fix it uniquely;
 // it is recovered in FP64 as M * frac(sum_i r_i y_i / m_i), y_i = (M/m_i)^{-1} mod m_i,
-// with y_i / m_i split into a part on a 2^-42 grid (whose weighted sum is exact) and a
+// with the weights split into a part on a 2^-41 grid (whose weighted sum is exact) and a
 // small remainder.  The only approximation is the rounding of the scaled operands to
 // integers; at 11 moduli that keeps 40 bits of each column's 2-norm.
 //

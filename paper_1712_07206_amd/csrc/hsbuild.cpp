@@ -159,7 +159,7 @@ FactCell fact_cell(const CellArgs& cell) {
 // Whether a residue handle runs the FP64 products for `cell`: eight types or more with fewer than 256 rows of all atoms
 // each.  k_fact_crt's chunks, its recombination of the residues (4 FP64 operations per modulus, entry and type) and the
 // phase and S products are per type, and there more than the FP64 products it saves: over 8 to 16 types of 1 to 4 atoms,
-// l_max 0 to 10, N_G 100 to 5000 the FP64 build took 0.2 to 0.93 of its time.  (The stacked residues had taken 0.45 to 5 of it: 16
+// l_max 0 to 10, N_G 100 to 5000 the FP64 build took 0.2 to 0.92 of its time.  (The stacked residues had taken 0.45 to 3.7 of it: 16
 // types of one atom, l_max = 2, N_G = 5000: bytes 994 us stacked, 1762 by types, FP64 744; l_max = 8: 3059, 4007, 3673.)
 bool crt_in_fp64(const CellArgs& cell) {
   int n_act = 0;

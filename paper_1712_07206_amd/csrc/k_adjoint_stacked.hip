@@ -1,7 +1,7 @@
 // Stacked adjoint of the H/S build: the products over all atoms' rows, for cells of many types with few atoms
 // each.  Its work is that of one product with the K = 2 N_atoms N_L stacked rows, whatever the types, where the
 // type-factored adjoint (k_adjoint.hip) writes and reads two N_G x N_G matrices for every type: at N_G = 5000 in 16 types of
-// one atom, l_max = 2, 3.2 ms against 9.9; in 6 types of two atoms, l_max = 8, 12.3 against 7.1 (which of them runs:
+// one atom, l_max = 2, 3.2 ms against 9.9; in 6 types of two atoms, l_max = 8, 11.5 against 6.5 (which of them runs:
 // adjoint_stacked in hsbuild.cpp).
 //
 // With W the stacked coefficients (rows k = (atom, A|B, L)), Y_a = T_t W_a and
